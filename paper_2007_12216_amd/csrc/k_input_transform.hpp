@@ -184,8 +184,10 @@ __global__ __launch_bounds__(256) void k1_input_transform(KParams P, const int8_
     advance(cur);
     if (step + 1 < nsteps) load_table(cur, bnext);
     const int p = P.p[i];
-    const float inv = P.inv_p[i];
+    const float inv = in_vgpr(P.inv_p[i]), qb = in_vgpr(P.quot_bias[i]);
     const double invd = P.inv_pd[i];
+    const int a0 = WIDE ? 0 : P.acc_bias[i];         // see biased_lowbyte()
+    const v4i start = (v4i){a0, a0, a0, a0};
 #pragma unroll
     for (int cc = 0; cc < K1_CPW; ++cc) {
       const int cbk = cg * K1_CPW + cc;
@@ -194,7 +196,7 @@ __global__ __launch_bounds__(256) void k1_input_transform(KParams P, const int8_
 #pragma unroll
       for (int pl = 0; pl < PL; ++pl)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) acc[pl][u] = (v4i){0, 0, 0, 0};
+        for (int u = 0; u < 4; ++u) acc[pl][u] = start;
 #pragma unroll
       for (int s = 0; s < KS1; ++s)
 #pragma unroll
@@ -226,12 +228,12 @@ __global__ __launch_bounds__(256) void k1_input_transform(KParams P, const int8_
           *(v4i *)(dst + 1024) = out_l;
         }
       } else {
-        // |acc| <= t*t * 126 * 128 < 2^24
+        // |sum| <= t*t * (p - 1)/2 * 128 <= 256 * 125 * 128 (moduli above 251 exclude t > 13), and |a| < 2^15: below 2^22
         v4i out;
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          out[u] = (int)pack_low_bytes(mod_lowbyte(acc[0][u][0], inv, -p), mod_lowbyte(acc[0][u][1], inv, -p),
-                                       mod_lowbyte(acc[0][u][2], inv, -p), mod_lowbyte(acc[0][u][3], inv, -p));
+          out[u] = (int)pack_low_bytes(biased_lowbyte(acc[0][u][0], inv, qb, -p), biased_lowbyte(acc[0][u][1], inv, qb, -p),
+                                       biased_lowbyte(acc[0][u][2], inv, qb, -p), biased_lowbyte(acc[0][u][3], inv, qb, -p));
         if (pt < P.P2) *(v4i *)dst = out;
       }
     }

@@ -17,13 +17,14 @@
 //
 // Fast conversion (8-bit moduli, KParams::fastcrt): the accumulator a_i is not reduced at all.  a_i is congruent to
 // w_i modulo p_i, and (P/p_i) p_i = P, so S = sum_i (P/p_i) a_i is congruent to y modulo P and y = S - P rint(S/P) with
-// S/P = sum_i a_i / p_i.  The accumulators start at 2^22 (|a_i| <= t*t * 126 * 128 <= 2^22), so that a_i + 2^22 is an
-// unsigned 23-bit number: one 24-bit multiply-add (P/p_i < 2^24) and one binary32 multiply-add per residue and
-// output; the constants that undo the offset sit in KParams (crt_sum0, crt_fs0).  The binary32 sum carries an
-// error of a few hundredths (bounded on the host from the moduli), so the host enables this path only when the
-// layer's worst case keeps |y/P| that far below 1/2 -- true for every layer whose moduli were chosen by the
-// range bound with a little room, e.g. all five benchmark workloads.  Otherwise (KParams::fastcrt == 2) the same sum
-// is taken in binary64, which is exact enough for every result the moduli can represent.
+// S/P = sum_i a_i / p_i.  |a_i| <= t*t * 126 * 128 <= 2^22, so accumulators that start at 0x4B400000 hold a_i in two forms
+// at once: read as binary32 they are the number 1.5*2^23 + a_i (no conversion before the quotient's sum), and their low
+// 24 bits are a_i + 2^22, an unsigned 23-bit number for one 24-bit multiply-add (P/p_i < 2^24).  The constants that undo
+// both offsets sit in KParams (crt_sum0, crt_fs0).  The binary32 sum carries an error of a few hundredths (bounded on the
+// host from the moduli), so the host enables this path only when the layer's worst case keeps |y/P| that far below
+// 1/2 -- true for every layer whose moduli were chosen by the range bound with a little room, e.g. all five benchmark
+// workloads.  Otherwise (KParams::fastcrt == 2) the same sum is taken in binary64 over accumulators that start at 2^22,
+// which is exact enough for every result the moduli can represent.
 //
 // Block = one unit of 16 consecutive (k, tile) pairs and four 16-output row blocks rb = 4*blockIdx.y + wave; every
 // wave loads the O operand itself (the copies hit in L1): a wave-uniform row of O plus a 32-bit lane offset per
@@ -90,20 +91,27 @@ __device__ __forceinline__ void crt_convert(const KParams &P, const uint32_t (&w
   }
 }
 
-// Fast conversion (see the header): w[i][j] = a_i + 2^22, unreduced.
+// Fast conversion (see the header): w[i][j] = a_i + 0x4B400000, unreduced; read as binary32 it is 1.5*2^23 + a_i, so the
+// sum for the quotient takes it as it is, and its low 24 bits are a_i + 2^22.  Adding 1.5*2^23 to that sum rounds it and
+// leaves the quotient in the mantissa; the multiples of P that its bias stands for are part of crt_sum0.
+// Per output and residue one float multiply-add with vector operands (2.6 cycles per wave and SIMD) and one 24-bit
+// multiply-add (4.8), then 2.6 + 4.4 + 2.6: 39 cycles with four residues (71 with conversions and scalar operands).
+struct FastCrt {
+  float inv[8], fs0;
+  uint32_t sum0;
+};
 template <int NRES>
-__device__ __forceinline__ void crt_convert_fast(const KParams &P, const uint32_t (&w)[NRES][4], int (&val)[4]) {
+__device__ __forceinline__ void crt_convert_fast(const KParams &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    uint32_t sum = P.crt_sum0;
-    float fs = P.crt_fs0;
+    uint32_t sum = fc.sum0;
+    float fs = fc.fs0;
 #pragma unroll
     for (int i = 0; i < NRES; ++i) {
-      sum += __umul24(P.crt_c[i], w[i][j]);
-      fs = __builtin_fmaf((float)w[i][j], P.inv_p[i], fs);
+      sum = mad_u24(P.crt_c[i], w[i][j], sum);
+      fs = __builtin_fmaf(__uint_as_float(w[i][j]), fc.inv[i], fs);
     }
-    const int kk = (int)__builtin_rintf(fs);
-    val[j] = (int)(sum - P.prod_mod32 * (uint32_t)kk);
+    val[j] = (int)(sum - mul_lo(P.prod_mod32, __float_as_uint(fs + 12582912.0f)));
   }
 }
 
@@ -111,26 +119,37 @@ __device__ __forceinline__ void crt_convert_fast(const KParams &P, const uint32_
 // result in [-(P-1)/2, (P-1)/2] (the host checks its bound against 1/(2P)), so layers at the edge of the dynamic
 // range and plans with an unchecked range take this form.
 template <int NRES>
-__device__ __forceinline__ void crt_convert_fast64(const KParams &P, const uint32_t (&w)[NRES][4], int (&val)[4]) {
+__device__ __forceinline__ void crt_convert_fast64(const KParams &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    uint32_t sum = P.crt_sum0;
+    uint32_t sum = fc.sum0;
     double fs = P.crt_fs0d;
 #pragma unroll
     for (int i = 0; i < NRES; ++i) {
-      sum += __umul24(P.crt_c[i], w[i][j]);
+      sum = mad_u24(P.crt_c[i], w[i][j], sum);
       fs = __builtin_fma((double)w[i][j], P.inv_pd[i], fs);
     }
     const int kk = __double2int_rn(fs);
-    val[j] = (int)(sum - P.prod_mod32 * (uint32_t)kk);
+    val[j] = (int)(sum - mul_lo(P.prod_mod32, (uint32_t)kk));
   }
 }
 
+// Constants of the fast conversion in vector registers, loaded once per kernel.
 template <int NRES, bool FAST>
-__device__ __forceinline__ void k3_convert(const KParams &P, const uint32_t (&w)[NRES][4], int (&val)[4]) {
+__device__ __forceinline__ FastCrt fast_crt_constants(const KParams &P) {
+  FastCrt fc;
+  fc.fs0 = FAST ? in_vgpr(P.crt_fs0) : 0.0f;
+  fc.sum0 = FAST ? in_vgpr(P.crt_sum0) : 0u;
+#pragma unroll
+  for (int i = 0; i < NRES; ++i) fc.inv[i] = FAST ? in_vgpr(P.inv_p[i]) : 0.0f;
+  return fc;
+}
+
+template <int NRES, bool FAST>
+__device__ __forceinline__ void k3_convert(const KParams &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
   if (FAST) {
-    if (P.fastcrt == 2) crt_convert_fast64<NRES>(P, w, val);   // uniform
-    else crt_convert_fast<NRES>(P, w, val);
+    if (P.fastcrt == 2) crt_convert_fast64<NRES>(P, fc, w, val);   // uniform
+    else crt_convert_fast<NRES>(P, fc, w, val);
   } else if (P.crt24) {               // uniform: one branch per call instead of one per multiply
     if (P.quot32) crt_convert<NRES, true, true>(P, w, val);
     else crt_convert<NRES, true, false>(P, w, val);
@@ -170,10 +189,10 @@ __device__ __forceinline__ void k3_store_m8(const KParams &P, const int (&val)[4
 }
 
 template <int NRES, bool FAST>
-__device__ __forceinline__ void k3_convert_and_store(const KParams &P, const uint32_t (&w)[NRES][4], int rb, int g,
+__device__ __forceinline__ void k3_convert_and_store(const KParams &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int rb, int g,
                                                      const TilePos &tp, int32_t *__restrict__ y) {
   int val[4];
-  k3_convert<NRES, FAST>(P, w, val);
+  k3_convert<NRES, FAST>(P, fc, w, val);
   const int m = P.m, mm = m * m;
   const float inv_m = 1.0f / (float)m;
   const int o0 = 16 * rb + 4 * g;
@@ -289,6 +308,7 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(KParams P, const uint32_t 
       }
   }
 
+  const FastCrt fc = fast_crt_constants<NRES, FAST>(P);
   {
     uint32_t w[NRES][4];
 #pragma unroll
@@ -318,12 +338,12 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(KParams P, const uint32_t 
           const long long tot = (long long)acc[0][j] * 65536 + (long long)acc[1][j] * 256 + (long long)acc[NACC - 1][j];
           w[i][j] = (uint32_t)(mod_near64(tot, P.inv_pd[i], P.p[i]) + P.p[i]);
         } else {
-          // |acc| <= t*t * 126 * 128 <= 2^22 (plus the 2^22 of the fast conversion, which then takes it as it is)
+          // |acc| <= t*t * 126 * 128 <= 2^22 (the fast conversion takes it as it is, start included)
           w[i][j] = FAST ? (uint32_t)acc[0][j] : mod_near_plus_p(acc[0][j], P.inv_p[i], -P.p[i], P.bias_p[i]);
         }
       }
     }
-    k3_convert_and_store<NRES, FAST>(P, w, rb, g, tile_position(P, k, tau), y);
+    k3_convert_and_store<NRES, FAST>(P, fc, w, rb, g, tile_position(P, k, tau), y);
   }
 }
 
@@ -375,8 +395,9 @@ __global__ __launch_bounds__(256) void k3_inverse_crt_stream(KParams P, const ui
     }
   };
 
+  const FastCrt fc = fast_crt_constants<NRES, FAST>(P);
   // One unit with its O operand in `o`.
-  const int a0 = FAST ? P.acc0 : 0;                 // 2^22 for the fast conversion
+  const int a0 = FAST ? P.acc0 : 0;
   const v4i acc_start = (v4i){a0, a0, a0, a0};
   // 8 x 8 tiles: outputs 16 rb + 4 g .. + 3 are row u = 2 rb + (g >> 1), columns v = 4 (g & 1) .. + 3 of the tile; in the
   // stored plane (pooled: half the rows and columns) row block rb + 1 lies m8_step elements after row block rb
@@ -407,7 +428,7 @@ __global__ __launch_bounds__(256) void k3_inverse_crt_stream(KParams P, const ui
             w[i][j] = FAST ? (uint32_t)acc[j] : mod_near_plus_p(acc[j], P.inv_p[i], -P.p[i], P.bias_p[i]);
         }
         int val[4];
-        k3_convert<NRES, FAST>(P, w, val);
+        k3_convert<NRES, FAST>(P, fc, w, val);
         k3_store_m8(P, val, 2 * rb + m8_u0, m8_v, m8_off0 + rb * m8_step, tp, y);
       }
       return;
@@ -422,13 +443,13 @@ __global__ __launch_bounds__(256) void k3_inverse_crt_stream(KParams P, const ui
           const v4i a = *(const v4i *)(ka_lds + (((i * P.RB3 + rb) * KS3) + s) * 1024 + lane * 16);
           acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, o[i][s], acc, 0, 0, 0);
         }
-        // |acc| <= t*t * 126 * 128 <= 2^22: the fast conversion takes acc + 2^22 as it is, the general one the
+        // |acc| <= t*t * 126 * 128 <= 2^22: the fast conversion takes it as it is, start included, the general one the
         // residue shifted by +p so that it is non-negative
 #pragma unroll
         for (int j = 0; j < 4; ++j)
           w[i][j] = FAST ? (uint32_t)acc[j] : mod_near_plus_p(acc[j], P.inv_p[i], -P.p[i], P.bias_p[i]);
       }
-      k3_convert_and_store<NRES, FAST>(P, w, rb, g, tp, y);
+      k3_convert_and_store<NRES, FAST>(P, fc, w, rb, g, tp, y);
     }
   };
   v4i oa[NRES][KS3];

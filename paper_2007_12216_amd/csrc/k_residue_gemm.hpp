@@ -52,7 +52,11 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(KParams P, const int8_t *
   const int pt = 4 * q + wave;
   const int kb0 = by * RM, tb0 = bz * NTB;
   const int p = P.p[i];
-  const float inv = P.inv_p[i];
+  const float inv = in_vgpr(P.inv_p[i]), qb = in_vgpr(P.quot_bias[i]);
+  // Up to four steps |sum| <= 256 * 126 * 127 < 2^22 - 2^15: the accumulators may start at acc_bias and skip a conversion
+  // per result (biased_lowbyte()).
+  const bool biased = !WIDE && ncb <= 4;
+  const int a0 = biased ? P.acc_bias[i] : 0;
 
   v4i acc[NACC][RM][NTB];
   if (pt < P.P2) {
@@ -85,7 +89,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(KParams P, const int8_t *
       // every load of the step is issued before its first product (left alone, the scheduler sinks the loads
       // between the products to save registers, and the wave then waits for them one at a time)
       __builtin_amdgcn_sched_barrier(0);
-      const v4i zero = (v4i){0, 0, 0, 0};
+      const v4i acc0 = (v4i){a0, a0, a0, a0};
 #pragma unroll
       for (int s = 0; s < KS; ++s)
 #pragma unroll
@@ -94,12 +98,12 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(KParams P, const int8_t *
           for (int tb = 0; tb < NTB; ++tb) {
             const bool start = FIRST && s == 0;
             if constexpr (WIDE) {
-              acc[0][rm][tb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[s][rm][0], b[s][tb][0], start ? zero : acc[0][rm][tb], 0, 0, 0);
-              acc[1][rm][tb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[s][rm][0], b[s][tb][PL - 1], start ? zero : acc[1][rm][tb], 0, 0, 0);
+              acc[0][rm][tb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[s][rm][0], b[s][tb][0], start ? acc0 : acc[0][rm][tb], 0, 0, 0);
+              acc[1][rm][tb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[s][rm][0], b[s][tb][PL - 1], start ? acc0 : acc[1][rm][tb], 0, 0, 0);
               acc[1][rm][tb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[s][rm][PL - 1], b[s][tb][0], acc[1][rm][tb], 0, 0, 0);
-              acc[NACC - 1][rm][tb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[s][rm][PL - 1], b[s][tb][PL - 1], start ? zero : acc[NACC - 1][rm][tb], 0, 0, 0);
+              acc[NACC - 1][rm][tb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[s][rm][PL - 1], b[s][tb][PL - 1], start ? acc0 : acc[NACC - 1][rm][tb], 0, 0, 0);
             } else {
-              acc[0][rm][tb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[s][rm][0], b[s][tb][0], start ? zero : acc[0][rm][tb], 0, 0, 0);
+              acc[0][rm][tb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[s][rm][0], b[s][tb][0], start ? acc0 : acc[0][rm][tb], 0, 0, 0);
             }
           }
       // 8-bit residues, |U|,|V| <= 127: 512 channels add at most 8.3e6, so reducing every 8 steps keeps
@@ -132,24 +136,29 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(KParams P, const int8_t *
   uint32_t lane_byte = (uint32_t)((4 * (lane >> 4)) * PITCH + (lane & 15) * PL) * 4 + wave;
   asm volatile("" : "+v"(lane_byte));
   uint8_t *tile8 = (uint8_t *)tile + lane_byte;
+  auto exchange = [&](auto biased_tag) {
+    constexpr bool BIASED = decltype(biased_tag)::value;
 #pragma unroll
-  for (int rm = 0; rm < RM; ++rm)
+    for (int rm = 0; rm < RM; ++rm)
 #pragma unroll
-    for (int tb = 0; tb < NTB; ++tb)
+      for (int tb = 0; tb < NTB; ++tb)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int at = ((rm * 16 + j) * PITCH + tb * 16 * PL) * 4;   // row rm*16 + 4*(lane>>4) + j, column tb*16 + lane%16
-        if constexpr (WIDE) {
-          const long long tot = (long long)acc[0][rm][tb][j] * 65536 + (long long)acc[1][rm][tb][j] * 256 +
-                                (long long)acc[NACC - 1][rm][tb][j];
-          const int v = storable16(mod_near64(tot, P.inv_pd[i], p), p);
-          const int lo = (int)(int8_t)(v & 0xFF), hi = (v - lo) >> 8;
-          tile8[at] = (uint8_t)hi;
-          tile8[at + (PL - 1) * 4] = (uint8_t)lo;
-        } else {
-          tile8[at] = (uint8_t)mod_lowbyte(acc[0][rm][tb][j], inv, -p);
+        for (int j = 0; j < 4; ++j) {
+          const int at = ((rm * 16 + j) * PITCH + tb * 16 * PL) * 4;   // row rm*16 + 4*(lane>>4) + j, column tb*16 + lane%16
+          if constexpr (WIDE) {
+            const long long tot = (long long)acc[0][rm][tb][j] * 65536 + (long long)acc[1][rm][tb][j] * 256 +
+                                  (long long)acc[NACC - 1][rm][tb][j];
+            const int v = storable16(mod_near64(tot, P.inv_pd[i], p), p);
+            const int lo = (int)(int8_t)(v & 0xFF), hi = (v - lo) >> 8;
+            tile8[at] = (uint8_t)hi;
+            tile8[at + (PL - 1) * 4] = (uint8_t)lo;
+          } else {
+            tile8[at] = (uint8_t)(BIASED ? biased_lowbyte(acc[0][rm][tb][j], inv, qb, -p) : mod_lowbyte(acc[0][rm][tb][j], inv, -p));
+          }
         }
-      }
+  };
+  if (biased) exchange(std::true_type{});
+  else exchange(std::false_type{});
   __syncthreads();
   // O is [Kp][n][Q][Tp] words (x PL) and smaller than 4 GiB: 32-bit word offsets.  16 bytes per thread; whole tile
   // rows are written, padding tiles included (nothing depends on what they hold); only rows >= Kp and tile blocks

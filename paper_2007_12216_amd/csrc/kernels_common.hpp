@@ -29,10 +29,12 @@ struct KParams {
   int crt24;                  // every prod_{l != i} p_l is below 2^24: 24-bit multiplies suffice
   int quot32;                 // the layer's worst-case |y| is at most 0.45 prod p_i: binary32 finds the CRT quotient
   int bias_p[8];              // p_i * 2^22 + p_i (8-bit moduli), see mod_near_plus_p()
-  // fast conversion out of the RNS (k_inverse_crt.hpp): unreduced accumulators that start at acc0 = 2^22
+  int acc_bias[8];            // 8-bit moduli: what an accumulator starts at for biased_lowbyte()
+  float quot_bias[8];         // and the constant that puts its quotient into the mantissa
+  // fast conversion out of the RNS (k_inverse_crt.hpp): unreduced accumulators that start at acc0
   int fastcrt, acc0;          // fastcrt: 0 = off, 1 = binary32 quotient, 2 = binary64 quotient
-  uint32_t crt_sum0;          // -acc0 * sum_i prod_{l != i} p_l mod 2^32
-  float crt_fs0;              // -acc0 * sum_i 1/p_i
+  uint32_t crt_sum0;          // undoes, modulo 2^32, the accumulators' start and the bias of the quotient
+  float crt_fs0;              // minus the start's share of the quotient
   double crt_fs0d;            // the same in binary64
   // fused re-quantisation in the inverse-transform kernel (chained layers): 0 = store int32 y,
   // 1 = store int8 clamp(y >> shift), 2 = the same after a 2x2 stride-2 max-pool
@@ -71,6 +73,43 @@ __device__ __forceinline__ uint32_t mod_lowbyte(int x, float inv_p, int neg_p) {
   return (uint32_t)r;
 }
 
+// The same from an accumulator that started at KParams::acc_bias = 0x4B400000 + a instead of zero.  Read as binary32
+// such an accumulator is the number 1.5*2^23 + a + x (|a + x| < 2^22: the sum stays in one binade, whose unit is 1), so
+// the sum needs no conversion.  a is a multiple of 256 with 1.5*2^23 + a = s p: then f/p + (1.5*2^23 - s) = 1.5*2^23 + x/p,
+// one multiply-add whose mantissa holds q = rint(x/p), and x - q p has its low byte in acc - q p.
+// 1/p carries a relative error of 2^-24 and f < 2^24, so x/p is off by less than 1/p and |x - q p| <= p/2 + 1.
+// Cost of the arithmetic on this chip, cycles per wave and SIMD: the float multiply-add with all operands in vector
+// registers 2.6 (with a scalar operand 4.8), v_mad_i32_i24 4.8, the conversion this saves 4.2.  The caller keeps inv_p
+// and quot_bias in vector registers (in_vgpr()).
+__device__ __forceinline__ uint32_t biased_lowbyte(int acc, float inv_p, float quot_bias, int neg_p) {
+  const float f = __builtin_fmaf(__int_as_float(acc), inv_p, quot_bias);
+  int r;
+  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(__float_as_int(f)), "s"(neg_p), "v"(acc));
+  return (uint32_t)r;
+}
+
+// A wave-uniform value in a vector register, hidden from the optimiser (which would put it back into a scalar one).
+template <typename T>
+__device__ __forceinline__ T in_vgpr(T v) {
+  asm("" : "+v"(v));
+  return v;
+}
+
+// c * (low 24 bits of w) + acc modulo 2^32, c < 2^24 wave-uniform: one instruction (the compiler, left to choose, splits
+// the products from their sums or takes 64-bit multiply-adds, each of which costs more than the 4.8 cycles of this).
+__device__ __forceinline__ uint32_t mad_u24(uint32_t c, uint32_t w, uint32_t acc) {
+  uint32_t r;
+  asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "s"(c), "v"(w), "v"(acc));
+  return r;
+}
+
+// Low 32 bits of c * v, c wave-uniform (4.4 cycles, full rate on this chip).
+__device__ __forceinline__ uint32_t mul_lo(uint32_t c, uint32_t v) {
+  uint32_t r;
+  asm("v_mul_lo_u32 %0, %1, %2" : "=v"(r) : "s"(c), "v"(v));
+  return r;
+}
+
 // That residue plus p (so that it is positive), 8-bit p: the low 24 bits of the biased float are 2^22 + q, the
 // 24-bit multiply-add gives x - q p - 2^22 p + bias with bias = 2^22 p + p.  Four full-rate instructions.
 __device__ __forceinline__ uint32_t mod_near_plus_p(int x, float inv_p, int neg_p, int bias) {
@@ -80,7 +119,7 @@ __device__ __forceinline__ uint32_t mod_near_plus_p(int x, float inv_p, int neg_
   return (uint32_t)r;
 }
 
-// byte 0 of a, b, c, d -> one word
+// byte 0 of a, b, c, d -> one word (the selectors sit in scalar registers: 4.4 cycles each)
 __device__ __forceinline__ uint32_t pack_low_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
   const uint32_t ab = __builtin_amdgcn_perm(b, a, 0x0c0c0400u);
   const uint32_t cd = __builtin_amdgcn_perm(d, c, 0x0c0c0400u);

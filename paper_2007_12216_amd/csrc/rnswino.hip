@@ -76,6 +76,14 @@ KParams make_params(const rnswino_plan_t *pl) {
     P.crt_c[i] = pl->crt_c[i];
     if (!pl->crt_c_exact_small[i]) P.crt24 = 0;
     P.bias_p[i] = d.wide ? 0 : (int)(pl->desc.moduli[i] * 4194304u + pl->desc.moduli[i]);
+    if (!d.wide) {
+      // biased_lowbyte(): the multiple a = 256 j of smallest magnitude for which 1.5 * 2^23 + a is a multiple of p (256 is
+      // a unit modulo the odd p, so |a| <= 128 (p - 1))
+      const int p = P.p[i], magic = 12582912;
+      const int a = 256 * sym_residue(-(int64_t)(magic % p) * mod_inverse(256 % p, p), p);
+      P.acc_bias[i] = 0x4B400000 + a;
+      P.quot_bias[i] = (float)(magic - (magic + a) / p);
+    }
   }
   {
     // binary32 is enough for the CRT quotient when 2 * (worst-case |y|) <= 0.9 * prod p_i
@@ -84,29 +92,46 @@ KParams make_params(const rnswino_plan_t *pl) {
     for (int i = 0; i < d.n; ++i) { prod *= pl->desc.moduli[i]; if (prod > cap) prod = cap; }
     const unsigned __int128 worst = output_bound(pl->desc, d);
     P.quot32 = (worst * 20 <= prod * 9) ? 1 : 0;
-    // Fast conversion: the binary32 sum of (a_i + 2^22) / p_i - B, B = 2^22 sum_i 1/p_i, stays within [-B, B]; it
-    // takes n + 1 roundings of at most half an ulp of 2B each, and the rounded 1/p_i add at most 2B 2^-23 in all.
-    // Enabled when the layer's worst case leaves twice that error below 0.49 - |y|/P.
+    // Fast conversion, binary32 quotient: the accumulators, read as binary32, are M + a_i with M = 1.5 * 2^23 and
+    // |a_i| <= 2^22.  The sum starts at -M sum_i v_i (v_i: 1/p_i as rounded, so the rounding of 1/p_i counts for a_i
+    // alone) and takes one multiply-add per residue; before residue i it lies within M sum_{l >= i} v_l +
+    // 2^22 sum_{l < i} v_l of zero, and every step rounds by at most half an ulp of that: 0.021 for three moduli near 240,
+    // 0.035 for four.  Enabled when the layer's worst case leaves twice the error below 0.49 - |y|/P, with the error taken
+    // as no less than n + 1 roundings at 2B and 2B 2^-23, B = 2^22 sum_i 1/p_i (0.028 and 0.056): that keeps a reserve, and
+    // layers beyond it take the binary64 quotient, whose cost they hardly see (1.3 times the instructions of a small stage).
     if (!d.wide && P.crt24 && prod < cap) {
+      const double M = 12582912.0, A = 4194304.0;
+      auto half_ulp = [](double bound, int mantissa) { int e = 0; std::frexp(bound, &e); return std::ldexp(1.0, e - mantissa - 1); };
       long double Bl = 0.0L;             // extended precision: the one rounding to binary64 is counted below
+      double start = 0.0, done = 0.0, err = 0.0;
       uint32_t c32 = 0;
-      for (int i = 0; i < d.n; ++i) { Bl += 4194304.0L / (long double)pl->desc.moduli[i]; c32 += pl->crt_c[i]; }
+      for (int i = 0; i < d.n; ++i) {
+        Bl += (long double)A / (long double)pl->desc.moduli[i];
+        c32 += pl->crt_c[i];
+        start += M * (double)P.inv_p[i];
+      }
+      double left = start;
+      err += half_ulp(left, 24);                                 // the start itself
+      for (int i = 0; i < d.n; ++i) {
+        left -= M * (double)P.inv_p[i];
+        done += A * (double)P.inv_p[i];
+        err += half_ulp(std::fabs(left) + done, 24) + A * std::fabs((double)P.inv_p[i] - 1.0 / (double)pl->desc.moduli[i]);
+      }
       const double B = (double)Bl;
-      int e = 0;
-      std::frexp(2.0 * B, &e);                                   // 2B = f * 2^e, f in [0.5, 1)
-      const double half_ulp = std::ldexp(1.0, e - 24 - 1);      // binary32: ulp = 2^(e - 24)
-      const double err = (d.n + 1) * half_ulp + 2.0 * B * std::ldexp(1.0, -23);
-      // The same sum in binary64 (ulp = 2^(e64 - 53)) must find the quotient for every |y| <= (P - 1)/2, i.e. stay
-      // within 1/(2P) of the true value: twice its error bound has to fit.
-      int e64 = 0;
-      std::frexp(B, &e64);                                       // every partial sum lies in [-B, B], B < 2^e64
-      const double err64 = (d.n + 1) * std::ldexp(1.0, e64 - 53 - 1) + 2.0 * B * std::ldexp(1.0, -52);
-      if ((double)worst / (double)prod + 2.0 * err <= 0.49) P.fastcrt = 1;
+      // The same sum over a_i + 2^22 in binary64 must find the quotient for every |y| <= (P - 1)/2, i.e. stay within
+      // 1/(2P) of the true value: it takes n + 1 roundings of at most half an ulp of B = 2^22 sum_i 1/p_i, and the rounded
+      // 1/p_i add at most 2B 2^-52 in all; twice that has to fit.
+      const double err64 = (d.n + 1) * half_ulp(B, 53) + 2.0 * B * std::ldexp(1.0, -52);
+      const double reserve = (d.n + 1) * half_ulp(2.0 * B, 24) + 2.0 * B * std::ldexp(1.0, -23);
+      if ((double)worst / (double)prod + 2.0 * std::fmax(err, reserve) <= 0.49) P.fastcrt = 1;
       else if (2.0 * err64 <= 0.5 / (double)prod) P.fastcrt = 2;
-      if (P.fastcrt) {
+      if (P.fastcrt == 1) {
+        P.acc0 = 0x4B400000;             // the bits of M; its low 24 bits are 2^22
+        P.crt_sum0 = 0u - 4194304u * c32 + pl->prod_mod32 * 0x4B400000u;
+        P.crt_fs0 = (float)(-start);
+      } else if (P.fastcrt == 2) {
         P.acc0 = 4194304;
         P.crt_sum0 = 0u - 4194304u * c32;
-        P.crt_fs0 = (float)(-B);
         P.crt_fs0d = -B;
       }
     }
