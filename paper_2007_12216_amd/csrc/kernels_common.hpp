@@ -19,9 +19,9 @@ struct KParams {
   int p[8];
   float inv_p[8];
   double inv_pd[8];           // 1 / p_i
-  const int32_t *G;           // device table [n][t*r] for the filter transform
   // transforms on the matrix cores: Kronecker tables in operand-fragment order (see plan_math.cpp)
   int CB1, KS1, RP1, RB3, KS3;
+  const int8_t *KG;           // (G kron G) mod p              [n][CB1][planes][64 lanes][16]
   const int8_t *KB;           // (B^T kron B^T) mod p          [n][CB1][KS1][planes][64 lanes][16]
   const int8_t *KA;           // (A^T kron A^T) crt_inv mod p  [n][RB3][KS3][planes][64 lanes][16]
   uint32_t crt_c[8];          // prod_{l != i} p_l mod 2^32
@@ -138,13 +138,5 @@ __device__ __forceinline__ int mod_near64(long long x, double inv_pd, int p) {
 
 // move a representative with |r| <= 32761 into the storable range
 __device__ __forceinline__ int storable16(int r, int p) { return r > 32639 ? r - p : r; }
-
-__device__ __forceinline__ int sym_mod64(long long v, int p) {   // exact, slow; offline kernels only
-  int r = (int)(v % p);
-  const int h = (p - 1) >> 1;
-  if (r > h) r -= p;
-  if (r < -h) r += p;
-  return r;
-}
 
 }  // namespace rnswino

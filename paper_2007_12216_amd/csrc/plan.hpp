@@ -65,7 +65,6 @@ struct rnswino_plan_s {
   std::vector<char> h_tables;               // the same bytes on the host (query calls)
   size_t d_tables_bytes;
   // offsets (bytes) into d_tables
-  size_t off_G;                             // int32 G matrices [n][t*r] (filter transform)
-  size_t off_KB, off_KA;                    // int8 Kronecker tables of the input / inverse transform
+  size_t off_KG, off_KB, off_KA;            // int8 Kronecker tables of the filter / input / inverse transform
   void *kparams;                            // the kernels' parameter block (rnswino::KParams), built once with the plan
 };

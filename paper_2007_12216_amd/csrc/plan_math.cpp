@@ -204,12 +204,15 @@ int validate_desc(const rnswino_desc_t &d, Dims &o) {
 //
 // The 2-D transforms are applied as Kronecker products on the matrix cores:
 //   vec(B^T d B) = (B^T kron B^T) vec(d),      vec(A^T O A) = (A^T kron A^T) vec(O),
-// so each residue needs a (t*t) x (t*t) and an (m*m) x (t*t) matrix modulo p.  They are stored in the operand
+// and vec(G g G^T) = (G kron G) vec(g), so each residue needs a (t*t) x (t*t), an (m*m) x (t*t) and a (t*t) x (r*r) matrix
+// modulo p.  They are stored in the operand
 // fragment order of v_mfma_i32_16x16x64_i8: a fragment is 16 rows (or columns) x 64 contraction elements,
 // lane l holds row l%16 and the 16 contraction elements of slice g = l/16.
 //   KB (input transform, B operand): fragment (cbk, s): column = transform point 16*cbk + l%16,
 //       contraction element (g, b) = slot f = 64s + 16g + b = pixel (row f / RP1, column f % RP1) of the tile, where a
 //       tile row takes RP1 = 4 ceil(t/4) slots; zero for column >= t or row >= t.
+//   KG (filter transform, A operand): fragment cbk: row = transform point 16*cbk + l%16, contraction element (g, b) =
+//       filter tap 16g + b (row tap / r, column tap % r); zero for tap >= r*r.
 //   KA (inverse transform, A operand): fragment (rb, s): row = output u*m+v = 16*rb + l%16,
 //       contraction element (g, b) = transform point 64s + 16g + b.  Each entry is multiplied by
 //       (P/p_i)^-1 mod p_i so that the kernel's accumulator is directly the CRT coefficient of the residue.
@@ -252,19 +255,28 @@ void build_tables(rnswino_plan_s &pl, std::vector<char> &blob) {
   }
 
   const int planes = d.wide ? 2 : 1;
-  const size_t szG = (size_t)d.n * d.t * d.r * 4;
+  const size_t szKG = (size_t)d.n * d.CB1 * planes * 1024;
   const size_t szKB = (size_t)d.n * d.CB1 * d.KS1 * planes * 1024;
   const size_t szKA = (size_t)d.n * d.RB3 * d.KS3 * planes * 1024;
-  pl.off_G = 0;
-  pl.off_KB = align256(pl.off_G + szG);
+  pl.off_KG = 0;
+  pl.off_KB = align256(pl.off_KG + szKG);
   pl.off_KA = align256(pl.off_KB + szKB);
   pl.d_tables_bytes = align256(pl.off_KA + szKA);
   blob.assign(pl.d_tables_bytes, 0);
 
   for (int i = 0; i < d.n; ++i) {
     const int64_t p = desc.moduli[i];
-    const std::vector<int32_t> &BT = pl.tf[i].BT, &AT = pl.tf[i].AT;
-    std::memcpy(blob.data() + pl.off_G + (size_t)i * d.t * d.r * 4, pl.tf[i].G.data(), (size_t)d.t * d.r * 4);
+    const std::vector<int32_t> &BT = pl.tf[i].BT, &AT = pl.tf[i].AT, &G = pl.tf[i].G;
+    int8_t *kg = (int8_t *)blob.data() + pl.off_KG + (size_t)i * d.CB1 * planes * 1024;
+    for (int cbk = 0; cbk < d.CB1; ++cbk)
+      for (int lane = 0; lane < 64; ++lane)
+        for (int b = 0; b < 16; ++b) {
+          const int pt = 16 * cbk + (lane & 15), tap = 16 * (lane >> 4) + b;
+          if (pt < d.P2 && tap < d.r * d.r) {
+            const int32_t v = sym_residue((int64_t)G[(size_t)(pt / d.t) * d.r + tap / d.r] * G[(size_t)(pt % d.t) * d.r + tap % d.r], p);
+            put_entry(kg + (size_t)cbk * planes * 1024, planes, lane, b, v, p);
+          }
+        }
     int8_t *kb = (int8_t *)blob.data() + pl.off_KB + (size_t)i * d.CB1 * d.KS1 * planes * 1024;
     for (int cbk = 0; cbk < d.CB1; ++cbk)
       for (int s = 0; s < d.KS1; ++s)

@@ -139,7 +139,7 @@ KParams make_params(const rnswino_plan_t *pl) {
   P.prod_mod32 = pl->prod_mod32;
   if (pl->d_tables) {                   // host-only plans are never executed: their table pointers stay null
     const char *base = (const char *)pl->d_tables;
-    P.G = (const int32_t *)(base + pl->off_G);
+    P.KG = (const int8_t *)(base + pl->off_KG);
     P.KB = (const int8_t *)(base + pl->off_KB);
     P.KA = (const int8_t *)(base + pl->off_KA);
   }
@@ -526,12 +526,17 @@ int rnswino_filter_transform(const rnswino_plan_t *plan, const int8_t *w_dev, vo
   if (!on_plan_device(plan)) return RNSWINO_E_INVALID;
   const Dims &d = plan->dims;
   const KParams P = *(const KParams *)plan->kparams;
-  const long long total = (long long)d.n * d.Kp * d.Cp;
   hipStream_t st = (hipStream_t)stream;
+  // one block per 16 rows x 64 channels, its (residue, 16-point block) items split over y until there are about four
+  // blocks per compute unit (512 x 512, t = 10: 46 us with one block per compute unit, 35.5 with two, 32 with four, 33 with
+  // seven, 36.5 with fourteen -- each block gathers its filters anew)
+  const long long gx = (long long)(d.Kp / 16) * (d.Cp / 64), items = (long long)d.n * d.CB1, want = (1024 + gx - 1) / gx;
+  const dim3 grid((unsigned)gx, (unsigned)(want < items ? want : items));
+  const size_t lds = (size_t)((d.r * d.r + 15) / 16) * 16384;
   if (d.wide)
-    hipLaunchKernelGGL(k0_filter_transform<true>, dim3(blocks_for(total, 256)), dim3(256), 0, st, P, w_dev, (int8_t *)U_dev);
+    hipLaunchKernelGGL(k0_filter_transform<true>, grid, dim3(256), lds, st, P, w_dev, (int8_t *)U_dev);
   else
-    hipLaunchKernelGGL(k0_filter_transform<false>, dim3(blocks_for(total, 256)), dim3(256), 0, st, P, w_dev, (int8_t *)U_dev);
+    hipLaunchKernelGGL(k0_filter_transform<false>, grid, dim3(256), lds, st, P, w_dev, (int8_t *)U_dev);
   return launch_status();
 }
 
