@@ -6,9 +6,9 @@
 // written: a column block's operand fragment for filter tap (i, j) and 64 channels is gathered straight from the
 // activations, 16 bytes (16 channels of one pixel) per lane.  For that the activations are first copied once into a
 // channel-innermost, zero-bordered layout (one pass over x; part of the timed call):
-//   xt [N][H + 2 pad][W + 2 pad][Cp]      Cp = C rounded up to 64, padding channels and the border are zero
+//   xt [Cp/64][N][H + 2 pad][W + 2 pad][64]      Cp = C rounded up to 64, padding channels and the border are zero
 // and the weights are packed ahead of time into matrix-core fragments (they are constants of the layer):
-//   wt [r*r taps][Kp/16][Cp/64][lane = k%16 + 16 g][16 B]     byte b of slice g = channel 64 cb + 16 g + b.
+//   wt [Cp/64][r*r taps][Kp/16][lane = k%16 + 16 g][16 B]     byte b of slice g = channel 64 cb + 16 g + b.
 // The GEMM kernel has the structure of the LDS-tiled residue GEMM (k_residue_gemm_lds.hpp): WM x WN waves of
 // RM x NT fragments each, operand fragments loaded from global memory straight into LDS S steps deep and shared by
 // the waves; a step is one (tap, 64-channel block).  The int32 sums are stored as they are (no modulus anywhere).
@@ -23,40 +23,77 @@ struct DirectParams {
   int npix;                     // N * Ho * Wo
 };
 
-// x [N][C][H][W] -> xt [N][Hp][Wp][Cp], zero border and zero padding channels.  One thread writes 16 channels of one
-// padded pixel; a block of 256 threads covers 64 consecutive padded pixels of one row and 64 channels, staged through
-// LDS so that both the reads (along W) and the writes (along C) are contiguous.
+// x [N][C][H][W] -> xt [Cp/64][N][Hp][Wp][64], zero border and zero padding channels.  A block takes 64 channels of 16 units
+// (a unit: 16 consecutive padded pixels of one row): every thread loads four 16-byte row segments (unaligned, masked to the
+// image), and after a transpose in LDS stores four pixels x 16 channels.  Bound by its two passes over the tensor; 256
+// channels at 56 x 56, batch 8 (6.4 MB read, 6.9 MB written): 6.5 us (one byte per load: 15.9).
 __global__ __launch_bounds__(256) void k_direct_to_nhwc(DirectParams P, const int8_t *__restrict__ x, int8_t *__restrict__ xt) {
-  __shared__ uint8_t tile[64][64 + 4];                 // [channel][pixel], rows padded against bank conflicts
-  const int xblocks = (P.Wp + 63) / 64;
-  int b = blockIdx.x;
-  const int xb = b % xblocks; b /= xblocks;
-  const int cb = b % (P.Cp / 64); b /= (P.Cp / 64);
-  const int yp = b % P.Hp, n = b / P.Hp;
-  const int iy = yp - P.pad;
+  // row segment of (unit, channel) at dword 272 unit + 68 (channel / 16) + 4 (channel % 16): both the 16-byte writes and the
+  // column reads below spread over all banks
+  __shared__ __attribute__((aligned(16))) uint32_t tile[16 * 272];
+  const int groups = (P.Wp + 15) >> 4, ncb = P.Cp >> 6;
+  const int nunits = P.N * P.Hp * groups;               // below 2^31: xt is
+  const int cb = blockIdx.x % ncb, ub = blockIdx.x / ncb;
   {
-    // read: thread (c = tid / 4, quarter q = tid % 4) takes 16 pixels of channel c
-    const int c = threadIdx.x >> 2, q = threadIdx.x & 3;
-    const int ch = cb * 64 + c;
+    const long long total = (long long)P.N * P.C * P.H * P.W;
+    const int unit = ub * 16 + (threadIdx.x & 15), c0 = threadIdx.x >> 4;
+    const int row = unit / groups, grp = unit - row * groups, n = row / P.Hp;
+    const int iy = row - n * P.Hp - P.pad, ix = grp * 16 - P.pad;      // image row and column of the segment's first pixel
+    const bool row_ok = unit < nunits && iy >= 0 && iy < P.H;
+    v4i val[4];
+    int state[4];                                       // 0: zeros, 1: plain 16-byte load, 2: ends of the tensor
+    long long at[4];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int xp = xb * 64 + q * 16 + e, ix = xp - P.pad;
-      uint8_t v = 0;
-      if (ch < P.C && iy >= 0 && iy < P.H && ix >= 0 && ix < P.W) v = (uint8_t)x[(((size_t)n * P.C + ch) * P.H + iy) * P.W + ix];
-      tile[c][q * 16 + e] = v;
+    for (int e = 0; e < 4; ++e) {
+      const int ch = cb * 64 + c0 + 16 * e;
+      at[e] = (((long long)n * P.C + ch) * P.H + iy) * P.W + ix;
+      state[e] = !(row_ok && ch < P.C) ? 0 : at[e] >= 0 && at[e] + 16 <= total ? 1 : 2;
+      val[e] = (v4i){0, 0, 0, 0};
+      if (state[e] == 1) __builtin_memcpy(&val[e], x + at[e], 16);
     }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (state[e] == 2) {
+        uint32_t wv[4] = {0, 0, 0, 0};
+        for (int b = 0; b < 16; ++b)
+          if (at[e] + b >= 0 && at[e] + b < total) wv[b >> 2] |= (uint32_t)(uint8_t)x[at[e] + b] << (8 * (b & 3));
+        val[e] = (v4i){(int)wv[0], (int)wv[1], (int)wv[2], (int)wv[3]};
+      }
+    // columns [lo, hi) of the segment lie inside the image
+    const int lo = min(max(-ix, 0), 16), hi = min(max(P.W - ix, 0), 16);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      uint32_t mask = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mask |= (4 * d + e >= lo && 4 * d + e < hi) ? 0xFFu << (8 * e) : 0u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) val[e][d] &= mask;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) *(v4i *)(tile + (threadIdx.x & 15) * 272 + e * 68 + c0 * 4) = val[e];
   }
   __syncthreads();
   {
-    // write: thread (pixel = tid / 4, slice g = tid % 4) stores channels 16 g .. 16 g + 15 of that pixel
-    const int px = threadIdx.x >> 2, g = threadIdx.x & 3;
-    const int xp = xb * 64 + px;
-    if (xp < P.Wp) {
-      uint32_t wv[4] = {0, 0, 0, 0};
+    const int g = threadIdx.x & 3, pq = (threadIdx.x >> 2) & 3, u = threadIdx.x >> 4, unit = ub * 16 + u;
+    if (unit >= nunits) return;
+    uint32_t in[16];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) wv[e >> 2] |= (uint32_t)tile[16 * g + e][px] << (8 * (e & 3));
-      *(v4i *)(xt + (((size_t)n * P.Hp + yp) * P.Wp + xp) * P.Cp + cb * 64 + 16 * g) = (v4i){(int)wv[0], (int)wv[1], (int)wv[2], (int)wv[3]};
+    for (int e = 0; e < 16; ++e) in[e] = tile[u * 272 + g * 68 + e * 4 + pq];
+    v4i out[4];                                         // pixel 4 pq + k: channels 16 g .. 16 g + 15
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      const uint32_t t0 = __builtin_amdgcn_perm(in[4 * d + 1], in[4 * d], 0x05010400u), t1 = __builtin_amdgcn_perm(in[4 * d + 1], in[4 * d], 0x07030602u);
+      const uint32_t t2 = __builtin_amdgcn_perm(in[4 * d + 3], in[4 * d + 2], 0x05010400u), t3 = __builtin_amdgcn_perm(in[4 * d + 3], in[4 * d + 2], 0x07030602u);
+      out[0][d] = (int)__builtin_amdgcn_perm(t2, t0, 0x05040100u);
+      out[1][d] = (int)__builtin_amdgcn_perm(t2, t0, 0x07060302u);
+      out[2][d] = (int)__builtin_amdgcn_perm(t3, t1, 0x05040100u);
+      out[3][d] = (int)__builtin_amdgcn_perm(t3, t1, 0x07060302u);
     }
+    const int row = unit / groups, xp = (unit - row * groups) * 16 + 4 * pq;
+    int8_t *dst = xt + (((size_t)cb * P.N * P.Hp + row) * P.Wp + xp) * 64 + 16 * g;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (xp + k < P.Wp) *(v4i *)(dst + k * 64) = out[k];
   }
 }
 
@@ -75,7 +112,7 @@ __global__ __launch_bounds__(256) void k_direct_pack_filter(DirectParams P, cons
     const int c = sl * 16 + e;
     if (k < P.K && c < P.C) wv[e >> 2] |= (uint32_t)(uint8_t)w[((size_t)k * P.C + c) * P.r * P.r + tap] << (8 * (e & 3));
   }
-  const size_t frag = ((size_t)tap * (P.Kp / 16) + (k >> 4)) * (P.Cp / 64) + cb;
+  const size_t frag = ((size_t)cb * P.r * P.r + tap) * (P.Kp / 16) + (k >> 4);
   *(v4i *)(wt + frag * 1024 + ((k & 15) + 16 * g) * 16) = (v4i){(int)wv[0], (int)wv[1], (int)wv[2], (int)wv[3]};
 }
 
@@ -107,7 +144,7 @@ __global__ __launch_bounds__(256) void k_direct_conv(DirectParams P, const int8_
     pix = min(pix, P.npix - 1);
     const int n = pix / (P.Ho * P.Wo), rem = pix - n * (P.Ho * P.Wo);
     const int oy = rem / P.Wo, ox = rem - oy * P.Wo;
-    return (uint32_t)(((n * P.Hp + oy) * P.Wp + ox) * P.Cp);        // xt is smaller than 4 GiB (checked on the host)
+    return (uint32_t)(((n * P.Hp + oy) * P.Wp + ox) * 64);          // xt is smaller than 4 GiB (checked on the host)
   };
   // this wave's loads of a step: fragment f = wave + 4 j: a weight fragment (contiguous) or a pixel-block fragment
   // (lane = pixel l % 16, channels 16 (l / 16) .. + 15); per step only the wave-uniform part of the address changes
@@ -119,9 +156,9 @@ __global__ __launch_bounds__(256) void k_direct_conv(DirectParams P, const int8_
     const int f = min(wave + 4 * j, NF - 1);
     is_w[j] = f < BRF;
     if (is_w[j]) {
-      base[j] = wt + (size_t)min(kb0 + f, nkb - 1) * ncb * 1024;
+      base[j] = wt + (size_t)min(kb0 + f, nkb - 1) * 1024;
       lane_off[j] = (uint32_t)lane * 16u;
-      tap_stride[j] = (uint32_t)(nkb * ncb) * 1024u;
+      tap_stride[j] = (uint32_t)nkb * 1024u;
     } else {
       base[j] = xt;
       lane_off[j] = pixel_origin((min(tb0 + f - BRF, ntb - 1)) * 16 + (lane & 15)) + (uint32_t)(lane >> 4) * 16u;
@@ -131,10 +168,10 @@ __global__ __launch_bounds__(256) void k_direct_conv(DirectParams P, const int8_
   const uint32_t stage_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t *)stage;
   auto issue = [&](int tap, int cb, int slot) {
     const int ti = tap / P.r, tj = tap - ti * P.r;
-    const size_t x_off = (size_t)(ti * P.Wp + tj) * P.Cp + (size_t)cb * 64;
+    const size_t x_off = ((size_t)cb * P.N * P.Hp * P.Wp + (size_t)(ti * P.Wp + tj)) * 64;
 #pragma unroll
     for (int j = 0; j < LPW; ++j) {
-      const int8_t *src = is_w[j] ? base[j] + (size_t)tap * tap_stride[j] + (size_t)cb * 1024 : base[j] + x_off;
+      const int8_t *src = is_w[j] ? base[j] + (size_t)(cb * taps + tap) * tap_stride[j] : base[j] + x_off;
       load_to_lds16(src, lane_off[j], stage_lds + (uint32_t)((slot * SLOTS + wave + 4 * j) * 1024));
     }
   };
@@ -187,6 +224,134 @@ __global__ __launch_bounds__(256) void k_direct_conv(DirectParams P, const int8_
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int k = (kb0 + wm * RM + rm) * 16 + 4 * (lane >> 4) + j;
+        if (k < P.K) ypix[(size_t)k * plane] = acc[rm][nt][j];
+      }
+  }
+}
+
+// The same product with the pixels of all taps staged once.  In xt the pixels of one 64-channel block are consecutive, so the
+// patch that 16 * WN * NT consecutive output pixels need for all r*r taps is ONE run of `patch` pixels (64 bytes each); it is
+// copied to LDS once per channel block (two buffers: the next block's patch arrives while this one is used) and every tap
+// reads its operand at another offset, instead of fetching it from L2 again for every tap.  The weights lie in memory in the
+// order of the steps and go from L2 straight into registers, D taps ahead.  A workgroup thus meets one barrier per channel
+// block instead of one per tap.
+// What bounds it is the instruction stream of the one or two waves a SIMD holds (a wave issues an instruction every four to
+// five cycles; 16 of a step's 60 are matrix instructions): running pointers instead of 64-bit address sums and the whole next
+// patch in one place took 256 -> 256 at 56 x 56, batch 8, from 33 to 28.5 us a call.  There, with 64 x 256 blocks, the kernel
+// takes 21 us (1.4 POP/s; k_direct_conv 37): 3.5 us less without the stores of y, 3 without the weights' loads, 3 without
+// the next patch, 1 without the reads of LDS.  An LDS layout swizzled against bank conflicts changed nothing.
+// Dynamic LDS: (ncb > 1 ? 2 : 1) * ceil(patch / 16) KiB.  Grid as k_direct_conv.
+template <int WM, int WN, int RM, int NT, int D>
+__global__ __launch_bounds__(256, 2) void k_direct_conv_patch(DirectParams P, int patch, const int8_t *__restrict__ xt,
+                                                              const int8_t *__restrict__ wt, int32_t *__restrict__ y) {
+  static_assert(WM * WN == 4, "four waves per workgroup");
+  constexpr int BRF = WM * RM, BTF = WN * NT;
+  extern __shared__ __attribute__((aligned(16))) uint8_t patch_lds[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int wm = wave / WN, wn = wave % WN;
+  const int nkb = P.Kp >> 4, ntb = (P.npix + 15) >> 4, ncb = P.Cp >> 6;
+  const int gy = (nkb + BRF - 1) / BRF, gz = (ntb + BTF - 1) / BTF;
+  const int pb = ((blockIdx.x >> 3) / gy) * 8 + (blockIdx.x & 7);
+  if (pb >= gz) return;                            // block-uniform: the grid is padded to a multiple of 8 pixel blocks
+  // the last row blocks are shifted to end with the tensor (rows computed twice are stored twice, the same values); the host
+  // takes RM <= nkb
+  const int kb0 = min((int)((blockIdx.x >> 3) % gy) * BRF + wm * RM, nkb - RM), tb0 = pb * BTF;
+  const int taps = P.r * P.r, total = taps * ncb;
+
+  // where output pixel `pix` (clamped to the last one) starts in a channel block of xt, in pixels
+  auto pixel_origin = [&](int pix) -> int {
+    pix = min(pix, P.npix - 1);
+    const int n = pix / (P.Ho * P.Wo), rem = pix - n * (P.Ho * P.Wo);
+    const int oy = rem / P.Wo, ox = rem - oy * P.Wo;
+    return (n * P.Hp + oy) * P.Wp + ox;
+  };
+  // the patch: from the first pixel's origin to the last tap of the last pixel (at most `patch` pixels: patch_pixels())
+  // (the divisions run on the vector unit; the results are the same in all lanes)
+  const int o0 = __builtin_amdgcn_readfirstlane(pixel_origin(tb0 * 16));
+  const int len = __builtin_amdgcn_readfirstlane(min(pixel_origin(tb0 * 16 + 16 * BTF - 1) - o0 + (P.r - 1) * (P.Wp + 1) + 1, patch));
+  const int pieces = (len + 15) >> 4;              // KiB
+  const uint32_t buffer = (uint32_t)((patch + 15) >> 4) * 1024u;
+  const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t *)patch_lds;
+  const size_t block_bytes = (size_t)P.N * P.Hp * P.Wp * 64;
+  auto fetch_patch = [&](int cb) {                 // this wave's share; lanes past the end repeat the last 16 bytes
+    const int8_t *src = xt + (size_t)cb * block_bytes + (size_t)o0 * 64;
+    for (int piece = wave; piece < pieces; piece += 4)
+      load_to_lds16(src, min((uint32_t)(piece * 1024 + lane * 16), (uint32_t)(len * 64 - 16)),
+                    __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(cb & 1) * buffer + (uint32_t)piece * 1024u));
+  };
+
+  uint32_t b_at[NT];                               // LDS offset of this lane's pixel and channel slice at tap (0, 0)
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+    b_at[nt] = (uint32_t)(pixel_origin((tb0 + wn * NT + nt) * 16 + (lane & 15)) - o0) * 64u + (uint32_t)(lane >> 4) * 16u;
+
+  // weights: consecutive in memory in the order of the steps; D register sets, the one a step has used is refilled for the
+  // step D later (past the last step the last one's weights are fetched again and not used)
+  const int8_t *a_next = wt + (size_t)kb0 * 1024;
+  const uint32_t a_step = (uint32_t)nkb * 1024u, a_lane = (uint32_t)lane * 16u;
+  int a_left = total - 1;
+  auto load_a = [&](v4i (&a)[RM]) {
+#pragma unroll
+    for (int rm = 0; rm < RM; ++rm) a[rm] = *(const v4i *)(a_next + rm * 1024 + a_lane);
+    a_next += a_left > 0 ? a_step : 0u;
+    --a_left;
+  };
+
+  fetch_patch(0);
+  v4i a[D][RM];
+#pragma unroll
+  for (int d = 0; d < D; ++d) load_a(a[d]);
+
+  v4i acc[RM][NT];
+#pragma unroll
+  for (int rm = 0; rm < RM; ++rm)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[rm][nt] = (v4i){0, 0, 0, 0};
+
+  int tap = 0, tj = 0, cb = 0;
+  uint32_t tap_off = 0;                            // LDS offset of the tap, this block's buffer included
+  const uint32_t row_skip = (uint32_t)(P.Wp - P.r + 1) * 64u;
+  auto step = [&](v4i (&aset)[RM]) {
+    if (tap == 0) {                                // everybody's share of this block's patch has landed; nobody reads the other buffer
+      wait_vmcnt<0>();
+      __syncthreads();
+      if (cb + 1 < ncb) fetch_patch(cb + 1);
+      tap_off = (uint32_t)(cb & 1) * buffer;
+    }
+    v4i b[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) b[nt] = *(const v4i *)(patch_lds + (b_at[nt] + tap_off));
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int rm = 0; rm < RM; ++rm) acc[rm][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aset[rm], b[nt], acc[rm][nt], 0, 0, 0);
+    load_a(aset);
+    tap_off += 64;
+    if (++tj == P.r) { tj = 0; tap_off += row_skip - 64u; }
+    if (++tap == taps) { tap = tj = 0; ++cb; }
+  };
+  int it = 0;
+  for (; it + D <= total; it += D)
+#pragma unroll
+    for (int d = 0; d < D; ++d) step(a[d]);
+#pragma unroll
+  for (int d = 0; d < D - 1; ++d)
+    if (it + d < total) step(a[d]);
+
+  // a lane holds rows 16 kb + 4 (lane / 16) + j of pixel 16 tb + lane % 16
+  const size_t plane = (size_t)P.Ho * P.Wo;
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    const int pix = (tb0 + wn * NT + nt) * 16 + (lane & 15);
+    if (pix >= P.npix) continue;
+    const int n = pix / (P.Ho * P.Wo), rem = pix - n * (P.Ho * P.Wo);
+    int32_t *ypix = y + (size_t)n * P.K * plane + rem;
+#pragma unroll
+    for (int rm = 0; rm < RM; ++rm)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int k = (kb0 + rm) * 16 + 4 * (lane >> 4) + j;
         if (k < P.K) ypix[(size_t)k * plane] = acc[rm][nt][j];
       }
   }

@@ -39,6 +39,17 @@ CASES = [
     (1, 20, 24, 19, 19, 7, 3),        # 7 x 7 filter
     (2, 130, 136, 64, 64, 3, 1),      # 128 x 128 blocks with ragged rows
     (1, 8, 8, 6, 6, 5, 0),            # 2 x 2 outputs
+    # staged patches: 64 x 256, 32 x 256, 64 x 128 and 32 x 64 blocks; blocks that span rows and images, one and more channel
+    # blocks, row blocks shifted back to the end of the filters
+    (5, 130, 200, 47, 61, 3, 1),
+    (8, 70, 24, 113, 111, 3, 1),
+    (8, 40, 72, 81, 40, 3, 1),
+    (3, 65, 17, 31, 29, 5, 2),
+    (9, 130, 16, 7, 7, 3, 1),
+    (4, 65, 40, 5, 3, 3, 1),          # several images in one pixel block
+    (2, 20, 90, 40, 170, 7, 3),
+    (1, 130, 24, 12, 700, 3, 1),      # a patch larger than LDS
+    (1, 20, 130, 70, 1100, 3, 1),     # the same with more work
 ]
 
 
