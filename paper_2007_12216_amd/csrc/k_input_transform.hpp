@@ -25,113 +25,115 @@ namespace rnswino {
 
 constexpr int K1_CPW = 2;
 
+// What the kernel reads, in the order in which it reads it, built once with the plan (the pointers per call).  The fields
+// up to `th` are fetched together at entry: scattered over the layer's full parameter block, they took three dependent fetches
+// of the launch's argument memory (about 500 cycles each) before the first pixel was asked for, and the divisions as many
+// again.  256 channels at 56 x 56 (800 blocks): 2000 cycles from entry to the last load, now 900; whole layer 23.4 -> 22.1 us,
+// 5 x 5 128 channels at 28 x 28 18.8 -> 17.1, 100 channels at 57 x 43 20.0 -> 18.3, VGG16 stack at batch 1 397 -> 379.
+struct K1Params {
+  const int8_t *x;
+  int8_t *V;
+  const int8_t *KB;           // (B^T kron B^T) mod p, [n][CB1][KS1][planes][64 lanes][16]
+  int units, per_xcd;         // T * Cp/64 (of the packed problem), and the grid's x extent / 8
+  int ncb, split;             // split: one residue per block (blockIdx.y)
+  FastDiv by_ncb, by_tw, by_th;
+  int C, H, W, HW, m, pad, t, tw, th;
+  int n, T, Tg, Cq, cq_shift;
+  long long total;            // N * C * H * W
+  int CB1, P2, RP1;
+  Residue8 res[8];
+  double inv_pd[8];           // 16-bit moduli
+};
+
+// bytes [lo, hi) of an 8-byte word that starts at byte `at`: a mask
+__device__ __forceinline__ unsigned long long byte_range(int lo, int hi, int at) {
+  const int l = min(max(lo - at, 0), 8), h = min(max(hi - at, 0), 8);
+  const unsigned long long below_h = h == 8 ? ~0ull : (1ull << (8 * h)) - 1, below_l = l == 8 ? ~0ull : (1ull << (8 * l)) - 1;
+  return below_h & ~below_l;
+}
+
 // PACK: the layer packs TL tiles into one 64-channel block (plan.hpp): block channel c' holds channel c' % Cq of tile
 // (c' / Cq) * Tg + tau, so every gathered row segment has its own tile origin; everything after the gather is the same.
 template <int KS1, bool WIDE, bool PACK>
-__global__ __launch_bounds__(256) void k1_input_transform(KParams P, const int8_t *__restrict__ x,
-                                                           int8_t *__restrict__ V) {
+__global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
   constexpr int ROWS = KS1 == 1 ? 8 : KS1 == 2 ? 10 : KS1 == 3 ? 12 : 16;   // largest t with this many steps
   constexpr int PL = WIDE ? 2 : 1;
   constexpr int CROW = (4 * KS1 + 1) * 16;   // bytes per channel in LDS: one 16-byte pad, so that the 16 channels a
                                              // fragment read touches fall into different banks
   __shared__ __attribute__((aligned(16))) uint8_t xs[64 * CROW];
+  // (fetched here, all together, instead of one after the other where they are used)
+  asm volatile("" ::"s"(P.x), "s"(P.KB), "s"(P.units), "s"(P.per_xcd), "s"(P.ncb), "s"(P.split), "s"(P.by_ncb.mul), "s"(P.by_ncb.shift),
+               "s"(P.by_tw.mul), "s"(P.by_tw.shift), "s"(P.by_th.mul), "s"(P.by_th.shift), "s"(P.C), "s"(P.H), "s"(P.W), "s"(P.HW),
+               "s"(P.m), "s"(P.pad), "s"(P.t), "s"(P.tw), "s"(P.th), "s"(P.n), "s"(P.total));
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: table addresses stay scalar
   const int lane = threadIdx.x & 63, g = lane >> 4;
-  const int ncb = P.Cp >> 6;
-  const int i0 = gridDim.y == 1 ? 0 : blockIdx.y, i1 = gridDim.y == 1 ? P.n : i0 + 1;   // residues of this block
-  const int unit = xcd_chunked(blockIdx.x, gridDim.x, P.Tg * ncb);  // neighbouring tiles (shared image lines) on one XCD
-  if (unit < 0) return;
-  const int cb = unit % ncb, tau = unit / ncb;     // tau: GEMM column (a group of TL tiles when PACK)
-  {
-    const long long total = (long long)P.N * P.C * P.H * P.W;
-    // origin, tile and channel of the row segment that goes to block channel cblk
-    struct Seg { long long base; int y0, x0; bool ok; };
-    auto tile_origin = [&](int tile, int ch) -> Seg {
-      const int trow = tile / P.tw;
-      const int tx = tile - trow * P.tw, img = trow / P.th, ty = trow - img * P.th;
-      Seg sg;
-      sg.y0 = ty * P.m - P.pad;
-      sg.x0 = tx * P.m - P.pad;
-      sg.ok = tile < P.T;
-      sg.base = (((long long)img * P.C + ch) * P.H + sg.y0) * P.W + sg.x0;   // byte index of (ch, row y0, column x0)
-      return sg;
-    };
-    const Seg block_seg = tile_origin(PACK ? 0 : tau, PACK ? 0 : cb * 64);   // not packed: one tile, block-uniform
-    auto segment = [&](int cblk) -> Seg {
-      if (PACK) {
-        Seg sg = tile_origin((cblk / P.Cq) * P.Tg + tau, cblk % P.Cq);
-        sg.ok = sg.ok && (cblk % P.Cq) < P.C;
-        return sg;
-      }
-      Seg sg = block_seg;
-      sg.ok = cb * 64 + cblk < P.C;
-      sg.base += (cblk * P.H) * P.W;               // 64 * H * W stays far below 2^31
-      return sg;
-    };
-    // columns b of the 16-pixel row segment that lie inside the image and inside the tile: [lo, hi)
-    auto column_mask = [&](int x0, uint32_t (&cmask)[4]) {
-      const int lo = x0 < 0 ? -x0 : 0;
-      const int hi = min(P.t, P.W - x0);
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        uint32_t mk = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) mk |= ((4 * d + e) >= lo && (4 * d + e) < hi) ? (0xFFu << (8 * e)) : 0u;
-        cmask[d] = mk;
-      }
-    };
-    // A thread's NT row segments are requested together and only then masked and written to LDS (one after the
-    // other, each load would be waited for in turn: three memory latencies instead of one).
-    constexpr int NT = (64 * ROWS + 255) / 256;
-    v4i val[NT];
-    long long b0[NT];
-    int sx0[NT];
-    int state[NT];                                     // 0: nothing to load, 1: plain 16-byte load, 2: tensor edge
+  const int ncb = P.ncb;
+  const int i0 = P.split ? blockIdx.y : 0, i1 = P.split ? i0 + 1 : P.n;   // residues of this block
+  // neighbouring tiles (shared image lines) on one XCD, see xcd_chunked()
+  const int unit = (int)(blockIdx.x & 7) * P.per_xcd + (int)(blockIdx.x >> 3);
+  if (unit >= P.units) return;
+  const int tau = (int)fast_div((uint32_t)unit, P.by_ncb), cb = unit - tau * ncb;   // tau: GEMM column (a group of TL tiles when PACK)
+  // first image row and column of a tile and the byte index of (channel ch, that row, that column)
+  struct Origin { long long base; int y0, x0; };
+  auto tile_origin = [&](int tile, int ch) -> Origin {
+    const int trow = (int)fast_div((uint32_t)tile, P.by_tw), tx = tile - trow * P.tw;
+    const int img = (int)fast_div((uint32_t)trow, P.by_th), ty = trow - img * P.th;
+    Origin o;
+    o.y0 = ty * P.m - P.pad;
+    o.x0 = tx * P.m - P.pad;
+    o.base = ((long long)img * P.C + ch) * P.HW + (long long)o.y0 * P.W + o.x0;
+    return o;
+  };
+  // A thread's NT row segments are requested together and only then masked and written to LDS (one after the
+  // other, each load would be waited for in turn: three memory latencies instead of one).  A segment that begins before
+  // the tensor or ends behind it is loaded from the nearest 16 bytes inside and moved into place afterwards (byte by byte,
+  // the few blocks it happens in took half as long again as all others, and the next kernel waits for them).
+  constexpr int NT = (64 * ROWS + 255) / 256;
+  const bool tiny = P.total < 16;                    // the tensor itself is smaller than a load
+  v4i val[NT];
+  bool there[NT];
+  int moved[NT];                                     // how far the load was moved, in bytes
+  unsigned long long mask0[PACK ? NT : 1], mask1[PACK ? NT : 1];   // columns inside the image and inside the tile
+  if constexpr (PACK) {
 #pragma unroll
     for (int k = 0; k < NT; ++k) {
       const int task = threadIdx.x + 256 * k;
-      const int c = task / ROWS, a = task - c * ROWS;
-      const Seg sg = segment(c);
-      const int gy = sg.y0 + a;
+      const int cblk = task / ROWS, a = task - cblk * ROWS;
+      const int ch = cblk & (P.Cq - 1), tile = (cblk >> P.cq_shift) * P.Tg + tau;
+      const Origin o = tile_origin(min(tile, P.T - 1), ch);
+      const int gy = o.y0 + a;
+      const long long from = o.base + (long long)a * P.W, at = max(min(from, P.total - 16), 0ll);
+      moved[k] = (int)(from - at);                   // rows inside the image: their segments overlap the tensor or are masked
+      there[k] = task < 64 * ROWS && tile < P.T && ch < P.C && a < P.t && gy >= 0 && gy < P.H;
       val[k] = (v4i){0, 0, 0, 0};
-      b0[k] = sg.base + (long long)a * P.W;
-      sx0[k] = sg.x0;
-      state[k] = 0;
-      if (task < 64 * ROWS && sg.ok && a < P.t && gy >= 0 && gy < P.H)
-        state[k] = (b0[k] >= 0 && b0[k] + 16 <= total) ? 1 : 2;
-      if (state[k] == 1) __builtin_memcpy(&val[k], x + b0[k], 16);      // one unaligned 16-byte load
+      if (there[k] && !tiny) __builtin_memcpy(&val[k], P.x + at, 16);       // one unaligned 16-byte load
+      mask0[k] = byte_range(max(-o.x0, 0), min(P.t, P.W - o.x0), 0);
+      mask1[k] = byte_range(max(-o.x0, 0), min(P.t, P.W - o.x0), 8);
     }
-#pragma unroll
-    for (int k = 0; k < NT; ++k) {
-      if (state[k] == 2) {                             // first / last bytes of the tensor
-        uint32_t wv[4] = {0, 0, 0, 0};
-        for (int b = 0; b < 16; ++b) {
-          const long long o = b0[k] + b;
-          if (o >= 0 && o < total) wv[b >> 2] |= (uint32_t)(uint8_t)x[o] << (8 * (b & 3));
-        }
-        val[k] = (v4i){(int)wv[0], (int)wv[1], (int)wv[2], (int)wv[3]};
-      }
-    }
+  } else {
+    const Origin o = tile_origin(tau, cb * 64);
+    // offsets from the origin that a 16-byte load may start at: [lo, hi] (rows outside the image are excluded
+    // separately, so saturating the bounds to 32 bits changes nothing)
+    const int lo = (int)min(max(-o.base, 0ll), 0x7FFFFFFFll);
+    const int hi = (int)max(min(P.total - 16 - o.base, 0x7FFFFFFFll), (long long)lo);
+    const int a_lo = max(-o.y0, 0), a_count = max(min(P.t, P.H - o.y0) - a_lo, 0);     // rows inside the image
+    const int chans = P.C - cb * 64;
+    const int8_t *xb = P.x + o.base;
 #pragma unroll
     for (int k = 0; k < NT; ++k) {
       const int task = threadIdx.x + 256 * k;
-      const int c = task / ROWS, a = task - c * ROWS;
-      uint32_t cmask[4];
-      column_mask(sx0[k], cmask);
-      val[k][0] &= cmask[0]; val[k][1] &= cmask[1]; val[k][2] &= cmask[2]; val[k][3] &= cmask[3];
-      // the first RP1 bytes of the segment are the row's slots (the slots past t * RP1 are never written: their
-      // table entries are zero, and any byte times zero is zero)
-      if (task < 64 * ROWS && a < P.t) {
-        uint32_t *row = (uint32_t *)(xs + c * CROW + a * P.RP1);
-        row[0] = (uint32_t)val[k][0];
-        if (P.RP1 > 4) row[1] = (uint32_t)val[k][1];
-        if (P.RP1 > 8) row[2] = (uint32_t)val[k][2];
-        if (P.RP1 > 12) row[3] = (uint32_t)val[k][3];
-      }
+      const int cblk = task / ROWS, a = task - cblk * ROWS;
+      const int from = cblk * P.HW + a * P.W, at = min(max(from, lo), hi);     // 64 * H * W stays far below 2^31
+      moved[k] = tiny ? (int)o.base + from : from - at;
+      there[k] = (256 * (k + 1) <= 64 * ROWS || task < 64 * ROWS) && cblk < chans && (uint32_t)(a - a_lo) < (uint32_t)a_count;
+      val[k] = (v4i){0, 0, 0, 0};
+      if (there[k] && !tiny) __builtin_memcpy(&val[k], xb + (uint32_t)at, 16);        // one unaligned 16-byte load
     }
+    mask0[0] = byte_range(max(-o.x0, 0), min(P.t, P.W - o.x0), 0);
+    mask1[0] = byte_range(max(-o.x0, 0), min(P.t, P.W - o.x0), 8);
   }
   // This wave's work: steps (residue i, column-block group cg) with cg = wave, wave + 4, ...  The table fragments
-  // of step k+1 are requested before step k is multiplied; those of step 0 before the barrier, so that their
+  // of step k+1 are requested before step k is multiplied; those of step 0 behind the gather's own loads, so that their
   // latency overlaps the gather.  A step's position is kept as wave-uniform scalars and advanced incrementally
   // (no divisions, and only a few scalar operations per column block: every instruction counts here).
   const int ncg = (P.CB1 + K1_CPW - 1) / K1_CPW;
@@ -160,10 +162,57 @@ __global__ __launch_bounds__(256) void k1_input_transform(KParams P, const int8_
   // address costs the vector unit next to nothing.  stride_pt = bytes between consecutive transform points.
   const uint32_t stride_pt = (uint32_t)(ncb * PL * 1024);
   const uint32_t lane_store = (uint32_t)(lane & 15) * stride_pt + g * 16;   // 16 points * ncb KiB: far below 2^32
-  int8_t *const Vtile = V + ((size_t)(tau >> 4) * (size_t)(P.n * P.P2) * ncb + cb) * (PL * 1024) + (tau & 15) * 64;
+  int8_t *const Vtile = P.V + ((size_t)(tau >> 4) * (size_t)(P.n * P.P2) * ncb + cb) * (PL * 1024) + (tau & 15) * 64;
   v4i bf[K1_CPW][KS1][PL], bn[K1_CPW][KS1][PL];
   Pos cur = {i0, wave};
+  Residue8 rf = P.res[i0], rn = rf;                   // the constants travel with the fragments
   if (nsteps > 0) load_table(cur, bf);
+  asm volatile("" ::"s"(rf.inv), "s"(rf.quot_bias), "s"(rf.neg_p), "s"(rf.acc_bias));
+  __builtin_amdgcn_sched_barrier(0);
+  if (tiny) {
+#pragma unroll
+    for (int k = 0; k < NT; ++k)
+      if (there[k]) {
+        uint32_t wv[4] = {0, 0, 0, 0};
+        for (int b = 0; b < (int)P.total; ++b) wv[b >> 2] |= (uint32_t)(uint8_t)P.x[b] << (8 * (b & 3));
+        val[k] = (v4i){(int)wv[0], (int)wv[1], (int)wv[2], (int)wv[3]};
+      }
+  }
+#pragma unroll
+  for (int k = 0; k < NT; ++k) {
+    if (there[k] && moved[k] != 0) {
+      // byte b of the segment is byte b + moved of what was loaded (16 and more bytes apart: everything is masked)
+      unsigned long long w0 = (uint32_t)val[k][0] | (unsigned long long)(uint32_t)val[k][1] << 32;
+      unsigned long long w1 = (uint32_t)val[k][2] | (unsigned long long)(uint32_t)val[k][3] << 32;
+      const int s = min(abs(moved[k]), 15);
+      if (moved[k] > 0) {
+        if (s >= 8) { w0 = w1; w1 = 0; }
+        if (s & 7) { w0 = w0 >> (8 * (s & 7)) | w1 << (64 - 8 * (s & 7)); w1 >>= 8 * (s & 7); }
+      } else {
+        if (s >= 8) { w1 = w0; w0 = 0; }
+        if (s & 7) { w1 = w1 << (8 * (s & 7)) | w0 >> (64 - 8 * (s & 7)); w0 <<= 8 * (s & 7); }
+      }
+      val[k] = (v4i){(int)(uint32_t)w0, (int)(uint32_t)(w0 >> 32), (int)(uint32_t)w1, (int)(uint32_t)(w1 >> 32)};
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < NT; ++k) {
+    const int task = threadIdx.x + 256 * k;
+    const int cblk = task / ROWS, a = task - cblk * ROWS;
+    const unsigned long long m0 = mask0[PACK ? k : 0], m1 = mask1[PACK ? k : 0];
+    val[k][0] &= (int)(uint32_t)m0; val[k][1] &= (int)(uint32_t)(m0 >> 32);
+    val[k][2] &= (int)(uint32_t)m1; val[k][3] &= (int)(uint32_t)(m1 >> 32);
+    // the first RP1 bytes of the segment are the row's slots (the slots past t * RP1 are never written: their
+    // table entries are zero, and any byte times zero is zero); RP1 is 4 or 8, 12, 12, 16 for KS1 = 1, 2, 3, 4
+    if (task < 64 * ROWS && a < P.t) {
+      const int rp = KS1 == 1 ? P.RP1 : KS1 == 4 ? 16 : 12;
+      uint32_t *row = (uint32_t *)(xs + cblk * CROW + a * rp);
+      row[0] = (uint32_t)val[k][0];
+      if (rp > 4) row[1] = (uint32_t)val[k][1];
+      if (rp > 8) row[2] = (uint32_t)val[k][2];
+      if (rp > 12) row[3] = (uint32_t)val[k][3];
+    }
+  }
   __syncthreads();
   if (nsteps <= 0) return;
   // All loads issued so far are awaited here, explicitly: otherwise the compiler, merging this entry state with the
@@ -179,14 +228,14 @@ __global__ __launch_bounds__(256) void k1_input_transform(KParams P, const int8_
   // One step with the fragments in `b`, while those of the following step travel into `bnext`.  The loop below
   // alternates the two register sets instead of copying one into the other: a copy would have to wait for every
   // memory operation issued before it, the step's own stores included.
-  auto do_step = [&](int step, v4i (&b)[K1_CPW][KS1][PL], v4i (&bnext)[K1_CPW][KS1][PL]) {
+  auto do_step = [&](int step, v4i (&b)[K1_CPW][KS1][PL], v4i (&bnext)[K1_CPW][KS1][PL], const Residue8 &rc, Residue8 &rnext) {
     const int i = cur.i, cg = cur.cg;
     advance(cur);
-    if (step + 1 < nsteps) load_table(cur, bnext);
-    const int p = P.p[i];
-    const float inv = in_vgpr(P.inv_p[i]), qb = in_vgpr(P.quot_bias[i]);
-    const double invd = P.inv_pd[i];
-    const int a0 = WIDE ? 0 : P.acc_bias[i];         // see biased_lowbyte()
+    if (step + 1 < nsteps) { load_table(cur, bnext); rnext = P.res[cur.i]; }
+    const int p = -rc.neg_p;
+    const float inv = in_vgpr(rc.inv), qb = in_vgpr(rc.quot_bias);
+    const double invd = WIDE ? P.inv_pd[i] : 0.0;
+    const int a0 = WIDE ? 0 : rc.acc_bias;           // see biased_lowbyte()
     const v4i start = (v4i){a0, a0, a0, a0};
 #pragma unroll
     for (int cc = 0; cc < K1_CPW; ++cc) {
@@ -239,8 +288,8 @@ __global__ __launch_bounds__(256) void k1_input_transform(KParams P, const int8_
     }
   };
   for (int step = 0; step < nsteps; step += 2) {
-    do_step(step, bf, bn);
-    if (step + 1 < nsteps) do_step(step + 1, bn, bf);
+    do_step(step, bf, bn, rf, rn);
+    if (step + 1 < nsteps) do_step(step + 1, bn, bf, rn, rf);
   }
 }
 

@@ -146,6 +146,14 @@ KParams make_params(const rnswino_plan_t *pl) {
   return P;
 }
 
+// ---- the kernels' own parameter blocks (pointers are filled in per call) ----
+struct LayerParams {
+  KParams k;
+  K1Params k1;
+};
+
+K1Params make_k1(const Dims &d, const KParams &P);
+
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 inline size_t elem_bytes(const Dims &d) { return d.wide ? 2 : 1; }
 inline size_t v_bytes(const Dims &d) { return (size_t)d.n * d.P2 * d.Tp * d.Cp * elem_bytes(d); }
@@ -197,6 +205,28 @@ K1Choice choose_k1(const Dims &d) {
   c.gx = (unsigned)((units + 7) / 8 * 8);
   c.gy = (unsigned)(units >= 512 ? 1 : d.n);
   return c;
+}
+
+K1Params make_k1(const Dims &d, const KParams &P) {
+  const K1Choice c = choose_k1(d);
+  K1Params q;
+  std::memset(&q, 0, sizeof(q));
+  q.KB = P.KB;
+  q.units = d.Tg * (d.Cp / 64);
+  q.per_xcd = (int)(c.gx / 8);
+  q.ncb = d.Cp / 64;
+  q.split = c.gy > 1;
+  q.by_ncb = make_fast_div((uint32_t)q.ncb); q.by_tw = make_fast_div((uint32_t)d.tw); q.by_th = make_fast_div((uint32_t)d.th);
+  q.C = d.C; q.H = d.H; q.W = d.W; q.HW = d.H * d.W; q.m = d.m; q.pad = d.pad; q.t = d.t; q.tw = d.tw; q.th = d.th;
+  q.n = d.n; q.T = d.T; q.Tg = d.Tg; q.Cq = d.Cq;
+  while ((1 << q.cq_shift) < d.Cq) ++q.cq_shift;
+  q.total = (long long)d.N * d.C * d.H * d.W;
+  q.CB1 = d.CB1; q.P2 = d.P2; q.RP1 = d.RP1;
+  for (int i = 0; i < d.n; ++i) {
+    q.res[i] = {P.inv_p[i], P.quot_bias[i], -P.p[i], P.acc_bias[i]};
+    q.inv_pd[i] = P.inv_pd[i];
+  }
+  return q;
 }
 
 // NTB = 16-tile column blocks per wave (1, 2 or 4, the smallest that covers Tp up to 64); KS = contraction steps
@@ -327,11 +357,13 @@ K3Choice choose_k3(const Dims &d, const KParams &P, int n_cus, int epi) {
   X(4, 1, false, false) X(4, 2, false, false)
 
 // ---- K1 ----  (dry: only report whether the instantiation exists)
-bool launch_k1(const Dims &d, const KParams &P, const int8_t *x, int8_t *V, hipStream_t st, Timing tm, bool dry = false) {
+bool launch_k1(const Dims &d, const K1Params &P1, const int8_t *x, int8_t *V, hipStream_t st, Timing tm, bool dry = false) {
   const K1Choice c = choose_k1(d);
   const dim3 grid(c.gx, c.gy);
+  K1Params P = P1;
+  P.x = x; P.V = V;
 #define RNSW_X(ks, wd, pk) \
-  if (c.KS1 == ks && c.wide == wd && c.pack == pk) { if (!dry) launch(k1_input_transform<ks, wd, pk>, grid, 0, st, tm, P, x, V); return true; }
+  if (c.KS1 == ks && c.wide == wd && c.pack == pk) { if (!dry) launch(k1_input_transform<ks, wd, pk>, grid, 0, st, tm, P); return true; }
   RNSW_K1_TABLE(RNSW_X)
 #undef RNSW_X
   return false;
@@ -408,7 +440,8 @@ int conv2d_impl(const rnswino_plan_t *plan, const int8_t *x_dev, const void *U_d
   if (((uintptr_t)U_dev | (uintptr_t)workspace_dev | (uintptr_t)y_dev) & 15) return RNSWINO_E_INVALID;
   if ((uintptr_t)act_dev & 3) return RNSWINO_E_INVALID;
   const Dims &d = plan->dims;
-  KParams P = *(const KParams *)plan->kparams;    // per call only the output mode differs
+  const LayerParams &L = *(const LayerParams *)plan->kparams;
+  KParams P = L.k;                                // per call only the output mode differs
   P.epi = epi; P.shift = shift; P.act = act_dev;
   hipStream_t st = (hipStream_t)stream;
   int8_t *Vp = (int8_t *)workspace_dev;
@@ -420,7 +453,7 @@ int conv2d_impl(const rnswino_plan_t *plan, const int8_t *x_dev, const void *U_d
     t3.start = (hipEvent_t)events[4]; t3.stop = (hipEvent_t)events[5];
   }
   // (rnswino_plan() has checked that all three instantiations exist)
-  if (!launch_k1(d, P, x_dev, Vp, st, t1) || !launch_k2(d, plan->desc.flags, P, (const int8_t *)U_dev, Vp, Op, st, t2) ||
+  if (!launch_k1(d, L.k1, x_dev, Vp, st, t1) || !launch_k2(d, plan->desc.flags, P, (const int8_t *)U_dev, Vp, Op, st, t2) ||
       !launch_k3(d, P, plan->n_cus, Op, y_dev, st, t3))
     return RNSWINO_E_UNSUPPORTED;
   return launch_status();
@@ -483,12 +516,15 @@ int rnswino_plan(rnswino_plan_t **out, const rnswino_desc_t *desc) {
       else (void)hipGetLastError();
     }
   }
-  pl->kparams = new (std::nothrow) KParams(make_params(pl));
-  if (!pl->kparams) { (void)rnswino_plan_destroy(pl); return RNSWINO_E_INVALID; }
+  LayerParams *params = new (std::nothrow) LayerParams;
+  pl->kparams = params;
+  if (!params) { (void)rnswino_plan_destroy(pl); return RNSWINO_E_INVALID; }
+  params->k = make_params(pl);
+  params->k1 = make_k1(d, params->k);
   {
     // every kernel the layer would launch, in each output mode, must be an instantiation that exists
-    KParams P = *(const KParams *)pl->kparams;
-    bool ok = launch_k1(d, P, nullptr, nullptr, nullptr, Timing(), true) && launch_k2(d, pl->desc.flags, P, nullptr, nullptr, nullptr, nullptr, Timing(), true);
+    KParams P = params->k;
+    bool ok = launch_k1(d, params->k1, nullptr, nullptr, nullptr, Timing(), true) && launch_k2(d, pl->desc.flags, P, nullptr, nullptr, nullptr, nullptr, Timing(), true);
     for (int epi = 0; epi < 3 && ok; ++epi) {
       P.epi = epi;
       ok = launch_k3(d, P, pl->n_cus, nullptr, nullptr, nullptr, Timing(), true);
@@ -503,7 +539,7 @@ int rnswino_plan_destroy(rnswino_plan_t *plan) {
   if (!plan) return RNSWINO_E_INVALID;
   int rc = RNSWINO_OK;
   if (plan->d_tables && hipFree(plan->d_tables) != hipSuccess) { (void)hipGetLastError(); rc = RNSWINO_E_HIP; }
-  delete (KParams *)plan->kparams;
+  delete (LayerParams *)plan->kparams;
   delete plan;
   return rc;
 }
@@ -525,7 +561,7 @@ int rnswino_filter_transform(const rnswino_plan_t *plan, const int8_t *w_dev, vo
   if (plan->device < 0) return RNSWINO_E_NO_DEVICE;
   if (!on_plan_device(plan)) return RNSWINO_E_INVALID;
   const Dims &d = plan->dims;
-  const KParams P = *(const KParams *)plan->kparams;
+  const KParams P = ((const LayerParams *)plan->kparams)->k;
   hipStream_t st = (hipStream_t)stream;
   // one block per 16 rows x 64 channels, its (residue, 16-point block) items split over y until there are about four
   // blocks per compute unit (512 x 512, t = 10: 46 us with one block per compute unit, 35.5 with two, 32 with four, 33 with
@@ -587,7 +623,7 @@ int rnswino_conv2d_static(const rnswino_plan_t *plan, const int8_t *x_dev, const
 int64_t rnswino_plan_describe(const rnswino_plan_t *plan, int32_t output_mode, char *host_out, size_t capacity) {
   if (!plan || output_mode < 0 || output_mode > 2) return RNSWINO_E_INVALID;
   const Dims &d = plan->dims;
-  const KParams &P = *(const KParams *)plan->kparams;
+  const KParams &P = ((const LayerParams *)plan->kparams)->k;
   const K1Choice c1 = choose_k1(d);
   const K2Choice c2 = choose_k2(d, plan->desc.flags);
   const K3Choice c3 = choose_k3(d, P, plan->n_cus, output_mode);
