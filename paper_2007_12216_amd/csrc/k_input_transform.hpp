@@ -16,7 +16,7 @@
 // step in flight while the current one is multiplied.  Accumulator rows are channels 4g+j, so the four channel
 // groups u give one lane exactly the 16 bytes of V it has to store (channel order of layout.hpp).
 // 16-bit moduli: the table has a high and a low byte plane, V = (256 * sum_h + sum_l) mod p, stored as two planes.
-// Grid: x = T * Cp/64 rounded up to a multiple of 8 (see xcd_chunked), y = n (one residue per block) or 1 (the block
+// Grid: x = T * Cp/64 rounded up to a multiple of 8 (see kernels_common.hpp), y = n (one residue per block) or 1 (the block
 // walks over all residues with the same gathered patch); 256 threads; 64 * (4*KS1 + 1) * 16 bytes of LDS.
 #pragma once
 #include "kernels_common.hpp"
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const int ncb = P.ncb;
   const int i0 = P.split ? blockIdx.y : 0, i1 = P.split ? i0 + 1 : P.n;   // residues of this block
-  // neighbouring tiles (shared image lines) on one XCD, see xcd_chunked()
+  // neighbouring tiles (shared image lines) on one XCD, see kernels_common.hpp
   const int unit = (int)(blockIdx.x & 7) * P.per_xcd + (int)(blockIdx.x >> 3);
   if (unit >= P.units) return;
   const int tau = (int)fast_div((uint32_t)unit, P.by_ncb), cb = unit - tau * ncb;   // tau: GEMM column (a group of TL tiles when PACK)

@@ -26,16 +26,42 @@
 // workloads.  Otherwise (KParams::fastcrt == 2) the same sum is taken in binary64 over accumulators that start at 2^22,
 // which is exact enough for every result the moduli can represent.
 //
-// Block = one unit of 16 consecutive (k, tile) pairs and four 16-output row blocks rb = 4*blockIdx.y + wave; every
-// wave loads the O operand itself (the copies hit in L1): a wave-uniform row of O plus a 32-bit lane offset per
-// word.  No LDS.
-// Grid: x = ceil(K*T/16) rounded up to a multiple of 8, y = ceil(RB3/4); 256 threads.
+// Block = one unit of 16 consecutive (k, tile) pairs and the 16-output row blocks rb = 4*blockIdx.y + wave, + 4*gridDim.y, ...
+// The four waves share the unit's O operand through LDS, each loading every fourth point group (a wave-uniform row of O plus a
+// 32-bit lane offset per word).
+// Grid: x = ceil(K*T/16) rounded up to a multiple of 8, y = 1 .. ceil(RB3/4); 256 threads.
 // 16-bit moduli: table and O are two byte planes each; three accumulators as in the GEMM.
 #pragma once
 #include "kernels_common.hpp"
 
 namespace rnswino {
 
+
+// What the kernels read, built once with the plan (the pointers and the output mode per call); the block kernel fetches the
+// fields up to `rb_step` together at entry, see K1Params.  With that, divisions by multiplication and the operand shared
+// through LDS: 128 channels 5 x 5 at 28 x 28 17.1 -> 13.3 us a layer, VGG16 stack at batch 1 379 -> 363, batch 8 864 -> 846.
+struct K3Params {
+  const uint32_t *O;
+  const int8_t *KA;           // (A^T kron A^T) (P/p_i)^-1 mod p  [n][RB3][KS3][planes][64 lanes][16]
+  int32_t *y;
+  int8_t *act;                // int8 output of modes 1 and 2
+  int units, per_xcd, npairs; // units of 16 pairs (streaming kernel: of 16 tiles of one row), grid x / 8, rows x tiles
+  FastDiv by_Tg, by_tw, by_th, by_ntb;
+  int Tg, tl_shift, T, Q, Tp, tw, th, RB3, rb_step;
+  int n, m, K, Ho, Wo;
+  // fused re-quantisation (chained layers): 0 = store int32 y, 1 = store int8 clamp(y >> shift), 2 = the same after a 2x2
+  // stride-2 max-pool
+  int epi, shift;
+  // conversion out of the RNS, see KParams
+  int fastcrt, crt24, quot32, acc0;
+  uint32_t crt_sum0, prod_mod32;
+  float crt_fs0, inv_m;
+  double crt_fs0d;
+  uint32_t crt_c[8];
+  float inv_p[8];
+  int p[8], bias_p[8];
+  double inv_pd[8];
+};
 
 // Where the output tile of a (k, tile) pair starts in y (or in the int8 activation plane): computed once per pair,
 // the row blocks of the pair only add their own row and column to it.
@@ -45,12 +71,12 @@ struct TilePos {
   bool ok;           // false for padding tiles and padding pairs
 };
 
-__device__ __forceinline__ TilePos tile_position(const KParams &P, int k, int tau) {
+__device__ __forceinline__ TilePos tile_position(const K3Params &P, int k, int tau) {
   TilePos tp;
   tp.ok = tau < P.T;
-  const int trow = tau / P.tw;
+  const int trow = (int)fast_div((uint32_t)tau, P.by_tw);
   const int tx = tau - trow * P.tw;
-  const int img = trow / P.th;
+  const int img = (int)fast_div((uint32_t)trow, P.by_th);
   const int ty = trow - img * P.th;
   tp.oy0 = ty * P.m;
   tp.ox0 = tx * P.m;
@@ -64,7 +90,7 @@ __device__ __forceinline__ TilePos tile_position(const KParams &P, int k, int ta
 // chained layers, int8 clamp(y >> shift) with an optional 2x2 max-pool (the shift is monotone, so it commutes with
 // the max).  Must be called by all lanes of a wave (the pooled mode exchanges rows between lanes).
 template <int NRES, bool CRT24, bool QUOT32>
-__device__ __forceinline__ void crt_convert(const KParams &P, const uint32_t (&w)[NRES][4], int (&val)[4]) {
+__device__ __forceinline__ void crt_convert(const K3Params &P, const uint32_t (&w)[NRES][4], int (&val)[4]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     uint32_t sum = 0;
@@ -101,7 +127,7 @@ struct FastCrt {
   uint32_t sum0;
 };
 template <int NRES>
-__device__ __forceinline__ void crt_convert_fast(const KParams &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
+__device__ __forceinline__ void crt_convert_fast(const K3Params &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     uint32_t sum = fc.sum0;
@@ -119,7 +145,7 @@ __device__ __forceinline__ void crt_convert_fast(const KParams &P, const FastCrt
 // result in [-(P-1)/2, (P-1)/2] (the host checks its bound against 1/(2P)), so layers at the edge of the dynamic
 // range and plans with an unchecked range take this form.
 template <int NRES>
-__device__ __forceinline__ void crt_convert_fast64(const KParams &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
+__device__ __forceinline__ void crt_convert_fast64(const K3Params &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     uint32_t sum = fc.sum0;
@@ -136,7 +162,7 @@ __device__ __forceinline__ void crt_convert_fast64(const KParams &P, const FastC
 
 // Constants of the fast conversion in vector registers, loaded once per kernel.
 template <int NRES, bool FAST>
-__device__ __forceinline__ FastCrt fast_crt_constants(const KParams &P) {
+__device__ __forceinline__ FastCrt fast_crt_constants(const K3Params &P) {
   FastCrt fc;
   fc.fs0 = FAST ? in_vgpr(P.crt_fs0) : 0.0f;
   fc.sum0 = FAST ? in_vgpr(P.crt_sum0) : 0u;
@@ -146,7 +172,7 @@ __device__ __forceinline__ FastCrt fast_crt_constants(const KParams &P) {
 }
 
 template <int NRES, bool FAST>
-__device__ __forceinline__ void k3_convert(const KParams &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
+__device__ __forceinline__ void k3_convert(const K3Params &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
   if (FAST) {
     if (P.fastcrt == 2) crt_convert_fast64<NRES>(P, fc, w, val);   // uniform
     else crt_convert_fast<NRES>(P, fc, w, val);
@@ -162,11 +188,11 @@ __device__ __forceinline__ void k3_convert(const KParams &P, const FastCrt &fc, 
 // and first column v (0 or 4) inside the tile and their offset `off` from the tile's origin in the stored plane do
 // not depend on the unit and are kept in registers by the caller.  Same modes as k3_convert_and_store; the host
 // selects this path for int32 output only when Wo is a multiple of 4.  Must be called by all lanes of a wave.
-__device__ __forceinline__ void k3_store_m8(const KParams &P, const int (&val)[4], int u, int v, uint32_t off,
-                                            const TilePos &tp, int32_t *__restrict__ y) {
+__device__ __forceinline__ void k3_store_m8(const K3Params &P, const int (&val)[4], int u, int v, uint32_t off,
+                                            const TilePos &tp) {
   const bool inside = tp.ok && tp.oy0 + u < P.Ho && tp.ox0 + v < P.Wo;
   if (P.epi == 0) {
-    if (inside) *(v4i *)(y + tp.origin + off) = (v4i){val[0], val[1], val[2], val[3]};
+    if (inside) *(v4i *)(P.y + tp.origin + off) = (v4i){val[0], val[1], val[2], val[3]};
   } else if (P.epi == 1) {
     uint32_t packed = 0;
 #pragma unroll
@@ -189,12 +215,12 @@ __device__ __forceinline__ void k3_store_m8(const KParams &P, const int (&val)[4
 }
 
 template <int NRES, bool FAST>
-__device__ __forceinline__ void k3_convert_and_store(const KParams &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int rb, int g,
-                                                     const TilePos &tp, int32_t *__restrict__ y) {
+__device__ __forceinline__ void k3_convert_and_store(const K3Params &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int rb, int g,
+                                                     const TilePos &tp) {
   int val[4];
   k3_convert<NRES, FAST>(P, fc, w, val);
   const int m = P.m, mm = m * m;
-  const float inv_m = 1.0f / (float)m;
+  const float inv_m = P.inv_m;
   const int o0 = 16 * rb + 4 * g;
   if (P.epi == 1 && (((m & 3) != 0) || (P.Wo & 1))) {
     // any other tile size or an odd row length: the four outputs may sit in two rows of the tile and at any byte
@@ -240,7 +266,7 @@ __device__ __forceinline__ void k3_convert_and_store(const KParams &P, const Fas
     return;
   }
   if (!tp.ok || o0 >= mm) return;
-  int32_t *ytile = y + tp.origin;
+  int32_t *ytile = P.y + tp.origin;
   if (((m & 3) == 0) && ((P.Wo & 3) == 0)) {   // four consecutive outputs stay in one row, 16-byte aligned
     const int u = (int)(((float)o0 + 0.5f) * inv_m);
     const int v = o0 - u * m;
@@ -258,70 +284,95 @@ __device__ __forceinline__ void k3_convert_and_store(const KParams &P, const Fas
 
 // FAST: the conversion with unreduced accumulators (the host launches it when KParams::fastcrt is set).
 template <int NRES, int KS3, bool WIDE, bool FAST>
-__global__ __launch_bounds__(256) void k3_inverse_crt(KParams P, const uint32_t *__restrict__ O,
-                                                       int32_t *__restrict__ y) {
+__global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
   constexpr int PL = WIDE ? 2 : 1;
   constexpr int NACC = WIDE ? 3 : 1;
+  constexpr bool AHEAD = NRES * KS3 * PL <= 16;    // the table fragments of a row block fit registers: requested ahead of their use
+  __shared__ __attribute__((aligned(16))) uint32_t o_lds[NRES * KS3 * PL * 256];   // [i][s][plane][lane][4 words]
+  asm volatile("" ::"s"(P.O), "s"(P.KA), "s"(P.units), "s"(P.per_xcd), "s"(P.npairs), "s"(P.by_Tg.mul), "s"(P.by_Tg.shift), "s"(P.by_tw.mul),
+               "s"(P.by_tw.shift), "s"(P.by_th.mul), "s"(P.by_th.shift), "s"(P.Tg), "s"(P.tl_shift), "s"(P.T), "s"(P.Q), "s"(P.Tp), "s"(P.tw),
+               "s"(P.th), "s"(P.RB3), "s"(P.rb_step));
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: row block and table addresses stay scalar
   const int lane = threadIdx.x & 63, g = lane >> 4;
-  const int rb = blockIdx.y * 4 + wave;            // this wave's block of 16 outputs
-  if (rb >= P.RB3) return;
   // A unit is 16 consecutive (k, tile) pairs of the flattened K x T index space (no padding tiles: a unit may span
   // several k's).  Workgroups go to the 8 XCDs round-robin by id; neighbouring units share 128-byte lines of O, so
   // each XCD gets one contiguous chunk of the units (grid.x is a multiple of 8).
   // (For layers that pack TL tiles into a channel block, GEMM row kg = k * TL + tile / Tg and GEMM column tile % Tg.)
-  const int npairs = P.Kg * P.Tg;                  // below 2^31 (checked when the plan is made)
-  const int unit = xcd_chunked(blockIdx.x, gridDim.x, (npairs + 15) >> 4);
-  if (unit < 0) return;
-  const int pair = unit * 16 + (lane & 15);
-  const bool pair_ok = pair < npairs;
-  const int kg = pair_ok ? pair / P.Tg : 0;
-  const int taug = pair_ok ? pair - kg * P.Tg : P.Tg;   // a padding lane's loads stay inside row 0
-  const int k = kg / P.TL;
-  const int tau = pair_ok ? (kg % P.TL) * P.Tg + taug : P.T;   // tau >= T marks a lane without output
+  const int unit = (int)(blockIdx.x & 7) * P.per_xcd + (int)(blockIdx.x >> 3);
+  if (unit >= P.units) return;
+  const int pair = min(unit * 16 + (lane & 15), P.npairs - 1);         // a padding lane repeats the last pair
+  const int kg = (int)fast_div((uint32_t)pair, P.by_Tg), taug = pair - kg * P.Tg;
 
   // O is [Kp][n][Q][Tp] words (x PL planes) and smaller than 4 GiB: the address of a word is a wave-uniform row
-  // (residue, point group 16s + e) plus a 32-bit lane offset (k, lane group 4g, tile).  Point groups >= Q of the
-  // last contraction step are clamped to Q - 1: the table is zero there, so whatever is read does not count.
-  const uint32_t rowstride = (uint32_t)P.Tp * PL;
-  const uint32_t lane_off = (uint32_t)(kg * P.n * P.Q) * rowstride + (uint32_t)taug * PL;
-  uint32_t voff[KS3][4];
+  // (residue) plus a 32-bit lane offset (k, point group, tile).  Word e of a lane's operand is point group 16s + 4g + e; wave e
+  // loads it for everybody (one load instruction touches four rows of 64 bytes and costs the address unit as much as a
+  // 16-byte load of 256: loading all of it four times over took 1800 cycles per block at two contraction steps and 4700 at
+  // four).  Point groups >= Q of the last contraction step are clamped to Q - 1: the table is zero there, so whatever is read
+  // does not count.
+  const uint32_t row_bytes = (uint32_t)P.Tp * (4 * PL);
+  const uint32_t lane_off = (uint32_t)(kg * NRES * P.Q) * row_bytes + (uint32_t)taug * (4 * PL);
+  uint32_t voff[KS3];
 #pragma unroll
-  for (int s = 0; s < KS3; ++s)
+  for (int s = 0; s < KS3; ++s) voff[s] = lane_off + (uint32_t)min(16 * s + 4 * g + wave, P.Q - 1) * row_bytes;
+  v2i mine[NRES][KS3];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) voff[s][e] = lane_off + (uint32_t)min(16 * s + 4 * g + e, P.Q - 1) * rowstride;
-  v4i of[NRES][KS3][PL];
+  for (int i = 0; i < NRES; ++i) {
+    const char *row = (const char *)P.O + (size_t)((uint32_t)(i * P.Q) * row_bytes);
 #pragma unroll
-  for (int i = 0; i < NRES; ++i) {       // residue by residue, the order in which the products below consume them
-    const uint32_t *row = O + (size_t)(i * P.Q) * rowstride;
+    for (int s = 0; s < KS3; ++s) {
+      if (WIDE) mine[i][s] = *(const v2i *)(row + voff[s]);
+      else mine[i][s][0] = *(const int *)(row + voff[s]);
+    }
+  }
+  int rb = blockIdx.y * 4 + wave;                  // this wave's first block of 16 outputs
+  v4i ka[AHEAD ? NRES : 1][AHEAD ? KS3 : 1][PL];
+  const uint32_t lane16 = (uint32_t)lane * 16u;
+  auto table = [&](int i, int r, int s, int pl) -> v4i {
+    return *(const v4i *)(P.KA + (size_t)((((uint32_t)i * P.RB3 + r) * KS3 + s) * PL + pl) * 1024 + lane16);
+  };
+  auto load_ka = [&](int r) {
+    if constexpr (AHEAD)
+#pragma unroll
+      for (int i = 0; i < NRES; ++i)
+#pragma unroll
+        for (int s = 0; s < KS3; ++s)
+#pragma unroll
+          for (int pl = 0; pl < PL; ++pl) ka[i][s][pl] = table(i, r, s, pl);
+  };
+  load_ka(min(rb, P.RB3 - 1));
+  const int k = kg >> P.tl_shift;
+  const int tau = unit * 16 + (lane & 15) < P.npairs ? (kg - (k << P.tl_shift)) * P.Tg + taug : P.T;   // tau >= T marks a lane without output
+  const TilePos tp = tile_position(P, k, tau);
+  const FastCrt fc = fast_crt_constants<NRES, FAST>(P);
+#pragma unroll
+  for (int i = 0; i < NRES; ++i)
 #pragma unroll
     for (int s = 0; s < KS3; ++s)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (WIDE) {
-          const v2i two = *(const v2i *)(row + voff[s][e]);
-          of[i][s][0][e] = two[0];
-          of[i][s][PL - 1][e] = two[1];
-        } else {
-          of[i][s][0][e] = (int)row[voff[s][e]];
-        }
-      }
-  }
+      for (int pl = 0; pl < PL; ++pl) o_lds[((i * KS3 + s) * PL + pl) * 256 + lane * 4 + wave] = (uint32_t)mine[i][s][pl];
+  __syncthreads();
+  if (rb >= P.RB3) return;
+  v4i of[NRES][KS3][PL];
+#pragma unroll
+  for (int i = 0; i < NRES; ++i)
+#pragma unroll
+    for (int s = 0; s < KS3; ++s)
+#pragma unroll
+      for (int pl = 0; pl < PL; ++pl) of[i][s][pl] = *(const v4i *)(o_lds + ((i * KS3 + s) * PL + pl) * 256 + lane * 4);
 
-  const FastCrt fc = fast_crt_constants<NRES, FAST>(P);
-  {
+  for (; rb < P.RB3; rb += P.rb_step) {
     uint32_t w[NRES][4];
 #pragma unroll
     for (int i = 0; i < NRES; ++i) {
       v4i acc[NACC];
 #pragma unroll
       for (int a = 0; a < NACC; ++a) acc[a] = FAST ? (v4i){P.acc0, P.acc0, P.acc0, P.acc0} : (v4i){0, 0, 0, 0};
-      const int8_t *ka = P.KA + (((size_t)i * P.RB3 + rb) * KS3) * (1024 * PL) + lane * 16;
 #pragma unroll
       for (int s = 0; s < KS3; ++s) {
-        const v4i ah = *(const v4i *)(ka + (size_t)s * (1024 * PL));
+        v4i ah, al;
+        if constexpr (AHEAD) { ah = ka[i][s][0]; al = ka[i][s][PL - 1]; }
+        else { ah = table(i, rb, s, 0); al = WIDE ? table(i, rb, s, PL - 1) : ah; }
         if (WIDE) {
-          const v4i al = *(const v4i *)(ka + (size_t)s * (1024 * PL) + 1024);
           acc[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ah, of[i][s][0], acc[0], 0, 0, 0);
           acc[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ah, of[i][s][PL - 1], acc[1], 0, 0, 0);
           acc[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al, of[i][s][0], acc[1], 0, 0, 0);
@@ -343,7 +394,8 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(KParams P, const uint32_t 
         }
       }
     }
-    k3_convert_and_store<NRES, FAST>(P, fc, w, rb, g, tile_position(P, k, tau), y);
+    if (rb + P.rb_step < P.RB3) load_ka(rb + P.rb_step);
+    k3_convert_and_store<NRES, FAST>(P, fc, w, rb, g, tp);
   }
 }
 
@@ -358,13 +410,12 @@ constexpr int K3_STREAM_BLOCKS = 1024;  // four resident blocks per CU (register
 // M8: 8 x 8 output tiles (four row blocks), the usual case: where a lane's outputs go inside the tile is computed once
 // per kernel instead of once per row block, and the table fragments of a row block sit at immediate LDS offsets.
 template <int NRES, int KS3, bool FAST, bool M8>
-__global__ __launch_bounds__(256) void k3_inverse_crt_stream(KParams P, const uint32_t *__restrict__ O,
-                                                              int32_t *__restrict__ y) {
+__global__ __launch_bounds__(256) void k3_inverse_crt_stream(K3Params P) {
   extern __shared__ __attribute__((aligned(16))) uint8_t ka_lds[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: unit arithmetic stays scalar
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const int ntb = P.Tp >> 4;
-  const int nunits = P.Kg * ntb;                   // below 2^31 (checked when the plan is made); rows and columns are the GEMM's
+  const int nunits = P.units;                      // (k, block of 16 tiles), the GEMM's rows and columns
   const int nwaves = gridDim.x * 4;
   {
     const int bytes = NRES * P.RB3 * KS3 * 1024;
@@ -383,8 +434,8 @@ __global__ __launch_bounds__(256) void k3_inverse_crt_stream(KParams P, const ui
     for (int e = 0; e < 4; ++e) voff[s][e] = (uint32_t)min(16 * s + 4 * g + e, P.Q - 1) * (uint32_t)P.Tp + (lane & 15);
 
   auto load_o = [&](int u, v4i (&of)[NRES][KS3]) {
-    const int k = u / ntb, tb = u - k * ntb;
-    const uint32_t *base = O + (size_t)k * P.n * P.Q * P.Tp + tb * 16;
+    const int k = (int)fast_div((uint32_t)u, P.by_ntb), tb = u - k * ntb;
+    const uint32_t *base = P.O + (size_t)k * NRES * P.Q * P.Tp + tb * 16;
 #pragma unroll
     for (int i = 0; i < NRES; ++i) {
       const uint32_t *row = base + (size_t)(i * P.Q) * P.Tp;
@@ -405,8 +456,8 @@ __global__ __launch_bounds__(256) void k3_inverse_crt_stream(KParams P, const ui
   const uint32_t m8_step = P.epi == 2 ? (uint32_t)(P.Wo >> 1) : (uint32_t)(2 * P.Wo);
   const uint32_t m8_off0 = P.epi == 2 ? (uint32_t)(m8_v >> 1) : (uint32_t)(m8_u0 * P.Wo + m8_v);
   auto do_unit = [&](int u, v4i (&o)[NRES][KS3]) {
-    const int kg = u / ntb, taug = (u - kg * ntb) * 16 + (lane & 15);
-    const int k = kg / P.TL, tau = taug < P.Tg ? (kg % P.TL) * P.Tg + taug : P.T;   // packed layers: see plan.hpp
+    const int kg = (int)fast_div((uint32_t)u, P.by_ntb), taug = (u - kg * ntb) * 16 + (lane & 15);
+    const int k = kg >> P.tl_shift, tau = taug < P.Tg ? (kg - (k << P.tl_shift)) * P.Tg + taug : P.T;   // packed layers: see plan.hpp
     const TilePos tp = tile_position(P, k, tau);
     if (M8) {
       // not unrolled: with the four row blocks in one basic block the scheduler requests all their table fragments
@@ -429,7 +480,7 @@ __global__ __launch_bounds__(256) void k3_inverse_crt_stream(KParams P, const ui
         }
         int val[4];
         k3_convert<NRES, FAST>(P, fc, w, val);
-        k3_store_m8(P, val, 2 * rb + m8_u0, m8_v, m8_off0 + rb * m8_step, tp, y);
+        k3_store_m8(P, val, 2 * rb + m8_u0, m8_v, m8_off0 + rb * m8_step, tp);
       }
       return;
     }
@@ -449,7 +500,7 @@ __global__ __launch_bounds__(256) void k3_inverse_crt_stream(KParams P, const ui
         for (int j = 0; j < 4; ++j)
           w[i][j] = FAST ? (uint32_t)acc[j] : mod_near_plus_p(acc[j], P.inv_p[i], -P.p[i], P.bias_p[i]);
       }
-      k3_convert_and_store<NRES, FAST>(P, fc, w, rb, g, tp, y);
+      k3_convert_and_store<NRES, FAST>(P, fc, w, rb, g, tp);
     }
   };
   v4i oa[NRES][KS3];

@@ -57,20 +57,11 @@ struct KParams {
   uint32_t crt_sum0;          // undoes, modulo 2^32, the accumulators' start and the bias of the quotient
   float crt_fs0;              // minus the start's share of the quotient
   double crt_fs0d;            // the same in binary64
-  // fused re-quantisation in the inverse-transform kernel (chained layers): 0 = store int32 y,
-  // 1 = store int8 clamp(y >> shift), 2 = the same after a 2x2 stride-2 max-pool
-  int epi, shift;
-  int8_t *act;                // int8 output of modes 1 and 2
 };
 
-// Workgroups are handed to the 8 XCDs (each with its own L2) round-robin by linear workgroup id.  For a grid
-// whose x extent is a multiple of 8, this maps block x to a work item such that each XCD gets one contiguous
-// chunk of the items: neighbours (which share input lines) then share an L2.  Items >= count are padding.
-__device__ __forceinline__ int xcd_chunked(int x, int gx, int count) {
-  const int per = gx >> 3;                 // blocks per XCD
-  const int item = (x & 7) * per + (x >> 3);
-  return item < count ? item : -1;
-}
+// Workgroups are handed to the 8 XCDs (each with its own L2) round-robin by linear workgroup id.  A grid whose x extent is a
+// multiple of 8 takes item (x % 8) * (gx / 8) + x / 8 in block x, so that each XCD gets one contiguous chunk of the items:
+// neighbours (which share input lines) then share an L2.  Items past the count are padding.
 
 // ---- residues of 8-bit moduli -------------------------------------------------------------------
 

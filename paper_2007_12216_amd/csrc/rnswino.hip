@@ -150,9 +150,8 @@ KParams make_params(const rnswino_plan_t *pl) {
 struct LayerParams {
   KParams k;
   K1Params k1;
+  K3Params k3[3];             // per output mode
 };
-
-K1Params make_k1(const Dims &d, const KParams &P);
 
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 inline size_t elem_bytes(const Dims &d) { return d.wide ? 2 : 1; }
@@ -199,7 +198,7 @@ K1Choice choose_k1(const Dims &d) {
   c.wide = d.wide != 0;
   c.pack = d.TL > 1;
   const long long units = (long long)d.Tg * (d.Cp / 64);
-  // x: multiple of 8 (see xcd_chunked()); y: one block per residue, or one block for all residues when there are
+  // x: multiple of 8 (see kernels_common.hpp); y: one block per residue, or one block for all residues when there are
   // enough units to fill the chip (the pixel gather is then done once instead of n times; measured on the VGG16
   // stack, two blocks per CU are already enough for that to win)
   c.gx = (unsigned)((units + 7) / 8 * 8);
@@ -322,10 +321,34 @@ K3Choice choose_k3(const Dims &d, const KParams &P, int n_cus, int epi) {
     c.m8 = c.fast && d.m == 8 && (epi == 0 ? (d.Wo & 3) == 0 : (d.Wo & 1) == 0);
   } else {
     const long long units = ((long long)d.Kg * d.Tg + 15) / 16;
-    c.gx = (unsigned)((units + 7) / 8 * 8);       // x multiple of 8: see xcd_chunked()
-    c.gy = (unsigned)((d.RB3 + 3) / 4);
+    c.gx = (unsigned)((units + 7) / 8 * 8);       // x multiple of 8: see kernels_common.hpp
+    // y: the blocks of a unit each load its operand, so no more of them than it takes to have two blocks per compute unit
+    // (28 x 28, m = 14: 512 units 47.9 us a layer with one block each, 48.9 with four; 128 units 61.0 and 57.5)
+    const long long most = (d.RB3 + 3) / 4, want = (512 + c.gx - 1) / c.gx;
+    c.gy = (unsigned)(want < most ? want : most);
   }
   return c;
+}
+
+K3Params make_k3(const Dims &d, const KParams &P, int n_cus, int epi) {
+  const K3Choice c = choose_k3(d, P, n_cus, epi);
+  K3Params q;
+  std::memset(&q, 0, sizeof(q));
+  q.KA = P.KA;
+  q.npairs = d.Kg * d.Tg;                          // below 2^31 (checked when the plan is made)
+  q.units = c.stream ? d.Kg * (d.Tp / 16) : (q.npairs + 15) / 16;
+  q.per_xcd = (int)(c.gx / 8);
+  q.by_Tg = make_fast_div((uint32_t)d.Tg); q.by_tw = make_fast_div((uint32_t)d.tw); q.by_th = make_fast_div((uint32_t)d.th);
+  q.by_ntb = make_fast_div((uint32_t)(d.Tp / 16));
+  q.Tg = d.Tg; q.T = d.T; q.Q = d.Q; q.Tp = d.Tp; q.tw = d.tw; q.th = d.th; q.RB3 = d.RB3; q.rb_step = 4 * (int)c.gy;
+  while ((1 << q.tl_shift) < d.TL) ++q.tl_shift;
+  q.n = d.n; q.m = d.m; q.K = d.K; q.Ho = d.Ho; q.Wo = d.Wo; q.epi = epi;
+  q.fastcrt = P.fastcrt; q.crt24 = P.crt24; q.quot32 = P.quot32; q.acc0 = P.acc0; q.crt_sum0 = P.crt_sum0; q.prod_mod32 = P.prod_mod32;
+  q.crt_fs0 = P.crt_fs0; q.crt_fs0d = P.crt_fs0d; q.inv_m = 1.0f / (float)d.m;
+  for (int i = 0; i < d.n; ++i) {
+    q.crt_c[i] = P.crt_c[i]; q.inv_p[i] = P.inv_p[i]; q.p[i] = P.p[i]; q.bias_p[i] = P.bias_p[i]; q.inv_pd[i] = P.inv_pd[i];
+  }
+  return q;
 }
 
 // The instantiations that exist, as tables: the launches below and rnswino_kernel_variants() both expand them.
@@ -389,20 +412,23 @@ bool launch_k2(const Dims &d, uint32_t flags, const KParams &P, const int8_t *U,
 }
 
 // ---- K3 ----
-bool launch_k3(const Dims &d, const KParams &P, int n_cus, const uint32_t *O, int32_t *y, hipStream_t st, Timing tm, bool dry = false) {
-  const K3Choice c = choose_k3(d, P, n_cus, P.epi);
+bool launch_k3(const Dims &d, const LayerParams &L, int n_cus, int epi, int shift, const uint32_t *O, int32_t *y, int8_t *act, hipStream_t st,
+               Timing tm, bool dry = false) {
+  const K3Choice c = choose_k3(d, L.k, n_cus, epi);
   const dim3 grid(c.gx, c.gy);
+  K3Params P = L.k3[epi];
+  P.O = O; P.y = y; P.act = act; P.shift = shift;
   if (c.stream) {
 #define RNSW_X(nres, ks3, fs, e8) \
     if (c.NRES == nres && c.KS3 == ks3 && c.fast == fs && c.m8 == e8) { \
-      if (!dry) launch(k3_inverse_crt_stream<nres, ks3, fs, e8>, grid, c.lds, st, tm, P, O, y); return true; }
+      if (!dry) launch(k3_inverse_crt_stream<nres, ks3, fs, e8>, grid, c.lds, st, tm, P); return true; }
     RNSW_K3S_TABLE(RNSW_X)
 #undef RNSW_X
     return false;
   }
 #define RNSW_X(nres, ks3, wd, fs) \
   if (c.NRES == nres && c.KS3 == ks3 && c.wide == wd && c.fast == fs) { \
-    if (!dry) launch(k3_inverse_crt<nres, ks3, wd, fs>, grid, 0, st, tm, P, O, y); return true; }
+    if (!dry) launch(k3_inverse_crt<nres, ks3, wd, fs>, grid, 0, st, tm, P); return true; }
   RNSW_K3_TABLE(RNSW_X)
 #undef RNSW_X
   return false;
@@ -441,8 +467,6 @@ int conv2d_impl(const rnswino_plan_t *plan, const int8_t *x_dev, const void *U_d
   if ((uintptr_t)act_dev & 3) return RNSWINO_E_INVALID;
   const Dims &d = plan->dims;
   const LayerParams &L = *(const LayerParams *)plan->kparams;
-  KParams P = L.k;                                // per call only the output mode differs
-  P.epi = epi; P.shift = shift; P.act = act_dev;
   hipStream_t st = (hipStream_t)stream;
   int8_t *Vp = (int8_t *)workspace_dev;
   uint32_t *Op = (uint32_t *)((char *)workspace_dev + align256(v_bytes(d)));
@@ -453,8 +477,8 @@ int conv2d_impl(const rnswino_plan_t *plan, const int8_t *x_dev, const void *U_d
     t3.start = (hipEvent_t)events[4]; t3.stop = (hipEvent_t)events[5];
   }
   // (rnswino_plan() has checked that all three instantiations exist)
-  if (!launch_k1(d, L.k1, x_dev, Vp, st, t1) || !launch_k2(d, plan->desc.flags, P, (const int8_t *)U_dev, Vp, Op, st, t2) ||
-      !launch_k3(d, P, plan->n_cus, Op, y_dev, st, t3))
+  if (!launch_k1(d, L.k1, x_dev, Vp, st, t1) || !launch_k2(d, plan->desc.flags, L.k, (const int8_t *)U_dev, Vp, Op, st, t2) ||
+      !launch_k3(d, L, plan->n_cus, epi, shift, Op, y_dev, act_dev, st, t3))
     return RNSWINO_E_UNSUPPORTED;
   return launch_status();
 }
@@ -521,14 +545,11 @@ int rnswino_plan(rnswino_plan_t **out, const rnswino_desc_t *desc) {
   if (!params) { (void)rnswino_plan_destroy(pl); return RNSWINO_E_INVALID; }
   params->k = make_params(pl);
   params->k1 = make_k1(d, params->k);
+  for (int epi = 0; epi < 3; ++epi) params->k3[epi] = make_k3(d, params->k, pl->n_cus, epi);
   {
     // every kernel the layer would launch, in each output mode, must be an instantiation that exists
-    KParams P = params->k;
-    bool ok = launch_k1(d, params->k1, nullptr, nullptr, nullptr, Timing(), true) && launch_k2(d, pl->desc.flags, P, nullptr, nullptr, nullptr, nullptr, Timing(), true);
-    for (int epi = 0; epi < 3 && ok; ++epi) {
-      P.epi = epi;
-      ok = launch_k3(d, P, pl->n_cus, nullptr, nullptr, nullptr, Timing(), true);
-    }
+    bool ok = launch_k1(d, params->k1, nullptr, nullptr, nullptr, Timing(), true) && launch_k2(d, pl->desc.flags, params->k, nullptr, nullptr, nullptr, nullptr, Timing(), true);
+    for (int epi = 0; epi < 3 && ok; ++epi) ok = launch_k3(d, *params, pl->n_cus, epi, 0, nullptr, nullptr, nullptr, nullptr, Timing(), true);
     if (!ok) { (void)rnswino_plan_destroy(pl); return RNSWINO_E_UNSUPPORTED; }
   }
   *out = pl;
