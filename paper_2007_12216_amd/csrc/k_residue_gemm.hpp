@@ -21,9 +21,43 @@
 
 namespace rnswino {
 
+// What the GEMM kernels read, built once with the plan (the pointers per call); the fields up to `slabs` are fetched
+// together at entry, see K1Params.
+struct K2Params {
+  const int8_t *U, *V;
+  uint32_t *O;
+  int xgroup, gy, gz;         // grid order: values of x per group, row blocks, tile blocks
+  FastDiv by_xgroup, by_gy, by_gz, by_Q;
+  int nkb, ntb, ncb;          // row and tile blocks of 16, channel blocks of 64
+  int xs, Q, P2, slabs;       // n * Q, point groups, points, n * P2
+  int Kp, Tp;
+  Residue8 res[8];
+  double inv_pd[8];           // 16-bit moduli
+};
+
+// Work item (x = residue and point group, y = row block, z = tile block) from the linear workgroup id.  Workgroups
+// are handed to the 8 XCDs round-robin by id, so x = 8 * (...) + id % 8 keeps one x on one XCD.  Within an XCD the
+// ids run over `xgroup` values of x first, then y, then z, then the groups of x: the workgroups that share a slice
+// of U (same x and y, along z) or of V (same x and z, along y) follow each other closely enough to find it in the
+// XCD's L2, while `xgroup` different x at a time spread the accesses over the L2's channels.
+struct K2Item { int x, i, q, y, z; };
+__device__ __forceinline__ K2Item k2_item(const K2Params &P, uint32_t id) {
+  K2Item w;
+  const uint32_t r0 = id >> 3, r1 = fast_div(r0, P.by_xgroup), r2 = fast_div(r1, P.by_gy), r3 = fast_div(r2, P.by_gz);
+  w.y = (int)(r1 - r2 * (uint32_t)P.gy);
+  w.z = (int)(r2 - r3 * (uint32_t)P.gz);
+  w.x = (int)((r3 * (uint32_t)P.xgroup + (r0 - r1 * (uint32_t)P.xgroup)) * 8 + (id & 7));
+  w.i = (int)fast_div((uint32_t)w.x, P.by_Q);
+  w.q = w.x - w.i * P.Q;
+  return w;
+}
+#define RNSW_K2_FETCH_ARGUMENTS(P)                                                                                                       \
+  asm volatile("" ::"s"(P.U), "s"(P.V), "s"(P.O), "s"(P.xgroup), "s"(P.gy), "s"(P.gz), "s"(P.by_xgroup.mul), "s"(P.by_xgroup.shift),     \
+               "s"(P.by_gy.mul), "s"(P.by_gy.shift), "s"(P.by_gz.mul), "s"(P.by_gz.shift), "s"(P.by_Q.mul), "s"(P.by_Q.shift), "s"(P.nkb), \
+               "s"(P.ntb), "s"(P.ncb), "s"(P.xs), "s"(P.Q), "s"(P.P2), "s"(P.slabs))
+
 template <int KS, int NTB, int RM, bool WIDE>
-__global__ __launch_bounds__(256) void k2_residue_gemm(KParams P, const int8_t *__restrict__ U,
-                                                        const int8_t *__restrict__ V, uint32_t *__restrict__ O, int xgroup) {
+__global__ __launch_bounds__(256) void k2_residue_gemm(K2Params P) {
   constexpr int PL = WIDE ? 2 : 1;
   constexpr int NACC = WIDE ? 3 : 1;
   constexpr int COLS = 16 * NTB;
@@ -33,30 +67,20 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(KParams P, const int8_t *
   __shared__ __attribute__((aligned(16))) uint32_t tile[ROWS * PITCH];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: slab addresses stay scalar
   const int lane = threadIdx.x & 63;
-  const int nkb = P.Kp >> 4, ntb = P.Tp >> 4, ncb = P.Cp >> 6;
-  // Work item (x = residue and point group, y = row block, z = tile block) from the linear workgroup id.  Workgroups
-  // are handed to the 8 XCDs round-robin by id, so x = 8 * (...) + id % 8 keeps one x on one XCD.  Within an XCD the
-  // ids run over `xgroup` values of x first, then y, then z, then the groups of x: the workgroups that share a slice
-  // of U (same x and y, along z) or of V (same x and z, along y) follow each other closely enough to find it in the
-  // XCD's L2, while `xgroup` different x at a time spread the accesses over the L2's channels.
-  const int gy = (nkb + RM - 1) / RM, gz = (ntb + NTB - 1) / NTB;
-  int rest = blockIdx.x >> 3;
-  const int xi = rest % xgroup;
-  rest /= xgroup;
-  const int by = rest % gy;
-  rest /= gy;
-  const int bz = rest % gz;
-  const int bx = ((rest / gz) * xgroup + xi) * 8 + (blockIdx.x & 7);
-  if (bx >= P.n * P.Q) return;                     // x is padded to a multiple of 8
-  const int i = bx / P.Q, q = bx % P.Q;
+  RNSW_K2_FETCH_ARGUMENTS(P);
+  const int nkb = P.nkb, ntb = P.ntb, ncb = P.ncb;
+  const K2Item item = k2_item(P, blockIdx.x);
+  if (item.x >= P.xs) return;                      // x is padded to a multiple of 8
+  const int i = item.i, q = item.q;
   const int pt = 4 * q + wave;
-  const int kb0 = by * RM, tb0 = bz * NTB;
-  const int p = P.p[i];
-  const float inv = in_vgpr(P.inv_p[i]), qb = in_vgpr(P.quot_bias[i]);
+  const int kb0 = item.y * RM, tb0 = item.z * NTB;
+  const Residue8 rc = P.res[i];
+  const int p = -rc.neg_p;
+  const float inv = in_vgpr(rc.inv), qb = in_vgpr(rc.quot_bias);
   // Up to four steps |sum| <= 256 * 126 * 127 < 2^22 - 2^15: the accumulators may start at acc_bias and skip a conversion
   // per result (biased_lowbyte()).
   const bool biased = !WIDE && ncb <= 4;
-  const int a0 = biased ? P.acc_bias[i] : 0;
+  const int a0 = biased ? rc.acc_bias : 0;
 
   v4i acc[NACC][RM][NTB];
   if (pt < P.P2) {
@@ -66,10 +90,10 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(KParams P, const int8_t *
     const int8_t *Ur[RM], *Vt[NTB];
 #pragma unroll
     for (int rm = 0; rm < RM; ++rm)
-      Ur[rm] = U + ((size_t)slab * nkb + min(kb0 + rm, nkb - 1)) * ncb * (1024 * PL) + lane * 16;
+      Ur[rm] = P.U + ((size_t)slab * nkb + min(kb0 + rm, nkb - 1)) * ncb * (1024 * PL) + lane * 16;
 #pragma unroll
     for (int tb = 0; tb < NTB; ++tb)
-      Vt[tb] = V + ((size_t)min(tb0 + tb, ntb - 1) * (P.n * P.P2) + slab) * ncb * (1024 * PL) + (lane & 15) * 64 + (lane >> 4) * 16;
+      Vt[tb] = P.V + ((size_t)min(tb0 + tb, ntb - 1) * P.slabs + slab) * ncb * (1024 * PL) + (lane & 15) * 64 + (lane >> 4) * 16;
 
     // KS contraction steps from s0 on; the very first step starts the accumulators (no zero fill)
     auto steps = [&](int s0, auto first_tag) {
@@ -165,7 +189,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(KParams P, const int8_t *
   // beyond Tp are left out.
   constexpr int VPR = ROWW / 4;           // 16-byte vectors per tile row
   constexpr int RP = 256 / VPR;           // rows per pass of the block
-  const uint32_t krow = (uint32_t)(P.n * P.Q * P.Tp) * PL;
+  const uint32_t krow = (uint32_t)(P.xs * P.Tp) * PL;
   const int r0 = threadIdx.x / VPR, c4 = threadIdx.x % VPR;
   const int valid_rows = min(ROWS, P.Kp - kb0 * 16);
   const bool vec_ok = tb0 * 16 * PL + 4 * c4 < P.Tp * PL;
@@ -173,7 +197,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(KParams P, const int8_t *
 #pragma unroll
   for (int ps = 0; ps < (ROWS + RP - 1) / RP; ++ps) {
     const int row = ps * RP + r0;
-    if (vec_ok && row < valid_rows) *(v4i *)(O + off) = *(const v4i *)(tile + row * PITCH + 4 * c4);
+    if (vec_ok && row < valid_rows) *(v4i *)(P.O + off) = *(const v4i *)(tile + row * PITCH + 4 * c4);
     off += RP * krow;
   }
 }

@@ -21,7 +21,7 @@
 // kernel has no other vector-memory loads, so the hand count is the whole count.
 // Grid: one-dimensional, as for k2_residue_gemm (x = residue and point group, y = row block, z = tile block).
 #pragma once
-#include "kernels_common.hpp"
+#include "k_residue_gemm.hpp"
 
 namespace rnswino {
 
@@ -40,8 +40,7 @@ __device__ __forceinline__ void load_to_lds16(const void *base, uint32_t lane_of
 }
 
 template <int WM, int WN, int RM, int NT, int S>
-__global__ __launch_bounds__(256) void k2_residue_gemm_lds(KParams P, const int8_t *__restrict__ U,
-                                                            const int8_t *__restrict__ V, uint32_t *__restrict__ O, int xgroup) {
+__global__ __launch_bounds__(256) void k2_residue_gemm_lds(K2Params P) {
   static_assert(WM * WN == 4, "four waves per workgroup");
   constexpr int BRF = WM * RM, BTF = WN * NT;     // U and V fragments per step
   constexpr int NF = BRF + BTF;
@@ -51,21 +50,15 @@ __global__ __launch_bounds__(256) void k2_residue_gemm_lds(KParams P, const int8
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int wm = wave / WN, wn = wave % WN;
-  const int nkb = P.Kp >> 4, ntb = P.Tp >> 4, ncb = P.Cp >> 6;
-  // work item from the linear id: same order as k2_residue_gemm (x on one XCD, groups of x, then rows, then tiles)
-  const int gy = (nkb + BRF - 1) / BRF, gz = (ntb + BTF - 1) / BTF;
-  int rest = blockIdx.x >> 3;
-  const int xi = rest % xgroup;
-  rest /= xgroup;
-  const int by = rest % gy;
-  rest /= gy;
-  const int bz = rest % gz;
-  const int bx = ((rest / gz) * xgroup + xi) * 8 + (blockIdx.x & 7);
-  if (bx >= P.n * P.Q) return;                    // x is padded to a multiple of 8 (block-uniform: no barrier is skipped by part of a block)
-  const int i = bx / P.Q, q = bx % P.Q;
-  const int kb0 = by * BRF, tb0 = bz * BTF;
-  const int p = P.p[i];
-  const float inv = P.inv_p[i];
+  RNSW_K2_FETCH_ARGUMENTS(P);
+  const int nkb = P.nkb, ntb = P.ntb, ncb = P.ncb;
+  const K2Item item = k2_item(P, blockIdx.x);     // same order as k2_residue_gemm
+  if (item.x >= P.xs) return;                     // x is padded to a multiple of 8 (block-uniform: no barrier is skipped by part of a block)
+  const int i = item.i, q = item.q;
+  const int kb0 = item.y * BRF, tb0 = item.z * BTF;
+  const Residue8 rc = P.res[i];
+  const int p = -rc.neg_p;
+  const float inv = rc.inv;
   const int npts = min(4, P.P2 - 4 * q);          // points of this group that exist (t*t need not be a multiple of 4)
   const int total = npts * ncb;                   // steps of the whole block
   const int slab0 = i * P.P2 + 4 * q;
@@ -79,11 +72,11 @@ __global__ __launch_bounds__(256) void k2_residue_gemm_lds(KParams P, const int8
   for (int j = 0; j < LPW; ++j) {
     const int f = min(wave + 4 * j, NF - 1);      // filler slots repeat the last fragment
     if (f < BRF) {
-      base[j] = U + (size_t)min(kb0 + f, nkb - 1) * ncb * 1024;
+      base[j] = P.U + (size_t)min(kb0 + f, nkb - 1) * ncb * 1024;
       slab_stride[j] = (uint32_t)(nkb * ncb) * 1024u;
       lane_off[j] = (uint32_t)lane * 16u;
     } else {
-      base[j] = V + (size_t)min(tb0 + f - BRF, ntb - 1) * (P.n * P.P2) * ncb * 1024;
+      base[j] = P.V + (size_t)min(tb0 + f - BRF, ntb - 1) * P.slabs * ncb * 1024;
       slab_stride[j] = (uint32_t)ncb * 1024u;
       lane_off[j] = (uint32_t)((lane & 15) * 64 + (lane >> 4) * 16);
     }
@@ -173,7 +166,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm_lds(KParams P, const int8
   }
   // O is [Kp][n][Q][Tp] words and smaller than 4 GiB.  A lane holds rows 16 (kb) + 4 (lane / 16) + j and tile
   // 16 (tb) + lane % 16: sixteen lanes write 64 consecutive bytes of a row.
-  const uint32_t krow = (uint32_t)(P.n * P.Q * P.Tp);
+  const uint32_t krow = (uint32_t)(P.xs * P.Tp);
 #pragma unroll
   for (int rm = 0; rm < RM; ++rm) {
     const int kb = kb0 + wm * RM + rm;
@@ -184,7 +177,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm_lds(KParams P, const int8
       if (tb >= ntb) break;
       const uint32_t off = (uint32_t)(kb * 16 + 4 * (lane >> 4)) * krow + (uint32_t)((i * P.Q + q) * P.Tp + tb * 16 + (lane & 15));
 #pragma unroll
-      for (int j = 0; j < 4; ++j) O[off + j * krow] = packed[rm][nt][j];
+      for (int j = 0; j < 4; ++j) P.O[off + j * krow] = packed[rm][nt][j];
     }
   }
 }

@@ -150,6 +150,7 @@ KParams make_params(const rnswino_plan_t *pl) {
 struct LayerParams {
   KParams k;
   K1Params k1;
+  K2Params k2;
   K3Params k3[3];             // per output mode
 };
 
@@ -296,6 +297,23 @@ K2Choice choose_k2(const Dims &d, uint32_t flags) {
   return c;
 }
 
+K2Params make_k2(const Dims &d, const KParams &P, uint32_t flags) {
+  const K2Choice c = choose_k2(d, flags);
+  const int brf = c.lds ? c.WM * c.RM : c.RM, btf = c.lds ? c.WN * c.NTB : c.NTB;
+  K2Params q;
+  std::memset(&q, 0, sizeof(q));
+  q.nkb = d.Kp / 16; q.ntb = d.Tp / 16; q.ncb = d.Cp / 64;
+  q.xgroup = c.xgroup; q.gy = (q.nkb + brf - 1) / brf; q.gz = (q.ntb + btf - 1) / btf;
+  q.by_xgroup = make_fast_div((uint32_t)c.xgroup); q.by_gy = make_fast_div((uint32_t)q.gy); q.by_gz = make_fast_div((uint32_t)q.gz);
+  q.by_Q = make_fast_div((uint32_t)d.Q);
+  q.xs = d.n * d.Q; q.Q = d.Q; q.P2 = d.P2; q.slabs = d.n * d.P2; q.Kp = d.Kp; q.Tp = d.Tp;
+  for (int i = 0; i < d.n; ++i) {
+    q.res[i] = {P.inv_p[i], P.quot_bias[i], -P.p[i], P.acc_bias[i]};
+    q.inv_pd[i] = P.inv_pd[i];
+  }
+  return q;
+}
+
 // stream: the streaming variant (8-bit moduli, table of all residues at most 64 KiB, n * KS3 <= 8: O operand in
 // registers) for layers with 3072 and more units (measured on the VGG16 stack);
 // fast: conversion out of the RNS from unreduced accumulators; m8: the 8 x 8 store path of the streaming variant
@@ -393,19 +411,21 @@ bool launch_k1(const Dims &d, const K1Params &P1, const int8_t *x, int8_t *V, hi
 }
 
 // ---- K2 ----
-bool launch_k2(const Dims &d, uint32_t flags, const KParams &P, const int8_t *U, const int8_t *V, uint32_t *O, hipStream_t st, Timing tm, bool dry = false) {
+bool launch_k2(const Dims &d, uint32_t flags, const K2Params &P2, const int8_t *U, const int8_t *V, uint32_t *O, hipStream_t st, Timing tm, bool dry = false) {
   const K2Choice c = choose_k2(d, flags);
   const dim3 grid(c.blocks);
+  K2Params P = P2;
+  P.U = U; P.V = V; P.O = O;
   if (c.lds) {
 #define RNSW_X(wm_, wn_, rm, ntb, s_) \
     if (c.WM == wm_ && c.WN == wn_ && c.RM == rm && c.NTB == ntb && c.S == s_) { \
-      if (!dry) launch(k2_residue_gemm_lds<wm_, wn_, rm, ntb, s_>, grid, 0, st, tm, P, U, V, O, c.xgroup); return true; }
+      if (!dry) launch(k2_residue_gemm_lds<wm_, wn_, rm, ntb, s_>, grid, 0, st, tm, P); return true; }
     RNSW_K2L_TABLE(RNSW_X)
 #undef RNSW_X
     return false;
   }
 #define RNSW_X(ks, ntb, rm, wd) \
-  if (c.KS == ks && c.NTB == ntb && c.RM == rm && c.wide == wd) { if (!dry) launch(k2_residue_gemm<ks, ntb, rm, wd>, grid, 0, st, tm, P, U, V, O, c.xgroup); return true; }
+  if (c.KS == ks && c.NTB == ntb && c.RM == rm && c.wide == wd) { if (!dry) launch(k2_residue_gemm<ks, ntb, rm, wd>, grid, 0, st, tm, P); return true; }
   RNSW_K2_TABLE(RNSW_X)
 #undef RNSW_X
   return false;
@@ -477,7 +497,7 @@ int conv2d_impl(const rnswino_plan_t *plan, const int8_t *x_dev, const void *U_d
     t3.start = (hipEvent_t)events[4]; t3.stop = (hipEvent_t)events[5];
   }
   // (rnswino_plan() has checked that all three instantiations exist)
-  if (!launch_k1(d, L.k1, x_dev, Vp, st, t1) || !launch_k2(d, plan->desc.flags, L.k, (const int8_t *)U_dev, Vp, Op, st, t2) ||
+  if (!launch_k1(d, L.k1, x_dev, Vp, st, t1) || !launch_k2(d, plan->desc.flags, L.k2, (const int8_t *)U_dev, Vp, Op, st, t2) ||
       !launch_k3(d, L, plan->n_cus, epi, shift, Op, y_dev, act_dev, st, t3))
     return RNSWINO_E_UNSUPPORTED;
   return launch_status();
@@ -545,10 +565,11 @@ int rnswino_plan(rnswino_plan_t **out, const rnswino_desc_t *desc) {
   if (!params) { (void)rnswino_plan_destroy(pl); return RNSWINO_E_INVALID; }
   params->k = make_params(pl);
   params->k1 = make_k1(d, params->k);
+  params->k2 = make_k2(d, params->k, pl->desc.flags);
   for (int epi = 0; epi < 3; ++epi) params->k3[epi] = make_k3(d, params->k, pl->n_cus, epi);
   {
     // every kernel the layer would launch, in each output mode, must be an instantiation that exists
-    bool ok = launch_k1(d, params->k1, nullptr, nullptr, nullptr, Timing(), true) && launch_k2(d, pl->desc.flags, params->k, nullptr, nullptr, nullptr, nullptr, Timing(), true);
+    bool ok = launch_k1(d, params->k1, nullptr, nullptr, nullptr, Timing(), true) && launch_k2(d, pl->desc.flags, params->k2, nullptr, nullptr, nullptr, nullptr, Timing(), true);
     for (int epi = 0; epi < 3 && ok; ++epi) ok = launch_k3(d, *params, pl->n_cus, epi, 0, nullptr, nullptr, nullptr, nullptr, Timing(), true);
     if (!ok) { (void)rnswino_plan_destroy(pl); return RNSWINO_E_UNSUPPORTED; }
   }
