@@ -7,6 +7,17 @@ import torch
 from . import binding as B
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def current_stream(device: torch.device) -> int:
+    """Handle of torch's current stream on `device`.  The raw accessor takes 0.1 us where building a torch.cuda.Stream object
+    takes 2 of the 13 us that a small layer's call costs on the host."""
+    if _raw_stream is not None and device.index is not None:
+        return _raw_stream(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
+
+
 class ConvLayer:
     """One stride-1 int8 convolution layer bound to device buffers.
 
@@ -26,7 +37,7 @@ class ConvLayer:
         self.y = torch.empty((N, K, p.Ho, p.Wo), dtype=torch.int32, device=self.device)
 
     def _stream(self) -> int:
-        return torch.cuda.current_stream(self.device).cuda_stream
+        return current_stream(self.device)
 
     def set_weights(self, w) -> None:
         """w: int8 [K][C][r][r] (numpy or torch); runs the offline filter transform."""

@@ -6,6 +6,7 @@ import numpy as np
 import torch
 
 from . import binding as B
+from .layer import current_stream
 from .select import fused_glue_supported
 
 
@@ -62,7 +63,7 @@ class ConvStack:
         self.y = torch.empty(y_elems, dtype=torch.int32, device=self.device)
 
     def _stream(self) -> int:
-        return torch.cuda.current_stream(self.device).cuda_stream
+        return current_stream(self.device)
 
     def set_weights(self, weights) -> None:
         """weights: one int8 [K][C][r][r] array per layer; runs the offline filter transforms."""
