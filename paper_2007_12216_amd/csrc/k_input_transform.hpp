@@ -26,7 +26,7 @@ namespace rnswino {
 constexpr int K1_CPW = 2;
 
 // What the kernel reads, in the order in which it reads it, built once with the plan (the pointers per call).  The fields
-// up to `th` are fetched together at entry: scattered over the layer's full parameter block, they took three dependent fetches
+// up to `total` are fetched together at entry: scattered over the layer's full parameter block, they took three dependent fetches
 // of the launch's argument memory (about 500 cycles each) before the first pixel was asked for, and the divisions as many
 // again.  256 channels at 56 x 56 (800 blocks): 2000 cycles from entry to the last load, now 900; whole layer 23.4 -> 22.1 us,
 // 5 x 5 128 channels at 28 x 28 18.8 -> 17.1, 100 channels at 57 x 43 20.0 -> 18.3, VGG16 stack at batch 1 397 -> 379.
@@ -38,9 +38,9 @@ struct K1Params {
   int ncb, split;             // split: one residue per block (blockIdx.y)
   FastDiv by_ncb, by_tw, by_th;
   int C, H, W, HW, m, pad, t, tw, th;
-  int n, T, Tg, Cq, cq_shift;
+  int n, CB1, P2;
   long long total;            // N * C * H * W
-  int CB1, P2, RP1;
+  int T, Tg, Cq, cq_shift, RP1;
   Residue8 res[8];
   double inv_pd[8];           // 16-bit moduli
 };
@@ -61,10 +61,12 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
   constexpr int CROW = (4 * KS1 + 1) * 16;   // bytes per channel in LDS: one 16-byte pad, so that the 16 channels a
                                              // fragment read touches fall into different banks
   __shared__ __attribute__((aligned(16))) uint8_t xs[64 * CROW];
+  Residue8 rf = P.res[blockIdx.y], rn = rf;           // constants of the first step's residue (y is 0 where a block takes all)
   // (fetched here, all together, instead of one after the other where they are used)
-  asm volatile("" ::"s"(P.x), "s"(P.KB), "s"(P.units), "s"(P.per_xcd), "s"(P.ncb), "s"(P.split), "s"(P.by_ncb.mul), "s"(P.by_ncb.shift),
-               "s"(P.by_tw.mul), "s"(P.by_tw.shift), "s"(P.by_th.mul), "s"(P.by_th.shift), "s"(P.C), "s"(P.H), "s"(P.W), "s"(P.HW),
-               "s"(P.m), "s"(P.pad), "s"(P.t), "s"(P.tw), "s"(P.th), "s"(P.n), "s"(P.total));
+  asm volatile("" ::"s"(rf.inv), "s"(rf.quot_bias), "s"(rf.neg_p), "s"(rf.acc_bias), "s"(P.x), "s"(P.V), "s"(P.KB), "s"(P.units),
+               "s"(P.per_xcd), "s"(P.ncb), "s"(P.split), "s"(P.by_ncb.mul), "s"(P.by_ncb.shift), "s"(P.by_tw.mul), "s"(P.by_tw.shift),
+               "s"(P.by_th.mul), "s"(P.by_th.shift), "s"(P.C), "s"(P.H), "s"(P.W), "s"(P.HW), "s"(P.m), "s"(P.pad), "s"(P.t), "s"(P.tw),
+               "s"(P.th), "s"(P.n), "s"(P.CB1), "s"(P.P2), "s"(P.total));
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: table addresses stay scalar
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const int ncb = P.ncb;
@@ -165,9 +167,7 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
   int8_t *const Vtile = P.V + ((size_t)(tau >> 4) * (size_t)(P.n * P.P2) * ncb + cb) * (PL * 1024) + (tau & 15) * 64;
   v4i bf[K1_CPW][KS1][PL], bn[K1_CPW][KS1][PL];
   Pos cur = {i0, wave};
-  Residue8 rf = P.res[i0], rn = rf;                   // the constants travel with the fragments
   if (nsteps > 0) load_table(cur, bf);
-  asm volatile("" ::"s"(rf.inv), "s"(rf.quot_bias), "s"(rf.neg_p), "s"(rf.acc_bias));
   __builtin_amdgcn_sched_barrier(0);
   if (tiny) {
 #pragma unroll

@@ -74,13 +74,9 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(K2Params P) {
   const int i = item.i, q = item.q;
   const int pt = 4 * q + wave;
   const int kb0 = item.y * RM, tb0 = item.z * NTB;
-  const Residue8 rc = P.res[i];
-  const int p = -rc.neg_p;
-  const float inv = in_vgpr(rc.inv), qb = in_vgpr(rc.quot_bias);
   // Up to four steps |sum| <= 256 * 126 * 127 < 2^22 - 2^15: the accumulators may start at acc_bias and skip a conversion
-  // per result (biased_lowbyte()).
+  // per result (biased_lowbyte()).  The constants are fetched behind the first step's operands.
   const bool biased = !WIDE && ncb <= 4;
-  const int a0 = biased ? rc.acc_bias : 0;
 
   v4i acc[NACC][RM][NTB];
   if (pt < P.P2) {
@@ -113,6 +109,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(K2Params P) {
       // every load of the step is issued before its first product (left alone, the scheduler sinks the loads
       // between the products to save registers, and the wave then waits for them one at a time)
       __builtin_amdgcn_sched_barrier(0);
+      const int a0 = FIRST && biased ? P.res[i].acc_bias : 0;
       const v4i acc0 = (v4i){a0, a0, a0, a0};
 #pragma unroll
       for (int s = 0; s < KS; ++s)
@@ -139,7 +136,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(K2Params P) {
 #pragma unroll
           for (int tb = 0; tb < NTB; ++tb)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[0][rm][tb][j] = mod_near(acc[0][rm][tb][j], inv, p);
+            for (int j = 0; j < 4; ++j) acc[0][rm][tb][j] = mod_near(acc[0][rm][tb][j], P.res[i].inv, -P.res[i].neg_p);
       }
     };
     steps(0, std::true_type{});
@@ -160,6 +157,9 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(K2Params P) {
   uint32_t lane_byte = (uint32_t)((4 * (lane >> 4)) * PITCH + (lane & 15) * PL) * 4 + wave;
   asm volatile("" : "+v"(lane_byte));
   uint8_t *tile8 = (uint8_t *)tile + lane_byte;
+  const Residue8 rc = P.res[i];
+  const int p = -rc.neg_p;
+  const float inv = in_vgpr(rc.inv), qb = in_vgpr(rc.quot_bias);
   auto exchange = [&](auto biased_tag) {
     constexpr bool BIASED = decltype(biased_tag)::value;
 #pragma unroll
