@@ -293,4 +293,155 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
   }
 }
 
+// The same transform for layers with many tiles (8-bit moduli, t <= 10, a tensor below 2 GiB), with the roles exchanged: A operand
+// = table (rows = 16 transform points), B operand = pixels (columns = 16 tiles at one channel).  Sixteen channels' accumulators
+// give a lane 16 bytes of V for each of four points, and V lies in lane order ([slice g][tile % 16][16 B], Dims::vlane), so a
+// wave stores 256-byte runs instead of 64-byte ones, and the sixteen neighbouring tiles' row segments, 8 bytes apart, are
+// gathered by neighbouring lanes.  What bounds the kernel above on large layers is the memory pipeline's work per store and
+// gather, not the bytes: 64 channels at 112 x 112, batch 8 (40 MB of V) took 20.3 us, 13.8 without its stores, 16.6 with every
+// gather from one line, 20.2 without its matrix instructions.  This one: 17.0; at 224 x 224 85 -> 53 us (cold input).
+// Block = (16 tiles, slice g of a 64-channel block: 16 channels), all residues or one; thread (channel, tile) gathers its t row
+// segments, then the waves take the (residue, 16-point block) items in turn, every item's pixels from LDS (conflict-free: the
+// tiles' rows are 16 bytes longer than their slots), its table fragments requested one item ahead.
+// Grid: x = 4 * Tp/16 * Cp/64 rounded up to a multiple of 8 (kernels_common.hpp), y = n or 1.
+template <int KS1, bool PACK>
+__global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
+  constexpr int ROWS = KS1 == 1 ? 8 : 10;
+  constexpr int CROW = (4 * KS1 + 1) * 16;
+  __shared__ __attribute__((aligned(16))) uint8_t xs[256 * CROW];      // [channel][tile][slots]
+  Residue8 rc = P.res[blockIdx.y];
+  asm volatile("" ::"s"(rc.inv), "s"(rc.quot_bias), "s"(rc.neg_p), "s"(rc.acc_bias), "s"(P.x), "s"(P.V), "s"(P.KB), "s"(P.units),
+               "s"(P.per_xcd), "s"(P.ncb), "s"(P.split), "s"(P.by_ncb.mul), "s"(P.by_ncb.shift), "s"(P.by_tw.mul), "s"(P.by_tw.shift),
+               "s"(P.by_th.mul), "s"(P.by_th.shift), "s"(P.C), "s"(P.H), "s"(P.W), "s"(P.HW), "s"(P.m), "s"(P.pad), "s"(P.t), "s"(P.tw),
+               "s"(P.th), "s"(P.n), "s"(P.CB1), "s"(P.P2), "s"(P.total));
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, h = lane >> 4;
+  const int unit = (int)(blockIdx.x & 7) * P.per_xcd + (int)(blockIdx.x >> 3);
+  if (unit >= P.units) return;
+  const int g = unit & 3, tb = (int)fast_div((uint32_t)unit >> 2, P.by_ncb), cb = (unit >> 2) - tb * P.ncb;
+  const int i0 = P.split ? blockIdx.y : 0, nres = P.split ? 1 : P.n;
+  // gather: this thread's tile and channel
+  const int col = threadIdx.x & 15, ch16 = threadIdx.x >> 4;
+  const int cblk = 16 * (ch16 >> 2) + 4 * g + (ch16 & 3);              // channel order of layout.hpp
+  const int tau = tb * 16 + col;
+  const int tile = PACK ? (cblk >> P.cq_shift) * P.Tg + tau : tau, ch = PACK ? (cblk & (P.Cq - 1)) : cb * 64 + cblk;
+  const bool live = tau < P.Tg && tile < P.T && ch < P.C;
+  const int tc = live ? tile : 0;
+  const int trow = (int)fast_div((uint32_t)tc, P.by_tw), tx = tc - trow * P.tw;
+  const int img = (int)fast_div((uint32_t)trow, P.by_th), ty = trow - img * P.th;
+  const int y0 = ty * P.m - P.pad, x0 = tx * P.m - P.pad;
+  const int plane = (img * P.C + (live ? ch : 0)) * P.HW;              // below 2^31, as the whole tensor
+  const int last = (int)P.total - 16;                                  // the layer's tensor has 16 bytes and more
+  v4i val[ROWS];
+  bool there[ROWS];
+  int moved[ROWS];                                                     // how far the load was moved, see above
+#pragma unroll
+  for (int a = 0; a < ROWS; ++a) {
+    const int gy = y0 + a;
+    there[a] = live && a < P.t && gy >= 0 && gy < P.H;
+    const int from = plane + (there[a] ? gy : 0) * P.W + x0, at = min(max(from, 0), last);
+    moved[a] = from - at;
+    val[a] = (v4i){0, 0, 0, 0};
+    if (there[a]) __builtin_memcpy(&val[a], P.x + (uint32_t)at, 16);   // one unaligned 16-byte load
+  }
+  // items of this wave: full 16-point blocks of all residues first (their stores need no test, so that the wait for the next
+  // item's table does not become a wait for them), then the residues' last, partial blocks
+  const int nfull = P.P2 >> 4;
+  constexpr uint32_t FRAG = KS1 * 1024;
+  const uint32_t lane16 = (uint32_t)lane * 16u;
+  auto load_table = [&](int i, int cbk, v4i (&b)[KS1]) {
+    const int8_t *frag = P.KB + (size_t)((uint32_t)(i * P.CB1 + cbk) * FRAG);
+#pragma unroll
+    for (int s = 0; s < KS1; ++s) b[s] = *(const v4i *)(frag + s * 1024 + lane16);
+  };
+  v4i ta[KS1], tn[KS1];
+  int i = i0, cbk = wave;
+  auto settle = [&]() { while (cbk >= nfull && i < i0 + nres) { cbk -= nfull; ++i; } };
+  if (nfull > 0) settle(); else i = i0 + nres;
+  if (i < i0 + nres) load_table(i, cbk, ta);
+  const unsigned long long m0 = byte_range(max(-x0, 0), min(P.t, P.W - x0), 0), m1 = byte_range(max(-x0, 0), min(P.t, P.W - x0), 8);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int a = 0; a < ROWS; ++a) {
+    if (there[a] && moved[a] != 0) {
+      unsigned long long w0 = (uint32_t)val[a][0] | (unsigned long long)(uint32_t)val[a][1] << 32;
+      unsigned long long w1 = (uint32_t)val[a][2] | (unsigned long long)(uint32_t)val[a][3] << 32;
+      const int s = min(abs(moved[a]), 15);
+      if (moved[a] > 0) {
+        if (s >= 8) { w0 = w1; w1 = 0; }
+        if (s & 7) { w0 = w0 >> (8 * (s & 7)) | w1 << (64 - 8 * (s & 7)); w1 >>= 8 * (s & 7); }
+      } else {
+        if (s >= 8) { w1 = w0; w0 = 0; }
+        if (s & 7) { w1 = w1 << (8 * (s & 7)) | w0 >> (64 - 8 * (s & 7)); w0 <<= 8 * (s & 7); }
+      }
+      val[a] = (v4i){(int)(uint32_t)w0, (int)(uint32_t)(w0 >> 32), (int)(uint32_t)w1, (int)(uint32_t)(w1 >> 32)};
+    }
+  }
+  uint8_t *const mine = xs + threadIdx.x * CROW;
+  const int rp = KS1 == 1 ? P.RP1 : 12;
+#pragma unroll
+  for (int a = 0; a < ROWS; ++a)
+    if (a < P.t) {
+      uint32_t *row = (uint32_t *)(mine + a * rp);
+      row[0] = (uint32_t)val[a][0] & (uint32_t)m0;
+      if (rp > 4) row[1] = (uint32_t)val[a][1] & (uint32_t)(m0 >> 32);
+      if (rp > 8) row[2] = (uint32_t)val[a][2] & (uint32_t)m1;
+    }
+  __syncthreads();
+
+  const uint8_t *px = xs + (lane & 15) * CROW + h * 16;
+  int8_t *const Vb = P.V + ((size_t)tb * (size_t)(P.n * P.P2) * P.ncb + cb) * 1024 + g * 256;
+  const uint32_t stride_pt = (uint32_t)P.ncb * 1024u;
+  const uint32_t lane_store = (uint32_t)(4 * h) * stride_pt + (uint32_t)(lane & 15) * 16u;
+  // out[e]: 16 channels of point 16 cbk + 4 h + e
+  auto compute = [&](const v4i (&tab)[KS1], const Residue8 &r, v4i (&out)[4]) {
+    const float inv = in_vgpr(r.inv), qb = in_vgpr(r.quot_bias);
+    const v4i start = (v4i){r.acc_bias, r.acc_bias, r.acc_bias, r.acc_bias};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      v4i acc[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        acc[j] = start;
+#pragma unroll
+        for (int s = 0; s < KS1; ++s)
+          acc[j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(tab[s], *(const v4i *)(px + (4 * u + j) * 16 * CROW + s * 64), acc[j], 0, 0, 0);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        out[e][u] = (int)pack_low_bytes(biased_lowbyte(acc[0][e], inv, qb, r.neg_p), biased_lowbyte(acc[1][e], inv, qb, r.neg_p),
+                                        biased_lowbyte(acc[2][e], inv, qb, r.neg_p), biased_lowbyte(acc[3][e], inv, qb, r.neg_p));
+    }
+  };
+  auto full_item = [&](v4i (&tab)[KS1], v4i (&next)[KS1]) {
+    const int ci = i, cc = cbk;
+    const Residue8 r = P.res[ci];
+    cbk += 4;
+    settle();
+    load_table(min(i, P.n - 1), i < i0 + nres ? cbk : 0, next);        // past the end: fetched, not used
+    v4i out[4];
+    compute(tab, r, out);
+    int8_t *dst = Vb + (size_t)(uint32_t)(ci * P.P2 + 16 * cc) * stride_pt + lane_store;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) *(v4i *)(dst + (uint32_t)e * stride_pt) = out[e];
+  };
+  while (i < i0 + nres) {
+    full_item(ta, tn);
+    if (i >= i0 + nres) break;
+    full_item(tn, ta);
+  }
+  if (P.P2 & 15) {
+    for (int pi = i0 + wave; pi < i0 + nres; pi += 4) {
+      v4i tab[KS1], out[4];
+      load_table(pi, nfull, tab);
+      const Residue8 r = P.res[pi];
+      compute(tab, r, out);
+      int8_t *dst = Vb + (size_t)(uint32_t)(pi * P.P2 + 16 * nfull) * stride_pt + lane_store;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (16 * nfull + 4 * h + e < P.P2) *(v4i *)(dst + (uint32_t)e * stride_pt) = out[e];
+    }
+  }
+}
+
 }  // namespace rnswino

@@ -30,7 +30,7 @@ struct K2Params {
   FastDiv by_xgroup, by_gy, by_gz, by_Q;
   int nkb, ntb, ncb;          // row and tile blocks of 16, channel blocks of 64
   int xs, Q, P2, slabs;       // n * Q, point groups, points, n * P2
-  int Kp, Tp;
+  int Kp, Tp, v_tile, v_slice;  // bytes between tiles and between 16-channel slices inside a fragment of V
   Residue8 res[8];
   double inv_pd[8];           // 16-bit moduli
 };
@@ -54,7 +54,7 @@ __device__ __forceinline__ K2Item k2_item(const K2Params &P, uint32_t id) {
 #define RNSW_K2_FETCH_ARGUMENTS(P)                                                                                                       \
   asm volatile("" ::"s"(P.U), "s"(P.V), "s"(P.O), "s"(P.xgroup), "s"(P.gy), "s"(P.gz), "s"(P.by_xgroup.mul), "s"(P.by_xgroup.shift),     \
                "s"(P.by_gy.mul), "s"(P.by_gy.shift), "s"(P.by_gz.mul), "s"(P.by_gz.shift), "s"(P.by_Q.mul), "s"(P.by_Q.shift), "s"(P.nkb), \
-               "s"(P.ntb), "s"(P.ncb), "s"(P.xs), "s"(P.Q), "s"(P.P2), "s"(P.slabs))
+               "s"(P.ntb), "s"(P.ncb), "s"(P.xs), "s"(P.Q), "s"(P.P2), "s"(P.slabs), "s"(P.Kp), "s"(P.Tp), "s"(P.v_tile), "s"(P.v_slice))
 
 template <int KS, int NTB, int RM, bool WIDE>
 __global__ __launch_bounds__(256) void k2_residue_gemm(K2Params P) {
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(K2Params P) {
       Ur[rm] = P.U + ((size_t)slab * nkb + min(kb0 + rm, nkb - 1)) * ncb * (1024 * PL) + lane * 16;
 #pragma unroll
     for (int tb = 0; tb < NTB; ++tb)
-      Vt[tb] = P.V + ((size_t)min(tb0 + tb, ntb - 1) * P.slabs + slab) * ncb * (1024 * PL) + (lane & 15) * 64 + (lane >> 4) * 16;
+      Vt[tb] = P.V + ((size_t)min(tb0 + tb, ntb - 1) * P.slabs + slab) * ncb * (1024 * PL) + (lane & 15) * P.v_tile + (lane >> 4) * P.v_slice;
 
     // KS contraction steps from s0 on; the very first step starts the accumulators (no zero fill)
     auto steps = [&](int s0, auto first_tag) {

@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm_lds(K2Params P) {
     } else {
       base[j] = P.V + (size_t)min(tb0 + f - BRF, ntb - 1) * P.slabs * ncb * 1024;
       slab_stride[j] = (uint32_t)ncb * 1024u;
-      lane_off[j] = (uint32_t)((lane & 15) * 64 + (lane >> 4) * 16);
+      lane_off[j] = (uint32_t)((lane & 15) * P.v_tile + (lane >> 4) * P.v_slice);
     }
   }
   const uint32_t stage_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t *)stage;

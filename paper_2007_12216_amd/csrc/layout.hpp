@@ -16,6 +16,8 @@
 //   U  [n][t*t][Kp/16][Cp/64][lane = (k%16) + 16*g][16 B]      (fragment-major: a wave reads 1 KiB runs)
 //   V  [Tp/16][n][t*t][Cp/64][tile%16][g][16 B]                 (fragment-major: 1 KiB per 16 tiles x 64 channels;
 //                               tile block outermost, so that everything one tile produces lies in one region)
+//                               or [Tp/16][n][t*t][Cp/64][g][tile%16][16 B], lane order as in U, where the input transform takes
+//                               16 tiles at a time (Dims::vlane)
 //   O  [Kp][n][Q][Tp][4 B]      byte e of the last axis is transform point 4*q + e; k outermost, so that the
 //                               n*Q words the inverse transform needs for one (k, tile) lie in one small region
 //
@@ -52,9 +54,10 @@ RNSW_HD size_t u_offset(int slab, int k, int c, int Kp, int Cp) {
   return frag * 1024 + (size_t)(((k & 15) + 16 * g) * 16 + b);
 }
 
-RNSW_HD size_t v_offset(int slab, int nslab, int tau, int c, int Cp) {
+RNSW_HD size_t v_offset(int slab, int nslab, int tau, int c, int Cp, int vlane) {
   const size_t frag = ((size_t)(tau >> 4) * nslab + slab) * (Cp >> 6) + (c >> 6);
-  return frag * 1024 + (size_t)((tau & 15) * 64 + chan_pos64(c & 63));
+  const int pos = chan_pos64(c & 63);
+  return frag * 1024 + (size_t)(vlane ? (pos >> 4) * 256 + (tau & 15) * 16 + (pos & 15) : (tau & 15) * 64 + pos);
 }
 
 RNSW_HD size_t o_offset(int i, int pt, int k, int tau, int n, int Q, int Kp, int Tp) {

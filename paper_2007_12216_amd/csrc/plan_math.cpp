@@ -189,6 +189,13 @@ int validate_desc(const rnswino_desc_t &d, Dims &o) {
   o.CB1 = (o.P2 + 15) / 16;
   o.RP1 = (t + 3) / 4 * 4;
   o.KS1 = (t * o.RP1 + 63) / 64;
+  // Input transform 16 tiles at a time: from 12 blocks of 16 tiles on, with about three workgroups per eight compute units (us
+  // per layer with blocks of one tile / of 16: 64 -> 64 channels at 224 x 224, batch 8 214 / 170; 128 -> 128 at 112 x 112, batch 8
+  // 89.6 / 84.4, batch 1 27.6 / 26.4; 100 -> 75 at 57 x 57, batch 3 21.4 / 20.5; below the line, 512 -> 512 at 28 x 28, batch 8
+  // (8 blocks of tiles) 50.8 / 51.5 and 256 -> 256 at 56 x 56 (49 tiles) 20.7 / 22.0).  Its offsets have 32 bits.
+  const long long elements = (long long)d.N * d.C * d.H * d.W;
+  o.vlane = !o.wide && o.KS1 <= 2 && elements >= 16 && elements < (1LL << 31) && o.Tp / 16 >= 12 &&
+            4LL * (o.Tp / 16) * (o.Cp / 64) >= 96;
   o.RB3 = (d.m * d.m + 15) / 16;
   o.KS3 = (o.P2 + 63) / 64;
   // the kernels address the GEMM output O = [Kp][n][Q][Tp] words (two planes for 16-bit moduli) with 32-bit byte

@@ -191,19 +191,23 @@ inline void launch(Kern kern, dim3 grid, size_t lds, hipStream_t st, Timing tm, 
 // with the report.
 // =============================================================================================
 
-struct K1Choice { int KS1; bool wide, pack; unsigned gx, gy; };
+struct K1Choice { int KS1; bool wide, pack, tiles; long long units; unsigned gx, gy; };
 
 K1Choice choose_k1(const Dims &d) {
   K1Choice c;
   c.KS1 = d.KS1 < 4 ? d.KS1 : 4;
   c.wide = d.wide != 0;
   c.pack = d.TL > 1;
-  const long long units = (long long)d.Tg * (d.Cp / 64);
+  c.tiles = d.vlane != 0;
+  const long long units = c.tiles ? 4LL * (d.Tp / 16) * (d.Cp / 64) : (long long)d.Tg * (d.Cp / 64);
+  c.units = units;
   // x: multiple of 8 (see kernels_common.hpp); y: one block per residue, or one block for all residues when there are
   // enough units to fill the chip (the pixel gather is then done once instead of n times; measured on the VGG16
-  // stack, two blocks per CU are already enough for that to win)
+  // stack, two blocks per CU are already enough for that to win; of the 16-tile blocks, which gather sixteen times as much, three
+  // for every four CUs: 128 -> 128 at 56 x 56, batch 8, 200 units 36.0 us a layer split, 34.5 not, and at 112 x 112, batch 1, 104
+  // units 26.4 and 28.3)
   c.gx = (unsigned)((units + 7) / 8 * 8);
-  c.gy = (unsigned)(units >= 512 ? 1 : d.n);
+  c.gy = (unsigned)(units >= (c.tiles ? 192 : 512) ? 1 : d.n);
   return c;
 }
 
@@ -212,7 +216,7 @@ K1Params make_k1(const Dims &d, const KParams &P) {
   K1Params q;
   std::memset(&q, 0, sizeof(q));
   q.KB = P.KB;
-  q.units = d.Tg * (d.Cp / 64);
+  q.units = (int)c.units;
   q.per_xcd = (int)(c.gx / 8);
   q.ncb = d.Cp / 64;
   q.split = c.gy > 1;
@@ -307,6 +311,7 @@ K2Params make_k2(const Dims &d, const KParams &P, uint32_t flags) {
   q.by_xgroup = make_fast_div((uint32_t)c.xgroup); q.by_gy = make_fast_div((uint32_t)q.gy); q.by_gz = make_fast_div((uint32_t)q.gz);
   q.by_Q = make_fast_div((uint32_t)d.Q);
   q.xs = d.n * d.Q; q.Q = d.Q; q.P2 = d.P2; q.slabs = d.n * d.P2; q.Kp = d.Kp; q.Tp = d.Tp;
+  q.v_tile = d.vlane ? 16 : 64; q.v_slice = d.vlane ? 256 : 16;
   for (int i = 0; i < d.n; ++i) {
     q.res[i] = {P.inv_p[i], P.quot_bias[i], -P.p[i], P.acc_bias[i]};
     q.inv_pd[i] = P.inv_pd[i];
@@ -379,6 +384,7 @@ K3Params make_k3(const Dims &d, const KParams &P, int n_cus, int epi) {
 #define RNSW_K1_TABLE(X) \
   X(1, false, false) X(1, false, true) X(1, true, false) X(1, true, true) X(2, false, false) X(2, false, true) X(2, true, false) X(2, true, true) \
   X(3, false, false) X(3, false, true) X(3, true, false) X(3, true, true) X(4, false, false) X(4, false, true) X(4, true, false) X(4, true, true)
+#define RNSW_K1T_TABLE(X) X(1, false) X(1, true) X(2, false) X(2, true)
 #define RNSW_K2_TABLE(X) \
   X(1, 1, 2, false) X(2, 1, 2, false) X(4, 1, 2, false) X(1, 2, 2, false) X(2, 2, 2, false) X(4, 2, 2, false) \
   X(1, 4, 2, false) X(2, 4, 2, false) X(4, 4, 2, false) X(1, 4, 4, false) X(2, 4, 4, false) \
@@ -403,8 +409,12 @@ bool launch_k1(const Dims &d, const K1Params &P1, const int8_t *x, int8_t *V, hi
   const dim3 grid(c.gx, c.gy);
   K1Params P = P1;
   P.x = x; P.V = V;
+#define RNSW_X(ks, pk) \
+  if (c.tiles && c.KS1 == ks && c.pack == pk) { if (!dry) launch(k1_input_transform_tiles<ks, pk>, grid, 0, st, tm, P); return true; }
+  RNSW_K1T_TABLE(RNSW_X)
+#undef RNSW_X
 #define RNSW_X(ks, wd, pk) \
-  if (c.KS1 == ks && c.wide == wd && c.pack == pk) { if (!dry) launch(k1_input_transform<ks, wd, pk>, grid, 0, st, tm, P); return true; }
+  if (!c.tiles && c.KS1 == ks && c.wide == wd && c.pack == pk) { if (!dry) launch(k1_input_transform<ks, wd, pk>, grid, 0, st, tm, P); return true; }
   RNSW_K1_TABLE(RNSW_X)
 #undef RNSW_X
   return false;
@@ -459,6 +469,9 @@ std::string all_kernel_variants() {
   std::string out;
 #define RNSW_X(ks, wd, pk) out += "k1_input_transform<" #ks ", " #wd ", " #pk ">\n";
   RNSW_K1_TABLE(RNSW_X)
+#undef RNSW_X
+#define RNSW_X(ks, pk) out += "k1_input_transform_tiles<" #ks ", " #pk ">\n";
+  RNSW_K1T_TABLE(RNSW_X)
 #undef RNSW_X
 #define RNSW_X(ks, ntb, rm, wd) out += "k2_residue_gemm<" #ks ", " #ntb ", " #rm ", " #wd ">\n";
   RNSW_K2_TABLE(RNSW_X)
@@ -671,7 +684,8 @@ int64_t rnswino_plan_describe(const rnswino_plan_t *plan, int32_t output_mode, c
   const K3Choice c3 = choose_k3(d, P, plan->n_cus, output_mode);
   auto tf = [](bool b) { return b ? "true" : "false"; };
   char buf[1024];
-  int len = std::snprintf(buf, sizeof(buf), "k1_input_transform<%d, %s, %s> grid=%ux%u\n", c1.KS1, tf(c1.wide), tf(c1.pack), c1.gx, c1.gy);
+  int len = c1.tiles ? std::snprintf(buf, sizeof(buf), "k1_input_transform_tiles<%d, %s> grid=%ux%u\n", c1.KS1, tf(c1.pack), c1.gx, c1.gy)
+                     : std::snprintf(buf, sizeof(buf), "k1_input_transform<%d, %s, %s> grid=%ux%u\n", c1.KS1, tf(c1.wide), tf(c1.pack), c1.gx, c1.gy);
   if (c2.lds)
     len += std::snprintf(buf + len, sizeof(buf) - len, "k2_residue_gemm_lds<%d, %d, %d, %d, %d> grid=%u xgroup=%d\n", c2.WM, c2.WN, c2.RM,
                          c2.NTB, c2.S, c2.blocks, c2.xgroup);
@@ -860,7 +874,7 @@ int rnswino_debug_stage(const rnswino_plan_t *plan, int stage, const void *src_d
             const int tg = tau % d.Tg, cg = (tau / d.Tg) * d.Cq + c;       // GEMM column and channel (cg = c when TL = 1)
             host_out[((size_t)slab * d.T + tau) * d.C + c] =
                 d.wide ? value(0, v_offset_wide(slab, d.n * d.P2, tg, cg, d.Cp, 0), v_offset_wide(slab, d.n * d.P2, tg, cg, d.Cp, 1))
-                       : value(v_offset(slab, d.n * d.P2, tg, cg, d.Cp), 0, 0);
+                       : value(v_offset(slab, d.n * d.P2, tg, cg, d.Cp, d.vlane), 0, 0);
           }
       } else {
         for (int k = 0; k < d.K; ++k)
