@@ -67,5 +67,5 @@ struct rnswino_plan_s {
   size_t d_tables_bytes;
   // offsets (bytes) into d_tables
   size_t off_KG, off_KB, off_KA;            // int8 Kronecker tables of the filter / input / inverse transform
-  void *kparams;                            // the kernels' parameter block (rnswino::KParams), built once with the plan
+  void *kparams;                            // the kernels' parameter blocks, built once with the plan
 };
