@@ -115,12 +115,14 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
   } else {
     const Origin o = tile_origin(tau, cb * 64);
     // offsets from the origin that a 16-byte load may start at: [lo, hi] (rows outside the image are excluded
-    // separately, so saturating the bounds to 32 bits changes nothing)
+    // separately, so saturating the bounds to 32 bits changes nothing).  An origin inside the last 16 bytes of the tensor makes
+    // hi negative, down to -15; the loads' base lies 16 bytes before the origin, so that their offsets are not.
     const int lo = (int)min(max(-o.base, 0ll), 0x7FFFFFFFll);
-    const int hi = (int)max(min(P.total - 16 - o.base, 0x7FFFFFFFll), (long long)lo);
-    const int a_lo = max(-o.y0, 0), a_count = max(min(P.t, P.H - o.y0) - a_lo, 0);     // rows inside the image
+    const int hi = (int)min(max(P.total - 16 - o.base, -16ll), 0x7FFFFFFFll);
+    const bool columns = o.x0 < P.W && o.x0 + P.t > 0;                                 // (wide padding: perhaps none)
+    const int a_lo = max(-o.y0, 0), a_count = columns ? max(min(P.t, P.H - o.y0) - a_lo, 0) : 0;     // rows inside the image
     const int chans = P.C - cb * 64;
-    const int8_t *xb = P.x + o.base;
+    const int8_t *xb = P.x + (o.base - 16);
 #pragma unroll
     for (int k = 0; k < NT; ++k) {
       const int task = threadIdx.x + 256 * k;
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
       moved[k] = tiny ? (int)o.base + from : from - at;
       there[k] = (256 * (k + 1) <= 64 * ROWS || task < 64 * ROWS) && cblk < chans && (uint32_t)(a - a_lo) < (uint32_t)a_count;
       val[k] = (v4i){0, 0, 0, 0};
-      if (there[k] && !tiny) __builtin_memcpy(&val[k], xb + (uint32_t)at, 16);        // one unaligned 16-byte load
+      if (there[k] && !tiny) __builtin_memcpy(&val[k], xb + (uint32_t)(at + 16), 16);   // one unaligned 16-byte load
     }
     mask0[0] = byte_range(max(-o.x0, 0), min(P.t, P.W - o.x0), 0);
     mask1[0] = byte_range(max(-o.x0, 0), min(P.t, P.W - o.x0), 8);
