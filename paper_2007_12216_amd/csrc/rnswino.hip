@@ -320,7 +320,8 @@ K2Params make_k2(const Dims &d, const KParams &P, uint32_t flags) {
 }
 
 // stream: the streaming variant (8-bit moduli, table of all residues at most 64 KiB, n * KS3 <= 8: O operand in
-// registers) for layers with 3072 and more units (measured on the VGG16 stack);
+// registers) for layers with 5000 and more units (us per layer, streaming / block form: 3136 units 33.7 / 32.0, 3200 35.0 / 33.5,
+// 4096 37.0 / 36.5, 6400 60.1 / 60.1, 12544 63.9 / 66.6, 25088 160 / 184; four resident blocks per CU already take 4096);
 // fast: conversion out of the RNS from unreduced accumulators; m8: the 8 x 8 store path of the streaming variant
 // (int32 output: only with rows that keep four outputs 16-byte aligned; int8 output: only with an even row length).
 struct K3Choice { bool stream, wide, fast, m8; int NRES, KS3; unsigned gx, gy; size_t lds; };
@@ -332,7 +333,7 @@ K3Choice choose_k3(const Dims &d, const KParams &P, int n_cus, int epi) {
   c.KS3 = d.KS3 < 4 ? d.KS3 : 4;
   c.fast = !c.wide && P.fastcrt != 0;
   c.stream = !c.wide && d.n * d.KS3 <= 8 && d.n <= 4 && d.KS3 <= 2 && (size_t)d.n * d.RB3 * d.KS3 * 1024 <= 65536 &&
-             (long long)d.Kg * (d.Tp / 16) >= 3072;
+             (long long)d.Kg * (d.Tp / 16) >= 5000;
   c.m8 = false;
   c.lds = 0;
   if (c.stream) {

@@ -65,13 +65,14 @@ def _candidates():
     for n, (r, m), mode in itertools.product(range(1, 5), ((3, 8), (3, 4), (3, 6), (3, 7)), (0, 1, 2)):
         for C, flags in ((33, 0), (33, UNCHECKED), (45, 0), (64, UNCHECKED), (200, UNCHECKED)):
             moduli = PRIMES8[:n]
-            for N, K, hw in ((8, 96, 8 * m), (8, 64, 56), (4, 48, 16 * m)):
+            for N, K, hw in ((8, 96, 8 * m), (8, 160, 8 * m), (8, 64, 56), (4, 48, 16 * m)):
                 if mode == 2 and (m not in (4, 8) or hw % 4):
                     continue
                 add(N, C, K, hw, hw, r, m, 1, moduli, flags, mode)
     # 1 x 1 filters with 8 x 8 tiles: one contraction step together with the 8 x 8 store path
     for n, mode in itertools.product(range(1, 5), (0, 1, 2)):
         add(8, 40, 96, 64, 64, 1, 8, 0, PRIMES8[:n], UNCHECKED, mode)
+        add(8, 40, 160, 64, 64, 1, 8, 0, PRIMES8[:n], UNCHECKED, mode)
     # four moduli whose product leaves the binary64 quotient of the unreduced form no room, on layers whose worst case
     # 2^14 r^2 C is above 0.38 of that product (binary32 has no room either): the conversion over reduced residues
     big4 = (253, 251, 247, 241)
@@ -80,11 +81,15 @@ def _candidates():
     add(1, 11600, 8, 8, 8, 3, 8, 1, big4, UNCHECKED)         # the same above 0.45 of the product: binary64 quotient
     add(1, 3600, 8, 8, 8, 5, 8, 2, big4, UNCHECKED)          # three (t = 12)
     for mode in (0, 1):
-        add(1, 1800, 48, 64, 64, 7, 2, 3, big4, UNCHECKED, mode)     # streaming, t = 8
+        add(1, 1800, 48, 64, 64, 7, 2, 3, big4, UNCHECKED, mode)
+        add(1, 1800, 80, 64, 64, 7, 2, 3, big4, UNCHECKED, mode)     # streaming, t = 8
     for mode in (0, 1, 2):
-        add(4, 1800, 48, 64, 64, 7, 4, 3, big4, UNCHECKED, mode)     # streaming, t = 10
+        add(4, 1800, 48, 64, 64, 7, 4, 3, big4, UNCHECKED, mode)
+        add(4, 1800, 80, 64, 64, 7, 4, 3, big4, UNCHECKED, mode)     # streaming, t = 10
+    add(4, 1800, 48, 64, 64, 7, 3, 3, big4, UNCHECKED, 0)            # streaming, t = 9: fewer operations per unit
     for mode in (0, 1):
-        add(8, 64, 128, 56, 56, 3, 8, 1, PRIMES8[:3], UNCHECKED, mode)              # binary64 quotient, streaming
+        add(8, 64, 128, 56, 56, 3, 8, 1, PRIMES8[:3], UNCHECKED, mode)
+        add(8, 64, 208, 56, 56, 3, 8, 1, PRIMES8[:3], UNCHECKED, mode)              # binary64 quotient, streaming
     out.sort(key=lambda cc: (cc[0], cc[1]))
     return out
 
