@@ -11,8 +11,8 @@ LIB = os.path.join(PKG, "librnswino.so")
 SOURCES = ("rnswino.hip", "plan_math.cpp")
 
 
-def build_library(verbose: bool = False) -> str:
-    """Compile every source with hipcc for gfx950 and link the shared library."""
+def compile_command(out: str) -> list:
+    """The hipcc command that compiles every source for gfx950 and links them to `out`."""
     cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
            # matrix-core results straight into ordinary vector registers: no accumulator-register copies in the
@@ -21,7 +21,12 @@ def build_library(verbose: bool = False) -> str:
            "-Wno-unused-command-line-argument",
            "-I", os.path.join(ROOT, "include"), "-I", CSRC]
     cmd += [os.path.join(CSRC, s) for s in SOURCES]
-    cmd += ["-o", LIB]
+    return cmd + ["-o", out]
+
+
+def build_library(verbose: bool = False) -> str:
+    """Compile every source with hipcc for gfx950 and link the shared library."""
+    cmd = compile_command(LIB)
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)

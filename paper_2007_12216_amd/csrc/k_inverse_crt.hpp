@@ -118,7 +118,8 @@ __device__ __forceinline__ void crt_convert(const K3Params &P, const uint32_t (&
 }
 
 // Fast conversion (see the header): w[i][j] = a_i + 0x4B400000, unreduced; read as binary32 it is 1.5*2^23 + a_i, so the
-// sum for the quotient takes it as it is, and its low 24 bits are a_i + 2^22.  Adding 1.5*2^23 to that sum rounds it and
+// sum for the quotient takes it as it is, and its low 24 bits are a_i + 2^22 (the first product, the compiler's own, takes all
+// 32 bits; mad_u24() says why).  Adding 1.5*2^23 to that sum rounds it and
 // leaves the quotient in the mantissa; the multiples of P that its bias stands for are part of crt_sum0.
 // Per output and residue one float multiply-add with vector operands (2.6 cycles per wave and SIMD) and one 24-bit
 // multiply-add (4.8), then 2.6 + 4.4 + 2.6: 39 cycles with four residues (71 with conversions and scalar operands).
@@ -130,14 +131,14 @@ template <int NRES>
 __device__ __forceinline__ void crt_convert_fast(const K3Params &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    uint32_t sum = fc.sum0;
+    uint32_t sum = 0;
     float fs = fc.fs0;
 #pragma unroll
     for (int i = 0; i < NRES; ++i) {
-      sum = mad_u24(P.crt_c[i], w[i][j], sum);
       fs = __builtin_fmaf(__uint_as_float(w[i][j]), fc.inv[i], fs);
+      sum = i == 0 ? P.crt_c[i] * w[i][j] : mad_u24(P.crt_c[i], w[i][j], sum, fs);
     }
-    val[j] = (int)(sum - mul_lo(P.prod_mod32, __float_as_uint(fs + 12582912.0f)));
+    val[j] = (int)(sum + fc.sum0 + mul_lo(0u - P.prod_mod32, __float_as_uint(fs + 12582912.0f)));
   }
 }
 
@@ -146,17 +147,20 @@ __device__ __forceinline__ void crt_convert_fast(const K3Params &P, const FastCr
 // range and plans with an unchecked range take this form.
 template <int NRES>
 __device__ __forceinline__ void crt_convert_fast64(const K3Params &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
+  uint32_t c0 = P.crt_c[0];
+  asm("" : "+s"(c0));       // keeps the first products of the two forms apart: taken in front of the branch, each would be copied behind it
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    uint32_t sum = fc.sum0;
+    uint32_t sum = 0;
     double fs = P.crt_fs0d;
 #pragma unroll
     for (int i = 0; i < NRES; ++i) {
-      sum = mad_u24(P.crt_c[i], w[i][j], sum);
-      fs = __builtin_fma((double)w[i][j], P.inv_pd[i], fs);
+      const double wd = (double)w[i][j];
+      sum = i == 0 ? c0 * w[i][j] : mad_u24(P.crt_c[i], w[i][j], sum, wd);
+      fs = __builtin_fma(wd, P.inv_pd[i], fs);
     }
     const int kk = __double2int_rn(fs);
-    val[j] = (int)(sum - mul_lo(P.prod_mod32, (uint32_t)kk));
+    val[j] = (int)(sum + fc.sum0 + mul_lo(0u - P.prod_mod32, (uint32_t)kk));
   }
 }
 

@@ -63,6 +63,13 @@ struct KParams {
 // multiple of 8 takes item (x % 8) * (gx / 8) + x / 8 in block x, so that each XCD gets one contiguous chunk of the items:
 // neighbours (which share input lines) then share an L2.  Items past the count are padding.
 
+// Instructions written as inline assembly.  The compiler keeps the wait states a matrix instruction's registers need (8 from a result
+// to its reader or overwriter, 3 from a C operand to its overwriter, on this chip) only for instructions it selects itself.  So each
+// of these overwrites one of its own inputs, never a register the allocator finds free, and reads a matrix result only behind a
+// compiler's instruction that has read it: through its other inputs, or through the operand `after`, which the text leaves out.
+// (Without the two, streaming inverse transforms of two and three moduli read results 5 and 7 states after their instruction, and
+// others overwrote a result or an operand still in use.)
+
 // ---- residues of 8-bit moduli -------------------------------------------------------------------
 
 // Residue of x modulo p for |x| < 2^24 and p <= 253, without division: q = rint(x/p) from one fused
@@ -80,8 +87,8 @@ __device__ __forceinline__ int mod_near(int x, float inv_p, int p) {
 // otherwise swap it for a quarter-rate 64-bit multiply-add.)
 __device__ __forceinline__ uint32_t mod_lowbyte(int x, float inv_p, int neg_p) {
   const float f = __builtin_fmaf((float)x, inv_p, 12582912.0f);
-  int r;
-  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(__float_as_int(f)), "v"(neg_p), "v"(x));
+  int r = __float_as_int(f);
+  asm("v_mad_i32_i24 %0, %0, %1, %2" : "+v"(r) : "v"(neg_p), "v"(x));
   return (uint32_t)r;
 }
 
@@ -95,8 +102,8 @@ __device__ __forceinline__ uint32_t mod_lowbyte(int x, float inv_p, int neg_p) {
 // and quot_bias in vector registers (in_vgpr()).
 __device__ __forceinline__ uint32_t biased_lowbyte(int acc, float inv_p, float quot_bias, int neg_p) {
   const float f = __builtin_fmaf(__int_as_float(acc), inv_p, quot_bias);
-  int r;
-  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(__float_as_int(f)), "s"(neg_p), "v"(acc));
+  int r = __float_as_int(f);
+  asm("v_mad_i32_i24 %0, %0, %1, %2" : "+v"(r) : "s"(neg_p), "v"(acc));
   return (uint32_t)r;
 }
 
@@ -109,25 +116,25 @@ __device__ __forceinline__ T in_vgpr(T v) {
 
 // c * (low 24 bits of w) + acc modulo 2^32, c < 2^24 wave-uniform: one instruction (the compiler, left to choose, splits
 // the products from their sums or takes 64-bit multiply-adds, each of which costs more than the 4.8 cycles of this).
-__device__ __forceinline__ uint32_t mad_u24(uint32_t c, uint32_t w, uint32_t acc) {
-  uint32_t r;
-  asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "s"(c), "v"(w), "v"(acc));
-  return r;
+// `after`: what a compiler's instruction made of w.
+template <typename T>
+__device__ __forceinline__ uint32_t mad_u24(uint32_t c, uint32_t w, uint32_t acc, T after) {
+  asm("v_mad_u32_u24 %0, %1, %2, %0" : "+v"(acc) : "s"(c), "v"(w), "v"(after));
+  return acc;
 }
 
 // Low 32 bits of c * v, c wave-uniform (4.4 cycles, full rate on this chip).
 __device__ __forceinline__ uint32_t mul_lo(uint32_t c, uint32_t v) {
-  uint32_t r;
-  asm("v_mul_lo_u32 %0, %1, %2" : "=v"(r) : "s"(c), "v"(v));
-  return r;
+  asm("v_mul_lo_u32 %0, %1, %0" : "+v"(v) : "s"(c));
+  return v;
 }
 
 // That residue plus p (so that it is positive), 8-bit p: the low 24 bits of the biased float are 2^22 + q, the
 // 24-bit multiply-add gives x - q p - 2^22 p + bias with bias = 2^22 p + p.  Four full-rate instructions.
 __device__ __forceinline__ uint32_t mod_near_plus_p(int x, float inv_p, int neg_p, int bias) {
   const float f = __builtin_fmaf((float)x, inv_p, 12582912.0f);
-  int r;
-  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(__float_as_int(f)), "v"(neg_p), "v"(x + bias));
+  int r = __float_as_int(f);
+  asm("v_mad_i32_i24 %0, %0, %1, %2" : "+v"(r) : "v"(neg_p), "v"(x + bias));
   return (uint32_t)r;
 }
 

@@ -127,7 +127,8 @@ KParams make_params(const rnswino_plan_t *pl) {
       else if (2.0 * err64 <= 0.5 / (double)prod) P.fastcrt = 2;
       if (P.fastcrt == 1) {
         P.acc0 = 0x4B400000;             // the bits of M; its low 24 bits are 2^22
-        P.crt_sum0 = 0u - 4194304u * c32 + pl->prod_mod32 * 0x4B400000u;
+        // (the first residue's product takes all 32 bits of its accumulator)
+        P.crt_sum0 = 0u - 4194304u * c32 - 0x4B000000u * pl->crt_c[0] + pl->prod_mod32 * 0x4B400000u;
         P.crt_fs0 = (float)(-start);
       } else if (P.fastcrt == 2) {
         P.acc0 = 4194304;
