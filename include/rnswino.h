@@ -202,6 +202,13 @@ int rnswino_direct_filter_pack(const int8_t *w_dev, void *wt_dev, int32_t C, int
 int rnswino_direct_conv2d(const int8_t *x_dev, const void *wt_dev, int32_t *y_dev, int32_t N, int32_t C, int32_t K, int32_t H,
                           int32_t W, int32_t r, int32_t pad, void *workspace_dev, void *stream);
 
+/* Which kernel instantiation multiplies in rnswino_direct_conv2d for these sizes, its grid and, where it stages patches, its LDS and
+ * patch size, as one line of text in the form of rnswino_plan_describe (same return convention; the error codes are those of the call
+ * it describes); and every instantiation there is, one name per line.  No GPU needed.  For tests and measurement scripts. */
+int64_t rnswino_direct_describe(int32_t N, int32_t C, int32_t K, int32_t H, int32_t W, int32_t r, int32_t pad, char *host_out,
+                                size_t capacity);
+int64_t rnswino_direct_variants(char *host_out, size_t capacity);
+
 /* ---- query / test surface ---- */
 
 /* Copy one transform matrix (which = RNSWINO_MATRIX_*, modulus_idx < n_moduli) to host_out (row-major int32). */

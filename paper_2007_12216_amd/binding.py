@@ -18,6 +18,7 @@ EXPORTED_SYMBOLS = (
     "rnswino_workspace_bytes", "rnswino_filter_transform", "rnswino_conv2d", "rnswino_conv2d_requant",
     "rnswino_conv2d_events", "rnswino_conv2d_static",
     "rnswino_direct_filter_bytes", "rnswino_direct_workspace_bytes", "rnswino_direct_filter_pack", "rnswino_direct_conv2d",
+    "rnswino_direct_describe", "rnswino_direct_variants",
     "rnswino_requant_pool",
     "rnswino_plan_get_matrix", "rnswino_plan_get_table", "rnswino_plan_get_mrc_inverse", "rnswino_plan_dynamic_range",
     "rnswino_plan_describe", "rnswino_kernel_variants", "rnswino_debug_empty_launch",
@@ -82,6 +83,10 @@ def lib():
         L.rnswino_direct_filter_pack.restype = ctypes.c_int
         L.rnswino_direct_conv2d.argtypes = [vp, vp, vp, i32, i32, i32, i32, i32, i32, i32, vp, vp]
         L.rnswino_direct_conv2d.restype = ctypes.c_int
+        L.rnswino_direct_describe.argtypes = [i32, i32, i32, i32, i32, i32, i32, ctypes.c_char_p, ctypes.c_size_t]
+        L.rnswino_direct_describe.restype = i64
+        L.rnswino_direct_variants.argtypes = [ctypes.c_char_p, ctypes.c_size_t]
+        L.rnswino_direct_variants.restype = i64
         L.rnswino_requant_pool.argtypes = [vp, vp, i64, i32, i32, i32, i32, vp]
         L.rnswino_requant_pool.restype = ctypes.c_int
         L.rnswino_plan_get_matrix.argtypes = [vp, ctypes.c_int, ctypes.c_int, vp]
@@ -220,6 +225,25 @@ def rnswino_direct_filter_pack(w_dev, wt_dev, C: int, K: int, r: int, stream: in
 def rnswino_direct_conv2d(x_dev, wt_dev, y_dev, N, C, K, H, W, r, pad, workspace_dev, stream: int = 0) -> None:
     _check(lib().rnswino_direct_conv2d(_ptr(x_dev), _ptr(wt_dev), _ptr(y_dev), N, C, K, H, W, r, pad, _ptr(workspace_dev), stream),
            "rnswino_direct_conv2d")
+
+
+def rnswino_direct_describe(N, C, K, H, W, r, pad) -> dict:
+    """The kernel rnswino_direct_conv2d multiplies with on these sizes: {"kernel": name, "grid": ..., "lds": ..., "patch": ...}
+    (lds and patch only where it stages patches)."""
+    n = lib().rnswino_direct_describe(N, C, K, H, W, r, pad, None, 0)
+    _check(int(min(n, 0)), "rnswino_direct_describe")
+    buf = ctypes.create_string_buffer(int(n))
+    lib().rnswino_direct_describe(N, C, K, H, W, r, pad, buf, int(n))
+    name, _, rest = buf.value.decode().strip().partition("> ")
+    return {"kernel": name + ">", **{k: int(v) for k, v in (f.split("=") for f in rest.split())}}
+
+
+def rnswino_direct_variants() -> list:
+    """Names of every kernel instantiation rnswino_direct_conv2d can multiply with."""
+    n = int(lib().rnswino_direct_variants(None, 0))
+    buf = ctypes.create_string_buffer(n)
+    lib().rnswino_direct_variants(buf, n)
+    return [l for l in buf.value.decode().splitlines() if l]
 
 
 def rnswino_requant_pool(y_dev, a_dev, planes: int, H: int, W: int, shift: int, pool: bool, stream: int = 0) -> None:

@@ -725,6 +725,50 @@ static int direct_params(int32_t N, int32_t C, int32_t K, int32_t H, int32_t W, 
   return RNSWINO_OK;
 }
 
+#define RNSW_DIRECT_PATCH_TABLE(X) X(1, 4, 2, 4, 4) X(1, 4, 4, 4, 4) X(2, 2, 2, 4, 4) X(2, 2, 1, 2, 8)
+#define RNSW_DIRECT_TABLE(X) X(1, 4, 4, 4, 3) X(2, 2, 4, 4, 3) X(4, 1, 2, 4, 4) X(4, 1, 1, 4, 4)
+
+// patch: pixels of the staged patch, 0 for k_direct_conv; depth: the kernel's D or S.
+struct DirectChoice {
+  int patch, WM, WN, RM, NT, depth;
+  unsigned blocks;
+  size_t lds;
+  bool is(int wm, int wn, int rm, int nt, int d) const { return WM == wm && WN == wn && RM == rm && NT == nt && depth == d; }
+};
+
+static DirectChoice choose_direct(const DirectParams &P) {
+  const long long nkb = P.Kp / 16, ntb = (P.npix + 15) / 16;
+  auto blocks = [&](int brf, int btf) { return ((nkb + brf - 1) / brf) * (((ntb + btf - 1) / btf + 7) / 8 * 8); };
+  // Patch kernel (k_direct_conv_patch) where its LDS leaves two workgroups per compute unit.  The longest patch of `pixels`
+  // consecutive output pixels: every row boundary among them adds r - 1 pixels of border, every image boundary r - 1 rows more.
+  auto patch_pixels = [&](long long pixels) {
+    const long long plane = (long long)P.Ho * P.Wo, images = P.N == 1 || plane % pixels == 0 ? 0 : (pixels - 2) / plane + 1;
+    return pixels + ((pixels - 2) / P.Wo + 1) * (P.r - 1) + images * (P.r - 1) * P.Wp + (P.r - 1) * (P.Wp + 1LL);
+  };
+  auto patch_lds = [&](int btf) { return (patch_pixels(16 * btf) + 15) / 16 * 1024 * (P.Cp > 64 ? 2 : 1); };
+  auto fits = [&](int btf) { return patch_lds(btf) <= 81920; };
+  auto patch = [&](int wm, int wn, int rm, int nt, int depth) {
+    return DirectChoice{(int)patch_pixels(16 * wn * nt), wm, wn, rm, nt, depth, (unsigned)blocks(wm * rm, wn * nt), (size_t)patch_lds(wn * nt)};
+  };
+  auto plain = [&](int wm, int wn, int rm, int nt, int depth) {
+    return DirectChoice{0, wm, wn, rm, nt, depth, (unsigned)blocks(wm * rm, wn * nt), 0};
+  };
+  // The largest block that still gives three workgroups per two compute units, 32 x 64 for the smallest layers (us per call,
+  // batch 8 unless noted, 64 x 256 / 64 x 128 / 32 x 256 / 32 x 64 / k_direct_conv: 256 -> 256 at 56 x 56 28.2 / 33.0 / 31.6 /
+  // 39.6 / 44.0; 512 -> 512 at 28 x 28 29.2 / 26.6 / 27.1 / 36.6 / 49.6; 64 -> 64 at 112 x 112 20.2 / 20.3 / 19.3 / 24.0 / 24.5;
+  // 512 -> 512 at 14 x 14 26.9 / 21.2 / 22.0 / 19.3 / 26.4; 256 -> 256 at 56 x 56, batch 1 18.3 / 15.0 / 15.0 / 13.4 / 16.6).
+  if (P.Kp <= 64 && P.Kp > 16 && blocks(2, 16) >= 384 && fits(16)) return patch(1, 4, 2, 4, 4);
+  if (P.Kp > 64 && blocks(4, 16) >= 384 && fits(16)) return patch(1, 4, 4, 4, 4);
+  if (P.Kp > 16 && blocks(4, 8) >= 384 && fits(8)) return patch(2, 2, 2, 4, 4);
+  if ((P.Kp <= 16 || blocks(4, 8) < 384) && fits(4)) return patch(2, 2, 1, 2, 8);
+  // The others -- planes so wide that a patch outgrows LDS -- fetch every tap's pixels anew.  Block shape: 128 x 128 when that
+  // still gives the chip two workgroups per compute unit, else 128 x 64, else 64 x 64; layers with at most 64 filters 64 x 256
+  if (P.Kp <= 64 && blocks(4, 16) >= 512) return plain(1, 4, 4, 4, 3);
+  if (P.Kp > 64 && blocks(8, 8) >= 512) return plain(2, 2, 4, 4, 3);
+  if (P.Kp > 64 && blocks(8, 4) >= 512) return plain(4, 1, 2, 4, 4);
+  return plain(4, 1, 1, 4, 4);
+}
+
 size_t rnswino_direct_filter_bytes(int32_t C, int32_t K, int32_t r) {
   DirectParams P;
   if (direct_params(1, C, K, r, r, r, 0, P) != RNSWINO_OK) return 0;
@@ -759,40 +803,45 @@ int rnswino_direct_conv2d(const int8_t *x_dev, const void *wt_dev, int32_t *y_de
   int8_t *xt = (int8_t *)workspace_dev;
   const long long tblocks = ((long long)N * P.Hp * ((P.Wp + 15) / 16) + 15) / 16 * (P.Cp / 64);
   hipLaunchKernelGGL(k_direct_to_nhwc, dim3((unsigned)tblocks), dim3(256), 0, st, P, x_dev, xt);
-  const long long nkb = P.Kp / 16, ntb = (P.npix + 15) / 16;
-  auto blocks = [&](int brf, int btf) { return ((nkb + brf - 1) / brf) * (((ntb + btf - 1) / btf + 7) / 8 * 8); };
-  // Patch kernel (k_direct_conv_patch) where its LDS leaves two workgroups per compute unit.  The longest patch of `pixels`
-  // consecutive output pixels: every row boundary among them adds r - 1 pixels of border, every image boundary r - 1 rows more.
-  auto patch_pixels = [&](long long pixels) {
-    const long long plane = (long long)P.Ho * P.Wo, images = N == 1 || plane % pixels == 0 ? 0 : (pixels - 2) / plane + 1;
-    return pixels + ((pixels - 2) / P.Wo + 1) * (r - 1) + images * (r - 1) * P.Wp + (r - 1) * (P.Wp + 1LL);
-  };
-  auto patch_lds = [&](int btf) { return (patch_pixels(16 * btf) + 15) / 16 * 1024 * (P.Cp > 64 ? 2 : 1); };
-  auto fits = [&](int btf) { return patch_lds(btf) <= 81920; };
-  auto launch_patch = [&](auto kern, int brf, int btf) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks(brf, btf)), dim3(256), (size_t)patch_lds(btf), st, P, (int)patch_pixels(16 * btf), xt,
-                       (const int8_t *)wt_dev, y_dev);
-    return launch_status();
-  };
-  // The largest block that still gives three workgroups per two compute units, 32 x 64 for the smallest layers (us per call,
-  // batch 8 unless noted, 64 x 256 / 64 x 128 / 32 x 256 / 32 x 64 / k_direct_conv: 256 -> 256 at 56 x 56 28.2 / 33.0 / 31.6 /
-  // 39.6 / 44.0; 512 -> 512 at 28 x 28 29.2 / 26.6 / 27.1 / 36.6 / 49.6; 64 -> 64 at 112 x 112 20.2 / 20.3 / 19.3 / 24.0 / 24.5;
-  // 512 -> 512 at 14 x 14 26.9 / 21.2 / 22.0 / 19.3 / 26.4; 256 -> 256 at 56 x 56, batch 1 18.3 / 15.0 / 15.0 / 13.4 / 16.6).
-  if (P.Kp <= 64 && P.Kp > 16 && blocks(2, 16) >= 384 && fits(16)) return launch_patch(k_direct_conv_patch<1, 4, 2, 4, 4>, 2, 16);
-  if (P.Kp > 64 && blocks(4, 16) >= 384 && fits(16)) return launch_patch(k_direct_conv_patch<1, 4, 4, 4, 4>, 4, 16);
-  if (P.Kp > 16 && blocks(4, 8) >= 384 && fits(8)) return launch_patch(k_direct_conv_patch<2, 2, 2, 4, 4>, 4, 8);
-  if ((P.Kp <= 16 || blocks(4, 8) < 384) && fits(4)) return launch_patch(k_direct_conv_patch<2, 2, 1, 2, 8>, 2, 4);
-  // The others -- planes so wide that a patch outgrows LDS -- fetch every tap's pixels anew.  Block shape: 128 x 128 when that
-  // still gives the chip two workgroups per compute unit, else 128 x 64, else 64 x 64; layers with at most 64 filters 64 x 256
-  if (P.Kp <= 64 && blocks(4, 16) >= 512)
-    hipLaunchKernelGGL((k_direct_conv<1, 4, 4, 4, 3>), dim3((unsigned)blocks(4, 16)), dim3(256), 0, st, P, xt, (const int8_t *)wt_dev, y_dev);
-  else if (P.Kp > 64 && blocks(8, 8) >= 512)
-    hipLaunchKernelGGL((k_direct_conv<2, 2, 4, 4, 3>), dim3((unsigned)blocks(8, 8)), dim3(256), 0, st, P, xt, (const int8_t *)wt_dev, y_dev);
-  else if (P.Kp > 64 && blocks(8, 4) >= 512)
-    hipLaunchKernelGGL((k_direct_conv<4, 1, 2, 4, 4>), dim3((unsigned)blocks(8, 4)), dim3(256), 0, st, P, xt, (const int8_t *)wt_dev, y_dev);
-  else
-    hipLaunchKernelGGL((k_direct_conv<4, 1, 1, 4, 4>), dim3((unsigned)blocks(4, 4)), dim3(256), 0, st, P, xt, (const int8_t *)wt_dev, y_dev);
-  return launch_status();
+  const DirectChoice c = choose_direct(P);
+#define RNSW_X(wm_, wn_, rm, nt, d_) \
+  if (c.patch > 0 && c.is(wm_, wn_, rm, nt, d_)) { \
+    hipLaunchKernelGGL((k_direct_conv_patch<wm_, wn_, rm, nt, d_>), dim3(c.blocks), dim3(256), c.lds, st, P, c.patch, xt, (const int8_t *)wt_dev, y_dev); \
+    return launch_status(); }
+  RNSW_DIRECT_PATCH_TABLE(RNSW_X)
+#undef RNSW_X
+#define RNSW_X(wm_, wn_, rm, nt, s_) \
+  if (c.patch == 0 && c.is(wm_, wn_, rm, nt, s_)) { \
+    hipLaunchKernelGGL((k_direct_conv<wm_, wn_, rm, nt, s_>), dim3(c.blocks), dim3(256), 0, st, P, xt, (const int8_t *)wt_dev, y_dev); \
+    return launch_status(); }
+  RNSW_DIRECT_TABLE(RNSW_X)
+#undef RNSW_X
+  return RNSWINO_E_UNSUPPORTED;
+}
+
+int64_t rnswino_direct_describe(int32_t N, int32_t C, int32_t K, int32_t H, int32_t W, int32_t r, int32_t pad, char *host_out, size_t capacity) {
+  DirectParams P;
+  const int rc = direct_params(N, C, K, H, W, r, pad, P);
+  if (rc != RNSWINO_OK) return rc;
+  const DirectChoice c = choose_direct(P);
+  char buf[256];
+  const int len = c.patch > 0 ? std::snprintf(buf, sizeof(buf), "k_direct_conv_patch<%d, %d, %d, %d, %d> grid=%u lds=%zu patch=%d\n", c.WM, c.WN, c.RM,
+                                              c.NT, c.depth, c.blocks, c.lds, c.patch)
+                              : std::snprintf(buf, sizeof(buf), "k_direct_conv<%d, %d, %d, %d, %d> grid=%u\n", c.WM, c.WN, c.RM, c.NT, c.depth, c.blocks);
+  if (host_out && capacity > (size_t)len) std::memcpy(host_out, buf, (size_t)len + 1);
+  return (int64_t)len + 1;
+}
+
+int64_t rnswino_direct_variants(char *host_out, size_t capacity) {
+  std::string all;
+#define RNSW_X(wm_, wn_, rm, nt, d_) all += "k_direct_conv_patch<" #wm_ ", " #wn_ ", " #rm ", " #nt ", " #d_ ">\n";
+  RNSW_DIRECT_PATCH_TABLE(RNSW_X)
+#undef RNSW_X
+#define RNSW_X(wm_, wn_, rm, nt, s_) all += "k_direct_conv<" #wm_ ", " #wn_ ", " #rm ", " #nt ", " #s_ ">\n";
+  RNSW_DIRECT_TABLE(RNSW_X)
+#undef RNSW_X
+  if (host_out && capacity > all.size()) std::memcpy(host_out, all.c_str(), all.size() + 1);
+  return (int64_t)all.size() + 1;
 }
 
 int rnswino_requant_pool(const int32_t *y_dev, int8_t *a_dev, int64_t planes, int32_t H, int32_t W, int32_t shift,

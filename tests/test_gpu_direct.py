@@ -31,25 +31,33 @@ CASES = [
     (1, 256, 256, 56, 56, 3, 1),      # workload 2
     (1, 128, 128, 28, 28, 5, 2),      # workload 3
     (1, 512, 512, 28, 28, 3, 1),      # workload 4
-    (2, 3, 64, 40, 44, 3, 1),         # first-layer shape: 3 channels, 64 filters (64 x 256 blocks when large enough)
+    (2, 3, 64, 40, 44, 3, 1),         # first-layer shape: 3 channels, 64 filters
     (8, 64, 64, 56, 56, 3, 1),        # 64 filters, many pixels
     (2, 5, 7, 13, 17, 3, 1),          # ragged everything
     (1, 70, 130, 20, 21, 3, 0),       # no padding, ragged channel and filter blocks
     (3, 64, 200, 33, 35, 1, 0),       # 1 x 1 filter
     (1, 20, 24, 19, 19, 7, 3),        # 7 x 7 filter
-    (2, 130, 136, 64, 64, 3, 1),      # 128 x 128 blocks with ragged rows
+    (2, 130, 136, 64, 64, 3, 1),      # three channel blocks, ragged rows
     (1, 8, 8, 6, 6, 5, 0),            # 2 x 2 outputs
-    # staged patches: 64 x 256, 32 x 256, 64 x 128 and 32 x 64 blocks; blocks that span rows and images, one and more channel
-    # blocks, row blocks shifted back to the end of the filters
-    (5, 130, 200, 47, 61, 3, 1),
-    (8, 70, 24, 113, 111, 3, 1),
-    (8, 40, 72, 81, 40, 3, 1),
-    (3, 65, 17, 31, 29, 5, 2),
+    # staged patches that span rows and images (test_variant_coverage.py: these lists reach every instantiation)
+    (5, 130, 200, 47, 61, 3, 1),      # 64 x 128 blocks, three channel blocks
+    (8, 70, 24, 113, 111, 3, 1),      # 64 x 128: with two buffers and an image boundary a 256-pixel patch outgrows LDS
+    (8, 40, 72, 81, 40, 3, 1),        # 64 x 128, the last row block shifted back to the end of the filters
+    (3, 65, 17, 31, 29, 5, 2),        # 32 x 64 from here on
     (9, 130, 16, 7, 7, 3, 1),
     (4, 65, 40, 5, 3, 3, 1),          # several images in one pixel block
-    (2, 20, 90, 40, 170, 7, 3),
-    (1, 130, 24, 12, 700, 3, 1),      # a patch larger than LDS
-    (1, 20, 130, 70, 1100, 3, 1),     # the same with more work
+    # planes so wide, or filters so large, that a patch outgrows LDS: k_direct_conv
+    (2, 20, 90, 40, 170, 7, 3),       # 64 x 64
+    (1, 130, 24, 12, 700, 3, 1),
+    (1, 20, 130, 70, 1100, 3, 1),     # 128 x 128
+    (1, 8, 32, 130, 1030, 3, 1),      # 64 x 256
+    (1, 8, 80, 40, 1030, 3, 1),       # 128 x 64
+    # patches for 256 pixels
+    (8, 20, 24, 113, 111, 3, 1),      # 32 x 256, one channel block
+    (8, 70, 40, 81, 80, 3, 1),        # 32 x 256, two channel blocks, shifted rows
+    (8, 20, 72, 113, 111, 3, 1),      # 64 x 256, one channel block, shifted rows
+    (9, 70, 72, 81, 80, 3, 1),        # 64 x 256, two channel blocks, shifted rows
+    (6, 3, 130, 150, 99, 1, 0),       # 64 x 256, 1 x 1 filter: a step per channel block
 ]
 
 

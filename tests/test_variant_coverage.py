@@ -29,6 +29,22 @@ def test_the_variant_cases_reach_every_instantiation():
     assert gop < 600.0
 
 
+def test_the_direct_convolution_cases_reach_every_instantiation():
+    from test_gpu_direct import CASES
+    reached = {}
+    for case in CASES:
+        reached.setdefault(rn.rnswino_direct_describe(*case)["kernel"], []).append(case)
+    assert sorted(reached) == sorted(rn.rnswino_direct_variants())
+    # staged patches of 256 pixels, also with the last row block shifted back (its rows are then stored by two blocks)
+    for kernel, rm in (("k_direct_conv_patch<1, 4, 2, 4, 4>", 2), ("k_direct_conv_patch<1, 4, 4, 4, 4>", 4)):
+        assert any(-(-case[2] // 16) % rm for case in reached[kernel])
+        assert {case[1] > 64 for case in reached[kernel]} == {True, False}       # one channel block, and the two buffers
+    for bad, code in (((1, 4, 4, 2, 2, 5, 0), -1), ((1, 1 << 20, 4, 8, 8, 3, 1), -2), ((1, 4, 4, 8, 8, 17, 8), -2)):
+        with pytest.raises(rn.RnsWinoError) as e:
+            rn.rnswino_direct_describe(*bad)
+        assert e.value.code == code
+
+
 def _conversion(C, moduli, r=3, m=8, flags=HOST, K=16, hw=16):
     plan = rn.rnswino_plan(1, C, K, hw, hw, r, m, r // 2, moduli, flags=flags)
     return rn.rnswino_plan_describe(plan)["conversion"]
