@@ -45,13 +45,6 @@ struct K1Params {
   double inv_pd[8];           // 16-bit moduli
 };
 
-// bytes [lo, hi) of an 8-byte word that starts at byte `at`: a mask
-__device__ __forceinline__ unsigned long long byte_range(int lo, int hi, int at) {
-  const int l = min(max(lo - at, 0), 8), h = min(max(hi - at, 0), 8);
-  const unsigned long long below_h = h == 8 ? ~0ull : (1ull << (8 * h)) - 1, below_l = l == 8 ? ~0ull : (1ull << (8 * l)) - 1;
-  return below_h & ~below_l;
-}
-
 // PACK: the layer packs TL tiles into one 64-channel block (plan.hpp): block channel c' holds channel c' % Cq of tile
 // (c' / Cq) * Tg + tau, so every gathered row segment has its own tile origin; everything after the gather is the same.
 template <int KS1, bool WIDE, bool PACK>
@@ -87,9 +80,9 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
     return o;
   };
   // A thread's NT row segments are requested together and only then masked and written to LDS (one after the
-  // other, each load would be waited for in turn: three memory latencies instead of one).  A segment that begins before
-  // the tensor or ends behind it is loaded from the nearest 16 bytes inside and moved into place afterwards (byte by byte,
-  // the few blocks it happens in took half as long again as all others, and the next kernel waits for them).
+  // other, each load would be waited for in turn: three memory latencies instead of one).  A segment that sticks out of the
+  // tensor is loaded from the nearest 16 bytes inside and moved into place (byte by byte, the few blocks it happens in took
+  // half as long again as all others, and the next kernel waits for them).
   constexpr int NT = (64 * ROWS + 255) / 256;
   const bool tiny = P.total < 16;                    // the tensor itself is smaller than a load
   v4i val[NT];
@@ -104,7 +97,7 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
       const int ch = cblk & (P.Cq - 1), tile = (cblk >> P.cq_shift) * P.Tg + tau;
       const Origin o = tile_origin(min(tile, P.T - 1), ch);
       const int gy = o.y0 + a;
-      const long long from = o.base + (long long)a * P.W, at = max(min(from, P.total - 16), 0ll);
+      const long long from = o.base + (long long)a * P.W, at = segment_at(from, P.total);
       moved[k] = (int)(from - at);                   // rows inside the image: their segments overlap the tensor or are masked
       there[k] = task < 64 * ROWS && tile < P.T && ch < P.C && a < P.t && gy >= 0 && gy < P.H;
       val[k] = (v4i){0, 0, 0, 0};
@@ -114,11 +107,8 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
     }
   } else {
     const Origin o = tile_origin(tau, cb * 64);
-    // offsets from the origin that a 16-byte load may start at: [lo, hi] (rows outside the image are excluded
-    // separately, so saturating the bounds to 32 bits changes nothing).  An origin inside the last 16 bytes of the tensor makes
-    // hi negative, down to -15; the loads' base lies 16 bytes before the origin, so that their offsets are not.
-    const int lo = (int)min(max(-o.base, 0ll), 0x7FFFFFFFll);
-    const int hi = (int)min(max(P.total - 16 - o.base, -16ll), 0x7FFFFFFFll);
+    // offsets from the origin that a load may start at (rows outside the image are excluded separately)
+    const SegmentRange inside = segment_range(o.base, P.total);
     const bool columns = o.x0 < P.W && o.x0 + P.t > 0;                                 // (wide padding: perhaps none)
     const int a_lo = max(-o.y0, 0), a_count = columns ? max(min(P.t, P.H - o.y0) - a_lo, 0) : 0;     // rows inside the image
     const int chans = P.C - cb * 64;
@@ -127,7 +117,7 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
     for (int k = 0; k < NT; ++k) {
       const int task = threadIdx.x + 256 * k;
       const int cblk = task / ROWS, a = task - cblk * ROWS;
-      const int from = cblk * P.HW + a * P.W, at = min(max(from, lo), hi);     // 64 * H * W stays far below 2^31
+      const int from = cblk * P.HW + a * P.W, at = segment_at(from, inside);   // 64 * H * W stays far below 2^31
       moved[k] = tiny ? (int)o.base + from : from - at;
       there[k] = (256 * (k + 1) <= 64 * ROWS || task < 64 * ROWS) && cblk < chans && (uint32_t)(a - a_lo) < (uint32_t)a_count;
       val[k] = (v4i){0, 0, 0, 0};
@@ -183,17 +173,9 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
 #pragma unroll
   for (int k = 0; k < NT; ++k) {
     if (there[k] && moved[k] != 0) {
-      // byte b of the segment is byte b + moved of what was loaded (16 and more bytes apart: everything is masked)
       unsigned long long w0 = (uint32_t)val[k][0] | (unsigned long long)(uint32_t)val[k][1] << 32;
       unsigned long long w1 = (uint32_t)val[k][2] | (unsigned long long)(uint32_t)val[k][3] << 32;
-      const int s = min(abs(moved[k]), 15);
-      if (moved[k] > 0) {
-        if (s >= 8) { w0 = w1; w1 = 0; }
-        if (s & 7) { w0 = w0 >> (8 * (s & 7)) | w1 << (64 - 8 * (s & 7)); w1 >>= 8 * (s & 7); }
-      } else {
-        if (s >= 8) { w1 = w0; w0 = 0; }
-        if (s & 7) { w1 = w1 << (8 * (s & 7)) | w0 >> (64 - 8 * (s & 7)); w0 <<= 8 * (s & 7); }
-      }
+      move_segment(moved[k], w0, w1);
       val[k] = (v4i){(int)(uint32_t)w0, (int)(uint32_t)(w0 >> 32), (int)(uint32_t)w1, (int)(uint32_t)(w1 >> 32)};
     }
   }
@@ -333,7 +315,7 @@ __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
   const int img = (int)fast_div((uint32_t)trow, P.by_th), ty = trow - img * P.th;
   const int y0 = ty * P.m - P.pad, x0 = tx * P.m - P.pad;
   const int plane = (img * P.C + (live ? ch : 0)) * P.HW;              // below 2^31, as the whole tensor
-  const int last = (int)P.total - 16;                                  // the layer's tensor has 16 bytes and more
+  const SegmentRange inside = {0, (int)P.total - 16};                  // the layer's tensor has 16 bytes and more
   v4i val[ROWS];
   bool there[ROWS];
   int moved[ROWS];                                                     // how far the load was moved, see above
@@ -341,7 +323,7 @@ __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
   for (int a = 0; a < ROWS; ++a) {
     const int gy = y0 + a;
     there[a] = live && a < P.t && gy >= 0 && gy < P.H;
-    const int from = plane + (there[a] ? gy : 0) * P.W + x0, at = min(max(from, 0), last);
+    const int from = plane + (there[a] ? gy : 0) * P.W + x0, at = segment_at(from, inside);
     moved[a] = from - at;
     val[a] = (v4i){0, 0, 0, 0};
     if (there[a]) __builtin_memcpy(&val[a], P.x + (uint32_t)at, 16);   // one unaligned 16-byte load
@@ -368,14 +350,7 @@ __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
     if (there[a] && moved[a] != 0) {
       unsigned long long w0 = (uint32_t)val[a][0] | (unsigned long long)(uint32_t)val[a][1] << 32;
       unsigned long long w1 = (uint32_t)val[a][2] | (unsigned long long)(uint32_t)val[a][3] << 32;
-      const int s = min(abs(moved[a]), 15);
-      if (moved[a] > 0) {
-        if (s >= 8) { w0 = w1; w1 = 0; }
-        if (s & 7) { w0 = w0 >> (8 * (s & 7)) | w1 << (64 - 8 * (s & 7)); w1 >>= 8 * (s & 7); }
-      } else {
-        if (s >= 8) { w1 = w0; w0 = 0; }
-        if (s & 7) { w1 = w1 << (8 * (s & 7)) | w0 >> (64 - 8 * (s & 7)); w0 <<= 8 * (s & 7); }
-      }
+      move_segment(moved[a], w0, w1);
       val[a] = (v4i){(int)(uint32_t)w0, (int)(uint32_t)(w0 >> 32), (int)(uint32_t)w1, (int)(uint32_t)(w1 >> 32)};
     }
   }

@@ -3,27 +3,12 @@
 #include <hip/hip_runtime.h>
 #include <cstdint>
 
-#include "layout.hpp"
+#include "address_math.hpp"
 
 namespace rnswino {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v2i __attribute__((ext_vector_type(2)));
-
-// Division of 0 <= n < 2^31 by a fixed d >= 1 as one high multiplication: mul = ceil(2^(31 + shift) / d), shift = ceil(log2 d),
-// so mul d - 2^(31 + shift) < d <= 2^shift and the quotient of 2n mul / 2^(32 + shift) is off by less than 1/d.  (The division
-// that the compiler writes is 25 dependent instructions, and a kernel's first load waits for up to five of them.)
-struct FastDiv {
-  uint32_t mul, shift;
-};
-inline FastDiv make_fast_div(uint32_t d) {
-  FastDiv f;
-  f.shift = 0;
-  while ((1ull << f.shift) < d) ++f.shift;
-  f.mul = (uint32_t)(((1ull << (31 + f.shift)) + d - 1) / d);
-  return f;
-}
-__device__ __forceinline__ uint32_t fast_div(uint32_t n, FastDiv d) { return __umulhi(n << 1, d.mul) >> d.shift; }
 
 // Constants of one 8-bit modulus for biased_lowbyte() and mod_near(): one 16-byte scalar load.
 struct Residue8 {

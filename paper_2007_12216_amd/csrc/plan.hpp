@@ -37,6 +37,9 @@ struct Transforms {
 // Exact modular helpers (plan_math.cpp).
 int64_t mod_inverse(int64_t a, int64_t p);              // -1 when gcd(a, p) != 1
 int32_t sym_residue(int64_t v, int64_t p);              // representative in [-(p-1)/2, (p-1)/2]
+// biased_lowbyte() (kernels_common.hpp) for an odd p <= 253: where an accumulator starts and the constant of its quotient.
+struct BiasedStart { int acc_bias; float quot_bias; };
+BiasedStart biased_start(int p);
 std::vector<int> interpolation_points(int t);           // the t-1 finite points 0, 1, -1, 2, -2, ...
 int build_transforms(int m, int r, uint32_t p, Transforms &out);   // RNSWINO_OK or an error code
 int validate_desc(const rnswino_desc_t &d, Dims &dims);            // fills dims; all host-side checks

@@ -45,6 +45,14 @@ int32_t sym_residue(int64_t v, int64_t p) {
   return (int32_t)(w - h);
 }
 
+BiasedStart biased_start(int p) {
+  // the multiple a = 256 j of smallest magnitude for which 1.5 * 2^23 + a is a multiple of p (256 is a unit modulo the odd p, so
+  // |a| <= 128 (p - 1))
+  const int magic = 12582912;
+  const int a = 256 * sym_residue(-(int64_t)(magic % p) * mod_inverse(256 % p, p), p);
+  return {0x4B400000 + a, (float)(magic - (magic + a) / p)};
+}
+
 std::vector<int> interpolation_points(int t) {
   std::vector<int> pts;
   pts.push_back(0);

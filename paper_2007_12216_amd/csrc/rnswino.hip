@@ -77,12 +77,9 @@ KParams make_params(const rnswino_plan_t *pl) {
     if (!pl->crt_c_exact_small[i]) P.crt24 = 0;
     P.bias_p[i] = d.wide ? 0 : (int)(pl->desc.moduli[i] * 4194304u + pl->desc.moduli[i]);
     if (!d.wide) {
-      // biased_lowbyte(): the multiple a = 256 j of smallest magnitude for which 1.5 * 2^23 + a is a multiple of p (256 is
-      // a unit modulo the odd p, so |a| <= 128 (p - 1))
-      const int p = P.p[i], magic = 12582912;
-      const int a = 256 * sym_residue(-(int64_t)(magic % p) * mod_inverse(256 % p, p), p);
-      P.acc_bias[i] = 0x4B400000 + a;
-      P.quot_bias[i] = (float)(magic - (magic + a) / p);
+      const BiasedStart start = biased_start(P.p[i]);
+      P.acc_bias[i] = start.acc_bias;
+      P.quot_bias[i] = start.quot_bias;
     }
   }
   {
@@ -739,12 +736,8 @@ struct DirectChoice {
 static DirectChoice choose_direct(const DirectParams &P) {
   const long long nkb = P.Kp / 16, ntb = (P.npix + 15) / 16;
   auto blocks = [&](int brf, int btf) { return ((nkb + brf - 1) / brf) * (((ntb + btf - 1) / btf + 7) / 8 * 8); };
-  // Patch kernel (k_direct_conv_patch) where its LDS leaves two workgroups per compute unit.  The longest patch of `pixels`
-  // consecutive output pixels: every row boundary among them adds r - 1 pixels of border, every image boundary r - 1 rows more.
-  auto patch_pixels = [&](long long pixels) {
-    const long long plane = (long long)P.Ho * P.Wo, images = P.N == 1 || plane % pixels == 0 ? 0 : (pixels - 2) / plane + 1;
-    return pixels + ((pixels - 2) / P.Wo + 1) * (P.r - 1) + images * (P.r - 1) * P.Wp + (P.r - 1) * (P.Wp + 1LL);
-  };
+  // Patch kernel (k_direct_conv_patch) where its LDS leaves two workgroups per compute unit.
+  auto patch_pixels = [&](long long pixels) { return rnswino::patch_pixels(pixels, P.N, P.Ho, P.Wo, P.Wp, P.r); };
   auto patch_lds = [&](int btf) { return (patch_pixels(16 * btf) + 15) / 16 * 1024 * (P.Cp > 64 ? 2 : 1); };
   auto fits = [&](int btf) { return patch_lds(btf) <= 81920; };
   auto patch = [&](int wm, int wn, int rm, int nt, int depth) {
