@@ -293,8 +293,8 @@ __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
   constexpr int ROWS = KS1 == 1 ? 8 : 10;
   constexpr int CROW = (4 * KS1 + 1) * 16;
   __shared__ __attribute__((aligned(16))) uint8_t xs[256 * CROW];      // [channel][tile][slots]
-  Residue8 rc = P.res[blockIdx.y];
-  asm volatile("" ::"s"(rc.inv), "s"(rc.quot_bias), "s"(rc.neg_p), "s"(rc.acc_bias), "s"(P.x), "s"(P.V), "s"(P.KB), "s"(P.units),
+  // (the residues' constants are fetched with their items)
+  asm volatile("" ::"s"(P.x), "s"(P.V), "s"(P.KB), "s"(P.units),
                "s"(P.per_xcd), "s"(P.ncb), "s"(P.split), "s"(P.by_ncb.mul), "s"(P.by_ncb.shift), "s"(P.by_tw.mul), "s"(P.by_tw.shift),
                "s"(P.by_th.mul), "s"(P.by_th.shift), "s"(P.C), "s"(P.H), "s"(P.W), "s"(P.HW), "s"(P.m), "s"(P.pad), "s"(P.t), "s"(P.tw),
                "s"(P.th), "s"(P.n), "s"(P.CB1), "s"(P.P2), "s"(P.total));
