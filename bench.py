@@ -23,15 +23,18 @@ One JSON line is printed: the contract fields plus
                   duration, measured with HIP events that take each kernel's own start and stop timestamps on the launch
                   stream (a pass of its own over the same rotation, same step count), against 8 TB/s HBM; `traffic` is
                   the HBM bytes per launch recorded from rocprofv3 counters in profiles/hbm_traffic.json for exactly the
-                  kernel instantiation that ran (null when the file has no entry for it);
+                  kernel instantiation that ran (null when the file has no entry for it; `traffic_source` says whether the
+                  kernels' code is still what was measured);
   cpu_baseline -- the direct-convolution oracle timed on this machine's host cores (context only).
 """
 from __future__ import annotations
 
 import argparse
 import ctypes
+import hashlib
 import json
 import os
+import re
 import statistics
 import sys
 import time
@@ -44,6 +47,7 @@ HBM_PEAK_GBS = 8000.0
 INT8_MFMA_PEAK_TOPS = 5000.0
 ROTATION_BYTES = 640 << 20      # operands cycled through in the cold loop (> 256 MB Infinity Cache + 32 MB L2)
 ROUNDS = 5
+CSRC = os.path.join(ROOT, "paper_2007_12216_amd", "csrc")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 STAGES = ("input_transform", "residue_gemm", "inverse_transform_crt")
 
@@ -109,6 +113,15 @@ def stage_mfma_ops(cfg, plan):
     return {"input_transform": 2.0 * n * up(t * t, 16) * slots1 * plan.T * Cp * (2 if wide else 1),
             "residue_gemm": 2.0 * n * t * t * Kp * Cp * Tp * (4 if wide else 1),
             "inverse_transform_crt": 2.0 * n * up(m * m, 16) * up(t * t, 64) * cfg["K"] * plan.T * (4 if wide else 1)}
+
+
+def kernel_code_digest(directory: str = None) -> str:
+    """Digest of the sources of the three kernels, comments and white space left out: what the recorded traffic was measured on."""
+    text = ""
+    for name in ("layout", "address_math", "kernels_common", "k_input_transform", "k_residue_gemm", "k_residue_gemm_lds", "k_inverse_crt"):
+        with open(os.path.join(directory or CSRC, name + ".hpp")) as f:
+            text += re.sub(r"//[^\n]*|/\*.*?\*/", "", f.read(), flags=re.S)
+    return hashlib.sha256("".join(text.split()).encode()).hexdigest()[:16]
 
 
 def recorded_traffic(kernel_name: str):
@@ -247,7 +260,8 @@ def bench_layer(idx, steps, warmup, dev, with_cpu, warm=False, events=True):
                     "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                     "traffic": rec["hbm_bytes"] if rec else None,
                     "traffic_source": ({"file": "profiles/hbm_traffic.json", "measured_at_commit": rec.get("commit"),
-                                        "workload": rec.get("workload")} if rec else None),
+                                        "workload": rec.get("workload"),
+                                        "kernels_unchanged_since": rec.get("kernel_code") == kernel_code_digest()} if rec else None),
                     "algorithmic_bytes": bytes_per[dominant],
                     "stage_us": {nm: round(stage_ms[nm] * 1e3, 2) for nm in names},
                     "stage_GBps": {nm: round(bytes_per[nm] / (stage_ms[nm] * 1e-3) / 1e9, 1) for nm in names},

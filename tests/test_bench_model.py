@@ -58,3 +58,20 @@ def test_recorded_traffic_belongs_to_the_kernels_workload_2_launches():
         assert e["hbm_bytes"] == e["hbm_read_bytes"] + e["hbm_write_bytes"] and 0.9 * want[stage] < e["hbm_bytes"] < 2.0 * want[stage]
         assert bench.recorded_traffic(kernel)["hbm_bytes"] == e["hbm_bytes"] and e["commit"]
     assert bench.recorded_traffic("k2_residue_gemm<9, 9, 9, false>") is None
+
+
+def test_the_digest_of_the_kernels_sees_code_and_not_comments(tmp_path):
+    import json
+    import os
+    import shutil
+    for name in os.listdir(bench.CSRC):
+        shutil.copy(os.path.join(bench.CSRC, name), tmp_path / name)
+    digest = bench.kernel_code_digest()
+    path = tmp_path / "k_inverse_crt.hpp"
+    text = path.read_text()
+    path.write_text("// a comment\n" + text.replace("\n", "   // and another\n", 1) + "/* and\none more */\n")
+    assert bench.kernel_code_digest(str(tmp_path)) == digest
+    path.write_text(text.replace("(unit >= P.units)", "(unit > P.units)"))
+    assert bench.kernel_code_digest(str(tmp_path)) != digest
+    with open(bench.TRAFFIC_FILE) as f:
+        assert all(len(e["kernel_code"]) == len(digest) for e in json.load(f)["kernels"])
