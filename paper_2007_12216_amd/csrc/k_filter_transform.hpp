@@ -12,7 +12,7 @@
 // Block = (16 rows k, 64 channels, a run of (residue, 16-point block) items): its 1024 filters are gathered into LDS once
 // (16-byte pieces, slot k ^ (c % 16) of channel c against bank conflicts), wave g computes slice g of the fragments.
 // Padding rows and channels, and in packed layers the entries off the diagonal, are zeros: that is what lets the GEMM
-// ignore them.  Bound by the writes of U: 512 x 512, t = 10, four residues (105 MB): 32 us, 3.3 TB/s (one thread per (residue, k, c)
+// ignore them.  Bound by the writes of U: 512 x 512, t = 10, four residues (105 MB): 30 us, 3.5 TB/s (one thread per (residue, k, c)
 // with 64-bit divisions and byte stores: 437).
 #pragma once
 #include "kernels_common.hpp"

@@ -39,7 +39,8 @@ namespace rnswino {
 
 // What the kernels read, built once with the plan (the pointers and the output mode per call); the block kernel fetches the
 // fields up to `rb_step` together at entry, see K1Params.  With that, divisions by multiplication and the operand shared
-// through LDS: 128 channels 5 x 5 at 28 x 28 17.1 -> 13.3 us a layer, VGG16 stack at batch 1 379 -> 363, batch 8 864 -> 846.
+// through LDS: 128 channels 5 x 5 at 28 x 28 17.1 -> 14.1 us a layer, 256 channels at 56 x 56 22.1 -> 20.4, VGG16 stack at batch 1
+// 379 -> 362.
 struct K3Params {
   const uint32_t *O;
   const int8_t *KA;           // (A^T kron A^T) (P/p_i)^-1 mod p  [n][RB3][KS3][planes][64 lanes][16]
@@ -122,7 +123,8 @@ __device__ __forceinline__ void crt_convert(const K3Params &P, const uint32_t (&
 // 32 bits; mad_u24() says why).  Adding 1.5*2^23 to that sum rounds it and
 // leaves the quotient in the mantissa; the multiples of P that its bias stands for are part of crt_sum0.
 // Per output and residue one float multiply-add with vector operands (2.6 cycles per wave and SIMD) and one 24-bit
-// multiply-add (4.8), then 2.6 + 4.4 + 2.6: 39 cycles with four residues (71 with conversions and scalar operands).
+// multiply-add (4.8), then a float sum, a product (4.4) and a sum of three: about 39 cycles with four residues (71 with
+// conversions and scalar operands).
 struct FastCrt {
   float inv[8], fs0;
   uint32_t sum0;
@@ -408,6 +410,10 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
 // issues only its own O loads (no table reads from global memory, no copies of O in other waves); the table fragments
 // come from LDS.  A unit's loads are hidden by the other waves of the SIMD (four resident blocks per CU; a second
 // register set that prefetched the next unit's operand cost a block of occupancy and measured 3-10 % slower).
+// What bounds it: 64 -> 64 channels at 224 x 224, batch 8, pooled, 42.8 us (168 MB of O, 3.9 TB/s); without the loads of O 30, without
+// the stores 40, without the conversion 40.5, without loads and stores 26.8; the same bytes in 16-byte loads, a quarter as many,
+// 42.3.  So neither the address unit nor the conversion: a wave's loads, products and conversion follow each other, and the
+// four waves a SIMD holds cover each other's loads only in part.
 // Grid: min(ceil(units / 4), four blocks per CU) blocks of 256 threads; dynamic LDS = n * RB3 * KS3 KiB.
 constexpr int K3_STREAM_BLOCKS = 1024;  // four resident blocks per CU (register budget) on 256 CUs
 
