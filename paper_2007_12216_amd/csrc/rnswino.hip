@@ -736,10 +736,20 @@ struct DirectChoice {
 static DirectChoice choose_direct(const DirectParams &P) {
   const long long nkb = P.Kp / 16, ntb = (P.npix + 15) / 16;
   auto blocks = [&](int brf, int btf) { return ((nkb + brf - 1) / brf) * (((ntb + btf - 1) / btf + 7) / 8 * 8); };
-  // Patch kernel (k_direct_conv_patch) where its LDS leaves two workgroups per compute unit.
+  // Patch kernel (k_direct_conv_patch) where its LDS leaves two workgroups per compute unit, unless there is too little to do with a
+  // patch (us per call, patch / k_direct_conv; steps of a block: taps x 64-channel blocks):
+  // - a single tap: a barrier per step, for which it has fetched one step ahead instead of three (2048 -> 256 at 7 x 7 17.3 / 13.4,
+  //   1024 -> 1024 at 14 x 14 12.7 / 11.3);
+  // - up to 18 steps and many blocks, where the stores of y decide and 128 x 128 blocks take them better (3 x 3, batch 8: 3 -> 512 at
+  //   112 x 112 63.1 / 55.1, 64 -> 256 42.2 / 39.5; with 832 blocks, 64 -> 256 at 56 x 56, 16.4 / 18.6);
+  // - 2 x 2 filters, up to 8 steps, from 800 of the smallest blocks on (batch 8, 64 -> 256 at 28 x 28 10.6 / 9.7, 64 -> 1024 19.4 / 16.8;
+  //   below, 64 -> 64, 8.1 / 8.5; from 1536 of the largest on, 64 -> 1024 at 56 x 56, 41.0 / 43.4).
+  const int steps = P.r * P.r * (P.Cp / 64);
+  const bool many = blocks(4, 16) >= 1536;
+  const bool patches = P.r > 2 ? !(steps <= 18 && P.Kp > 64 && many) : P.r == 2 ? !(steps <= 8 && blocks(2, 4) >= 800 && !many) : false;
   auto patch_pixels = [&](long long pixels) { return rnswino::patch_pixels(pixels, P.N, P.Ho, P.Wo, P.Wp, P.r); };
   auto patch_lds = [&](int btf) { return (patch_pixels(16 * btf) + 15) / 16 * 1024 * (P.Cp > 64 ? 2 : 1); };
-  auto fits = [&](int btf) { return patch_lds(btf) <= 81920; };
+  auto fits = [&](int btf) { return patches && patch_lds(btf) <= 81920; };
   auto patch = [&](int wm, int wn, int rm, int nt, int depth) {
     return DirectChoice{(int)patch_pixels(16 * wn * nt), wm, wn, rm, nt, depth, (unsigned)blocks(wm * rm, wn * nt), (size_t)patch_lds(wn * nt)};
   };
@@ -754,7 +764,7 @@ static DirectChoice choose_direct(const DirectParams &P) {
   if (P.Kp > 64 && blocks(4, 16) >= 384 && fits(16)) return patch(1, 4, 4, 4, 4);
   if (P.Kp > 16 && blocks(4, 8) >= 384 && fits(8)) return patch(2, 2, 2, 4, 4);
   if ((P.Kp <= 16 || blocks(4, 8) < 384) && fits(4)) return patch(2, 2, 1, 2, 8);
-  // The others -- planes so wide that a patch outgrows LDS -- fetch every tap's pixels anew.  Block shape: 128 x 128 when that
+  // The others -- planes so wide that a patch outgrows LDS, and the cases above -- fetch every tap's pixels anew.  Block shape: 128 x 128 when that
   // still gives the chip two workgroups per compute unit, else 128 x 64, else 64 x 64; layers with at most 64 filters 64 x 256
   if (P.Kp <= 64 && blocks(4, 16) >= 512) return plain(1, 4, 4, 4, 3);
   if (P.Kp > 64 && blocks(8, 8) >= 512) return plain(2, 2, 4, 4, 3);

@@ -57,7 +57,12 @@ CASES = [
     (8, 70, 40, 81, 80, 3, 1),        # 32 x 256, two channel blocks, shifted rows
     (8, 20, 72, 113, 111, 3, 1),      # 64 x 256, one channel block, shifted rows
     (9, 70, 72, 81, 80, 3, 1),        # 64 x 256, two channel blocks, shifted rows
-    (6, 3, 130, 150, 99, 1, 0),       # 64 x 256, 1 x 1 filter: a step per channel block
+    # too few steps for patches: 1 x 1 filters, 2 x 2 filters on many pixels, few channels with many filters and pixels
+    (6, 3, 130, 150, 99, 1, 0),
+    (2, 330, 40, 9, 11, 1, 0),
+    (8, 70, 250, 27, 29, 2, 1),
+    (5, 9, 30, 31, 20, 2, 0),         # 2 x 2 filters, patches
+    (8, 20, 200, 113, 111, 3, 1),
 ]
 
 

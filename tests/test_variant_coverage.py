@@ -45,6 +45,18 @@ def test_the_direct_convolution_cases_reach_every_instantiation():
         assert e.value.code == code
 
 
+@pytest.mark.parametrize("case,patches", [
+    ((1, 2048, 512, 7, 7, 1, 0), False), ((8, 64, 64, 56, 56, 1, 0), False),                  # a single tap
+    ((8, 3, 512, 112, 112, 3, 1), False), ((8, 128, 256, 112, 112, 3, 1), False),             # few steps, many blocks
+    ((8, 64, 256, 56, 56, 3, 1), True), ((8, 129, 256, 112, 112, 3, 1), True), ((8, 64, 64, 224, 224, 3, 1), True),
+    ((8, 64, 256, 28, 28, 2, 1), False), ((8, 64, 1024, 28, 28, 2, 1), False),                # 2 x 2 filters
+    ((8, 64, 64, 28, 28, 2, 1), True), ((8, 64, 1024, 56, 56, 2, 1), True), ((8, 256, 1024, 28, 28, 2, 1), True),
+    ((8, 256, 256, 56, 56, 3, 1), True), ((1, 3, 8, 7, 7, 3, 1), True)])
+def test_the_direct_convolution_stages_patches_only_where_they_are_used_often_enough(case, patches):
+    """Both sides of each line, measured (times beside choose_direct); with patches the 1 x 1 layers took up to 1.5 times as long."""
+    assert rn.rnswino_direct_describe(*case)["kernel"].startswith("k_direct_conv_patch") == patches
+
+
 def _conversion(C, moduli, r=3, m=8, flags=HOST, K=16, hw=16):
     plan = rn.rnswino_plan(1, C, K, hw, hw, r, m, r // 2, moduli, flags=flags)
     return rn.rnswino_plan_describe(plan)["conversion"]
