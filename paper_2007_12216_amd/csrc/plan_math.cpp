@@ -199,13 +199,26 @@ int validate_desc(const rnswino_desc_t &d, Dims &o) {
   o.CB1 = (o.P2 + 15) / 16;
   o.RP1 = (t + 3) / 4 * 4;
   o.KS1 = (t * o.RP1 + 63) / 64;
-  // Input transform 16 tiles at a time: from 12 blocks of 16 tiles on, with about three workgroups per eight compute units (us
-  // per layer with blocks of one tile / of 16: 64 -> 64 channels at 224 x 224, batch 8 214 / 170; 128 -> 128 at 112 x 112, batch 8
-  // 89.6 / 84.4, batch 1 27.6 / 26.4; 100 -> 75 at 57 x 57, batch 3 21.4 / 20.5; below the line, 512 -> 512 at 28 x 28, batch 8
-  // (8 blocks of tiles) 50.8 / 51.5 and 256 -> 256 at 56 x 56 (49 tiles) 20.7 / 22.0).  Its offsets have 32 bits.
+  // Input transform 16 tiles at a time, where its larger workgroups are many enough; in between the layers with one tile per block
+  // are faster (us per layer, cold inputs, blocks of one tile / of 16; F(8,3), four moduli, unless noted):
+  // - t <= 8: from 384 (block, modulus) pairs on (F(4,5), 128 channels at 14 x 14, batch 12 (384) 15.5 / 14.8; F(4,3), two moduli, at
+  //   35 x 35, batch 4 (336) 12.9 / 13.6);
+  // - t = 9, 10 and planes of 49 tiles: from 384 blocks on (128 channels at 112 x 112, batch 4 (392) 40.4 / 37.7, 64 at batch 8 48.7 /
+  //   46.3, one modulus 29.6 / 28.4; 256 at 56 x 56, batch 6 (304) 31.1 / 32.6), and from 400 pairs on where the blocks of one tile
+  //   are fewer than 512 and gather once per modulus (128 channels at 112 x 112, batch 1 (416) 23.9 / 22.8; three moduli (312) 20.1 / 20.4);
+  // - smaller planes, whose tiles' row segments lie further apart: from 384 blocks and 1152 pairs on (three moduli, 256 channels at
+  //   28 x 28, batch 24 (1152) 31.7 / 31.0; two, batch 21, 35 x 35 (1056) 31.5 / 31.8);
+  // - planes of one tile, nothing adjacent: from 4096 pairs on (256 channels at 8 x 8, batch 1000 (4032) 79.4 / 70.6, warm 66.6 / 68.4;
+  //   128 channels, batch 320 27.9 / 35.9).
+  // Its offsets have 32 bits.
   const long long elements = (long long)d.N * d.C * d.H * d.W;
-  o.vlane = !o.wide && o.KS1 <= 2 && elements >= 16 && elements < (1LL << 31) && o.Tp / 16 >= 12 &&
-            4LL * (o.Tp / 16) * (o.Cp / 64) >= 96;
+  const long long blocks1 = (long long)o.Tg * (o.Cp / 64), blocks16 = 4LL * (o.Tp / 16) * (o.Cp / 64), pairs16 = blocks16 * o.n;
+  const int plane = o.th * o.tw;
+  const bool many = plane == 1   ? pairs16 >= 4096
+                    : o.KS1 == 1 ? pairs16 >= 384
+                    : plane < 49 ? blocks16 >= 384 && pairs16 >= 1152
+                                 : blocks16 >= 384 || (blocks1 < 512 && pairs16 >= 400);
+  o.vlane = !o.wide && o.KS1 <= 2 && elements >= 16 && elements < (1LL << 31) && o.Tp / 16 >= 12 && many;
   o.RB3 = (d.m * d.m + 15) / 16;
   o.KS3 = (o.P2 + 63) / 64;
   // the kernels address the GEMM output O = [Kp][n][Q][Tp] words (two planes for 16-bit moduli) with 32-bit byte

@@ -203,7 +203,7 @@ K1Choice choose_k1(const Dims &d) {
   // enough units to fill the chip (the pixel gather is then done once instead of n times; measured on the VGG16
   // stack, two blocks per CU are already enough for that to win; of the 16-tile blocks, which gather sixteen times as much, three
   // for every four CUs: 128 -> 128 at 56 x 56, batch 8, 200 units 36.0 us a layer split, 34.5 not, and at 112 x 112, batch 1, 104
-  // units 26.4 and 28.3)
+  // units 26.4 and 28.3; with 200 units only layers of t <= 8 and planes of one tile still take them)
   c.gx = (unsigned)((units + 7) / 8 * 8);
   c.gy = (unsigned)(units >= (c.tiles ? 192 : 512) ? 1 : d.n);
   return c;

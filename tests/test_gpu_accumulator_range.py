@@ -11,25 +11,29 @@ from oracle import direct_conv2d
 pytestmark = pytest.mark.gpu
 
 
-# one image per modulus (blocks of one tile), and many images (blocks of 16 tiles: all residues in one, one residue each with packed channels)
-@pytest.mark.parametrize("images,C", [(0, 16), (800, 64), (1600, 16)])
+# one tile per modulus (blocks of one tile), and many images of 2 x 2 tiles (blocks of 16 tiles, also with packed channels: all residues
+# in one for the tiles of 8, one residue each for those of 2), each with one tile that drives the sum, in every lane of a block in turn
+@pytest.mark.parametrize("images,C", [(0, 16), (384, 64), (1536, 16)])
 @pytest.mark.parametrize("m,moduli", [(8, (251, 241, 239)), (8, (253, 251, 247)), (14, (251, 241, 239)), (2, (3, 5, 7, 11, 13, 17, 19, 23))])
 @pytest.mark.parametrize("sign", [1, -1])
 def test_tiles_that_drive_one_transform_point_to_its_largest_sum(m, moduli, sign, images, C):
     from paper_2007_12216_amd.layer import ConvLayer
-    r, t, K, N = 3, m + 2, 16, images or len(moduli)
+    r, t, K = 3, m + 2, 16
+    N, H = (images if m == 8 else images // 8, t + m) if images else (len(moduli), t)
     print("accumulator range", m, moduli, sign, N, C, flush=True)
-    layer = ConvLayer(N, C, K, t, t, r, m, 0, moduli, flags=rn.FLAG_ALLOW_UNCHECKED_RANGE)
+    layer = ConvLayer(N, C, K, H, H, r, m, 0, moduli, flags=rn.FLAG_ALLOW_UNCHECKED_RANGE)
     sixteen = rn.rnswino_plan_describe(layer.plan)["kernels"][0].startswith("k1_input_transform_tiles")
     assert sixteen == (images > 0 and t <= 10)
-    x = np.empty((N, C, t, t), dtype=np.int8)
+    x = si.int8_tensor(612, (N, C, H, H))
     for i in range(len(moduli)):
         bt = rn.rnswino_plan_get_matrix(layer.plan, rn.MATRIX_BT, i).astype(np.int64)
         kron = np.einsum("ab,cd->acbd", bt, bt).reshape(t * t, t * t)
         p = moduli[i]
         kron = (kron + (p - 1) // 2) % p - (p - 1) // 2
         row = kron[np.abs(kron).sum(axis=1).argmax()].reshape(t, t)          # the worst row of modulus i, in every len(moduli)-th image
-        x[i::len(moduli)] = np.where(sign * row > 0, 127, -128)
+        for img in range(i, N, len(moduli)):
+            j, k = divmod(img // len(moduli) % 4, 2) if images else (0, 0)
+            x[img, :, j * m:j * m + t, k * m:k * m + t] = np.where(sign * row > 0, 127, -128)
     w = si.int8_tensor(611, (K, C, r, r))
     w = (w // 32).astype(np.int8) if np.prod([float(p) for p in moduli]) < 1e8 else w     # inside the range of the set
     layer.set_weights(w)

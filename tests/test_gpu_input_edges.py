@@ -34,14 +34,14 @@ def test_segments_at_the_ends_of_the_tensor(N, C, K, H, W, r, m, pad, moduli):
 
 
 @pytest.mark.parametrize("N,C,K,H,W,r,m,pad,moduli", [
-    (8, 65, 2, 41, 43, 3, 8, 1, THREE[:2] + (239, 233)),         # two channel blocks, the second with one channel
+    (5, 65, 2, 50, 51, 3, 8, 1, THREE[:2] + (239, 233)),         # two channel blocks, the second with one channel
     (4, 70, 3, 57, 43, 3, 6, 1, THREE + (233,)),                 # 8 contraction slots a row, t * t a multiple of 16
     (9, 64, 2, 50, 47, 3, 7, 0, THREE + (233,)),                 # t = 9: a last block of one point, ragged tiles and tile block
-    (8, 40, 2, 31, 23, 1, 4, 0, THREE),                          # 1 x 1 filter, one full block of points
+    (11, 40, 2, 31, 23, 1, 4, 0, THREE),                         # 1 x 1 filter, one full block of points
     (9, 64, 2, 21, 22, 1, 3, 0, THREE),                          # t = 3: no full block of points
-    (48, 33, 2, 17, 18, 3, 8, 3, THREE),                         # several images in one block of tiles, wide padding
-    (1, 64, 2, 150, 160, 3, 8, 1, THREE + (233,)),               # a residue per block
-    (9, 3, 4, 200, 211, 3, 8, 1, THREE), (9, 17, 3, 75, 77, 3, 6, 1, THREE)])     # packed tiles, ragged last slot
+    (171, 33, 2, 17, 18, 3, 8, 3, THREE),                        # several images in one block of tiles, wide padding
+    (1, 64, 2, 150, 161, 3, 8, 1, THREE + (233,)),               # a residue per block
+    (10, 3, 4, 200, 211, 3, 8, 1, THREE + (233,)), (9, 17, 3, 75, 77, 3, 6, 1, THREE)])     # packed tiles, ragged last slot
 def test_sixteen_tiles_at_a_time(N, C, K, H, W, r, m, pad, moduli):
     from paper_2007_12216_amd.layer import ConvLayer
     print("sixteen tiles", N, C, K, H, W, r, m, pad, moduli, flush=True)

@@ -57,6 +57,20 @@ def test_the_direct_convolution_stages_patches_only_where_they_are_used_often_en
     assert rn.rnswino_direct_describe(*case)["kernel"].startswith("k_direct_conv_patch") == patches
 
 
+@pytest.mark.parametrize("n,N,C,hw,r,m,sixteen", [
+    (4, 12, 128, 14, 5, 4, True), (2, 4, 128, 35, 3, 4, False), (1, 4, 128, 56, 3, 4, True),            # t <= 8
+    (4, 4, 128, 112, 3, 8, True), (1, 8, 64, 112, 3, 8, True), (4, 8, 64, 224, 3, 8, True),             # t = 9, 10: 384 blocks
+    (4, 6, 256, 56, 3, 8, False), (4, 6, 128, 56, 3, 8, False), (1, 7, 256, 56, 3, 8, False),
+    (4, 1, 128, 112, 3, 8, True), (3, 1, 128, 112, 3, 8, False), (4, 8, 64, 56, 3, 8, True),            # few blocks of one tile
+    (3, 24, 256, 28, 3, 8, True), (2, 21, 256, 35, 3, 8, False), (4, 32, 512, 28, 3, 8, True),          # planes below 49 tiles
+    (4, 320, 128, 8, 3, 8, False), (3, 1600, 128, 8, 3, 8, False), (4, 1100, 256, 8, 3, 8, True),       # planes of one tile
+    (4, 1, 256, 56, 3, 8, False), (1, 1, 16, 16, 3, 8, False)])
+def test_the_input_transform_takes_16_tiles_at_a_time_only_where_that_is_faster(n, N, C, hw, r, m, sixteen):
+    """Both sides of each line, measured (times beside the rule); on the layers of one tile per plane 16 tiles took up to 1.3 times as long."""
+    plan = rn.rnswino_plan(N, C, 64, hw, hw, r, m, r // 2, (251, 241, 239, 233)[:n], flags=HOST | UNCHECKED)
+    assert rn.rnswino_plan_describe(plan)["kernels"][0].startswith("k1_input_transform_tiles") == sixteen
+
+
 def _conversion(C, moduli, r=3, m=8, flags=HOST, K=16, hw=16):
     plan = rn.rnswino_plan(1, C, K, hw, hw, r, m, r // 2, moduli, flags=flags)
     return rn.rnswino_plan_describe(plan)["conversion"]

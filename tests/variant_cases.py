@@ -55,7 +55,7 @@ def _candidates():
     add(1, 70, 40, 40, 40, 3, 8, 1, PRIMES8[:4], rn.FLAG_GEMM_BLOCK_64X16)       # the measurement form of the LDS-tiled GEMM
     # (b3) the input transform by 16 tiles with packed tiles (few channels, hundreds of packed columns)
     for m in (4, 8):
-        add(8, 20, 5, 10 * m, 10 * m, 3, m, 1, PRIMES8[:3])
+        add(8, 20, 5, 10 * m, 10 * m, 3, m, 1, PRIMES8[:4])
     # (c) 64-row GEMM blocks: K >= 256, two or more channel blocks (even and odd), enough work items
     for C in (128, 192):
         add(3, C, 256, 64, 64, 3, 8, 1, PRIMES8[:4])
