@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 def test_tiles_that_drive_one_transform_point_to_its_largest_sum(m, moduli, sign, images, C):
     from paper_2007_12216_amd.layer import ConvLayer
     r, t, K = 3, m + 2, 16
-    N, H = (images if m == 8 else images // 8, t + m) if images else (len(moduli), t)
+    N, H = (images if m == 8 else images // 4, t + m) if images else (len(moduli), t)
     print("accumulator range", m, moduli, sign, N, C, flush=True)
     layer = ConvLayer(N, C, K, H, H, r, m, 0, moduli, flags=rn.FLAG_ALLOW_UNCHECKED_RANGE)
     sixteen = rn.rnswino_plan_describe(layer.plan)["kernels"][0].startswith("k1_input_transform_tiles")

@@ -64,10 +64,11 @@ def test_the_direct_convolution_stages_patches_only_where_they_are_used_often_en
     (4, 1, 128, 112, 3, 8, True), (3, 1, 128, 112, 3, 8, False), (4, 8, 64, 56, 3, 8, True),            # few blocks of one tile
     (3, 24, 256, 28, 3, 8, True), (2, 21, 256, 35, 3, 8, False), (4, 32, 512, 28, 3, 8, True),          # planes below 49 tiles
     (4, 320, 128, 8, 3, 8, False), (3, 1600, 128, 8, 3, 8, False), (4, 1100, 256, 8, 3, 8, True),       # planes of one tile
+    (8, 12, 64, 14, 5, 4, False), (8, 24, 64, 14, 5, 4, True),                                          # many moduli, 48 and 96 blocks
     (4, 1, 256, 56, 3, 8, False), (1, 1, 16, 16, 3, 8, False)])
 def test_the_input_transform_takes_16_tiles_at_a_time_only_where_that_is_faster(n, N, C, hw, r, m, sixteen):
     """Both sides of each line, measured (times beside the rule); on the layers of one tile per plane 16 tiles took up to 1.3 times as long."""
-    plan = rn.rnswino_plan(N, C, 64, hw, hw, r, m, r // 2, (251, 241, 239, 233)[:n], flags=HOST | UNCHECKED)
+    plan = rn.rnswino_plan(N, C, 64, hw, hw, r, m, r // 2, (251, 241, 239, 233, 229, 227, 223, 211)[:n], flags=HOST | UNCHECKED)
     assert rn.rnswino_plan_describe(plan)["kernels"][0].startswith("k1_input_transform_tiles") == sixteen
 
 
