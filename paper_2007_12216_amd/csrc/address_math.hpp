@@ -44,6 +44,14 @@ RNSW_HD int segment_at(int from, SegmentRange r) {
   return at < r.hi ? at : r.hi;
 }
 
+// Where the load of the segment at `want` begins that starts at a multiple of four if it can: offsets from the multiple of four at or
+// before the tensor's start, `mis` bytes before it; loads of 16 bytes begin in [mis, last].  A wave's 16-byte loads from any byte take 59
+// cycles of a compute unit's address unit (37 with several waves at it), from multiples of four 27 (21).
+RNSW_HD int aligned_segment_at(int want, int mis, int last) {
+  const int at = (want & ~3) > mis ? (want & ~3) : mis;
+  return at < last ? at : last;
+}
+
 // byte b of the segment is byte b + moved of what was loaded (16 and more bytes apart: everything is masked)
 RNSW_HD void move_segment(int moved, unsigned long long &w0, unsigned long long &w1) {
   const int dist = moved < 0 ? -moved : moved, s = dist < 15 ? dist : 15;

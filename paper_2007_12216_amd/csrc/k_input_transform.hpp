@@ -285,14 +285,18 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
 // gather, not the bytes: 64 channels at 112 x 112, batch 8 (40 MB of V) took 20.3 us, 13.8 without its stores, 16.6 with every
 // gather from one line, 20.2 without its matrix instructions.  This one: 17.0; at 224 x 224 85 -> 53 us (cold input).
 // Block = (16 tiles, slice g of a 64-channel block: 16 channels), all residues or one; thread (channel, tile) gathers its t row
-// segments, then the waves take the (residue, 16-point block) items in turn, every item's pixels from LDS (conflict-free: the
-// tiles' rows are 16 bytes longer than their slots), its table fragments requested one item ahead.
+// segments into operand fragments, then the waves take the (residue, 16-point block) items in turn, every item's pixels from LDS in lane
+// order, its table fragments requested one item ahead.  (With one padded row per thread instead of fragments, half of the LDS cycles
+// were bank conflicts; a gather of unaligned loads, each with a branch of its own, took 4100 cycles of a block's 30000: 100 channels
+// at 57 x 43, batch 3, 14.9 -> 14.2 us a layer, 64 -> 128 at 112 x 112, batch 8, 66.4 -> 65.5, 64 -> 64 at 224 x 224 45.6 -> 44.6 the kernel.)
+// What is left, on that last shape: no stores 38.1, no residues 40.5, no products 37.4, neither gather nor table 37.8, all of these removed
+// 26.4, so nothing alone holds it.  Two items a step against the same pixels, half the LDS reads, take 160 registers: 16.7 against 17.1 us
+// with 392 blocks, 48 against 44.6 with 1568.
 // Grid: x = 4 * Tp/16 * Cp/64 rounded up to a multiple of 8 (kernels_common.hpp), y = n or 1.
 template <int KS1, bool PACK>
 __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
   constexpr int ROWS = KS1 == 1 ? 8 : 10;
-  constexpr int CROW = (4 * KS1 + 1) * 16;
-  __shared__ __attribute__((aligned(16))) uint8_t xs[256 * CROW];      // [channel][tile][slots]
+  __shared__ __attribute__((aligned(16))) uint8_t xs[16 * KS1 * 1024];     // fragments [channel][step][slice h][tile][16 slots]
   // (the residues' constants are fetched with their items)
   asm volatile("" ::"s"(P.x), "s"(P.V), "s"(P.KB), "s"(P.units),
                "s"(P.per_xcd), "s"(P.ncb), "s"(P.split), "s"(P.by_ncb.mul), "s"(P.by_ncb.shift), "s"(P.by_tw.mul), "s"(P.by_tw.shift),
@@ -315,18 +319,23 @@ __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
   const int img = (int)fast_div((uint32_t)trow, P.by_th), ty = trow - img * P.th;
   const int y0 = ty * P.m - P.pad, x0 = tx * P.m - P.pad;
   const int plane = (img * P.C + (live ? ch : 0)) * P.HW;              // below 2^31, as the whole tensor
-  const SegmentRange inside = {0, (int)P.total - 16};                  // the layer's tensor has 16 bytes and more
+  // Row segments as offsets from the multiple of four at or before the tensor's start; rows outside the image repeat its first or last
+  // row and are masked.  Only what the tensor holds is loaded: where clamping moves a load, the segment is put right below.
+  const int mis = (int)((uint32_t)(uintptr_t)P.x & 3u), last = (int)P.total - 16 + mis;     // (the tensor has 16 bytes and more)
+  const int8_t *const xa = P.x - mis;
+  const int from = plane + x0 + mis;
   v4i val[ROWS];
-  bool there[ROWS];
-  int moved[ROWS];                                                     // how far the load was moved, see above
+  int clamped = 0;
+  if (live) {
 #pragma unroll
-  for (int a = 0; a < ROWS; ++a) {
-    const int gy = y0 + a;
-    there[a] = live && a < P.t && gy >= 0 && gy < P.H;
-    const int from = plane + (there[a] ? gy : 0) * P.W + x0, at = segment_at(from, inside);
-    moved[a] = from - at;
-    val[a] = (v4i){0, 0, 0, 0};
-    if (there[a]) __builtin_memcpy(&val[a], P.x + (uint32_t)at, 16);   // one unaligned 16-byte load
+    for (int a = 0; a < ROWS; ++a) {
+      const int want = from + min(max(y0 + a, 0), P.H - 1) * P.W, at = aligned_segment_at(want, mis, last);
+      clamped |= at ^ (want & ~3);
+      __builtin_memcpy(&val[a], xa + (uint32_t)at, 16);                // one 16-byte load
+    }
+  } else {
+#pragma unroll
+    for (int a = 0; a < ROWS; ++a) val[a] = (v4i){0, 0, 0, 0};
   }
   // items of this wave: full 16-point blocks of all residues first (their stores need no test, so that the wait for the next
   // item's table does not become a wait for them), then the residues' last, partial blocks
@@ -344,29 +353,48 @@ __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
   if (nfull > 0) settle(); else i = i0 + nres;
   if (i < i0 + nres) load_table(i, cbk, ta);
   const unsigned long long m0 = byte_range(max(-x0, 0), min(P.t, P.W - x0), 0), m1 = byte_range(max(-x0, 0), min(P.t, P.W - x0), 8);
+  const uint32_t mask[3] = {live ? (uint32_t)m0 : 0u, live ? (uint32_t)(m0 >> 32) : 0u, live ? (uint32_t)m1 : 0u};
+  const int rows_in = min(P.t, P.H - y0);                              // row a is inside the image and the tile: -y0 <= a < rows_in
   __builtin_amdgcn_sched_barrier(0);
+  constexpr int WPR = KS1 == 1 ? 2 : 3;                                // words of a row
+  uint32_t slots[16 * KS1];
 #pragma unroll
-  for (int a = 0; a < ROWS; ++a) {
-    if (there[a] && moved[a] != 0) {
+  for (int d = 0; d < 16 * KS1; ++d) slots[d] = 0;
+  if (__builtin_expect(__any(clamped != 0), 0)) {
+#pragma unroll
+    for (int a = 0; a < ROWS; ++a) {
+      const int want = from + min(max(y0 + a, 0), P.H - 1) * P.W, at = aligned_segment_at(want, mis, last);
       unsigned long long w0 = (uint32_t)val[a][0] | (unsigned long long)(uint32_t)val[a][1] << 32;
       unsigned long long w1 = (uint32_t)val[a][2] | (unsigned long long)(uint32_t)val[a][3] << 32;
-      move_segment(moved[a], w0, w1);
-      val[a] = (v4i){(int)(uint32_t)w0, (int)(uint32_t)(w0 >> 32), (int)(uint32_t)w1, (int)(uint32_t)(w1 >> 32)};
+      move_segment(want - at, w0, w1);
+      slots[a * WPR] = (uint32_t)w0; slots[a * WPR + 1] = (uint32_t)(w0 >> 32);
+      if (WPR > 2) slots[a * WPR + 2] = (uint32_t)w1;
+    }
+  } else {
+#pragma unroll
+    for (int a = 0; a < ROWS; ++a) {
+      const uint32_t by = (uint32_t)(from + min(max(y0 + a, 0), P.H - 1) * P.W);           // its low two bits count
+#pragma unroll
+      for (int d = 0; d < WPR; ++d) slots[a * WPR + d] = __builtin_amdgcn_alignbyte((uint32_t)val[a][d + 1], (uint32_t)val[a][d], by);
     }
   }
-  uint8_t *const mine = xs + threadIdx.x * CROW;
-  const int rp = KS1 == 1 ? P.RP1 : 12;
 #pragma unroll
-  for (int a = 0; a < ROWS; ++a)
-    if (a < P.t) {
-      uint32_t *row = (uint32_t *)(mine + a * rp);
-      row[0] = (uint32_t)val[a][0] & (uint32_t)m0;
-      if (rp > 4) row[1] = (uint32_t)val[a][1] & (uint32_t)(m0 >> 32);
-      if (rp > 8) row[2] = (uint32_t)val[a][2] & (uint32_t)m1;
-    }
+  for (int a = 0; a < ROWS; ++a) {
+    const bool in = a >= -y0 && a < rows_in;
+#pragma unroll
+    for (int d = 0; d < WPR; ++d) slots[a * WPR + d] &= in ? mask[d] : 0u;
+  }
+  if (KS1 == 1 && P.RP1 == 4) {                                        // uniform: rows of one word
+#pragma unroll
+    for (int a = 0; a < ROWS; ++a) slots[a] = slots[2 * a];
+  }
+  uint8_t *const mine = xs + ch16 * (KS1 * 1024) + col * 16;
+#pragma unroll
+  for (int q = 0; q < 4 * KS1; ++q)
+    *(v4i *)(mine + q * 256) = (v4i){(int)slots[4 * q], (int)slots[4 * q + 1], (int)slots[4 * q + 2], (int)slots[4 * q + 3]};
   __syncthreads();
 
-  const uint8_t *px = xs + (lane & 15) * CROW + h * 16;
+  const uint8_t *px = xs + lane * 16;
   int8_t *const Vb = P.V + ((size_t)tb * (size_t)(P.n * P.P2) * P.ncb + cb) * 1024 + g * 256;
   const uint32_t stride_pt = (uint32_t)P.ncb * 1024u;
   const uint32_t lane_store = (uint32_t)(4 * h) * stride_pt + (uint32_t)(lane & 15) * 16u;
@@ -382,7 +410,7 @@ __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
         acc[j] = start;
 #pragma unroll
         for (int s = 0; s < KS1; ++s)
-          acc[j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(tab[s], *(const v4i *)(px + (4 * u + j) * 16 * CROW + s * 64), acc[j], 0, 0, 0);
+          acc[j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(tab[s], *(const v4i *)(px + ((4 * u + j) * KS1 + s) * 1024), acc[j], 0, 0, 0);
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e)

@@ -212,7 +212,7 @@ int validate_desc(const rnswino_desc_t &d, Dims &o) {
   //   128 channels, batch 320 27.9 / 35.9).
   // Below 96 blocks, where only five and more moduli would come, one tile per block stays (64 channels; eight moduli, F(4,3) at
   // 14 x 14, batch 12 (48 blocks) 14.8 / 15.5; six, F(8,3) at 56 x 56, batch 7 (88) 30.4 / 31.6; eight, F(6,3) at 112 x 112, batch 1
-  // (92) would gain, 31.5 / 28.4).  Its offsets have 32 bits.
+  // (92) would gain, 31.5 / 28.4).  Its offsets have 32 bits, a segment behind the last column included.
   const long long elements = (long long)d.N * d.C * d.H * d.W;
   const long long blocks1 = (long long)o.Tg * (o.Cp / 64), blocks16 = 4LL * (o.Tp / 16) * (o.Cp / 64), pairs16 = blocks16 * o.n;
   const int plane = o.th * o.tw;
@@ -220,7 +220,7 @@ int validate_desc(const rnswino_desc_t &d, Dims &o) {
                     : o.KS1 == 1 ? pairs16 >= 384
                     : plane < 49 ? blocks16 >= 384 && pairs16 >= 1152
                                  : blocks16 >= 384 || (blocks1 < 512 && pairs16 >= 400);
-  o.vlane = !o.wide && o.KS1 <= 2 && elements >= 16 && elements < (1LL << 31) && o.Tp / 16 >= 12 && blocks16 >= 96 && many;
+  o.vlane = !o.wide && o.KS1 <= 2 && elements >= 16 && elements + o.W + 2LL * o.pad + 16 < (1LL << 31) && o.Tp / 16 >= 12 && blocks16 >= 96 && many;
   o.RB3 = (d.m * d.m + 15) / 16;
   o.KS3 = (o.P2 + 63) / 64;
   // the kernels address the GEMM output O = [Kp][n][Q][Tp] words (two planes for 16-bit moduli) with 32-bit byte
