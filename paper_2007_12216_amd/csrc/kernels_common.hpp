@@ -92,6 +92,15 @@ __device__ __forceinline__ uint32_t biased_lowbyte(int acc, float inv_p, float q
   return (uint32_t)r;
 }
 
+// The same low byte as mod_lowbyte(x), to the bit, from an accumulator 0x4B400000 + x: read as binary32 it is 1.5*2^23 + x, and one
+// subtraction (2.6 cycles) gives the x that mod_lowbyte() converts (4.2).  The caller keeps magic = 1.5*2^23 and inv_p in vector registers.
+__device__ __forceinline__ uint32_t centred_lowbyte(int acc, float magic, float inv_p, int neg_p) {
+  const float f = __builtin_fmaf(__int_as_float(acc) - magic, inv_p, magic);
+  int r = __float_as_int(f);
+  asm("v_mad_i32_i24 %0, %0, %1, %2" : "+v"(r) : "s"(neg_p), "v"(acc));
+  return (uint32_t)r;
+}
+
 // A wave-uniform value in a vector register, hidden from the optimiser (which would put it back into a scalar one).
 template <typename T>
 __device__ __forceinline__ T in_vgpr(T v) {

@@ -623,10 +623,11 @@ int rnswino_filter_transform(const rnswino_plan_t *plan, const int8_t *w_dev, vo
   const long long gx = (long long)(d.Kp / 16) * (d.Cp / 64), items = (long long)d.n * d.CB1, want = (1024 + gx - 1) / gx;
   const dim3 grid((unsigned)gx, (unsigned)(want < items ? want : items));
   const size_t lds = (size_t)((d.r * d.r + 15) / 16) * 16384;
-  if (d.wide)
-    hipLaunchKernelGGL(k0_filter_transform<true>, grid, dim3(256), lds, st, P, w_dev, (int8_t *)U_dev);
-  else
-    hipLaunchKernelGGL(k0_filter_transform<false>, grid, dim3(256), lds, st, P, w_dev, (int8_t *)U_dev);
+  const int pieces = (d.r * d.r + 15) / 16;               // a filter's 16-tap slices: 1, 2, 3 or 4
+#define RNSW_K0(wd, pp) hipLaunchKernelGGL((k0_filter_transform<wd, pp>), grid, dim3(256), lds, st, P, w_dev, (int8_t *)U_dev)
+  if (d.wide) { if (pieces == 1) RNSW_K0(true, 1); else if (pieces == 2) RNSW_K0(true, 2); else RNSW_K0(true, 4); }
+  else { if (pieces == 1) RNSW_K0(false, 1); else if (pieces == 2) RNSW_K0(false, 2); else RNSW_K0(false, 4); }
+#undef RNSW_K0
   return launch_status();
 }
 
