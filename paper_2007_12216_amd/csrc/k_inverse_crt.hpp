@@ -32,6 +32,8 @@
 // Grid: x = ceil(K*T/16) rounded up to a multiple of 8, y = 1 .. ceil(RB3/4); 256 threads.
 // 16-bit moduli: table and O are two byte planes each; three accumulators as in the GEMM.
 #pragma once
+#include <type_traits>
+
 #include "kernels_common.hpp"
 
 namespace rnswino {
@@ -67,7 +69,7 @@ struct K3Params {
 // Where the output tile of a (k, tile) pair starts in y (or in the int8 activation plane): computed once per pair,
 // the row blocks of the pair only add their own row and column to it.
 struct TilePos {
-  size_t origin;     // element index of output (oy0, ox0) of channel k of image img
+  uint32_t origin;   // element index of output (oy0, ox0) of channel k of image img (O, at least a byte per output, is smaller than 4 GiB)
   int oy0, ox0;      // top-left output of the tile
   bool ok;           // false for padding tiles and padding pairs
 };
@@ -81,9 +83,9 @@ __device__ __forceinline__ TilePos tile_position(const K3Params &P, int k, int t
   const int ty = trow - img * P.th;
   tp.oy0 = ty * P.m;
   tp.ox0 = tx * P.m;
-  const size_t plane = (size_t)img * P.K + k;
-  if (P.epi == 2) tp.origin = (plane * (P.Ho >> 1) + (tp.oy0 >> 1)) * (P.Wo >> 1) + (tp.ox0 >> 1);
-  else tp.origin = (plane * P.Ho + tp.oy0) * P.Wo + tp.ox0;
+  const uint32_t plane = (uint32_t)img * P.K + k;
+  const int half = P.epi == 2 ? 1 : 0;               // pooled planes have half the rows and columns
+  tp.origin = (plane * (P.Ho >> half) + (tp.oy0 >> half)) * (P.Wo >> half) + (tp.ox0 >> half);
   return tp;
 }
 
@@ -190,33 +192,32 @@ __device__ __forceinline__ void k3_convert(const K3Params &P, const FastCrt &fc,
   }
 }
 
-// Store of a lane's four outputs for 8 x 8 output tiles (the streaming kernel's unrolled path): the lane's row u
-// and first column v (0 or 4) inside the tile and their offset `off` from the tile's origin in the stored plane do
-// not depend on the unit and are kept in registers by the caller.  Same modes as k3_convert_and_store; the host
-// selects this path for int32 output only when Wo is a multiple of 4.  Must be called by all lanes of a wave.
-__device__ __forceinline__ void k3_store_m8(const K3Params &P, const int (&val)[4], int u, int v, uint32_t off,
-                                            const TilePos &tp) {
-  const bool inside = tp.ok && tp.oy0 + u < P.Ho && tp.ox0 + v < P.Wo;
-  if (P.epi == 0) {
-    if (inside) *(v4i *)(P.y + tp.origin + off) = (v4i){val[0], val[1], val[2], val[3]};
-  } else if (P.epi == 1) {
+// Store of a lane's four outputs for 8 x 8 output tiles (the streaming kernel): `inside` says whether they exist (their first two,
+// where the row ends in the middle; `right` then: the other two) and, pooled, whether the lane stores; `at` is the first one's place in
+// the stored plane.  Same modes as k3_convert_and_store; the host selects this path for int32 output only when Wo is a multiple
+// of 4.  Must be called by all lanes of a wave.
+template <int EPI>
+__device__ __forceinline__ void k3_store_m8(const K3Params &P, const int (&val)[4], bool inside, bool right, uint32_t at) {
+  if constexpr (EPI == 0) {
+    if (inside) *(v4i *)(P.y + at) = (v4i){val[0], val[1], val[2], val[3]};
+  } else if constexpr (EPI == 1) {
     uint32_t packed = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) packed |= ((uint32_t)min(127, max(-128, val[j] >> P.shift)) & 0xFFu) << (8 * j);
-    int8_t *dst = P.act + tp.origin + off;
+    int8_t *dst = P.act + at;
     if ((P.Wo & 3) == 0) {
       if (inside) *(uint32_t *)dst = packed;
     } else {
       if (inside) *(uint16_t *)dst = (uint16_t)packed;
-      if (inside && tp.ox0 + v + 2 < P.Wo) *(uint16_t *)(dst + 2) = (uint16_t)(packed >> 16);
+      if (inside && right) *(uint16_t *)(dst + 2) = (uint16_t)(packed >> 16);
     }
   } else {
-    // rows u and u + 1 (u even) of the tile sit in lanes l and l ^ 32
-    const int h0 = max(val[0], val[1]), h1 = max(val[2], val[3]);
-    const int o0p = __shfl_xor(h0, 32), o1p = __shfl_xor(h1, 32);
-    const int p0 = min(127, max(-128, max(h0, o0p) >> P.shift)), p1 = min(127, max(-128, max(h1, o1p) >> P.shift));
-    if (inside && (u & 1) == 0)
-      *(uint16_t *)(P.act + tp.origin + off) = (uint16_t)(((uint32_t)p0 & 0xFFu) | (((uint32_t)p1 & 0xFFu) << 8));
+    // Rows u and u + 1 (u even) of the tile sit in lanes l < 32 and l + 32.  Exchanging the upper half of one register with the lower half of
+    // the other leaves the two rows of the left pair in the lower lanes and those of the right pair in the upper ones.
+    const auto rows = __builtin_amdgcn_permlane32_swap((uint32_t)max(val[0], val[1]), (uint32_t)max(val[2], val[3]), false, false);
+    const int pooled = min(127, max(-128, max((int)rows[0], (int)rows[1]) >> P.shift));
+    const auto pair = __builtin_amdgcn_permlane32_swap((uint32_t)pooled, (uint32_t)pooled, false, false);
+    if (inside) *(uint16_t *)(P.act + at) = (uint16_t)((pair[0] & 0xFFu) | ((pair[1] & 0xFFu) << 8));
   }
 }
 
@@ -238,7 +239,7 @@ __device__ __forceinline__ void k3_convert_and_store(const K3Params &P, const Fa
       const int u = (int)(((float)o + 0.5f) * inv_m);
       const int v = o - u * m;
       if (o < mm && tp.oy0 + u < P.Ho && tp.ox0 + v < P.Wo)
-        P.act[tp.origin + (uint32_t)(u * P.Wo + v)] = (int8_t)min(127, max(-128, val[j] >> P.shift));
+        P.act[(size_t)(tp.origin + (uint32_t)(u * P.Wo + v))] = (int8_t)min(127, max(-128, val[j] >> P.shift));
     }
     return;
   }
@@ -408,12 +409,14 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
 // Streaming variant for layers with many tiles (8-bit moduli, table of all residues <= 64 KiB): the table is staged
 // once per block in LDS, and every wave walks over units = (k, block of 16 tiles) with a grid stride.  Per unit a wave
 // issues only its own O loads (no table reads from global memory, no copies of O in other waves); the table fragments
-// come from LDS.  A unit's loads are hidden by the other waves of the SIMD (four resident blocks per CU; a second
-// register set that prefetched the next unit's operand cost a block of occupancy and measured 3-10 % slower).
-// What bounds it: 64 -> 64 channels at 224 x 224, batch 8, pooled, 42.8 us (168 MB of O, 3.9 TB/s); without the loads of O 30, without
-// the stores 40, without the conversion 40.5, without loads and stores 26.8; the same bytes in 16-byte loads, a quarter as many,
-// 42.3.  So neither the address unit nor the conversion: a wave's loads, products and conversion follow each other, and the
-// four waves a SIMD holds cover each other's loads only in part.
+// come from LDS.  A unit's loads are hidden by the other waves of the SIMD (four resident blocks per CU).
+// Loads with a wave-uniform base and a 32-bit lane offset, positions in 32 bits and one loop per output mode took a unit's vector
+// instructions from 390 to 250: 64 -> 128 at 112 x 112, batch 8, pooled, 19.6 -> 18.2 us; the median of the layers of the VGG16 stack, batch 8,
+// that come here 21.3 -> 20.4.
+// What bounds it, on 64 -> 64 at 224 x 224, batch 8, pooled (168 MB of O, 42.8 us before that): without the loads of O 30, without the stores 40, without the conversion 40.5, without
+// loads and stores 26.8; the same bytes in 16-byte loads, a quarter as many, 42.3.  More loads in flight make it slower: the next
+// unit's operand requested a unit ahead 23.2 us against that 20.4, five blocks per compute unit 22.3, units of 32 tiles (whole lines of O,
+// three blocks) 22.7.
 // Grid: min(ceil(units / 4), four blocks per CU) blocks of 256 threads; dynamic LDS = n * RB3 * KS3 KiB.
 constexpr int K3_STREAM_BLOCKS = 1024;  // four resident blocks per CU (register budget) on 256 CUs
 
@@ -435,65 +438,92 @@ __global__ __launch_bounds__(256) void k3_inverse_crt_stream(K3Params P) {
   int unit = blockIdx.x * 4 + wave;
   if (unit >= nunits) return;
 
-  // lane part of an O address, the same for every unit: point group (clamped to Q - 1 where the table is zero)
-  // and tile within the block of 16; the unit contributes a wave-uniform base
+  // lane part of an O address in bytes, the same for every unit: point group (clamped to Q - 1 where the table is zero)
+  // and tile within the block of 16; the unit contributes a wave-uniform base (O is smaller than 4 GiB)
+  const uint32_t row_bytes = (uint32_t)P.Tp * 4u;
   uint32_t voff[KS3][4];
 #pragma unroll
   for (int s = 0; s < KS3; ++s)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) voff[s][e] = (uint32_t)min(16 * s + 4 * g + e, P.Q - 1) * (uint32_t)P.Tp + (lane & 15);
+    for (int e = 0; e < 4; ++e) voff[s][e] = (uint32_t)min(16 * s + 4 * g + e, P.Q - 1) * row_bytes + (uint32_t)(lane & 15) * 4u;
 
-  auto load_o = [&](int u, v4i (&of)[NRES][KS3]) {
-    const int k = (int)fast_div((uint32_t)u, P.by_ntb), tb = u - k * ntb;
-    const uint32_t *base = P.O + (size_t)k * NRES * P.Q * P.Tp + tb * 16;
+  auto load_o = [&](int k, int tb, v4i (&of)[NRES][KS3]) {
 #pragma unroll
     for (int i = 0; i < NRES; ++i) {
-      const uint32_t *row = base + (size_t)(i * P.Q) * P.Tp;
+      const char *row = (const char *)P.O + (size_t)((uint32_t)((k * NRES + i) * P.Q) * row_bytes + (uint32_t)tb * 64u);
 #pragma unroll
       for (int s = 0; s < KS3; ++s)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) of[i][s][e] = (int)row[voff[s][e]];
+        for (int e = 0; e < 4; ++e) of[i][s][e] = *(const int *)(row + voff[s][e]);
     }
   };
 
   const FastCrt fc = fast_crt_constants<NRES, FAST>(P);
-  // One unit with its O operand in `o`.
   const int a0 = FAST ? P.acc0 : 0;
   const v4i acc_start = (v4i){a0, a0, a0, a0};
-  // 8 x 8 tiles: outputs 16 rb + 4 g .. + 3 are row u = 2 rb + (g >> 1), columns v = 4 (g & 1) .. + 3 of the tile; in the
-  // stored plane (pooled: half the rows and columns) row block rb + 1 lies m8_step elements after row block rb
-  const int m8_u0 = g >> 1, m8_v = 4 * (g & 1);
-  const uint32_t m8_step = P.epi == 2 ? (uint32_t)(P.Wo >> 1) : (uint32_t)(2 * P.Wo);
-  const uint32_t m8_off0 = P.epi == 2 ? (uint32_t)(m8_v >> 1) : (uint32_t)(m8_u0 * P.Wo + m8_v);
-  auto do_unit = [&](int u, v4i (&o)[NRES][KS3]) {
-    const int kg = (int)fast_div((uint32_t)u, P.by_ntb), taug = (u - kg * ntb) * 16 + (lane & 15);
-    const int k = kg >> P.tl_shift, tau = taug < P.Tg ? (kg - (k << P.tl_shift)) * P.Tg + taug : P.T;   // packed layers: see plan.hpp
-    const TilePos tp = tile_position(P, k, tau);
-    if (M8) {
-      // not unrolled: with the four row blocks in one basic block the scheduler requests all their table fragments
-      // at once and the kernel needs twice the registers
+  // GEMM row kg = k * TL + slot and columns 16 tb .. + 15 of a unit (TL > 1: packed layers, plan.hpp)
+  auto position = [&](int kg, int tb) {
+    const int taug = tb * 16 + (lane & 15), k = kg >> P.tl_shift;
+    return tile_position(P, k, taug < P.Tg ? (kg - (k << P.tl_shift)) * P.Tg + taug : P.T);
+  };
+  if constexpr (M8) {
+    // 8 x 8 tiles: outputs 16 rb + 4 g .. + 3 are row u = 2 rb + (g >> 1), columns v = 4 (g & 1) .. + 3 of the tile.  One loop per
+    // output mode and form of the conversion: tested inside it, the two cost a dozen branches per row block.
+    const int u0 = g >> 1, v = 4 * (g & 1);
+    auto units = [&](auto epi_tag, auto binary64_tag) {
+      constexpr int EPI = decltype(epi_tag)::value;
+      constexpr bool BINARY64 = decltype(binary64_tag)::value;
+      // elements between row blocks, and of the lane's first output from the tile's origin
+      const uint32_t step = EPI == 2 ? (uint32_t)(P.Wo >> 1) : (uint32_t)(2 * P.Wo), off0 = EPI == 2 ? (uint32_t)(v >> 1) : (uint32_t)(u0 * P.Wo + v);
+      for (; unit < nunits; unit += nwaves) {
+        const int kg = (int)fast_div((uint32_t)unit, P.by_ntb), tb = unit - kg * ntb;
+        v4i o[NRES][KS3];
+        load_o(kg, tb, o);
+        const TilePos tp = position(kg, tb);
+        const bool columns = tp.ok && tp.ox0 + v < P.Wo && (EPI != 2 || lane < 32), right = tp.ox0 + v + 2 < P.Wo;
+        const int rows = P.Ho - tp.oy0 - u0;               // of this lane that exist: 2 rb < rows
+        uint32_t at = tp.origin + off0;
+        // not unrolled: with the four row blocks in one basic block the scheduler requests all their table fragments
+        // at once and the kernel needs twice the registers
 #pragma clang loop unroll(disable)
-      for (int rb = 0; rb < 4; ++rb) {
-        uint32_t w[NRES][4];
-        const uint8_t *ka_rb = ka_lds + lane * 16 + rb * (KS3 * 1024);
+        for (int rb = 0; rb < 4; ++rb) {
+          uint32_t w[NRES][4];
+          const uint8_t *ka_rb = ka_lds + lane * 16 + rb * (KS3 * 1024);
 #pragma unroll
-        for (int i = 0; i < NRES; ++i) {
-          v4i acc = acc_start;
+          for (int i = 0; i < NRES; ++i) {
+            v4i acc = acc_start;
 #pragma unroll
-          for (int s = 0; s < KS3; ++s) {
-            const v4i a = *(const v4i *)(ka_rb + (i * 4 * KS3 + s) * 1024);
-            acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, o[i][s], acc, 0, 0, 0);
+            for (int s = 0; s < KS3; ++s) {
+              const v4i a = *(const v4i *)(ka_rb + (i * 4 * KS3 + s) * 1024);
+              acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, o[i][s], acc, 0, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              w[i][j] = FAST ? (uint32_t)acc[j] : mod_near_plus_p(acc[j], P.inv_p[i], -P.p[i], P.bias_p[i]);
           }
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            w[i][j] = FAST ? (uint32_t)acc[j] : mod_near_plus_p(acc[j], P.inv_p[i], -P.p[i], P.bias_p[i]);
+          int val[4];
+          if constexpr (FAST && BINARY64) crt_convert_fast64<NRES>(P, fc, w, val);
+          else if constexpr (FAST) crt_convert_fast<NRES>(P, fc, w, val);
+          else k3_convert<NRES, FAST>(P, fc, w, val);
+          k3_store_m8<EPI>(P, val, columns && 2 * rb < rows, right, at);
+          at += step;
         }
-        int val[4];
-        k3_convert<NRES, FAST>(P, fc, w, val);
-        k3_store_m8(P, val, 2 * rb + m8_u0, m8_v, m8_off0 + rb * m8_step, tp);
       }
-      return;
-    }
+    };
+    auto modes = [&](auto binary64_tag) {
+      if (P.epi == 0) units(std::integral_constant<int, 0>(), binary64_tag);
+      else if (P.epi == 1) units(std::integral_constant<int, 1>(), binary64_tag);
+      else units(std::integral_constant<int, 2>(), binary64_tag);
+    };
+    if (FAST && P.fastcrt == 2) modes(std::true_type());
+    else modes(std::false_type());
+    return;
+  }
+  for (; unit < nunits; unit += nwaves) {
+    const int kg = (int)fast_div((uint32_t)unit, P.by_ntb), tb = unit - kg * ntb;
+    v4i o[NRES][KS3];
+    load_o(kg, tb, o);
+    const TilePos tp = position(kg, tb);
     for (int rb = 0; rb < P.RB3; ++rb) {
       uint32_t w[NRES][4];
 #pragma unroll
@@ -512,11 +542,6 @@ __global__ __launch_bounds__(256) void k3_inverse_crt_stream(K3Params P) {
       }
       k3_convert_and_store<NRES, FAST>(P, fc, w, rb, g, tp);
     }
-  };
-  v4i oa[NRES][KS3];
-  for (; unit < nunits; unit += nwaves) {
-    load_o(unit, oa);
-    do_unit(unit, oa);
   }
 }
 
