@@ -133,7 +133,7 @@ __global__ __launch_bounds__(256, WIDE ? 2 : PP == 1 ? 4 : 3) void k0_filter_tra
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             const int tot = acc[0][j][e] * 256 + acc[PL - 1][j][e];           // |tot| <= 49 * 128 * 32896 < 2^28
-            const int v = storable16(tot - __double2int_rn((double)tot * q.invd) * p, p);
+            const int v = storable16(mod_near32(tot, q.invd, p), p);
             const int lo = (int)(int8_t)(v & 0xFF), hi = (v - lo) >> 8;
             wh |= ((uint32_t)hi & 0xFFu) << (8 * j);
             wl |= ((uint32_t)lo & 0xFFu) << (8 * j);

@@ -248,7 +248,7 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             const int tot = acc[0][u][j] * 256 + acc[PL - 1][u][j];
-            const int v = storable16(mod_near64((long long)tot, invd, p), p);
+            const int v = storable16(mod_near32(tot, invd, p), p);
             const int lo = (int)(int8_t)(v & 0xFF), hi = (v - lo) >> 8;
             wh |= ((uint32_t)hi & 0xFFu) << (8 * j);
             wl |= ((uint32_t)lo & 0xFFu) << (8 * j);

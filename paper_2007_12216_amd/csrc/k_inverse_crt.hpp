@@ -393,8 +393,7 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
       for (int j = 0; j < 4; ++j) {
         if (WIDE) {
           // per accumulator |sum| <= t*t * 2^15: the combination stays below 2^40
-          const long long tot = (long long)acc[0][j] * 65536 + (long long)acc[1][j] * 256 + (long long)acc[NACC - 1][j];
-          w[i][j] = (uint32_t)(mod_near64(tot, P.inv_pd[i], P.p[i]) + P.p[i]);
+          w[i][j] = (uint32_t)(mod_near64(acc[0][j], acc[1][j], acc[NACC - 1][j], P.inv_pd[i], (double)P.p[i]) + P.p[i]);
         } else {
           // |acc| <= t*t * 126 * 128 <= 2^22 (the fast conversion takes it as it is, start included)
           w[i][j] = FAST ? (uint32_t)acc[0][j] : mod_near_plus_p(acc[0][j], P.inv_p[i], -P.p[i], P.bias_p[i]);
