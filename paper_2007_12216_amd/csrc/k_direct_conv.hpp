@@ -21,6 +21,10 @@ struct DirectParams {
   int N, C, K, H, W, r, pad;
   int Ho, Wo, Hp, Wp, Cp, Kp;
   int npix;                     // N * Ho * Wo
+  FastDiv by_plane, by_Wo;      // by Ho * Wo, Wo
+  FastDiv by_groups, by_Hp, by_ncb;   // k_direct_to_nhwc: by the 16-pixel groups of a padded row, Hp, Cp / 64
+  FastDiv by_gy;                // GEMM kernels: by the row blocks, gy of them
+  int gy;
 };
 
 // x [N][C][H][W] -> xt [Cp/64][N][Hp][Wp][64], zero border and zero padding channels.  A block takes 64 channels of 16 units
@@ -33,11 +37,11 @@ __global__ __launch_bounds__(256) void k_direct_to_nhwc(DirectParams P, const in
   __shared__ __attribute__((aligned(16))) uint32_t tile[16 * 272];
   const int groups = (P.Wp + 15) >> 4, ncb = P.Cp >> 6;
   const int nunits = P.N * P.Hp * groups;               // below 2^31: xt is
-  const int cb = blockIdx.x % ncb, ub = blockIdx.x / ncb;
+  const int ub = (int)fast_div(blockIdx.x, P.by_ncb), cb = (int)blockIdx.x - ub * ncb;
   {
     const long long total = (long long)P.N * P.C * P.H * P.W;
     const int unit = ub * 16 + (threadIdx.x & 15), c0 = threadIdx.x >> 4;
-    const int row = unit / groups, grp = unit - row * groups, n = row / P.Hp;
+    const int row = (int)fast_div((uint32_t)unit, P.by_groups), grp = unit - row * groups, n = (int)fast_div((uint32_t)row, P.by_Hp);
     const int iy = row - n * P.Hp - P.pad, ix = grp * 16 - P.pad;      // image row and column of the segment's first pixel
     const bool row_ok = unit < nunits && iy >= 0 && iy < P.H;
     v4i val[4];
@@ -89,7 +93,7 @@ __global__ __launch_bounds__(256) void k_direct_to_nhwc(DirectParams P, const in
       out[2][d] = (int)__builtin_amdgcn_perm(t3, t1, 0x05040100u);
       out[3][d] = (int)__builtin_amdgcn_perm(t3, t1, 0x07060302u);
     }
-    const int row = unit / groups, xp = (unit - row * groups) * 16 + 4 * pq;
+    const int row = (int)fast_div((uint32_t)unit, P.by_groups), xp = (unit - row * groups) * 16 + 4 * pq;
     int8_t *dst = xt + (((size_t)cb * P.N * P.Hp + row) * P.Wp + xp) * 64 + 16 * g;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
@@ -132,18 +136,18 @@ __global__ __launch_bounds__(256) void k_direct_conv(DirectParams P, const int8_
   const int lane = threadIdx.x & 63;
   const int wm = wave / WN, wn = wave % WN;
   const int nkb = P.Kp >> 4, ntb = (P.npix + 15) >> 4, ncb = P.Cp >> 6;
-  const int gy = (nkb + BRF - 1) / BRF, gz = (ntb + BTF - 1) / BTF;
-  const int pb = ((blockIdx.x >> 3) / gy) * 8 + (blockIdx.x & 7);
+  const int gy = P.gy, gz = (ntb + BTF - 1) / BTF;
+  const int pb8 = (int)fast_div(blockIdx.x >> 3, P.by_gy), pb = pb8 * 8 + (int)(blockIdx.x & 7);
   if (pb >= gz) return;                            // block-uniform: the grid is padded to a multiple of 8 pixel blocks
-  const int kb0 = ((blockIdx.x >> 3) % gy) * BRF, tb0 = pb * BTF;
+  const int kb0 = ((int)(blockIdx.x >> 3) - pb8 * gy) * BRF, tb0 = pb * BTF;
   const int taps = P.r * P.r;
   const int total = taps * ncb;
 
   // where output pixel `pix` (clamped to the last one) starts in xt: the patch origin (oy, ox) of image n
   auto pixel_origin = [&](int pix) -> uint32_t {
     pix = min(pix, P.npix - 1);
-    const int n = pix / (P.Ho * P.Wo), rem = pix - n * (P.Ho * P.Wo);
-    const int oy = rem / P.Wo, ox = rem - oy * P.Wo;
+    const int n = (int)fast_div((uint32_t)pix, P.by_plane), rem = pix - n * (P.Ho * P.Wo);
+    const int oy = (int)fast_div((uint32_t)rem, P.by_Wo), ox = rem - oy * P.Wo;
     return (uint32_t)(((n * P.Hp + oy) * P.Wp + ox) * 64);          // xt is smaller than 4 GiB (checked on the host)
   };
   // this wave's loads of a step: fragment f = wave + 4 j: a weight fragment (contiguous) or a pixel-block fragment
@@ -226,7 +230,7 @@ __global__ __launch_bounds__(256) void k_direct_conv(DirectParams P, const int8_
   for (int nt = 0; nt < NT; ++nt) {
     const int pix = (tb0 + wn * NT + nt) * 16 + (lane & 15);
     if (pix >= P.npix) continue;
-    const int n = pix / (P.Ho * P.Wo), rem = pix - n * (P.Ho * P.Wo);
+    const int n = (int)fast_div((uint32_t)pix, P.by_plane), rem = pix - n * (P.Ho * P.Wo);
     int32_t *ypix = y + (size_t)n * P.K * plane + rem;
 #pragma unroll
     for (int rm = 0; rm < RM; ++rm)
@@ -244,11 +248,11 @@ __global__ __launch_bounds__(256) void k_direct_conv(DirectParams P, const int8_
 // reads its operand at another offset, instead of fetching it from L2 again for every tap.  The weights lie in memory in the
 // order of the steps and go from L2 straight into registers, D taps ahead.  A workgroup thus meets one barrier per channel
 // block instead of one per tap.
-// What bounds it is the instruction stream of the one or two waves a SIMD holds (a wave issues an instruction every four to
-// five cycles; 16 of a step's 60 are matrix instructions): running pointers instead of 64-bit address sums and the whole next
-// patch in one place took 256 -> 256 at 56 x 56, batch 8, from 33 to 28.5 us a call.  There, with 64 x 256 blocks, the kernel
-// takes 21 us (1.4 POP/s; k_direct_conv 37): 3.5 us less without the stores of y, 3 without the weights' loads, 3 without
-// the next patch, 1 without the reads of LDS.  An LDS layout swizzled against bank conflicts changed nothing.
+// 256 -> 256 at 56 x 56, batch 8, 64 x 256 blocks: of a block's 35000 cycles 2200 went before its first load (the compiler's
+// divisions), 3000 for its first patch, 23000 for 36 steps -- 640 each, of which 256 multiply: a step read its pixels and waited for them,
+// and at each channel block for all weights in flight -- and 6600 for storing y.  With the pixels read a step ahead, counted waits and
+// divisions by multiplication 26.8 -> 25.3 us a call; 512 -> 512 at 28 x 28 26.3 -> 22.8, at 14 x 14 19.1 -> 14.9, batch 1 16.4 -> 13.1.
+// What is left: the blocks are 1.5 per compute unit, and all store at the end.
 // Dynamic LDS: (ncb > 1 ? 2 : 1) * ceil(patch / 16) KiB.  Grid as k_direct_conv.
 template <int WM, int WN, int RM, int NT, int D>
 __global__ __launch_bounds__(256, 2) void k_direct_conv_patch(DirectParams P, int patch, const int8_t *__restrict__ xt,
@@ -260,19 +264,19 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_patch(DirectParams P, in
   const int lane = threadIdx.x & 63;
   const int wm = wave / WN, wn = wave % WN;
   const int nkb = P.Kp >> 4, ntb = (P.npix + 15) >> 4, ncb = P.Cp >> 6;
-  const int gy = (nkb + BRF - 1) / BRF, gz = (ntb + BTF - 1) / BTF;
-  const int pb = ((blockIdx.x >> 3) / gy) * 8 + (blockIdx.x & 7);
+  const int gy = P.gy, gz = (ntb + BTF - 1) / BTF;
+  const int pb8 = (int)fast_div(blockIdx.x >> 3, P.by_gy), pb = pb8 * 8 + (int)(blockIdx.x & 7);
   if (pb >= gz) return;                            // block-uniform: the grid is padded to a multiple of 8 pixel blocks
   // the last row blocks are shifted to end with the tensor (rows computed twice are stored twice, the same values); the host
   // takes RM <= nkb
-  const int kb0 = min((int)((blockIdx.x >> 3) % gy) * BRF + wm * RM, nkb - RM), tb0 = pb * BTF;
+  const int kb0 = min(((int)(blockIdx.x >> 3) - pb8 * gy) * BRF + wm * RM, nkb - RM), tb0 = pb * BTF;
   const int taps = P.r * P.r, total = taps * ncb;
 
   // where output pixel `pix` (clamped to the last one) starts in a channel block of xt, in pixels
   auto pixel_origin = [&](int pix) -> int {
     pix = min(pix, P.npix - 1);
-    const int n = pix / (P.Ho * P.Wo), rem = pix - n * (P.Ho * P.Wo);
-    const int oy = rem / P.Wo, ox = rem - oy * P.Wo;
+    const int n = (int)fast_div((uint32_t)pix, P.by_plane), rem = pix - n * (P.Ho * P.Wo);
+    const int oy = (int)fast_div((uint32_t)rem, P.by_Wo), ox = rem - oy * P.Wo;
     return (n * P.Hp + oy) * P.Wp + ox;
   };
   // the patch: from the first pixel's origin to the last tap of the last pixel (at most `patch` pixels: patch_pixels())
@@ -318,35 +322,51 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_patch(DirectParams P, in
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) acc[rm][nt] = (v4i){0, 0, 0, 0};
 
-  int tap = 0, tj = 0, cb = 0;
-  uint32_t tap_off = 0;                            // LDS offset of the tap, this block's buffer included
+  // A step's pixels are read from LDS while the step before it multiplies.
+  int tap = 0, tj = 0, cb = 0;                     // of the step whose pixels are read next
+  uint32_t tap_off = 0;                            // LDS offset of that tap, its block's buffer included
   const uint32_t row_skip = (uint32_t)(P.Wp - P.r + 1) * 64u;
-  auto step = [&](v4i (&aset)[RM]) {
-    if (tap == 0) {                                // everybody's share of this block's patch has landed; nobody reads the other buffer
-      wait_vmcnt<0>();
-      __syncthreads();
-      if (cb + 1 < ncb) fetch_patch(cb + 1);
-      tap_off = (uint32_t)(cb & 1) * buffer;
+  v4i b[2][NT];
+  auto read_next = [&](v4i (&into)[NT]) {
+    if (tap == taps) {
+      // a new channel block: everybody's share of its patch has landed (the weights' loads behind the patch's, RM for each of at least
+      // three steps, need not have), and everybody has read the last of the block before, whose buffer is refilled
+      tap = tj = 0;
+      tap_off = 0;                                 // (behind the last step: read, not used)
+      if (++cb < ncb) {
+        wait_vmcnt<RM * (D < 3 ? D : 3)>();
+        __syncthreads();
+        if (cb + 1 < ncb) fetch_patch(cb + 1);
+        tap_off = (uint32_t)(cb & 1) * buffer;
+      }
     }
-    v4i b[NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) b[nt] = *(const v4i *)(patch_lds + (b_at[nt] + tap_off));
+    for (int nt = 0; nt < NT; ++nt) into[nt] = *(const v4i *)(patch_lds + (b_at[nt] + tap_off));
+    ++tap;
+    tap_off += 64;
+    if (++tj == P.r) { tj = 0; tap_off += row_skip - 64u; }
+  };
+  auto step = [&](v4i (&aset)[RM], v4i (&use)[NT], v4i (&next)[NT]) {
+    read_next(next);
+    __builtin_amdgcn_sched_barrier(0);             // (left alone, the scheduler moves the reads behind the products)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-      for (int rm = 0; rm < RM; ++rm) acc[rm][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aset[rm], b[nt], acc[rm][nt], 0, 0, 0);
+      for (int rm = 0; rm < RM; ++rm) acc[rm][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aset[rm], use[nt], acc[rm][nt], 0, 0, 0);
     load_a(aset);
-    tap_off += 64;
-    if (++tj == P.r) { tj = 0; tap_off += row_skip - 64u; }
-    if (++tap == taps) { tap = tj = 0; ++cb; }
   };
+  static_assert(D % 2 == 0, "the two sets of pixels alternate");
+  wait_vmcnt<RM * D>();
+  __syncthreads();
+  if (ncb > 1) fetch_patch(1);
+  read_next(b[0]);
   int it = 0;
   for (; it + D <= total; it += D)
 #pragma unroll
-    for (int d = 0; d < D; ++d) step(a[d]);
+    for (int d = 0; d < D; ++d) step(a[d], b[d & 1], b[1 - (d & 1)]);
 #pragma unroll
   for (int d = 0; d < D - 1; ++d)
-    if (it + d < total) step(a[d]);
+    if (it + d < total) step(a[d], b[d & 1], b[1 - (d & 1)]);
 
   // a lane holds rows 16 kb + 4 (lane / 16) + j of pixel 16 tb + lane % 16
   const size_t plane = (size_t)P.Ho * P.Wo;
@@ -354,7 +374,7 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_patch(DirectParams P, in
   for (int nt = 0; nt < NT; ++nt) {
     const int pix = (tb0 + wn * NT + nt) * 16 + (lane & 15);
     if (pix >= P.npix) continue;
-    const int n = pix / (P.Ho * P.Wo), rem = pix - n * (P.Ho * P.Wo);
+    const int n = (int)fast_div((uint32_t)pix, P.by_plane), rem = pix - n * (P.Ho * P.Wo);
     int32_t *ypix = y + (size_t)n * P.K * plane + rem;
 #pragma unroll
     for (int rm = 0; rm < RM; ++rm)

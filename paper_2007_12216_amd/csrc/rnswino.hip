@@ -720,6 +720,8 @@ static int direct_params(int32_t N, int32_t C, int32_t K, int32_t H, int32_t W, 
   const long long npix = (long long)N * Ho * Wo, xt = (long long)N * P.Hp * P.Wp * P.Cp;
   if (npix >= (1LL << 28) || xt >= (1LL << 31) || (long long)r * r * P.Kp * P.Cp >= (1LL << 31)) return RNSWINO_E_UNSUPPORTED;   // 32-bit offsets
   P.npix = (int)npix;
+  P.by_plane = make_fast_div((uint32_t)(Ho * Wo)); P.by_Wo = make_fast_div((uint32_t)Wo);
+  P.by_groups = make_fast_div((uint32_t)((P.Wp + 15) / 16)); P.by_Hp = make_fast_div((uint32_t)P.Hp); P.by_ncb = make_fast_div((uint32_t)(P.Cp / 64));
   return RNSWINO_OK;
 }
 
@@ -808,6 +810,8 @@ int rnswino_direct_conv2d(const int8_t *x_dev, const void *wt_dev, int32_t *y_de
   const long long tblocks = ((long long)N * P.Hp * ((P.Wp + 15) / 16) + 15) / 16 * (P.Cp / 64);
   hipLaunchKernelGGL(k_direct_to_nhwc, dim3((unsigned)tblocks), dim3(256), 0, st, P, x_dev, xt);
   const DirectChoice c = choose_direct(P);
+  P.gy = (P.Kp / 16 + c.WM * c.RM - 1) / (c.WM * c.RM);
+  P.by_gy = make_fast_div((uint32_t)P.gy);
 #define RNSW_X(wm_, wn_, rm, nt, d_) \
   if (c.patch > 0 && c.is(wm_, wn_, rm, nt, d_)) { \
     hipLaunchKernelGGL((k_direct_conv_patch<wm_, wn_, rm, nt, d_>), dim3(c.blocks), dim3(256), c.lds, st, P, c.patch, xt, (const int8_t *)wt_dev, y_dev); \
