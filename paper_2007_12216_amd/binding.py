@@ -175,11 +175,10 @@ def rnswino_workspace_bytes(plan: Plan) -> int:
 
 def _ptr(obj) -> int:
     """Device (or host) address of a torch tensor / numpy array / raw int."""
-    if isinstance(obj, int):
-        return obj
-    if hasattr(obj, "data_ptr"):
+    try:
         return obj.data_ptr()
-    return obj.ctypes.data
+    except AttributeError:
+        return obj if isinstance(obj, int) else obj.ctypes.data
 
 
 def rnswino_filter_transform(plan: Plan, w_dev, U_dev, stream: int = 0) -> None:
@@ -187,13 +186,16 @@ def rnswino_filter_transform(plan: Plan, w_dev, U_dev, stream: int = 0) -> None:
 
 
 def rnswino_conv2d(plan: Plan, x_dev, U_dev, y_dev, workspace_dev, stream: int = 0) -> None:
-    _check(lib().rnswino_conv2d(plan.handle, _ptr(x_dev), _ptr(U_dev), _ptr(y_dev), _ptr(workspace_dev), stream),
-           "rnswino_conv2d")
+    code = (_lib or lib()).rnswino_conv2d(plan.handle, _ptr(x_dev), _ptr(U_dev), _ptr(y_dev), _ptr(workspace_dev), stream)
+    if code:
+        _check(code, "rnswino_conv2d")
 
 
 def rnswino_conv2d_requant(plan: Plan, x_dev, U_dev, a_dev, shift: int, pool: bool, workspace_dev, stream: int = 0) -> None:
-    _check(lib().rnswino_conv2d_requant(plan.handle, _ptr(x_dev), _ptr(U_dev), _ptr(a_dev), shift, int(bool(pool)),
-                                        _ptr(workspace_dev), stream), "rnswino_conv2d_requant")
+    code = (_lib or lib()).rnswino_conv2d_requant(plan.handle, _ptr(x_dev), _ptr(U_dev), _ptr(a_dev), shift, 1 if pool else 0,
+                                                  _ptr(workspace_dev), stream)
+    if code:
+        _check(code, "rnswino_conv2d_requant")
 
 
 def rnswino_conv2d_events(plan: Plan, x_dev, U_dev, y_dev, workspace_dev, stream: int, events) -> None:

@@ -51,9 +51,9 @@ class ConvLayer:
         """x: int8 [N][C][H][W] on the device, contiguous.  Returns the int32 output tensor (owned by the layer
         unless `y` is given)."""
         p = self.plan
-        assert x.dtype == torch.int8 and x.is_contiguous() and tuple(x.shape) == (p.N, p.C, p.H, p.W)
+        assert x.dtype == torch.int8 and x.is_contiguous() and x.shape == (p.N, p.C, p.H, p.W)
         out = self.y if y is None else y
-        B.rnswino_conv2d(p, x, self.U, out, self.workspace, self._stream())
+        B.rnswino_conv2d(p, x, self.U, out, self.workspace, current_stream(self.device))
         return out
 
     def stage(self, which: int) -> np.ndarray:
