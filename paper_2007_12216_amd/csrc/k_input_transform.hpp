@@ -288,9 +288,9 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
 // segments into operand fragments, then the waves take the (residue, 16-point block) items in turn, every item's pixels from LDS in lane
 // order, its table fragments requested one item ahead.  (With one padded row per thread instead of fragments, half of the LDS cycles
 // were bank conflicts; a gather of unaligned loads, each with a branch of its own, took 4100 cycles of a block's 30000: 100 channels
-// at 57 x 43, batch 3, 14.9 -> 14.2 us a layer, 64 -> 128 at 112 x 112, batch 8, 66.4 -> 65.5, 64 -> 64 at 224 x 224 45.6 -> 44.6 the kernel.)
-// What is left, on that last shape: no stores 38.1, no residues 40.5, no products 37.4, neither gather nor table 37.8, all of these removed
-// 26.4, so nothing alone holds it.  Two items a step against the same pixels, half the LDS reads, take 160 registers: 16.7 against 17.1 us
+// at 57 x 43, batch 3, 14.9 -> 14.2 us a layer.)
+// Of 44.6 us on 64 -> 64 at 224 x 224, batch 8, there are left: without stores 38.1, residues 40.5, products 37.4, stores and gather 37.8, all but
+// products and table 28.9, so nothing alone holds it.  Two items a step against the same pixels, half the LDS reads, take 160 registers: 16.7 against 17.1 us
 // with 392 blocks, 48 against 44.6 with 1568.
 // Grid: x = 4 * Tp/16 * Cp/64 rounded up to a multiple of 8 (kernels_common.hpp), y = n or 1.
 template <int KS1, bool PACK>
@@ -337,21 +337,28 @@ __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
 #pragma unroll
     for (int a = 0; a < ROWS; ++a) val[a] = (v4i){0, 0, 0, 0};
   }
-  // items of this wave: full 16-point blocks of all residues first (their stores need no test, so that the wait for the next
-  // item's table does not become a wait for them), then the residues' last, partial blocks
-  const int nfull = P.P2 >> 4;
+  // Items of this wave, wave, wave + 4, ...: full 16-point blocks of all residues first (their stores need no test, so that the wait for
+  // the next item's table does not become a wait for them), then the residues' last, partial blocks.  Item n is block n % nfull of residue
+  // n / nfull, by a multiplication that is exact up to n = 4096, and wave-uniform for the compiler too: counted up in a loop, it took the
+  // residue for a lane's own and fetched its constants by vector loads, which waited for the stores before them (64 -> 64 at 224 x 224,
+  // batch 8: 44.6 us, so 42.9; 256 channels at 56 x 56, batch 8: 20.0 and 18.4; 64 -> 128 at 112 x 112, pooled, 66.5 and 64.2 a layer).
+  const int nfull = P.P2 >> 4, nitems = nfull * nres;
+  const uint32_t per_block = __builtin_amdgcn_readfirstlane(nfull > 0 ? (65535u + (uint32_t)nfull) / (uint32_t)nfull : 0);
   constexpr uint32_t FRAG = KS1 * 1024;
   const uint32_t lane16 = (uint32_t)lane * 16u;
+  auto residue_of = [&](int n) { return (int)(((uint32_t)n * per_block) >> 16); };
   auto load_table = [&](int i, int cbk, v4i (&b)[KS1]) {
     const int8_t *frag = P.KB + (size_t)((uint32_t)(i * P.CB1 + cbk) * FRAG);
 #pragma unroll
     for (int s = 0; s < KS1; ++s) b[s] = *(const v4i *)(frag + s * 1024 + lane16);
   };
+  auto load_item = [&](int n, v4i (&b)[KS1]) {
+    const int m = min(n, max(nitems - 1, 0)), k = residue_of(m);       // past the end: fetched, not used
+    load_table(i0 + k, m - k * nfull, b);
+  };
   v4i ta[KS1], tn[KS1];
-  int i = i0, cbk = wave;
-  auto settle = [&]() { while (cbk >= nfull && i < i0 + nres) { cbk -= nfull; ++i; } };
-  if (nfull > 0) settle(); else i = i0 + nres;
-  if (i < i0 + nres) load_table(i, cbk, ta);
+  int item = wave;
+  load_item(item, ta);
   const unsigned long long m0 = byte_range(max(-x0, 0), min(P.t, P.W - x0), 0), m1 = byte_range(max(-x0, 0), min(P.t, P.W - x0), 8);
   const uint32_t mask[3] = {live ? (uint32_t)m0 : 0u, live ? (uint32_t)(m0 >> 32) : 0u, live ? (uint32_t)m1 : 0u};
   const int rows_in = min(P.t, P.H - y0);                              // row a is inside the image and the tile: -y0 <= a < rows_in
@@ -419,20 +426,22 @@ __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
     }
   };
   auto full_item = [&](v4i (&tab)[KS1], v4i (&next)[KS1]) {
-    const int ci = i, cc = cbk;
-    const Residue8 r = P.res[ci];
-    cbk += 4;
-    settle();
-    load_table(min(i, P.n - 1), i < i0 + nres ? cbk : 0, next);        // past the end: fetched, not used
+    const int k = __builtin_amdgcn_readfirstlane(residue_of(item));
+    const Residue8 r = P.res[i0 + k];
+    int8_t *dst = Vb + (size_t)(uint32_t)((i0 + k) * P.P2 + 16 * (item - k * nfull)) * stride_pt + lane_store;
+    item += 4;
+    load_item(item, next);
     v4i out[4];
     compute(tab, r, out);
-    int8_t *dst = Vb + (size_t)(uint32_t)(ci * P.P2 + 16 * cc) * stride_pt + lane_store;
 #pragma unroll
     for (int e = 0; e < 4; ++e) *(v4i *)(dst + (uint32_t)e * stride_pt) = out[e];
   };
-  while (i < i0 + nres) {
+  // The first table is awaited here: otherwise the compiler, merging this entry state with the loop's own, makes every other item wait
+  // for the stores of the one before.
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), other counters untouched
+  while (item < nitems) {
     full_item(ta, tn);
-    if (i >= i0 + nres) break;
+    if (item >= nitems) break;
     full_item(tn, ta);
   }
   if (P.P2 & 15) {
