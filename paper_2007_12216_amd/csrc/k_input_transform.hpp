@@ -17,7 +17,7 @@
 // groups u give one lane exactly the 16 bytes of V it has to store (channel order of layout.hpp).
 // 16-bit moduli: the table has a high and a low byte plane, V = (256 * sum_h + sum_l) mod p, stored as two planes.
 // Grid: x = T * Cp/64 rounded up to a multiple of 8 (see kernels_common.hpp), y = n (one residue per block) or 1 (the block
-// walks over all residues with the same gathered patch); 256 threads; 64 * (4*KS1 + 1) * 16 bytes of LDS.
+// walks over all residues with the same gathered patch), z = 1 or 2 (blocks that share a residue's column blocks); 256 threads; 64 * (4*KS1 + 1) * 16 bytes of LDS.
 #pragma once
 #include "kernels_common.hpp"
 
@@ -41,6 +41,7 @@ struct K1Params {
   int n, CB1, P2;
   long long total;            // N * C * H * W
   int T, Tg, Cq, cq_shift, RP1;
+  int part_shift;             // log2 of the blocks that share a residue's column blocks (blockIdx.z: which)
   Residue8 res[8];
   double inv_pd[8];           // 16-bit moduli
 };
@@ -126,17 +127,18 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
     mask0[0] = byte_range(max(-o.x0, 0), min(P.t, P.W - o.x0), 0);
     mask1[0] = byte_range(max(-o.x0, 0), min(P.t, P.W - o.x0), 8);
   }
-  // This wave's work: steps (residue i, column-block group cg) with cg = wave, wave + 4, ...  The table fragments
+  // This wave's work: steps (residue i, column-block group cg) with cg = first, first + stride, ...  The table fragments
   // of step k+1 are requested before step k is multiplied; those of step 0 behind the gather's own loads, so that their
   // latency overlaps the gather.  A step's position is kept as wave-uniform scalars and advanced incrementally
   // (no divisions, and only a few scalar operations per column block: every instruction counts here).
   const int ncg = (P.CB1 + K1_CPW - 1) / K1_CPW;
-  const int per_i = (ncg - wave + 3) >> 2;            // groups of this wave per residue
+  const int first = wave + 4 * (int)blockIdx.z, stride = 4 << P.part_shift;
+  const int per_i = max(ncg - first + stride - 1, 0) >> (2 + P.part_shift);            // groups of this wave per residue
   const int nsteps = (i1 - i0) * per_i;
   struct Pos { int i, cg; };                          // residue and column-block group
   auto advance = [&](Pos &q) {
-    q.cg += 4;
-    if (q.cg >= ncg) { q.cg = wave; ++q.i; }
+    q.cg += stride;
+    if (q.cg >= ncg) { q.cg = first; ++q.i; }
   };
   constexpr uint32_t FRAG = KS1 * PL * 1024;          // table bytes per column block (all steps and planes)
   const int8_t *KBl = P.KB + lane * 16;
@@ -158,7 +160,7 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
   const uint32_t lane_store = (uint32_t)(lane & 15) * stride_pt + g * 16;   // 16 points * ncb KiB: far below 2^32
   int8_t *const Vtile = P.V + ((size_t)(tau >> 4) * (size_t)(P.n * P.P2) * ncb + cb) * (PL * 1024) + (tau & 15) * 64;
   v4i bf[K1_CPW][KS1][PL], bn[K1_CPW][KS1][PL];
-  Pos cur = {i0, wave};
+  Pos cur = {i0, first};
   if (nsteps > 0) load_table(cur, bf);
   __builtin_amdgcn_sched_barrier(0);
   if (tiny) {
