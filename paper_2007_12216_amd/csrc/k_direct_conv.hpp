@@ -242,6 +242,11 @@ __global__ __launch_bounds__(256) void k_direct_conv(DirectParams P, const int8_
   }
 }
 
+// Every access to LDS of this wave, and every scalar load, is done.
+__device__ __forceinline__ void wait_lds() {
+  __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0), other counters untouched
+}
+
 // The same product with the pixels of all taps staged once.  In xt the pixels of one 64-channel block are consecutive, so the
 // patch that 16 * WN * NT consecutive output pixels need for all r*r taps is ONE run of `patch` pixels (64 bytes each); it is
 // copied to LDS once per channel block (two buffers: the next block's patch arrives while this one is used) and every tap
@@ -251,7 +256,9 @@ __global__ __launch_bounds__(256) void k_direct_conv(DirectParams P, const int8_
 // 256 -> 256 at 56 x 56, batch 8, 64 x 256 blocks: of a block's 35000 cycles 2200 went before its first load (the compiler's
 // divisions), 3000 for its first patch, 23000 for 36 steps -- 640 each, of which 256 multiply: a step read its pixels and waited for them,
 // and at each channel block for all weights in flight -- and 6600 for storing y.  With the pixels read a step ahead, counted waits and
-// divisions by multiplication 26.8 -> 25.3 us a call; 512 -> 512 at 28 x 28 26.3 -> 22.8, at 14 x 14 19.1 -> 14.9, batch 1 16.4 -> 13.1.
+// divisions by multiplication 26.4 -> 24.6 us a call; 512 -> 512 at 28 x 28 25.9 -> 22.3, at 14 x 14 18.8 -> 14.2, batch 1 16.5 -> 12.1.
+// (Of the last two 0.5 and 0.7 come with the loop's entry: without its wait, and with the weights in the compiler's order, every D-th step
+// waited for everything in flight.)
 // What is left: the blocks are 1.5 per compute unit, and all store at the end.
 // Dynamic LDS: (ncb > 1 ? 2 : 1) * ceil(patch / 16) KiB.  Grid as k_direct_conv.
 template <int WM, int WN, int RM, int NT, int D>
@@ -311,10 +318,15 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_patch(DirectParams P, in
     --a_left;
   };
 
+  // The waits below count these loads; a plain load of constant memory is ordered against them by nothing but the scheduling barriers.
   fetch_patch(0);
+  __builtin_amdgcn_sched_barrier(0);
   v4i a[D][RM];
 #pragma unroll
-  for (int d = 0; d < D; ++d) load_a(a[d]);
+  for (int d = 0; d < D; ++d) {
+    load_a(a[d]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 
   v4i acc[RM][NT];
 #pragma unroll
@@ -330,11 +342,13 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_patch(DirectParams P, in
   auto read_next = [&](v4i (&into)[NT]) {
     if (tap == taps) {
       // a new channel block: everybody's share of its patch has landed (the weights' loads behind the patch's, RM for each of at least
-      // three steps, need not have), and everybody has read the last of the block before, whose buffer is refilled
+      // three steps, need not have: hence r >= 2, which the host checks), and everybody has read the last of the block before, whose buffer
+      // is refilled (waited for here: of a barrier's own wait the compiler keeps only what it finds in flight at the loop's entry)
       tap = tj = 0;
       tap_off = 0;                                 // (behind the last step: read, not used)
       if (++cb < ncb) {
         wait_vmcnt<RM * (D < 3 ? D : 3)>();
+        wait_lds();
         __syncthreads();
         if (cb + 1 < ncb) fetch_patch(cb + 1);
         tap_off = (uint32_t)(cb & 1) * buffer;
@@ -360,6 +374,9 @@ __global__ __launch_bounds__(256, 2) void k_direct_conv_patch(DirectParams P, in
   __syncthreads();
   if (ncb > 1) fetch_patch(1);
   read_next(b[0]);
+  // Awaited here, with the pointer of y that the compiler fetches above: scalar and LDS loads share a counter and return in any order, and
+  // with it pending at the loop's entry the first step of every D would wait for the pixels it has just requested.
+  wait_lds();
   int it = 0;
   for (; it + D <= total; it += D)
 #pragma unroll

@@ -815,6 +815,7 @@ int rnswino_direct_conv2d(const int8_t *x_dev, const void *wt_dev, int32_t *y_de
   const long long tblocks = ((long long)N * P.Hp * ((P.Wp + 15) / 16) + 15) / 16 * (P.Cp / 64);
   hipLaunchKernelGGL(k_direct_to_nhwc, dim3((unsigned)tblocks), dim3(256), 0, st, P, x_dev, xt);
   const DirectChoice c = choose_direct(P);
+  if (c.patch > 0 && r < 2) return RNSWINO_E_UNSUPPORTED;   // k_direct_conv_patch counts on three steps and more per channel block, whatever the timings say
   P.gy = (P.Kp / 16 + c.WM * c.RM - 1) / (c.WM * c.RM);
   P.by_gy = make_fast_div((uint32_t)P.gy);
 #define RNSW_X(wm_, wn_, rm, nt, d_) \
