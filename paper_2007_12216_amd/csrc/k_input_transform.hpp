@@ -35,14 +35,13 @@ struct K1Params {
   int8_t *V;
   const int8_t *KB;           // (B^T kron B^T) mod p, [n][CB1][KS1][planes][64 lanes][16]
   int units, per_xcd;         // T * Cp/64 (of the packed problem), and the grid's x extent / 8
-  int ncb, split;             // split: one residue per block (blockIdx.y)
+  int ncb, split;             // 0: a block takes all residues; else it takes one (blockIdx.y), and `split` blocks share its column blocks (blockIdx.z)
   FastDiv by_ncb, by_tw, by_th;
   int C, H, W, HW, m, pad, t, tw, th;
   int n, CB1, P2;
   long long total;            // N * C * H * W
   int T, Tg, Cq, cq_shift, RP1;
-  int part_shift;             // log2 of the blocks that share a residue's column blocks (blockIdx.z: which)
-  Residue8 res[8];
+  alignas(16) Residue8 res[8];
   double inv_pd[8];           // 16-bit moduli
 };
 
@@ -132,8 +131,9 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
   // latency overlaps the gather.  A step's position is kept as wave-uniform scalars and advanced incrementally
   // (no divisions, and only a few scalar operations per column block: every instruction counts here).
   const int ncg = (P.CB1 + K1_CPW - 1) / K1_CPW;
-  const int first = wave + 4 * (int)blockIdx.z, stride = 4 << P.part_shift;
-  const int per_i = max(ncg - first + stride - 1, 0) >> (2 + P.part_shift);            // groups of this wave per residue
+  const int part_shift = P.split >> 1;                // log2 of the blocks that share a residue: one or two
+  const int first = wave + 4 * (int)blockIdx.z, stride = 4 << part_shift;
+  const int per_i = max(ncg - first + stride - 1, 0) >> (2 + part_shift);              // groups of this wave per residue
   const int nsteps = (i1 - i0) * per_i;
   struct Pos { int i, cg; };                          // residue and column-block group
   auto advance = [&](Pos &q) {

@@ -189,7 +189,7 @@ inline void launch(Kern kern, dim3 grid, size_t lds, hipStream_t st, Timing tm, 
 // with the report.
 // =============================================================================================
 
-struct K1Choice { int KS1; bool wide, pack, tiles; long long units; unsigned gx, gy; int part_shift; };
+struct K1Choice { int KS1; bool wide, pack, tiles; long long units; unsigned gx, gy, gz; };
 
 K1Choice choose_k1(const Dims &d) {
   K1Choice c;
@@ -209,7 +209,7 @@ K1Choice choose_k1(const Dims &d) {
   // Where that leaves half of the CUs without a block and a wave more than one group of column blocks (t >= 12), two blocks share them,
   // each gathering anew (us per layer, one / two blocks: 128 channels 5 x 5, F(12,5), at 28 x 28 (72 blocks) 13.7 / 13.1; F(14,3), two 16-bit moduli, 512
   // at 28 x 28 (64) 70.3 / 68.7, 64 at 28 x 28 (8) 14.0 / 12.6; four 8-bit ones, 64 -> 512 at 20 x 20 18.6 / 17.9).
-  c.part_shift = !c.tiles && c.gy > 1 && units * d.n <= 128 && d.CB1 > 4 * K1_CPW ? 1 : 0;
+  c.gz = !c.tiles && c.gy > 1 && units * d.n <= 128 && d.CB1 > 4 * K1_CPW ? 2 : 1;
   return c;
 }
 
@@ -221,8 +221,7 @@ K1Params make_k1(const Dims &d, const KParams &P) {
   q.units = (int)c.units;
   q.per_xcd = (int)(c.gx / 8);
   q.ncb = d.Cp / 64;
-  q.split = c.gy > 1;
-  q.part_shift = c.part_shift;
+  q.split = c.gy > 1 ? (int)c.gz : 0;
   q.by_ncb = make_fast_div((uint32_t)q.ncb); q.by_tw = make_fast_div((uint32_t)d.tw); q.by_th = make_fast_div((uint32_t)d.th);
   q.C = d.C; q.H = d.H; q.W = d.W; q.HW = d.H * d.W; q.m = d.m; q.pad = d.pad; q.t = d.t; q.tw = d.tw; q.th = d.th;
   q.n = d.n; q.T = d.T; q.Tg = d.Tg; q.Cq = d.Cq;
@@ -410,7 +409,7 @@ K3Params make_k3(const Dims &d, const KParams &P, int n_cus, int epi) {
 // ---- K1 ----  (dry: only report whether the instantiation exists)
 bool launch_k1(const Dims &d, const K1Params &P1, const int8_t *x, int8_t *V, hipStream_t st, Timing tm, bool dry = false) {
   const K1Choice c = choose_k1(d);
-  const dim3 grid(c.gx, c.gy, 1u << c.part_shift);
+  const dim3 grid(c.gx, c.gy, c.gz);
   K1Params P = P1;
   P.x = x; P.V = V;
 #define RNSW_X(ks, pk) \

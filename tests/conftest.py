@@ -33,3 +33,19 @@ def load_paper_matrices():
 @pytest.fixture(scope="session")
 def paper_matrices():
     return load_paper_matrices()
+
+
+@pytest.fixture(scope="session")
+def assembly(tmp_path_factory):
+    """{kernel: (instructions, {label: index})} of the library's sources, compiled to assembly (test_isa_wait_states.functions)."""
+    import shutil
+    import subprocess
+    from paper_2007_12216_amd.build import compile_command
+    from test_isa_wait_states import functions
+    if shutil.which("hipcc") is None:
+        pytest.skip("hipcc not available")
+    path = str(tmp_path_factory.mktemp("isa") / "rnswino.s")
+    source = [a for a in compile_command(path) if not a.endswith("plan_math.cpp") and a != "-shared"]
+    build = subprocess.run(source + ["-S", "--cuda-device-only"], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert build.returncode == 0, build.stdout
+    return functions(path)

@@ -5,13 +5,10 @@ the steps after it in flight, for a step's pixels with those of the next step in
 loads in the order of the source, and it gains something only while it adds no full wait of its own.  A barrier stands for "everybody has
 read this buffer" only where the reads before it have returned."""
 import re
-import shutil
-import subprocess
 
 import pytest
 
 import paper_2007_12216_amd as rn
-from paper_2007_12216_amd.build import compile_command
 from test_isa_wait_states import functions
 
 
@@ -51,19 +48,8 @@ def test_the_walk_sees_a_barrier_that_does_not_wait(tmp_path):
         assert len(in_flight_at_barriers(code, labels)) == bad
 
 
-@pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    if shutil.which("hipcc") is None:
-        pytest.skip("hipcc not available")
-    path = str(tmp_path_factory.mktemp("isa") / "rnswino.s")
-    source = [a for a in compile_command(path) if not a.endswith("plan_math.cpp") and a != "-shared"]
-    build = subprocess.run(source + ["-S", "--cuda-device-only"], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    assert build.returncode == 0, build.stdout
-    return functions(path)
-
-
-def test_every_access_to_lds_is_done_before_a_barrier(kernels):
-    found = {name: v for name, (code, labels) in kernels.items() for v in [in_flight_at_barriers(code, labels)] if v}
+def test_every_access_to_lds_is_done_before_a_barrier(assembly):
+    found = {name: v for name, (code, labels) in assembly.items() for v in [in_flight_at_barriers(code, labels)] if v}
     assert not found, "\n".join(f"{name}: {v[0]} ({len(v)} in all)" for name, v in found.items())
 
 
@@ -73,11 +59,11 @@ def count(text, counter):
 
 
 @pytest.mark.parametrize("variant", [v for v in rn.rnswino_direct_variants() if v.startswith("k_direct_conv_patch")])
-def test_the_patch_kernel_counts_the_loads_it_means(kernels, variant):
+def test_the_patch_kernel_counts_the_loads_it_means(assembly, variant):
     numbers = re.findall(r"\d+", variant.partition("<")[2])
     _, _, RM, NT, D = map(int, numbers)
-    name, = [n for n in kernels if "k_direct_conv_patchI" + "".join(f"Li{n}E" for n in numbers) in n]
-    code = [(op, text) for op, _, _, text in kernels[name][0]]
+    name, = [n for n in assembly if "k_direct_conv_patchI" + "".join(f"Li{n}E" for n in numbers) in n]
+    code = [(op, text) for op, _, _, text in assembly[name][0]]
     ops = [op for op, _ in code]
 
     def weights(lo, hi):
