@@ -33,6 +33,7 @@ import argparse
 import ctypes
 import hashlib
 import json
+import math
 import os
 import re
 import statistics
@@ -156,6 +157,12 @@ def timed_rounds(step_fn, steps, warmup, sync):
     return statistics.median(per_round), per_round
 
 
+def empty_grid(report: str):
+    """Extents x and y of a launch of as many workgroups as the reported one has ("grid=200x4", "grid=72x4x2 ...")."""
+    extents = [int(v) for v in report.split()[0].partition("=")[2].split("x")]
+    return extents[0], math.prod(extents[1:])
+
+
 def bench_layer(idx, steps, warmup, dev, with_cpu, warm=False, events=True):
     """One single-layer workload: cold time per call, per-kernel durations, roofline of the dominant kernel, the library's
     own direct convolution on the same shape, and the oracle comparison."""
@@ -217,8 +224,7 @@ def bench_layer(idx, steps, warmup, dev, with_cpu, warm=False, events=True):
         # the host's launch rate does not enter), time per launch
         grids = {}
         for nm, g in zip(names, rn.rnswino_plan_describe(plan, 0)["grids"]):
-            gx, _, gy = g.split()[0].split("=")[1].partition("x")
-            grids[nm] = (int(gx), int(gy or 1))
+            grids[nm] = empty_grid(g)
         floor_ms = {}
         for nm in names:
             try:

@@ -238,6 +238,7 @@ int rnswino_plan_get_mrc_inverse(const rnswino_plan_t *plan, int l, int j, uint3
  *   k2_residue_gemm<4, 4, 2, false> grid=6400 xgroup=1
  *   k3_inverse_crt<4, 2, false, true> grid=784x1
  *   conversion=unreduced-binary32
+ * (grid=XxYxZ where the launch has a third extent).
  * conversion: "unreduced-binary32" / "unreduced-binary64" = CRT sum over unreduced accumulators with the quotient rounded
  * in that precision; "reduced-binary32" / "reduced-binary64" = over reduced residues; "reduced-binary64-mul32" = the same
  * with full 32-bit multiplies (a partial product P/m_i of 2^24 or more).  Works on host-only plans (grids of the

@@ -688,8 +688,10 @@ int64_t rnswino_plan_describe(const rnswino_plan_t *plan, int32_t output_mode, c
   const K3Choice c3 = choose_k3(d, P, plan->n_cus, output_mode);
   auto tf = [](bool b) { return b ? "true" : "false"; };
   char buf[1024];
-  int len = c1.tiles ? std::snprintf(buf, sizeof(buf), "k1_input_transform_tiles<%d, %s> grid=%ux%u\n", c1.KS1, tf(c1.pack), c1.gx, c1.gy)
-                     : std::snprintf(buf, sizeof(buf), "k1_input_transform<%d, %s, %s> grid=%ux%u\n", c1.KS1, tf(c1.wide), tf(c1.pack), c1.gx, c1.gy);
+  int len = c1.tiles ? std::snprintf(buf, sizeof(buf), "k1_input_transform_tiles<%d, %s> grid=%ux%u", c1.KS1, tf(c1.pack), c1.gx, c1.gy)
+                     : std::snprintf(buf, sizeof(buf), "k1_input_transform<%d, %s, %s> grid=%ux%u", c1.KS1, tf(c1.wide), tf(c1.pack), c1.gx, c1.gy);
+  if (c1.gz > 1) len += std::snprintf(buf + len, sizeof(buf) - len, "x%u", c1.gz);
+  len += std::snprintf(buf + len, sizeof(buf) - len, "\n");
   if (c2.lds)
     len += std::snprintf(buf + len, sizeof(buf) - len, "k2_residue_gemm_lds<%d, %d, %d, %d, %d> grid=%u xgroup=%d\n", c2.WM, c2.WN, c2.RM,
                          c2.NTB, c2.S, c2.blocks, c2.xgroup);

@@ -37,6 +37,12 @@ def test_matrix_core_operation_counts_of_workload_2():
     assert ops["inverse_transform_crt"] == 2.0 * 4 * 64 * 128 * 256 * 49
 
 
+def test_the_empty_launch_has_as_many_workgroups_as_the_reported_one():
+    assert bench.empty_grid("grid=200x4") == (200, 4)
+    assert bench.empty_grid("grid=24x4x2") == (24, 8)
+    assert bench.empty_grid("grid=6400 xgroup=1") == (6400, 1)
+
+
 def test_recorded_traffic_belongs_to_the_kernels_workload_2_launches():
     """profiles/hbm_traffic.json holds counter-derived HBM bytes per kernel instantiation; bench.py reports them as
     roofline.traffic only for an instantiation of that name.  A change of the dispatch must not leave stale figures behind:

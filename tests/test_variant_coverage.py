@@ -72,6 +72,16 @@ def test_the_input_transform_takes_16_tiles_at_a_time_only_where_that_is_faster(
     assert rn.rnswino_plan_describe(plan)["kernels"][0].startswith("k1_input_transform_tiles") == sixteen
 
 
+@pytest.mark.parametrize("N,C,K,hw,r,m,moduli,grid", [
+    (1, 128, 128, 28, 5, 12, (251, 241, 239, 233), "grid=24x4x2"), (1, 512, 512, 28, 3, 14, (65521, 65519), "grid=32x2x2"),
+    (1, 20, 3, 20, 3, 10, (251, 241, 239), "grid=8x3x2"), (1, 20, 3, 18, 3, 9, (251, 241, 239), "grid=8x3"),               # 9 column blocks, 8
+    (2, 128, 3, 56, 3, 14, (65521, 65519), "grid=64x2x2"), (2, 192, 3, 56, 3, 14, (65521, 65519), "grid=96x2"),            # 128 blocks, 192
+    (1, 128, 3, 28, 5, 12, (251,), "grid=24x1"), (8, 512, 3, 224, 3, 14, (251, 241), "grid=16384x1")])                     # all residues in a block
+def test_the_report_tells_which_input_transforms_share_column_blocks(N, C, K, hw, r, m, moduli, grid):
+    plan = rn.rnswino_plan(N, C, K, hw, hw, r, m, r // 2, moduli, flags=HOST | UNCHECKED)
+    assert rn.rnswino_plan_describe(plan)["grids"][0] == grid
+
+
 def _conversion(C, moduli, r=3, m=8, flags=HOST, K=16, hw=16):
     plan = rn.rnswino_plan(1, C, K, hw, hw, r, m, r // 2, moduli, flags=flags)
     return rn.rnswino_plan_describe(plan)["conversion"]
