@@ -39,3 +39,23 @@ def test_subclasses_are_taken_too():
     assert binding._ptr(Address(12)) == 12 and binding._ptr(True) == 1
     assert binding._ptr(ARRAY.view(Array)) == ARRAY.ctypes.data
     assert binding._ptr(torch.nn.Parameter(TENSOR, requires_grad=False)) == TENSOR.data_ptr()
+
+
+@pytest.mark.parametrize("kinds", ["tttt", "aaaa", "iiii", "tiii", "ittt", "taia"])
+def test_the_calls_take_any_mixture_of_addresses(kinds, monkeypatch):
+    make = {"t": lambda k: (t := torch.zeros(4 + k), t.data_ptr()), "a": lambda k: (a := np.zeros(4 + k), a.ctypes.data), "i": lambda k: (4096 + k, 4096 + k)}
+    given, want = zip(*(make[kind](k) for k, kind in enumerate(kinds)))
+    seen = []
+
+    class Library:
+        def rnswino_conv2d(self, *args):
+            seen.append(args)
+            return 0
+
+        rnswino_conv2d_requant = rnswino_conv2d
+
+    monkeypatch.setattr(binding, "_lib", Library())
+    plan = type("Plan", (), {"handle": 7})()
+    binding.rnswino_conv2d(plan, *given, 9)
+    binding.rnswino_conv2d_requant(plan, *given[:3], 5, True, given[3], 9)
+    assert seen == [(7, *want, 9), (7, *want[:3], 5, 1, want[3], 9)]
