@@ -64,6 +64,7 @@ struct K3Params {
   float inv_p[8];
   int p[8], bias_p[8];
   double inv_pd[8];
+  double pd[8];               // 16-bit moduli: p
 };
 
 // Where the output tile of a (k, tile) pair starts in y (or in the int8 activation plane): computed once per pair,
@@ -221,11 +222,7 @@ __device__ __forceinline__ void k3_store_m8(const K3Params &P, const int (&val)[
   }
 }
 
-template <int NRES, bool FAST>
-__device__ __forceinline__ void k3_convert_and_store(const K3Params &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int rb, int g,
-                                                     const TilePos &tp) {
-  int val[4];
-  k3_convert<NRES, FAST>(P, fc, w, val);
+__device__ __forceinline__ void k3_store(const K3Params &P, const int (&val)[4], int rb, int g, const TilePos &tp) {
   const int m = P.m, mm = m * m;
   const float inv_m = P.inv_m;
   const int o0 = 16 * rb + 4 * g;
@@ -289,12 +286,27 @@ __device__ __forceinline__ void k3_convert_and_store(const K3Params &P, const Fa
   }
 }
 
+template <int NRES, bool FAST>
+__device__ __forceinline__ void k3_convert_and_store(const K3Params &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int rb, int g,
+                                                     const TilePos &tp) {
+  int val[4];
+  k3_convert<NRES, FAST>(P, fc, w, val);
+  k3_store(P, val, rb, g, tp);
+}
+
 // FAST: the conversion with unreduced accumulators (the host launches it when KParams::fastcrt is set).
+// Three and more 16-bit moduli: a residue goes into the sum and the binary64 quotient of the conversion as soon as it is there, signed.  Kept
+// until all were there, shifted and converted again for the quotient, with p converted in registers of its own, the residues cost most of
+// these kernels a wave per SIMD: 64 -> 256 at 56 x 56, batch 4, five, six, seven, eight moduli at F(4,3) 52, 57.8, 65.7, 126 us, so 28.8,
+// 52.6, 59.5, 63.7; three at F(14,3) 39.5, so 26.6.
+// Where the products of several residues at once would cost a wave, the residues stay apart (APART): five at F(8,3) 25.2 -> 22.2, at F(14,3)
+// 43.4 -> 40.8; six at F(8,3) 32.5 -> 26.0, at F(10,3) 55.8 -> 43.3; elsewhere it loses up to a tenth.
 template <int NRES, int KS3, bool WIDE, bool FAST>
 __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
   constexpr int PL = WIDE ? 2 : 1;
   constexpr int NACC = WIDE ? 3 : 1;
   constexpr bool AHEAD = NRES * KS3 * PL <= 16;    // the table fragments of a row block fit registers: requested ahead of their use
+  constexpr bool EACH = WIDE && NRES >= 3, APART = WIDE && ((NRES == 5 && KS3 % 2 == 0) || (NRES == 6 && (KS3 == 2 || KS3 == 3)));
   __shared__ __attribute__((aligned(16))) uint32_t o_lds[NRES * KS3 * PL * 256];   // [i][s][plane][lane][4 words]
   asm volatile("" ::"s"(P.O), "s"(P.KA), "s"(P.units), "s"(P.per_xcd), "s"(P.npairs), "s"(P.by_Tg.mul), "s"(P.by_Tg.shift), "s"(P.by_tw.mul),
                "s"(P.by_tw.shift), "s"(P.by_th.mul), "s"(P.by_th.shift), "s"(P.Tg), "s"(P.tl_shift), "s"(P.T), "s"(P.Q), "s"(P.Tp), "s"(P.tw),
@@ -368,7 +380,8 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
       for (int pl = 0; pl < PL; ++pl) of[i][s][pl] = *(const v4i *)(o_lds + ((i * KS3 + s) * PL + pl) * 256 + lane * 4);
 
   for (; rb < P.RB3; rb += P.rb_step) {
-    uint32_t w[NRES][4];
+    uint32_t w[NRES][4], sum[4] = {0, 0, 0, 0};
+    double fs[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int i = 0; i < NRES; ++i) {
       v4i acc[NACC];
@@ -391,17 +404,31 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
       // residue shifted by +p so that it is non-negative
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        if (WIDE) {
+        if constexpr (WIDE) {
           // per accumulator |sum| <= t*t * 2^15: the combination stays below 2^40
-          w[i][j] = (uint32_t)(mod_near64(acc[0][j], acc[1][j], acc[NACC - 1][j], P.inv_pd[i], (double)P.p[i]) + P.p[i]);
+          const double r = mod_near64(acc[0][j], acc[1][j], acc[2][j], P.inv_pd[i], P.pd[i]);
+          if (EACH) {
+            sum[j] += P.crt_c[i] * (uint32_t)(int)r;
+            fs[j] = __builtin_fma(r, P.inv_pd[i], fs[j]);
+          } else {
+            w[i][j] = (uint32_t)((int)r + P.p[i]);
+          }
         } else {
           // |acc| <= t*t * 126 * 128 <= 2^22 (the fast conversion takes it as it is, start included)
           w[i][j] = FAST ? (uint32_t)acc[0][j] : mod_near_plus_p(acc[0][j], P.inv_p[i], -P.p[i], P.bias_p[i]);
         }
       }
+      if (APART) __builtin_amdgcn_sched_barrier(0);
     }
     if (rb + P.rb_step < P.RB3) load_ka(rb + P.rb_step);
-    k3_convert_and_store<NRES, FAST>(P, fc, w, rb, g, tp);
+    if constexpr (EACH) {
+      int val[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) val[j] = (int)(sum[j] - P.prod_mod32 * (uint32_t)__double2int_rn(fs[j]));
+      k3_store(P, val, rb, g, tp);
+    } else {
+      k3_convert_and_store<NRES, FAST>(P, fc, w, rb, g, tp);
+    }
   }
 }
 

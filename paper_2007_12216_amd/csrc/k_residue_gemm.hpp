@@ -170,7 +170,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(K2Params P) {
         for (int j = 0; j < 4; ++j) {
           const int at = ((rm * 16 + j) * PITCH + tb * 16 * PL) * 4;   // row rm*16 + 4*(lane>>4) + j, column tb*16 + lane%16
           if constexpr (WIDE) {
-            const int v = storable16(mod_near64(acc[0][rm][tb][j], acc[1][rm][tb][j], acc[NACC - 1][rm][tb][j], P.inv_pd[i], (double)p), p);
+            const int v = storable16((int)mod_near64(acc[0][rm][tb][j], acc[1][rm][tb][j], acc[NACC - 1][rm][tb][j], P.inv_pd[i], (double)p), p);
             const int lo = (int)(int8_t)(v & 0xFF), hi = (v - lo) >> 8;
             tile8[at] = (uint8_t)hi;
             tile8[at + (PL - 1) * 4] = (uint8_t)lo;

@@ -147,9 +147,9 @@ __device__ __forceinline__ uint32_t pack_low_bytes(uint32_t a, uint32_t b, uint3
 // remainder in binary64 (the sum and the remainder exact): nine instructions, about thirty with the sum, the quotient and its
 // product as 64-bit integers.  64 -> 64 channels, 16-bit moduli, at 112 x 112, batch 8: GEMM 31.6 -> 21.9 us, inverse transform 23.2 -> 19.1,
 // input transform (mod_near32()) 26.2 -> 24.4.
-__device__ __forceinline__ int mod_near64(int hh, int hl, int ll, double inv_pd, double p) {
+__device__ __forceinline__ double mod_near64(int hh, int hl, int ll, double inv_pd, double p) {
   const double x = __builtin_fma((double)hh, 65536.0, __builtin_fma((double)hl, 256.0, (double)ll));
-  return (int)__builtin_fma(-__builtin_rint(x * inv_pd), p, x);
+  return __builtin_fma(-__builtin_rint(x * inv_pd), p, x);
 }
 
 // The same of a 32-bit x.

@@ -372,7 +372,7 @@ K3Params make_k3(const Dims &d, const KParams &P, int n_cus, int epi) {
   q.fastcrt = P.fastcrt; q.crt24 = P.crt24; q.quot32 = P.quot32; q.acc0 = P.acc0; q.crt_sum0 = P.crt_sum0; q.prod_mod32 = P.prod_mod32;
   q.crt_fs0 = P.crt_fs0; q.crt_fs0d = P.crt_fs0d; q.inv_m = 1.0f / (float)d.m;
   for (int i = 0; i < d.n; ++i) {
-    q.crt_c[i] = P.crt_c[i]; q.inv_p[i] = P.inv_p[i]; q.p[i] = P.p[i]; q.bias_p[i] = P.bias_p[i]; q.inv_pd[i] = P.inv_pd[i];
+    q.crt_c[i] = P.crt_c[i]; q.inv_p[i] = P.inv_p[i]; q.p[i] = P.p[i]; q.bias_p[i] = P.bias_p[i]; q.inv_pd[i] = P.inv_pd[i]; q.pd[i] = (double)P.p[i];
   }
   return q;
 }
@@ -706,7 +706,7 @@ int64_t rnswino_plan_describe(const rnswino_plan_t *plan, int32_t output_mode, c
                          tf(c3.fast), c3.gx, c3.gy);
   const char *conv = P.fastcrt == 1 ? "unreduced-binary32"
                      : P.fastcrt == 2 ? "unreduced-binary64"
-                     : !P.crt24 ? "reduced-binary64-mul32"
+                     : !P.crt24 || (d.wide && d.n >= 3) ? "reduced-binary64-mul32"
                      : P.quot32 ? "reduced-binary32" : "reduced-binary64";
   len += std::snprintf(buf + len, sizeof(buf) - len, "conversion=%s\n", conv);
   if (host_out && capacity > (size_t)len) std::memcpy(host_out, buf, (size_t)len + 1);

@@ -36,16 +36,30 @@ def paper_matrices():
 
 
 @pytest.fixture(scope="session")
-def assembly(tmp_path_factory):
-    """{kernel: (instructions, {label: index})} of the library's sources, compiled to assembly (test_isa_wait_states.functions)."""
+def assembly_file(tmp_path_factory):
+    """The library's sources, compiled to assembly."""
     import shutil
     import subprocess
     from paper_2007_12216_amd.build import compile_command
-    from test_isa_wait_states import functions
     if shutil.which("hipcc") is None:
         pytest.skip("hipcc not available")
     path = str(tmp_path_factory.mktemp("isa") / "rnswino.s")
     source = [a for a in compile_command(path) if not a.endswith("plan_math.cpp") and a != "-shared"]
     build = subprocess.run(source + ["-S", "--cuda-device-only"], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert build.returncode == 0, build.stdout
-    return functions(path)
+    return path
+
+
+@pytest.fixture(scope="session")
+def assembly(assembly_file):
+    """{kernel: (instructions, {label: index})}, see test_isa_wait_states.functions."""
+    from test_isa_wait_states import functions
+    return functions(assembly_file)
+
+
+@pytest.fixture(scope="session")
+def vector_registers(assembly_file):
+    """{kernel: vector registers of a wave}, from the assembly's metadata."""
+    import re
+    found = re.findall(r"\.name:\s+(_Z\w+)(?:(?!\.name:).)*?\.vgpr_count:\s+(\d+)", open(assembly_file).read(), re.S)
+    return {name: int(count) for name, count in found}
