@@ -241,8 +241,8 @@ int rnswino_plan_get_mrc_inverse(const rnswino_plan_t *plan, int l, int j, uint3
  * (grid=XxYxZ where the launch has a third extent).
  * conversion: "unreduced-binary32" / "unreduced-binary64" = CRT sum over unreduced accumulators with the quotient rounded
  * in that precision; "reduced-binary32" / "reduced-binary64" = over reduced residues; "reduced-binary64-mul32" = the same
- * with full 32-bit multiplies (a partial product P/m_i of 2^24 or more).  Works on host-only plans (grids of the
- * streaming inverse transform then assume 256 compute units).  Returns the number of bytes including the terminating
+ * with full 32-bit multiplies (a partial product P/m_i of 2^24 or more).  Works on host-only plans (their
+ * grids assume 256 compute units).  Returns the number of bytes including the terminating
  * zero (copied only if capacity suffices), or a negative code.  For tests and measurement scripts.
  */
 int64_t rnswino_plan_describe(const rnswino_plan_t *plan, int32_t output_mode, char *host_out, size_t capacity);

@@ -12,7 +12,7 @@
 //
 // Block = (tile, block of 64 channels, one residue or all of them): its 64 x t x RP1 pixel patch is gathered once into
 // LDS (the gather of 16-byte row segments is what costs; sharing it between the four waves pays), then each wave
-// walks over its steps (residue, every fourth group of K1_CPW column blocks), the table fragments of the next
+// walks over its steps (residue, group of K1_CPW column blocks: every fourth, every eighth where two blocks share them), the table fragments of the next
 // step in flight while the current one is multiplied.  Accumulator rows are channels 4g+j, so the four channel
 // groups u give one lane exactly the 16 bytes of V it has to store (channel order of layout.hpp).
 // 16-bit moduli: the table has a high and a low byte plane, V = (256 * sum_h + sum_l) mod p, stored as two planes.

@@ -191,7 +191,7 @@ inline void launch(Kern kern, dim3 grid, size_t lds, hipStream_t st, Timing tm, 
 
 struct K1Choice { int KS1; bool wide, pack, tiles; long long units; unsigned gx, gy, gz; };
 
-K1Choice choose_k1(const Dims &d) {
+K1Choice choose_k1(const Dims &d, int n_cus) {
   K1Choice c;
   c.KS1 = d.KS1 < 4 ? d.KS1 : 4;
   c.wide = d.wide != 0;
@@ -207,14 +207,17 @@ K1Choice choose_k1(const Dims &d) {
   c.gx = (unsigned)((units + 7) / 8 * 8);
   c.gy = (unsigned)(units >= (c.tiles ? 192 : 512) ? 1 : d.n);
   // Where that leaves half of the CUs without a block and a wave more than one group of column blocks (t >= 12), two blocks share them,
-  // each gathering anew (us per layer, one / two blocks: 128 channels 5 x 5, F(12,5), at 28 x 28 (72 blocks) 13.7 / 13.1; F(14,3), two 16-bit moduli, 512
-  // at 28 x 28 (64) 70.3 / 68.7, 64 at 28 x 28 (8) 14.0 / 12.6; four 8-bit ones, 64 -> 512 at 20 x 20 18.6 / 17.9).
-  c.gz = !c.tiles && c.gy > 1 && units * d.n <= 128 && d.CB1 > 4 * K1_CPW ? 2 : 1;
+  // each gathering anew.  345 layers (two to six 8-bit moduli, two and three 16-bit ones; 3 to 512 channels at 14 x 14 to 80 x 80, batch 1 to 8; us per
+  // layer replayed from a graph): up to 128 blocks of 256 CUs two take 0.97 of one's time with 8-bit and 0.955 with 16-bit moduli at t = 12, where the
+  // second has work for one wave, 0.945 and 0.91 at t = 13 to 16 (F(14,3), 128 -> 64 at 24 x 24, batch 3, four 8-bit 11.7 and 11.0, 128 -> 128 at 20 x 20, two
+  // 16-bit 15.5 and 13.9); with 129 to 160 blocks 0.985 (256 -> 64 at 40 x 40, four 8-bit 14.6 and 14.6), to 256 0.99, above 1.00.
+  const int cus = n_cus > 0 ? n_cus : 256;
+  c.gz = !c.tiles && c.gy > 1 && 2 * units * d.n <= cus && d.CB1 > 4 * K1_CPW ? 2 : 1;
   return c;
 }
 
-K1Params make_k1(const Dims &d, const KParams &P) {
-  const K1Choice c = choose_k1(d);
+K1Params make_k1(const Dims &d, const KParams &P, int n_cus) {
+  const K1Choice c = choose_k1(d, n_cus);
   K1Params q;
   std::memset(&q, 0, sizeof(q));
   q.KB = P.KB;
@@ -407,8 +410,8 @@ K3Params make_k3(const Dims &d, const KParams &P, int n_cus, int epi) {
   X(4, 1, false, false) X(4, 2, false, false)
 
 // ---- K1 ----  (dry: only report whether the instantiation exists)
-bool launch_k1(const Dims &d, const K1Params &P1, const int8_t *x, int8_t *V, hipStream_t st, Timing tm, bool dry = false) {
-  const K1Choice c = choose_k1(d);
+bool launch_k1(const Dims &d, int n_cus, const K1Params &P1, const int8_t *x, int8_t *V, hipStream_t st, Timing tm, bool dry = false) {
+  const K1Choice c = choose_k1(d, n_cus);
   const dim3 grid(c.gx, c.gy, c.gz);
   K1Params P = P1;
   P.x = x; P.V = V;
@@ -513,7 +516,7 @@ int conv2d_impl(const rnswino_plan_t *plan, const int8_t *x_dev, const void *U_d
     t3.start = (hipEvent_t)events[4]; t3.stop = (hipEvent_t)events[5];
   }
   // (rnswino_plan() has checked that all three instantiations exist)
-  if (!launch_k1(d, L.k1, x_dev, Vp, st, t1) || !launch_k2(d, plan->desc.flags, L.k2, (const int8_t *)U_dev, Vp, Op, st, t2) ||
+  if (!launch_k1(d, plan->n_cus, L.k1, x_dev, Vp, st, t1) || !launch_k2(d, plan->desc.flags, L.k2, (const int8_t *)U_dev, Vp, Op, st, t2) ||
       !launch_k3(d, L, plan->n_cus, epi, shift, Op, y_dev, act_dev, st, t3))
     return RNSWINO_E_UNSUPPORTED;
   return launch_status();
@@ -580,12 +583,12 @@ int rnswino_plan(rnswino_plan_t **out, const rnswino_desc_t *desc) {
   pl->kparams = params;
   if (!params) { (void)rnswino_plan_destroy(pl); return RNSWINO_E_INVALID; }
   params->k = make_params(pl);
-  params->k1 = make_k1(d, params->k);
+  params->k1 = make_k1(d, params->k, pl->n_cus);
   params->k2 = make_k2(d, params->k, pl->desc.flags);
   for (int epi = 0; epi < 3; ++epi) params->k3[epi] = make_k3(d, params->k, pl->n_cus, epi);
   {
     // every kernel the layer would launch, in each output mode, must be an instantiation that exists
-    bool ok = launch_k1(d, params->k1, nullptr, nullptr, nullptr, Timing(), true) && launch_k2(d, pl->desc.flags, params->k2, nullptr, nullptr, nullptr, nullptr, Timing(), true);
+    bool ok = launch_k1(d, pl->n_cus, params->k1, nullptr, nullptr, nullptr, Timing(), true) && launch_k2(d, pl->desc.flags, params->k2, nullptr, nullptr, nullptr, nullptr, Timing(), true);
     for (int epi = 0; epi < 3 && ok; ++epi) ok = launch_k3(d, *params, pl->n_cus, epi, 0, nullptr, nullptr, nullptr, nullptr, Timing(), true);
     if (!ok) { (void)rnswino_plan_destroy(pl); return RNSWINO_E_UNSUPPORTED; }
   }
@@ -683,7 +686,7 @@ int64_t rnswino_plan_describe(const rnswino_plan_t *plan, int32_t output_mode, c
   if (!plan || output_mode < 0 || output_mode > 2) return RNSWINO_E_INVALID;
   const Dims &d = plan->dims;
   const KParams &P = ((const LayerParams *)plan->kparams)->k;
-  const K1Choice c1 = choose_k1(d);
+  const K1Choice c1 = choose_k1(d, plan->n_cus);
   const K2Choice c2 = choose_k2(d, plan->desc.flags);
   const K3Choice c3 = choose_k3(d, P, plan->n_cus, output_mode);
   auto tf = [](bool b) { return b ? "true" : "false"; };
