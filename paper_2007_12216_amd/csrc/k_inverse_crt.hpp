@@ -361,8 +361,14 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
   load_ka(min(rb, P.RB3 - 1));
   const int k = kg >> P.tl_shift;
   const int tau = unit * 16 + (lane & 15) < P.npairs ? (kg - (k << P.tl_shift)) * P.Tg + taug : P.T;   // tau >= T marks a lane without output
-  const TilePos tp = tile_position(P, k, tau);
   const FastCrt fc = fast_crt_constants<NRES, FAST>(P);
+  TilePos tp = tile_position(P, k, tau);
+  if constexpr (!WIDE) {
+    // 8-bit moduli: the position here, while the loads are in flight.  Left alone, the compiler moves it and the fetch of its arguments behind the
+    // barrier (0.1 us of a small layer's 7.8; nothing to see with 16-bit moduli).
+    asm volatile("" : "+v"(tp.origin));
+    __builtin_amdgcn_sched_barrier(0);
+  }
 #pragma unroll
   for (int i = 0; i < NRES; ++i)
 #pragma unroll
