@@ -23,10 +23,15 @@ def expected(plan, w):
     return np.stack(out)
 
 
-@pytest.mark.parametrize("C,K,r,m,moduli,T", [
+CASES = [
     (1, 1, 1, 2, NARROW, 1), (65, 17, 2, 3, NARROW, 1), (64, 16, 3, 8, NARROW, 1), (130, 33, 4, 5, NARROW, 1), (3, 5, 5, 12, NARROW, 1),
     (20, 18, 6, 7, NARROW, 1), (65, 15, 7, 10, NARROW, 1), (63, 31, 7, 4, WIDE, 1), (70, 19, 3, 14, WIDE, 1), (3, 5, 3, 4, NARROW, 16),
-    (12, 9, 3, 6, WIDE, 12)])
+    (12, 9, 3, 6, WIDE, 12),
+    # more channels than a fragment holds, for each number of channels a fragment holds
+    (70, 19, 5, 12, NARROW, 1), (65, 17, 6, 7, NARROW, 1), (70, 19, 5, 12, WIDE, 1), (65, 17, 6, 7, WIDE, 1)]
+
+
+@pytest.mark.parametrize("C,K,r,m,moduli,T", CASES)
 @pytest.mark.parametrize("extreme", [False, True])
 def test_filter_transform(C, K, r, m, moduli, T, extreme):
     print("filter transform", C, K, r, m, moduli, T, flush=True)

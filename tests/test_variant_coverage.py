@@ -45,6 +45,17 @@ def test_the_direct_convolution_cases_reach_every_instantiation():
         assert e.value.code == code
 
 
+def test_the_filter_transform_cases_fill_the_fragments_of_every_instantiation():
+    """k0_filter_transform<width, PP>: a filter takes PP = 1, 2 or 4 of a fragment's four slices, the fragment 4 / PP channels."""
+    from test_gpu_filter_transform import CASES
+    reached = set()
+    for C, K, r, m, moduli, T in CASES:
+        pieces = (r * r + 15) // 16
+        if C >= 64:
+            reached.add((moduli[0] > 255, 4 if pieces > 2 else pieces))
+    assert reached == {(wide, pp) for wide in (False, True) for pp in (1, 2, 4)}
+
+
 @pytest.mark.parametrize("case,patches", [
     ((1, 2048, 512, 7, 7, 1, 0), False), ((8, 64, 64, 56, 56, 1, 0), False),                  # a single tap
     ((8, 3, 512, 112, 112, 3, 1), False), ((8, 128, 256, 112, 112, 3, 1), False),             # few steps, many blocks
