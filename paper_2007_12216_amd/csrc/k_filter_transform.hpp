@@ -14,7 +14,8 @@
 // Padding rows and channels, and in packed layers the entries off the diagonal, are zeros: that is what lets the GEMM
 // ignore them.  512 x 512, t = 10, four residues (105 MB): 26.5 us, 4.0 TB/s (31.7 with the filters read from LDS for every item and the sums
 // converted to binary32; one thread per (residue, k, c) with 64-bit divisions and byte stores: 437).  What bounds it: the blocks are all
-// resident at once, so that the gather (4 us with the launch), the residues (6) and the stores (6) follow each other; two, three, five
+// resident at once, so that its parts follow each other: into eight buffers in turn (28.3 us) 18.6 without the stores, 24 without the residues, 27
+// without the products, and 10 without residues and stores, launch, gather, table and products.  Two, three, five
 // to fourteen blocks per compute unit instead of four take 35 to 40.
 #pragma once
 #include "kernels_common.hpp"

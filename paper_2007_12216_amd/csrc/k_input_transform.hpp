@@ -341,9 +341,11 @@ __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
   }
   // Items of this wave, wave, wave + 4, ...: full 16-point blocks of all residues first (their stores need no test, so that the wait for
   // the next item's table does not become a wait for them), then the residues' last, partial blocks.  Item n is block n % nfull of residue
-  // n / nfull, by a multiplication that is exact up to n = 4096, and wave-uniform for the compiler too: counted up in a loop, it took the
-  // residue for a lane's own and fetched its constants by vector loads, which waited for the stores before them (64 -> 64 at 224 x 224,
-  // batch 8: 44.6 us, so 42.9; 256 channels at 56 x 56, batch 8: 20.0 and 18.4; 64 -> 128 at 112 x 112, pooled, 66.5 and 64.2 a layer).
+  // n / nfull, by a multiplication that is exact up to n = 4096.  The residue is wave-uniform for the compiler too: counted up in a loop, it took
+  // it for a lane's own and fetched its constants by vector loads, which waited for the stores before them (64 -> 64 at 224 x 224,
+  // batch 8: 44.6 us, so 42.9; 256 channels at 56 x 56, batch 8: 20.0 and 18.4; 64 -> 128 at 112 x 112, pooled, 66.5 and 64.2 a layer).  The rest is
+  // not: the division here runs on the vector unit, in front of the first table load, and with it the number of items, the loop's condition and
+  // the addresses of an item's table and output.
   const int nfull = P.P2 >> 4, nitems = nfull * nres;
   const uint32_t per_block = __builtin_amdgcn_readfirstlane(nfull > 0 ? (65535u + (uint32_t)nfull) / (uint32_t)nfull : 0);
   constexpr uint32_t FRAG = KS1 * 1024;

@@ -30,7 +30,8 @@
 // The four waves share the unit's O operand through LDS, each loading every fourth point group (a wave-uniform row of O plus a
 // 32-bit lane offset per word).
 // Grid: x = ceil(K*T/16) rounded up to a multiple of 8, y = 1 .. ceil(RB3/4); 256 threads.
-// 16-bit moduli: table and O are two byte planes each; three accumulators as in the GEMM.
+// 16-bit moduli: table and O are two byte planes each; three accumulators as in the GEMM; three and more of them are converted residue by
+// residue, with the rounding in binary64.
 #pragma once
 #include <type_traits>
 
@@ -442,10 +443,12 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
 // once per block in LDS, and every wave walks over units = (k, block of 16 tiles) with a grid stride.  Per unit a wave
 // issues only its own O loads (no table reads from global memory, no copies of O in other waves); the table fragments
 // come from LDS.  A unit's loads are hidden by the other waves of the SIMD (four resident blocks per CU).
-// Loads with a wave-uniform base and a 32-bit lane offset, positions in 32 bits and one loop per output mode took a unit's vector
-// instructions from 390 to 250: 64 -> 128 at 112 x 112, batch 8, pooled, 19.6 -> 18.2 us; the median of the layers of the VGG16 stack, batch 8,
-// that come here 21.3 -> 20.4.
-// What bounds it, on 64 -> 64 at 224 x 224, batch 8, pooled (168 MB of O, 42.8 us before that): without the loads of O 30, without the stores 40, without the conversion 40.5, without
+// Positions in 32 bits, pooling by lane swaps and one loop per output mode and conversion took a unit's vector instructions from about 350 to
+// 300 (four residues, two steps, pooled, binary32): 64 -> 128 at 112 x 112, batch 8, pooled, 19.6 -> 18.2 us; the median of the layers of the VGG16
+// stack, batch 8, that come here 21.3 -> 20.4.  32 of the 300 still add addresses: the lane offsets of the loads are the same for every unit, so the
+// compiler widens them to 64 bits in front of the loop and adds the unit's base to them, once a load.
+// What bounds it: a unit's first products wait for all its loads and for the stores of the unit before.  On 64 -> 64 at 224 x 224, batch 8,
+// pooled (168 MB of O, 42.8 us before that): without the loads of O 30, without the stores 40, without the conversion 40.5, without
 // loads and stores 26.8; the same bytes in 16-byte loads, a quarter as many, 42.3.  More loads in flight make it slower: the next
 // unit's operand requested a unit ahead 23.2 us against that 20.4, five blocks per compute unit 22.3, units of 32 tiles (whole lines of O,
 // three blocks) 22.7.
