@@ -307,11 +307,13 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
   constexpr int PL = WIDE ? 2 : 1;
   constexpr int NACC = WIDE ? 3 : 1;
   constexpr bool AHEAD = NRES * KS3 * PL <= 16;    // the table fragments of a row block fit registers: requested ahead of their use
+  constexpr bool FEW = !WIDE && NRES * KS3 <= 8;   // loads of a lane
   constexpr bool EACH = WIDE && NRES >= 3, APART = WIDE && ((NRES == 5 && KS3 % 2 == 0) || (NRES == 6 && (KS3 == 2 || KS3 == 3)));
   __shared__ __attribute__((aligned(16))) uint32_t o_lds[NRES * KS3 * PL * 256];   // [i][s][plane][lane][4 words]
   asm volatile("" ::"s"(P.O), "s"(P.KA), "s"(P.units), "s"(P.per_xcd), "s"(P.npairs), "s"(P.by_Tg.mul), "s"(P.by_Tg.shift), "s"(P.by_tw.mul),
                "s"(P.by_tw.shift), "s"(P.by_th.mul), "s"(P.by_th.shift), "s"(P.Tg), "s"(P.tl_shift), "s"(P.T), "s"(P.Q), "s"(P.Tp), "s"(P.tw),
                "s"(P.th), "s"(P.RB3), "s"(P.rb_step));
+  if constexpr (FEW) asm volatile("" ::"s"(P.m), "s"(P.K), "s"(P.Ho), "s"(P.Wo), "s"(P.epi));
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: row block and table addresses stay scalar
   const int lane = threadIdx.x & 63, g = lane >> 4;
   // A unit is 16 consecutive (k, tile) pairs of the flattened K x T index space (no padding tiles: a unit may span
@@ -364,9 +366,10 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
   const int tau = unit * 16 + (lane & 15) < P.npairs ? (kg - (k << P.tl_shift)) * P.Tg + taug : P.T;   // tau >= T marks a lane without output
   const FastCrt fc = fast_crt_constants<NRES, FAST>(P);
   TilePos tp = tile_position(P, k, tau);
-  if constexpr (!WIDE) {
-    // 8-bit moduli: the position here, while the loads are in flight.  Left alone, the compiler moves it and the fetch of its arguments behind the
-    // barrier (0.1 us of a small layer's 7.8; nothing to see with 16-bit moduli).
+  if constexpr (FEW) {
+    // The position here, while the loads are in flight, its arguments fetched at entry.  Left alone, the compiler moves both behind the barrier
+    // (0.1 us of the 8 to 9.5 of a small layer, 100 channels at 57 x 43, batch 3, 14.07 and 13.93).  With more loads what it moves there covers the
+    // table's fetch: 48 -> 64 channels, 5 x 5, at 35 x 35, batch 8 (16 loads), 18.45 us here and 18.30 there.  Nothing to see with 16-bit moduli.
     asm volatile("" : "+v"(tp.origin));
     __builtin_amdgcn_sched_barrier(0);
   }

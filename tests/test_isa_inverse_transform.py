@@ -1,6 +1,6 @@
 """Registers of the inverse transform over 16-bit moduli, read off the compiler's metadata (no GPU): its loads, products and binary64
 arithmetic follow each other, so that a wave per SIMD less takes up to twice as long.  And of the one over 8-bit moduli, read off the assembly, that
-the divisions of a lane's position are done while its loads are in flight."""
+the divisions of a lane's position are done while its loads are in flight, where these are few."""
 import pytest
 
 import paper_2007_12216_amd as rn
@@ -15,7 +15,8 @@ def test_waves_per_simd(vector_registers, moduli, steps):
     assert REGISTERS // (-(-count // 8) * 8) >= WAVES[moduli][steps - 1], count
 
 
-@pytest.mark.parametrize("variant", [v for v in rn.rnswino_kernel_variants() if v.startswith("k3_inverse_crt<") and v.split(", ")[2] == "false"])
+@pytest.mark.parametrize("variant", [v for v in rn.rnswino_kernel_variants() if v.startswith("k3_inverse_crt<") and v.split(", ")[2] == "false" and
+                                     int(v[15]) * int(v[18]) <= 8])
 def test_the_position_is_known_before_the_barrier(assembly, variant):
     moduli, steps, _, fast = variant.partition("<")[2].rstrip(">").split(", ")
     name, = [n for n in assembly if f"14k3_inverse_crtILi{moduli}ELi{steps}ELb0ELb{int(fast == 'true')}E" in n]
