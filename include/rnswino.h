@@ -241,7 +241,7 @@ int rnswino_plan_get_mrc_inverse(const rnswino_plan_t *plan, int l, int j, uint3
  * (grid=XxYxZ where the launch has a third extent).
  * conversion: "unreduced-binary32" / "unreduced-binary64" = CRT sum over unreduced accumulators with the quotient rounded
  * in that precision; "reduced-binary32" / "reduced-binary64" = over reduced residues; "reduced-binary64-mul32" = the same
- * with full 32-bit multiplies (a partial product P/m_i of 2^24 or more, or three and more 16-bit moduli).  Works on host-only plans (their
+ * with full 32-bit multiplies (a partial product P/m_i of 2^24 or more, or three and more 16-bit moduli in most cases).  Works on host-only plans (their
  * grids assume 256 compute units).  Returns the number of bytes including the terminating
  * zero (copied only if capacity suffices), or a negative code.  For tests and measurement scripts.
  */

@@ -30,8 +30,8 @@
 // The four waves share the unit's O operand through LDS, each loading every fourth point group (a wave-uniform row of O plus a
 // 32-bit lane offset per word).
 // Grid: x = ceil(K*T/16) rounded up to a multiple of 8, y = 1 .. ceil(RB3/4); 256 threads.
-// 16-bit moduli: table and O are two byte planes each; three accumulators as in the GEMM; three and more of them are converted residue by
-// residue, with the rounding in binary64.
+// 16-bit moduli: table and O are two byte planes each; three accumulators as in the GEMM; three and more of them are mostly
+// converted residue by residue (k3_converts_each), with the rounding in binary64.
 #pragma once
 #include <type_traits>
 
@@ -295,20 +295,22 @@ __device__ __forceinline__ void k3_convert_and_store(const K3Params &P, const Fa
   k3_store(P, val, rb, g, tp);
 }
 
-// FAST: the conversion with unreduced accumulators (the host launches it when KParams::fastcrt is set).
 // Three and more 16-bit moduli: a residue goes into the sum and the binary64 quotient of the conversion as soon as it is there, signed.  Kept
 // until all were there, shifted and converted again for the quotient, with p converted in registers of its own, the residues cost most of
 // these kernels a wave per SIMD: 64 -> 256 at 56 x 56, batch 4, five, six, seven, eight moduli at F(4,3) 52, 57.8, 65.7, 126 us, so 28.8,
-// 52.6, 59.5, 63.7; three at F(14,3) 39.5, so 26.6.
-// Where the products of several residues at once would cost a wave, the residues stay apart (APART): five at F(8,3) 25.2 -> 22.2, at F(14,3)
-// 43.4 -> 40.8; six at F(8,3) 32.5 -> 26.0, at F(10,3) 55.8 -> 43.3; elsewhere it loses up to a tenth.
+// 52.6, 59.5, 63.7; three at F(14,3) 39.5, so 26.6.  Six and eight moduli at two steps keep them: 28.8 us there, so 32.1, eight 34.9 and 35.5.
+constexpr bool k3_converts_each(int nres, int ks3) { return nres >= 3 && !(ks3 == 2 && (nres == 6 || nres == 8)); }
+
+// FAST: the conversion with unreduced accumulators (the host launches it when KParams::fastcrt is set).
+// Where the products of several residues at once would cost a wave, the residues stay apart (APART): five 16-bit moduli at F(8,3) 25.2 -> 22.2
+// us, at F(14,3) 43.4 -> 40.8; six at F(10,3) 55.8 -> 43.3; elsewhere it loses up to a tenth.
 template <int NRES, int KS3, bool WIDE, bool FAST>
 __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
   constexpr int PL = WIDE ? 2 : 1;
   constexpr int NACC = WIDE ? 3 : 1;
   constexpr bool AHEAD = NRES * KS3 * PL <= 16;    // the table fragments of a row block fit registers: requested ahead of their use
   constexpr bool FEW = !WIDE && NRES * KS3 <= 8;   // loads of a lane
-  constexpr bool EACH = WIDE && NRES >= 3, APART = WIDE && ((NRES == 5 && KS3 % 2 == 0) || (NRES == 6 && (KS3 == 2 || KS3 == 3)));
+  constexpr bool EACH = WIDE && k3_converts_each(NRES, KS3), APART = WIDE && ((NRES == 5 && KS3 % 2 == 0) || (NRES == 6 && KS3 == 3));
   __shared__ __attribute__((aligned(16))) uint32_t o_lds[NRES * KS3 * PL * 256];   // [i][s][plane][lane][4 words]
   asm volatile("" ::"s"(P.O), "s"(P.KA), "s"(P.units), "s"(P.per_xcd), "s"(P.npairs), "s"(P.by_Tg.mul), "s"(P.by_Tg.shift), "s"(P.by_tw.mul),
                "s"(P.by_tw.shift), "s"(P.by_th.mul), "s"(P.by_th.shift), "s"(P.Tg), "s"(P.tl_shift), "s"(P.T), "s"(P.Q), "s"(P.Tp), "s"(P.tw),
@@ -416,7 +418,7 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
       for (int j = 0; j < 4; ++j) {
         if constexpr (WIDE) {
           // per accumulator |sum| <= t*t * 2^15: the combination stays below 2^40
-          const double r = mod_near64(acc[0][j], acc[1][j], acc[2][j], P.inv_pd[i], P.pd[i]);
+          const double r = mod_near64(acc[0][j], acc[1][j], acc[2][j], P.inv_pd[i], EACH || NRES < 3 ? P.pd[i] : (double)P.p[i]);
           if (EACH) {
             sum[j] += P.crt_c[i] * (uint32_t)(int)r;
             fs[j] = __builtin_fma(r, P.inv_pd[i], fs[j]);

@@ -709,7 +709,7 @@ int64_t rnswino_plan_describe(const rnswino_plan_t *plan, int32_t output_mode, c
                          tf(c3.fast), c3.gx, c3.gy);
   const char *conv = P.fastcrt == 1 ? "unreduced-binary32"
                      : P.fastcrt == 2 ? "unreduced-binary64"
-                     : !P.crt24 || (d.wide && d.n >= 3) ? "reduced-binary64-mul32"
+                     : !P.crt24 || (d.wide && k3_converts_each(d.n, c3.KS3)) ? "reduced-binary64-mul32"
                      : P.quot32 ? "reduced-binary32" : "reduced-binary64";
   len += std::snprintf(buf + len, sizeof(buf) - len, "conversion=%s\n", conv);
   if (host_out && capacity > (size_t)len) std::memcpy(host_out, buf, (size_t)len + 1);
