@@ -25,58 +25,66 @@ namespace rnswino {
 
 constexpr int K1_CPW = 2;
 
-// What the kernel reads, in the order in which it reads it, built once with the plan (the pointers per call).  The fields
-// up to `total` are fetched together at entry: scattered over the layer's full parameter block, they took three dependent fetches
+// The kernels' arguments, fetched together at entry: scattered over the layer's full parameter block, they took three dependent fetches
 // of the launch's argument memory (about 500 cycles each) before the first pixel was asked for, and the divisions as many
 // again.  256 channels at 56 x 56 (800 blocks): 2000 cycles from entry to the last load, now 900; whole layer 23.4 -> 22.1 us,
 // 5 x 5 128 channels at 28 x 28 18.8 -> 17.1, 100 channels at 57 x 43 20.0 -> 18.3, VGG16 stack at batch 1 397 -> 379.
-struct K1Params {
+struct K1Args {
+  const ResidueParams *more;
   const int8_t *x;
   int8_t *V;
   const int8_t *KB;           // (B^T kron B^T) mod p, [n][CB1][KS1][planes][64 lanes][16]
   int units, per_xcd;         // T * Cp/64 (of the packed problem), and the grid's x extent / 8
-  int ncb, split;             // 0: a block takes all residues; else it takes one (blockIdx.y), and `split` blocks share its column blocks (blockIdx.z)
-  FastDiv by_ncb, by_tw, by_th;
-  int C, H, W, HW, m, pad, t, tw, th;
-  int n, CB1, P2;
+  int ncb;                    // channel blocks of 64
+  uint32_t ncb_mul, tw_mul, th_mul;          // FastDiv's, with the shifts below
+  int C, H, W, pad, tw, th, T, Tg;
   long long total;            // N * C * H * W
-  int T, Tg, Cq, cq_shift, RP1;
-  alignas(16) Residue8 res[8];
-  double inv_pd[8];           // 16-bit moduli
+  uint32_t shifts;            // bytes: of the divisions by ncb, tw, th; log2 of a tile's channel slots
+  uint32_t sizes;             // bytes: m, t, n, split
+  RNSW_HD FastDiv by_ncb() const { return {ncb_mul, shifts & 31u}; }
+  RNSW_HD FastDiv by_tw() const { return {tw_mul, shifts >> 8 & 31u}; }
+  RNSW_HD FastDiv by_th() const { return {th_mul, shifts >> 16 & 31u}; }
+  RNSW_HD int cq_shift() const { return (int)(shifts >> 24); }
+  RNSW_HD int m() const { return (int)byte_of(sizes, 0); }
+  RNSW_HD int t() const { return (int)byte_of(sizes, 1); }
+  RNSW_HD int n() const { return (int)byte_of(sizes, 2); }
+  // 0: a block takes all residues; else it takes one (blockIdx.y), and `split` blocks share its column blocks (blockIdx.z)
+  RNSW_HD int split() const { return (int)(sizes >> 24); }
 };
+static_assert(sizeof(K1Args) <= 112, "kernels_common.hpp");
+#define RNSW_K1_FETCH_ARGUMENTS(P)                                                                                                       \
+  asm volatile("" ::"s"(P.x), "s"(P.V), "s"(P.KB), "s"(P.units), "s"(P.per_xcd), "s"(P.ncb), "s"(P.ncb_mul), "s"(P.tw_mul), "s"(P.th_mul), "s"(P.C), \
+               "s"(P.H), "s"(P.W), "s"(P.pad), "s"(P.tw), "s"(P.th), "s"(P.total), "s"(P.shifts), "s"(P.sizes))
 
 // PACK: the layer packs TL tiles into one 64-channel block (plan.hpp): block channel c' holds channel c' % Cq of tile
 // (c' / Cq) * Tg + tau, so every gathered row segment has its own tile origin; everything after the gather is the same.
 template <int KS1, bool WIDE, bool PACK>
-__global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
+__global__ __launch_bounds__(256) void k1_input_transform(K1Args P) {
+  Constant<ResidueParams> &R = constant(P.more);
   constexpr int ROWS = KS1 == 1 ? 8 : KS1 == 2 ? 10 : KS1 == 3 ? 12 : 16;   // largest t with this many steps
   constexpr int PL = WIDE ? 2 : 1;
   constexpr int CROW = (4 * KS1 + 1) * 16;   // bytes per channel in LDS: one 16-byte pad, so that the 16 channels a
                                              // fragment read touches fall into different banks
   __shared__ __attribute__((aligned(16))) uint8_t xs[64 * CROW];
-  Residue8 rf = P.res[blockIdx.y], rn = rf;           // constants of the first step's residue (y is 0 where a block takes all)
-  // (fetched here, all together, instead of one after the other where they are used)
-  asm volatile("" ::"s"(rf.inv), "s"(rf.quot_bias), "s"(rf.neg_p), "s"(rf.acc_bias), "s"(P.x), "s"(P.V), "s"(P.KB), "s"(P.units),
-               "s"(P.per_xcd), "s"(P.ncb), "s"(P.split), "s"(P.by_ncb.mul), "s"(P.by_ncb.shift), "s"(P.by_tw.mul), "s"(P.by_tw.shift),
-               "s"(P.by_th.mul), "s"(P.by_th.shift), "s"(P.C), "s"(P.H), "s"(P.W), "s"(P.HW), "s"(P.m), "s"(P.pad), "s"(P.t), "s"(P.tw),
-               "s"(P.th), "s"(P.n), "s"(P.CB1), "s"(P.P2), "s"(P.total));
+  RNSW_K1_FETCH_ARGUMENTS(P);
+  const int t = P.t(), P2 = t * t, CB1 = (P2 + 15) >> 4, HW = P.H * P.W;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: table addresses stay scalar
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const int ncb = P.ncb;
-  const int i0 = P.split ? blockIdx.y : 0, i1 = P.split ? i0 + 1 : P.n;   // residues of this block
+  const int i0 = P.split() ? blockIdx.y : 0, i1 = P.split() ? i0 + 1 : P.n();   // residues of this block
   // neighbouring tiles (shared image lines) on one XCD, see kernels_common.hpp
   const int unit = (int)(blockIdx.x & 7) * P.per_xcd + (int)(blockIdx.x >> 3);
   if (unit >= P.units) return;
-  const int tau = (int)fast_div((uint32_t)unit, P.by_ncb), cb = unit - tau * ncb;   // tau: GEMM column (a group of TL tiles when PACK)
+  const int tau = (int)fast_div((uint32_t)unit, P.by_ncb()), cb = unit - tau * ncb;   // tau: GEMM column (a group of TL tiles when PACK)
   // first image row and column of a tile and the byte index of (channel ch, that row, that column)
   struct Origin { long long base; int y0, x0; };
   auto tile_origin = [&](int tile, int ch) -> Origin {
-    const int trow = (int)fast_div((uint32_t)tile, P.by_tw), tx = tile - trow * P.tw;
-    const int img = (int)fast_div((uint32_t)trow, P.by_th), ty = trow - img * P.th;
+    const int trow = (int)fast_div((uint32_t)tile, P.by_tw()), tx = tile - trow * P.tw;
+    const int img = (int)fast_div((uint32_t)trow, P.by_th()), ty = trow - img * P.th;
     Origin o;
-    o.y0 = ty * P.m - P.pad;
-    o.x0 = tx * P.m - P.pad;
-    o.base = ((long long)img * P.C + ch) * P.HW + (long long)o.y0 * P.W + o.x0;
+    o.y0 = ty * P.m() - P.pad;
+    o.x0 = tx * P.m() - P.pad;
+    o.base = ((long long)img * P.C + ch) * HW + (long long)o.y0 * P.W + o.x0;
     return o;
   };
   // A thread's NT row segments are requested together and only then masked and written to LDS (one after the
@@ -94,44 +102,44 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
     for (int k = 0; k < NT; ++k) {
       const int task = threadIdx.x + 256 * k;
       const int cblk = task / ROWS, a = task - cblk * ROWS;
-      const int ch = cblk & (P.Cq - 1), tile = (cblk >> P.cq_shift) * P.Tg + tau;
+      const int ch = cblk & ((1 << P.cq_shift()) - 1), tile = (cblk >> P.cq_shift()) * P.Tg + tau;
       const Origin o = tile_origin(min(tile, P.T - 1), ch);
       const int gy = o.y0 + a;
       const long long from = o.base + (long long)a * P.W, at = segment_at(from, P.total);
       moved[k] = (int)(from - at);                   // rows inside the image: their segments overlap the tensor or are masked
-      there[k] = task < 64 * ROWS && tile < P.T && ch < P.C && a < P.t && gy >= 0 && gy < P.H;
+      there[k] = task < 64 * ROWS && tile < P.T && ch < P.C && a < t && gy >= 0 && gy < P.H;
       val[k] = (v4i){0, 0, 0, 0};
       if (there[k] && !tiny) __builtin_memcpy(&val[k], P.x + at, 16);       // one unaligned 16-byte load
-      mask0[k] = byte_range(max(-o.x0, 0), min(P.t, P.W - o.x0), 0);
-      mask1[k] = byte_range(max(-o.x0, 0), min(P.t, P.W - o.x0), 8);
+      mask0[k] = byte_range(max(-o.x0, 0), min(t, P.W - o.x0), 0);
+      mask1[k] = byte_range(max(-o.x0, 0), min(t, P.W - o.x0), 8);
     }
   } else {
     const Origin o = tile_origin(tau, cb * 64);
     // offsets from the origin that a load may start at (rows outside the image are excluded separately)
     const SegmentRange inside = segment_range(o.base, P.total);
-    const bool columns = o.x0 < P.W && o.x0 + P.t > 0;                                 // (wide padding: perhaps none)
-    const int a_lo = max(-o.y0, 0), a_count = columns ? max(min(P.t, P.H - o.y0) - a_lo, 0) : 0;     // rows inside the image
+    const bool columns = o.x0 < P.W && o.x0 + t > 0;                                 // (wide padding: perhaps none)
+    const int a_lo = max(-o.y0, 0), a_count = columns ? max(min(t, P.H - o.y0) - a_lo, 0) : 0;     // rows inside the image
     const int chans = P.C - cb * 64;
     const int8_t *xb = P.x + (o.base - 16);
 #pragma unroll
     for (int k = 0; k < NT; ++k) {
       const int task = threadIdx.x + 256 * k;
       const int cblk = task / ROWS, a = task - cblk * ROWS;
-      const int from = cblk * P.HW + a * P.W, at = segment_at(from, inside);   // 64 * H * W stays far below 2^31
+      const int from = cblk * HW + a * P.W, at = segment_at(from, inside);   // 64 * H * W stays far below 2^31
       moved[k] = tiny ? (int)o.base + from : from - at;
       there[k] = (256 * (k + 1) <= 64 * ROWS || task < 64 * ROWS) && cblk < chans && (uint32_t)(a - a_lo) < (uint32_t)a_count;
       val[k] = (v4i){0, 0, 0, 0};
       if (there[k] && !tiny) __builtin_memcpy(&val[k], xb + (uint32_t)(at + 16), 16);   // one unaligned 16-byte load
     }
-    mask0[0] = byte_range(max(-o.x0, 0), min(P.t, P.W - o.x0), 0);
-    mask1[0] = byte_range(max(-o.x0, 0), min(P.t, P.W - o.x0), 8);
+    mask0[0] = byte_range(max(-o.x0, 0), min(t, P.W - o.x0), 0);
+    mask1[0] = byte_range(max(-o.x0, 0), min(t, P.W - o.x0), 8);
   }
   // This wave's work: steps (residue i, column-block group cg) with cg = first, first + stride, ...  The table fragments
   // of step k+1 are requested before step k is multiplied; those of step 0 behind the gather's own loads, so that their
   // latency overlaps the gather.  A step's position is kept as wave-uniform scalars and advanced incrementally
   // (no divisions, and only a few scalar operations per column block: every instruction counts here).
-  const int ncg = (P.CB1 + K1_CPW - 1) / K1_CPW;
-  const int part_shift = P.split >> 1;                // log2 of the blocks that share a residue: one or two
+  const int ncg = (CB1 + K1_CPW - 1) / K1_CPW;
+  const int part_shift = P.split() >> 1;                // log2 of the blocks that share a residue: one or two
   const int first = wave + 4 * (int)blockIdx.z, stride = 4 << part_shift;
   const int per_i = max(ncg - first + stride - 1, 0) >> (2 + part_shift);              // groups of this wave per residue
   const int nsteps = (i1 - i0) * per_i;
@@ -145,8 +153,8 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
   auto load_table = [&](const Pos &q, v4i (&b)[K1_CPW][KS1][PL]) {
 #pragma unroll
     for (int cc = 0; cc < K1_CPW; ++cc) {
-      const int cbk = min(q.cg * K1_CPW + cc, P.CB1 - 1);
-      const int8_t *frag = KBl + (uint32_t)(q.i * P.CB1 + cbk) * FRAG;   // the whole table is far below 4 GiB
+      const int cbk = min(q.cg * K1_CPW + cc, CB1 - 1);
+      const int8_t *frag = KBl + (uint32_t)(q.i * CB1 + cbk) * FRAG;   // the whole table is far below 4 GiB
 #pragma unroll
       for (int s = 0; s < KS1; ++s)
 #pragma unroll
@@ -158,11 +166,12 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
   // address costs the vector unit next to nothing.  stride_pt = bytes between consecutive transform points.
   const uint32_t stride_pt = (uint32_t)(ncb * PL * 1024);
   const uint32_t lane_store = (uint32_t)(lane & 15) * stride_pt + g * 16;   // 16 points * ncb KiB: far below 2^32
-  int8_t *const Vtile = P.V + ((size_t)(tau >> 4) * (size_t)(P.n * P.P2) * ncb + cb) * (PL * 1024) + (tau & 15) * 64;
+  int8_t *const Vtile = P.V + ((size_t)(tau >> 4) * (size_t)(P.n() * P2) * ncb + cb) * (PL * 1024) + (tau & 15) * 64;
   v4i bf[K1_CPW][KS1][PL], bn[K1_CPW][KS1][PL];
   Pos cur = {i0, first};
   if (nsteps > 0) load_table(cur, bf);
   __builtin_amdgcn_sched_barrier(0);
+  Residue8 rf = residue(R.res[i0]), rn = rf;          // constants of the first step's residue: fetched behind the loads, not in front of them
   if (tiny) {
 #pragma unroll
     for (int k = 0; k < NT; ++k)
@@ -190,8 +199,8 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
     val[k][2] &= (int)(uint32_t)m1; val[k][3] &= (int)(uint32_t)(m1 >> 32);
     // the first RP1 bytes of the segment are the row's slots (the slots past t * RP1 are never written: their
     // table entries are zero, and any byte times zero is zero); RP1 is 4 or 8, 12, 12, 16 for KS1 = 1, 2, 3, 4
-    if (task < 64 * ROWS && a < P.t) {
-      const int rp = KS1 == 1 ? P.RP1 : KS1 == 4 ? 16 : 12;
+    if (task < 64 * ROWS && a < t) {
+      const int rp = KS1 == 1 ? ((t + 3) & ~3) : KS1 == 4 ? 16 : 12;
       uint32_t *row = (uint32_t *)(xs + cblk * CROW + a * rp);
       row[0] = (uint32_t)val[k][0];
       if (rp > 4) row[1] = (uint32_t)val[k][1];
@@ -217,16 +226,16 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
   auto do_step = [&](int step, v4i (&b)[K1_CPW][KS1][PL], v4i (&bnext)[K1_CPW][KS1][PL], const Residue8 &rc, Residue8 &rnext) {
     const int i = cur.i, cg = cur.cg;
     advance(cur);
-    if (step + 1 < nsteps) { load_table(cur, bnext); rnext = P.res[cur.i]; }
+    if (step + 1 < nsteps) { load_table(cur, bnext); rnext = residue(R.res[cur.i]); }
     const int p = -rc.neg_p;
     const float inv = in_vgpr(rc.inv), qb = in_vgpr(rc.quot_bias);
-    const double invd = WIDE ? P.inv_pd[i] : 0.0;
+    const double invd = WIDE ? R.inv_pd[i] : 0.0;
     const int a0 = WIDE ? 0 : rc.acc_bias;           // see biased_lowbyte()
     const v4i start = (v4i){a0, a0, a0, a0};
 #pragma unroll
     for (int cc = 0; cc < K1_CPW; ++cc) {
       const int cbk = cg * K1_CPW + cc;
-      if (cbk >= P.CB1) break;
+      if (cbk >= CB1) break;
       v4i acc[PL][4];
 #pragma unroll
       for (int pl = 0; pl < PL; ++pl)
@@ -240,7 +249,7 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
           for (int u = 0; u < 4; ++u)
             acc[pl][u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[u][s], b[cc][s][pl], acc[pl][u], 0, 0, 0);
       const int pt = 16 * cbk + (lane & 15);
-      int8_t *dst = Vtile + (size_t)(uint32_t)(i * P.P2 + 16 * cbk) * stride_pt + lane_store;
+      int8_t *dst = Vtile + (size_t)(uint32_t)(i * P2 + 16 * cbk) * stride_pt + lane_store;
       if (WIDE) {
         // per plane |acc| <= t*t * 128 * 128 = 2^22, so 256 * acc_h + acc_l fits 32 bits
         v4i out_h, out_l;
@@ -258,7 +267,7 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
           out_h[u] = (int)wh;
           out_l[u] = (int)wl;
         }
-        if (pt < P.P2) {
+        if (pt < P2) {
           *(v4i *)dst = out_h;
           *(v4i *)(dst + 1024) = out_l;
         }
@@ -269,7 +278,7 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
         for (int u = 0; u < 4; ++u)
           out[u] = (int)pack_low_bytes(biased_lowbyte(acc[0][u][0], inv, qb, -p), biased_lowbyte(acc[0][u][1], inv, qb, -p),
                                        biased_lowbyte(acc[0][u][2], inv, qb, -p), biased_lowbyte(acc[0][u][3], inv, qb, -p));
-        if (pt < P.P2) *(v4i *)dst = out;
+        if (pt < P2) *(v4i *)dst = out;
       }
     }
   };
@@ -296,31 +305,29 @@ __global__ __launch_bounds__(256) void k1_input_transform(K1Params P) {
 // with 392 blocks, 48 against 44.6 with 1568.
 // Grid: x = 4 * Tp/16 * Cp/64 rounded up to a multiple of 8 (kernels_common.hpp), y = n or 1.
 template <int KS1, bool PACK>
-__global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
+__global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Args P) {
+  Constant<ResidueParams> &R = constant(P.more);
   constexpr int ROWS = KS1 == 1 ? 8 : 10;
   __shared__ __attribute__((aligned(16))) uint8_t xs[16 * KS1 * 1024];     // fragments [channel][step][slice h][tile][16 slots]
-  // (the residues' constants are fetched with their items)
-  asm volatile("" ::"s"(P.x), "s"(P.V), "s"(P.KB), "s"(P.units),
-               "s"(P.per_xcd), "s"(P.ncb), "s"(P.split), "s"(P.by_ncb.mul), "s"(P.by_ncb.shift), "s"(P.by_tw.mul), "s"(P.by_tw.shift),
-               "s"(P.by_th.mul), "s"(P.by_th.shift), "s"(P.C), "s"(P.H), "s"(P.W), "s"(P.HW), "s"(P.m), "s"(P.pad), "s"(P.t), "s"(P.tw),
-               "s"(P.th), "s"(P.n), "s"(P.CB1), "s"(P.P2), "s"(P.total));
+  RNSW_K1_FETCH_ARGUMENTS(P);                      // (the residues' constants are fetched with their items)
+  const int t = P.t(), P2 = t * t, CB1 = (P2 + 15) >> 4, HW = P.H * P.W;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, h = lane >> 4;
   const int unit = (int)(blockIdx.x & 7) * P.per_xcd + (int)(blockIdx.x >> 3);
   if (unit >= P.units) return;
-  const int g = unit & 3, tb = (int)fast_div((uint32_t)unit >> 2, P.by_ncb), cb = (unit >> 2) - tb * P.ncb;
-  const int i0 = P.split ? blockIdx.y : 0, nres = P.split ? 1 : P.n;
+  const int g = unit & 3, tb = (int)fast_div((uint32_t)unit >> 2, P.by_ncb()), cb = (unit >> 2) - tb * P.ncb;
+  const int i0 = P.split() ? blockIdx.y : 0, nres = P.split() ? 1 : P.n();
   // gather: this thread's tile and channel
   const int col = threadIdx.x & 15, ch16 = threadIdx.x >> 4;
   const int cblk = 16 * (ch16 >> 2) + 4 * g + (ch16 & 3);              // channel order of layout.hpp
   const int tau = tb * 16 + col;
-  const int tile = PACK ? (cblk >> P.cq_shift) * P.Tg + tau : tau, ch = PACK ? (cblk & (P.Cq - 1)) : cb * 64 + cblk;
+  const int tile = PACK ? (cblk >> P.cq_shift()) * P.Tg + tau : tau, ch = PACK ? (cblk & ((1 << P.cq_shift()) - 1)) : cb * 64 + cblk;
   const bool live = tau < P.Tg && tile < P.T && ch < P.C;
   const int tc = live ? tile : 0;
-  const int trow = (int)fast_div((uint32_t)tc, P.by_tw), tx = tc - trow * P.tw;
-  const int img = (int)fast_div((uint32_t)trow, P.by_th), ty = trow - img * P.th;
-  const int y0 = ty * P.m - P.pad, x0 = tx * P.m - P.pad;
-  const int plane = (img * P.C + (live ? ch : 0)) * P.HW;              // below 2^31, as the whole tensor
+  const int trow = (int)fast_div((uint32_t)tc, P.by_tw()), tx = tc - trow * P.tw;
+  const int img = (int)fast_div((uint32_t)trow, P.by_th()), ty = trow - img * P.th;
+  const int y0 = ty * P.m() - P.pad, x0 = tx * P.m() - P.pad;
+  const int plane = (img * P.C + (live ? ch : 0)) * HW;              // below 2^31, as the whole tensor
   // Row segments as offsets from the multiple of four at or before the tensor's start; rows outside the image repeat its first or last
   // row and are masked.  Only what the tensor holds is loaded: where clamping moves a load, the segment is put right below.
   const int mis = (int)((uint32_t)(uintptr_t)P.x & 3u), last = (int)P.total - 16 + mis;     // (the tensor has 16 bytes and more)
@@ -346,13 +353,13 @@ __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
   // batch 8: 44.6 us, so 42.9; 256 channels at 56 x 56, batch 8: 20.0 and 18.4; 64 -> 128 at 112 x 112, pooled, 66.5 and 64.2 a layer).  The rest is
   // not: the division here runs on the vector unit, in front of the first table load, and with it the number of items, the loop's condition and
   // the addresses of an item's table and output.
-  const int nfull = P.P2 >> 4, nitems = nfull * nres;
+  const int nfull = P2 >> 4, nitems = nfull * nres;
   const uint32_t per_block = __builtin_amdgcn_readfirstlane(nfull > 0 ? (65535u + (uint32_t)nfull) / (uint32_t)nfull : 0);
   constexpr uint32_t FRAG = KS1 * 1024;
   const uint32_t lane16 = (uint32_t)lane * 16u;
   auto residue_of = [&](int n) { return (int)(((uint32_t)n * per_block) >> 16); };
   auto load_table = [&](int i, int cbk, v4i (&b)[KS1]) {
-    const int8_t *frag = P.KB + (size_t)((uint32_t)(i * P.CB1 + cbk) * FRAG);
+    const int8_t *frag = P.KB + (size_t)((uint32_t)(i * CB1 + cbk) * FRAG);
 #pragma unroll
     for (int s = 0; s < KS1; ++s) b[s] = *(const v4i *)(frag + s * 1024 + lane16);
   };
@@ -363,9 +370,9 @@ __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
   v4i ta[KS1], tn[KS1];
   int item = wave;
   load_item(item, ta);
-  const unsigned long long m0 = byte_range(max(-x0, 0), min(P.t, P.W - x0), 0), m1 = byte_range(max(-x0, 0), min(P.t, P.W - x0), 8);
+  const unsigned long long m0 = byte_range(max(-x0, 0), min(t, P.W - x0), 0), m1 = byte_range(max(-x0, 0), min(t, P.W - x0), 8);
   const uint32_t mask[3] = {live ? (uint32_t)m0 : 0u, live ? (uint32_t)(m0 >> 32) : 0u, live ? (uint32_t)m1 : 0u};
-  const int rows_in = min(P.t, P.H - y0);                              // row a is inside the image and the tile: -y0 <= a < rows_in
+  const int rows_in = min(t, P.H - y0);                              // row a is inside the image and the tile: -y0 <= a < rows_in
   __builtin_amdgcn_sched_barrier(0);
   constexpr int WPR = KS1 == 1 ? 2 : 3;                                // words of a row
   uint32_t slots[16 * KS1];
@@ -395,7 +402,7 @@ __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
 #pragma unroll
     for (int d = 0; d < WPR; ++d) slots[a * WPR + d] &= in ? mask[d] : 0u;
   }
-  if (KS1 == 1 && P.RP1 == 4) {                                        // uniform: rows of one word
+  if (KS1 == 1 && ((t + 3) & ~3) == 4) {                                        // uniform: rows of one word
 #pragma unroll
     for (int a = 0; a < ROWS; ++a) slots[a] = slots[2 * a];
   }
@@ -406,7 +413,7 @@ __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
   __syncthreads();
 
   const uint8_t *px = xs + lane * 16;
-  int8_t *const Vb = P.V + ((size_t)tb * (size_t)(P.n * P.P2) * P.ncb + cb) * 1024 + g * 256;
+  int8_t *const Vb = P.V + ((size_t)tb * (size_t)(P.n() * P2) * P.ncb + cb) * 1024 + g * 256;
   const uint32_t stride_pt = (uint32_t)P.ncb * 1024u;
   const uint32_t lane_store = (uint32_t)(4 * h) * stride_pt + (uint32_t)(lane & 15) * 16u;
   // out[e]: 16 channels of point 16 cbk + 4 h + e
@@ -431,8 +438,8 @@ __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
   };
   auto full_item = [&](v4i (&tab)[KS1], v4i (&next)[KS1]) {
     const int k = __builtin_amdgcn_readfirstlane(residue_of(item));
-    const Residue8 r = P.res[i0 + k];
-    int8_t *dst = Vb + (size_t)(uint32_t)((i0 + k) * P.P2 + 16 * (item - k * nfull)) * stride_pt + lane_store;
+    const Residue8 r = residue(R.res[i0 + k]);
+    int8_t *dst = Vb + (size_t)(uint32_t)((i0 + k) * P2 + 16 * (item - k * nfull)) * stride_pt + lane_store;
     item += 4;
     load_item(item, next);
     v4i out[4];
@@ -448,16 +455,16 @@ __global__ __launch_bounds__(256, 4) void k1_input_transform_tiles(K1Params P) {
     if (item >= nitems) break;
     full_item(tn, ta);
   }
-  if (P.P2 & 15) {
+  if (P2 & 15) {
     for (int pi = i0 + wave; pi < i0 + nres; pi += 4) {
       v4i tab[KS1], out[4];
       load_table(pi, nfull, tab);
-      const Residue8 r = P.res[pi];
+      const Residue8 r = residue(R.res[pi]);
       compute(tab, r, out);
-      int8_t *dst = Vb + (size_t)(uint32_t)(pi * P.P2 + 16 * nfull) * stride_pt + lane_store;
+      int8_t *dst = Vb + (size_t)(uint32_t)(pi * P2 + 16 * nfull) * stride_pt + lane_store;
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        if (16 * nfull + 4 * h + e < P.P2) *(v4i *)(dst + (uint32_t)e * stride_pt) = out[e];
+        if (16 * nfull + 4 * h + e < P2) *(v4i *)(dst + (uint32_t)e * stride_pt) = out[e];
     }
   }
 }

@@ -40,23 +40,36 @@
 namespace rnswino {
 
 
-// What the kernels read, built once with the plan (the pointers and the output mode per call); the block kernel fetches the
-// fields up to `rb_step` together at entry, see K1Params.  With that, divisions by multiplication and the operand shared
+// The kernels' arguments: the block kernel fetches them together at entry, see K1Args.  With that, divisions by multiplication and the operand shared
 // through LDS: 128 channels 5 x 5 at 28 x 28 17.1 -> 14.1 us a layer, 256 channels at 56 x 56 22.1 -> 20.4, VGG16 stack at batch 1
 // 379 -> 362.
-struct K3Params {
+struct K3Params;
+struct K3Args {
+  const K3Params *more;
   const uint32_t *O;
   const int8_t *KA;           // (A^T kron A^T) (P/p_i)^-1 mod p  [n][RB3][KS3][planes][64 lanes][16]
-  int32_t *y;
-  int8_t *act;                // int8 output of modes 1 and 2
+  void *out;                  // int32 y, or the int8 activations of modes 1 and 2
   int units, per_xcd, npairs; // units of 16 pairs (streaming kernel: of 16 tiles of one row), grid x / 8, rows x tiles
-  FastDiv by_Tg, by_tw, by_th, by_ntb;
-  int Tg, tl_shift, T, Q, Tp, tw, th, RB3, rb_step;
-  int n, m, K, Ho, Wo;
+  uint32_t Tg_mul, tw_mul, th_mul;           // FastDiv's, with the shifts below
+  int Tg, T, Tp, tw, th, K, Ho, Wo;
+  uint32_t shifts;            // bytes: of the divisions by Tg, tw, th; log2 of the tiles a channel block holds
+  uint32_t sizes;             // bytes: Q, RB3, rb_step, m
   // fused re-quantisation (chained layers): 0 = store int32 y, 1 = store int8 clamp(y >> shift), 2 = the same after a 2x2
   // stride-2 max-pool
   int epi, shift;
-  // conversion out of the RNS, see KParams
+  RNSW_HD FastDiv by_Tg() const { return {Tg_mul, shifts & 31u}; }
+  RNSW_HD FastDiv by_tw() const { return {tw_mul, shifts >> 8 & 31u}; }
+  RNSW_HD FastDiv by_th() const { return {th_mul, shifts >> 16 & 31u}; }
+  RNSW_HD int tl_shift() const { return (int)(shifts >> 24); }
+  RNSW_HD int Q() const { return (int)byte_of(sizes, 0); }
+  RNSW_HD int RB3() const { return (int)byte_of(sizes, 1); }
+  RNSW_HD int rb_step() const { return (int)byte_of(sizes, 2); }
+  RNSW_HD int m() const { return (int)(sizes >> 24); }
+};
+static_assert(sizeof(K3Args) <= 112, "kernels_common.hpp");
+
+// What they read behind their first loads, built once with the plan: the conversion out of the RNS, see KParams.
+struct K3Params {
   int fastcrt, crt24, quot32, acc0;
   uint32_t crt_sum0, prod_mod32;
   float crt_fs0, inv_m;
@@ -66,6 +79,8 @@ struct K3Params {
   int p[8], bias_p[8];
   double inv_pd[8];
   double pd[8];               // 16-bit moduli: p
+  FastDiv by_ntb;             // streaming kernel
+  int nwaves;                 // streaming kernel: waves of the grid
 };
 
 // Where the output tile of a (k, tile) pair starts in y (or in the int8 activation plane): computed once per pair,
@@ -76,15 +91,15 @@ struct TilePos {
   bool ok;           // false for padding tiles and padding pairs
 };
 
-__device__ __forceinline__ TilePos tile_position(const K3Params &P, int k, int tau) {
+__device__ __forceinline__ TilePos tile_position(const K3Args &P, int k, int tau) {
   TilePos tp;
   tp.ok = tau < P.T;
-  const int trow = (int)fast_div((uint32_t)tau, P.by_tw);
+  const int trow = (int)fast_div((uint32_t)tau, P.by_tw());
   const int tx = tau - trow * P.tw;
-  const int img = (int)fast_div((uint32_t)trow, P.by_th);
+  const int img = (int)fast_div((uint32_t)trow, P.by_th());
   const int ty = trow - img * P.th;
-  tp.oy0 = ty * P.m;
-  tp.ox0 = tx * P.m;
+  tp.oy0 = ty * P.m();
+  tp.ox0 = tx * P.m();
   const uint32_t plane = (uint32_t)img * P.K + k;
   const int half = P.epi == 2 ? 1 : 0;               // pooled planes have half the rows and columns
   tp.origin = (plane * (P.Ho >> half) + (tp.oy0 >> half)) * (P.Wo >> half) + (tp.ox0 >> half);
@@ -92,10 +107,10 @@ __device__ __forceinline__ TilePos tile_position(const K3Params &P, int k, int t
 }
 
 // CRT conversion of the four outputs of one lane (row block rb, lane group g) and their store: int32 y, or, for
-// chained layers, int8 clamp(y >> shift) with an optional 2x2 max-pool (the shift is monotone, so it commutes with
+// chained layers, int8 clamp(y >> P.shift) with an optional 2x2 max-pool (the shift is monotone, so it commutes with
 // the max).  Must be called by all lanes of a wave (the pooled mode exchanges rows between lanes).
 template <int NRES, bool CRT24, bool QUOT32>
-__device__ __forceinline__ void crt_convert(const K3Params &P, const uint32_t (&w)[NRES][4], int (&val)[4]) {
+__device__ __forceinline__ void crt_convert(Constant<K3Params> &P, const uint32_t (&w)[NRES][4], int (&val)[4]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     uint32_t sum = 0;
@@ -134,7 +149,7 @@ struct FastCrt {
   uint32_t sum0;
 };
 template <int NRES>
-__device__ __forceinline__ void crt_convert_fast(const K3Params &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
+__device__ __forceinline__ void crt_convert_fast(Constant<K3Params> &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     uint32_t sum = 0;
@@ -152,7 +167,7 @@ __device__ __forceinline__ void crt_convert_fast(const K3Params &P, const FastCr
 // result in [-(P-1)/2, (P-1)/2] (the host checks its bound against 1/(2P)), so layers at the edge of the dynamic
 // range and plans with an unchecked range take this form.
 template <int NRES>
-__device__ __forceinline__ void crt_convert_fast64(const K3Params &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
+__device__ __forceinline__ void crt_convert_fast64(Constant<K3Params> &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
   uint32_t c0 = P.crt_c[0];
   asm("" : "+s"(c0));       // keeps the first products of the two forms apart: taken in front of the branch, each would be copied behind it
 #pragma unroll
@@ -172,7 +187,7 @@ __device__ __forceinline__ void crt_convert_fast64(const K3Params &P, const Fast
 
 // Constants of the fast conversion in vector registers, loaded once per kernel.
 template <int NRES, bool FAST>
-__device__ __forceinline__ FastCrt fast_crt_constants(const K3Params &P) {
+__device__ __forceinline__ FastCrt fast_crt_constants(Constant<K3Params> &P) {
   FastCrt fc;
   fc.fs0 = FAST ? in_vgpr(P.crt_fs0) : 0.0f;
   fc.sum0 = FAST ? in_vgpr(P.crt_sum0) : 0u;
@@ -182,7 +197,7 @@ __device__ __forceinline__ FastCrt fast_crt_constants(const K3Params &P) {
 }
 
 template <int NRES, bool FAST>
-__device__ __forceinline__ void k3_convert(const K3Params &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
+__device__ __forceinline__ void k3_convert(Constant<K3Params> &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int (&val)[4]) {
   if (FAST) {
     if (P.fastcrt == 2) crt_convert_fast64<NRES>(P, fc, w, val);   // uniform
     else crt_convert_fast<NRES>(P, fc, w, val);
@@ -199,14 +214,14 @@ __device__ __forceinline__ void k3_convert(const K3Params &P, const FastCrt &fc,
 // the stored plane.  Same modes as k3_convert_and_store; the host selects this path for int32 output only when Wo is a multiple
 // of 4.  Must be called by all lanes of a wave.
 template <int EPI>
-__device__ __forceinline__ void k3_store_m8(const K3Params &P, const int (&val)[4], bool inside, bool right, uint32_t at) {
+__device__ __forceinline__ void k3_store_m8(const K3Args &P, const int (&val)[4], bool inside, bool right, uint32_t at) {
   if constexpr (EPI == 0) {
-    if (inside) *(v4i *)(P.y + at) = (v4i){val[0], val[1], val[2], val[3]};
+    if (inside) *(v4i *)((int32_t *)P.out + at) = (v4i){val[0], val[1], val[2], val[3]};
   } else if constexpr (EPI == 1) {
     uint32_t packed = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) packed |= ((uint32_t)min(127, max(-128, val[j] >> P.shift)) & 0xFFu) << (8 * j);
-    int8_t *dst = P.act + at;
+    int8_t *dst = (int8_t *)P.out + at;
     if ((P.Wo & 3) == 0) {
       if (inside) *(uint32_t *)dst = packed;
     } else {
@@ -219,13 +234,12 @@ __device__ __forceinline__ void k3_store_m8(const K3Params &P, const int (&val)[
     const auto rows = __builtin_amdgcn_permlane32_swap((uint32_t)max(val[0], val[1]), (uint32_t)max(val[2], val[3]), false, false);
     const int pooled = min(127, max(-128, max((int)rows[0], (int)rows[1]) >> P.shift));
     const auto pair = __builtin_amdgcn_permlane32_swap((uint32_t)pooled, (uint32_t)pooled, false, false);
-    if (inside) *(uint16_t *)(P.act + at) = (uint16_t)((pair[0] & 0xFFu) | ((pair[1] & 0xFFu) << 8));
+    if (inside) *(uint16_t *)((int8_t *)P.out + at) = (uint16_t)((pair[0] & 0xFFu) | ((pair[1] & 0xFFu) << 8));
   }
 }
 
-__device__ __forceinline__ void k3_store(const K3Params &P, const int (&val)[4], int rb, int g, const TilePos &tp) {
-  const int m = P.m, mm = m * m;
-  const float inv_m = P.inv_m;
+__device__ __forceinline__ void k3_store(const K3Args &P, float inv_m, const int (&val)[4], int rb, int g, const TilePos &tp) {
+  const int m = P.m(), mm = m * m;
   const int o0 = 16 * rb + 4 * g;
   if (P.epi == 1 && (((m & 3) != 0) || (P.Wo & 1))) {
     // any other tile size or an odd row length: the four outputs may sit in two rows of the tile and at any byte
@@ -237,7 +251,7 @@ __device__ __forceinline__ void k3_store(const K3Params &P, const int (&val)[4],
       const int u = (int)(((float)o + 0.5f) * inv_m);
       const int v = o - u * m;
       if (o < mm && tp.oy0 + u < P.Ho && tp.ox0 + v < P.Wo)
-        P.act[(size_t)(tp.origin + (uint32_t)(u * P.Wo + v))] = (int8_t)min(127, max(-128, val[j] >> P.shift));
+        ((int8_t *)P.out)[(size_t)(tp.origin + (uint32_t)(u * P.Wo + v))] = (int8_t)min(127, max(-128, val[j] >> P.shift));
     }
     return;
   }
@@ -250,7 +264,7 @@ __device__ __forceinline__ void k3_store(const K3Params &P, const int (&val)[4],
       uint32_t packed = 0;
 #pragma unroll
       for (int j = 0; j < 4; ++j) packed |= ((uint32_t)min(127, max(-128, val[j] >> P.shift)) & 0xFFu) << (8 * j);
-      int8_t *dst = P.act + tp.origin + (uint32_t)(u * P.Wo + v);
+      int8_t *dst = (int8_t *)P.out + tp.origin + (uint32_t)(u * P.Wo + v);
       if ((P.Wo & 3) == 0) {
         if (inside) *(uint32_t *)dst = packed;
       } else {
@@ -265,13 +279,13 @@ __device__ __forceinline__ void k3_store(const K3Params &P, const int (&val)[4],
       const int o0p = __shfl_xor(h0, delta), o1p = __shfl_xor(h1, delta);
       const int p0 = min(127, max(-128, max(h0, o0p) >> P.shift)), p1 = min(127, max(-128, max(h1, o1p) >> P.shift));
       if (inside && (u & 1) == 0)
-        *(uint16_t *)(P.act + tp.origin + (uint32_t)((u >> 1) * (P.Wo >> 1) + (v >> 1))) =
+        *(uint16_t *)((int8_t *)P.out + tp.origin + (uint32_t)((u >> 1) * (P.Wo >> 1) + (v >> 1))) =
             (uint16_t)(((uint32_t)p0 & 0xFFu) | (((uint32_t)p1 & 0xFFu) << 8));
     }
     return;
   }
   if (!tp.ok || o0 >= mm) return;
-  int32_t *ytile = P.y + tp.origin;
+  int32_t *ytile = (int32_t *)P.out + tp.origin;
   if (((m & 3) == 0) && ((P.Wo & 3) == 0)) {   // four consecutive outputs stay in one row, 16-byte aligned
     const int u = (int)(((float)o0 + 0.5f) * inv_m);
     const int v = o0 - u * m;
@@ -288,11 +302,11 @@ __device__ __forceinline__ void k3_store(const K3Params &P, const int (&val)[4],
 }
 
 template <int NRES, bool FAST>
-__device__ __forceinline__ void k3_convert_and_store(const K3Params &P, const FastCrt &fc, const uint32_t (&w)[NRES][4], int rb, int g,
+__device__ __forceinline__ void k3_convert_and_store(const K3Args &P, Constant<K3Params> &M, const FastCrt &fc, const uint32_t (&w)[NRES][4], int rb, int g,
                                                      const TilePos &tp) {
   int val[4];
-  k3_convert<NRES, FAST>(P, fc, w, val);
-  k3_store(P, val, rb, g, tp);
+  k3_convert<NRES, FAST>(M, fc, w, val);
+  k3_store(P, M.inv_m, val, rb, g, tp);
 }
 
 // Three and more 16-bit moduli: a residue goes into the sum and the binary64 quotient of the conversion as soon as it is there, signed.  Kept
@@ -305,17 +319,16 @@ constexpr bool k3_converts_each(int nres, int ks3) { return nres >= 3 && !(ks3 =
 // Where the products of several residues at once would cost a wave, the residues stay apart (APART): five 16-bit moduli at F(8,3) 25.2 -> 22.2
 // us, at F(14,3) 43.4 -> 40.8; six at F(10,3) 55.8 -> 43.3; elsewhere it loses up to a tenth.
 template <int NRES, int KS3, bool WIDE, bool FAST>
-__global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
+__global__ __launch_bounds__(256) void k3_inverse_crt(K3Args P) {
+  Constant<K3Params> &M = constant(P.more);
   constexpr int PL = WIDE ? 2 : 1;
   constexpr int NACC = WIDE ? 3 : 1;
   constexpr bool AHEAD = NRES * KS3 * PL <= 16;    // the table fragments of a row block fit registers: requested ahead of their use
   constexpr bool FEW = !WIDE && NRES * KS3 <= 8;   // loads of a lane
   constexpr bool EACH = WIDE && k3_converts_each(NRES, KS3), APART = WIDE && ((NRES == 5 && KS3 % 2 == 0) || (NRES == 6 && KS3 == 3));
   __shared__ __attribute__((aligned(16))) uint32_t o_lds[NRES * KS3 * PL * 256];   // [i][s][plane][lane][4 words]
-  asm volatile("" ::"s"(P.O), "s"(P.KA), "s"(P.units), "s"(P.per_xcd), "s"(P.npairs), "s"(P.by_Tg.mul), "s"(P.by_Tg.shift), "s"(P.by_tw.mul),
-               "s"(P.by_tw.shift), "s"(P.by_th.mul), "s"(P.by_th.shift), "s"(P.Tg), "s"(P.tl_shift), "s"(P.T), "s"(P.Q), "s"(P.Tp), "s"(P.tw),
-               "s"(P.th), "s"(P.RB3), "s"(P.rb_step));
-  if constexpr (FEW) asm volatile("" ::"s"(P.m), "s"(P.K), "s"(P.Ho), "s"(P.Wo), "s"(P.epi));
+  asm volatile("" ::"s"(P.O), "s"(P.KA), "s"(P.units), "s"(P.per_xcd), "s"(P.npairs), "s"(P.Tg_mul), "s"(P.tw_mul), "s"(P.th_mul), "s"(P.Tg), "s"(P.T),
+               "s"(P.Tp), "s"(P.tw), "s"(P.th), "s"(P.shifts), "s"(P.sizes), "s"(P.K), "s"(P.Ho), "s"(P.Wo));
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: row block and table addresses stay scalar
   const int lane = threadIdx.x & 63, g = lane >> 4;
   // A unit is 16 consecutive (k, tile) pairs of the flattened K x T index space (no padding tiles: a unit may span
@@ -325,7 +338,7 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
   const int unit = (int)(blockIdx.x & 7) * P.per_xcd + (int)(blockIdx.x >> 3);
   if (unit >= P.units) return;
   const int pair = min(unit * 16 + (lane & 15), P.npairs - 1);         // a padding lane repeats the last pair
-  const int kg = (int)fast_div((uint32_t)pair, P.by_Tg), taug = pair - kg * P.Tg;
+  const int kg = (int)fast_div((uint32_t)pair, P.by_Tg()), taug = pair - kg * P.Tg;
 
   // O is [Kp][n][Q][Tp] words (x PL planes) and smaller than 4 GiB: the address of a word is a wave-uniform row
   // (residue) plus a 32-bit lane offset (k, point group, tile).  Word e of a lane's operand is point group 16s + 4g + e; wave e
@@ -334,14 +347,14 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
   // four).  Point groups >= Q of the last contraction step are clamped to Q - 1: the table is zero there, so whatever is read
   // does not count.
   const uint32_t row_bytes = (uint32_t)P.Tp * (4 * PL);
-  const uint32_t lane_off = (uint32_t)(kg * NRES * P.Q) * row_bytes + (uint32_t)taug * (4 * PL);
+  const uint32_t lane_off = (uint32_t)(kg * NRES * P.Q()) * row_bytes + (uint32_t)taug * (4 * PL);
   uint32_t voff[KS3];
 #pragma unroll
-  for (int s = 0; s < KS3; ++s) voff[s] = lane_off + (uint32_t)min(16 * s + 4 * g + wave, P.Q - 1) * row_bytes;
+  for (int s = 0; s < KS3; ++s) voff[s] = lane_off + (uint32_t)min(16 * s + 4 * g + wave, P.Q() - 1) * row_bytes;
   v2i mine[NRES][KS3];
 #pragma unroll
   for (int i = 0; i < NRES; ++i) {
-    const char *row = (const char *)P.O + (size_t)((uint32_t)(i * P.Q) * row_bytes);
+    const char *row = (const char *)P.O + (size_t)((uint32_t)(i * P.Q()) * row_bytes);
 #pragma unroll
     for (int s = 0; s < KS3; ++s) {
       if (WIDE) mine[i][s] = *(const v2i *)(row + voff[s]);
@@ -352,7 +365,7 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
   v4i ka[AHEAD ? NRES : 1][AHEAD ? KS3 : 1][PL];
   const uint32_t lane16 = (uint32_t)lane * 16u;
   auto table = [&](int i, int r, int s, int pl) -> v4i {
-    return *(const v4i *)(P.KA + (size_t)((((uint32_t)i * P.RB3 + r) * KS3 + s) * PL + pl) * 1024 + lane16);
+    return *(const v4i *)(P.KA + (size_t)((((uint32_t)i * P.RB3() + r) * KS3 + s) * PL + pl) * 1024 + lane16);
   };
   auto load_ka = [&](int r) {
     if constexpr (AHEAD)
@@ -363,10 +376,10 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
 #pragma unroll
           for (int pl = 0; pl < PL; ++pl) ka[i][s][pl] = table(i, r, s, pl);
   };
-  load_ka(min(rb, P.RB3 - 1));
-  const int k = kg >> P.tl_shift;
-  const int tau = unit * 16 + (lane & 15) < P.npairs ? (kg - (k << P.tl_shift)) * P.Tg + taug : P.T;   // tau >= T marks a lane without output
-  const FastCrt fc = fast_crt_constants<NRES, FAST>(P);
+  load_ka(min(rb, P.RB3() - 1));
+  const int k = kg >> P.tl_shift();
+  const int tau = unit * 16 + (lane & 15) < P.npairs ? (kg - (k << P.tl_shift())) * P.Tg + taug : P.T;   // tau >= T marks a lane without output
+  const FastCrt fc = fast_crt_constants<NRES, FAST>(M);
   TilePos tp = tile_position(P, k, tau);
   if constexpr (FEW) {
     // The position here, while the loads are in flight, its arguments fetched at entry.  Left alone, the compiler moves both behind the barrier
@@ -382,7 +395,7 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
 #pragma unroll
       for (int pl = 0; pl < PL; ++pl) o_lds[((i * KS3 + s) * PL + pl) * 256 + lane * 4 + wave] = (uint32_t)mine[i][s][pl];
   __syncthreads();
-  if (rb >= P.RB3) return;
+  if (rb >= P.RB3()) return;
   v4i of[NRES][KS3][PL];
 #pragma unroll
   for (int i = 0; i < NRES; ++i)
@@ -391,14 +404,14 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
 #pragma unroll
       for (int pl = 0; pl < PL; ++pl) of[i][s][pl] = *(const v4i *)(o_lds + ((i * KS3 + s) * PL + pl) * 256 + lane * 4);
 
-  for (; rb < P.RB3; rb += P.rb_step) {
+  for (; rb < P.RB3(); rb += P.rb_step()) {
     uint32_t w[NRES][4], sum[4] = {0, 0, 0, 0};
     double fs[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int i = 0; i < NRES; ++i) {
       v4i acc[NACC];
 #pragma unroll
-      for (int a = 0; a < NACC; ++a) acc[a] = FAST ? (v4i){P.acc0, P.acc0, P.acc0, P.acc0} : (v4i){0, 0, 0, 0};
+      for (int a = 0; a < NACC; ++a) acc[a] = FAST ? (v4i){M.acc0, M.acc0, M.acc0, M.acc0} : (v4i){0, 0, 0, 0};
 #pragma unroll
       for (int s = 0; s < KS3; ++s) {
         v4i ah, al;
@@ -418,28 +431,28 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Params P) {
       for (int j = 0; j < 4; ++j) {
         if constexpr (WIDE) {
           // per accumulator |sum| <= t*t * 2^15: the combination stays below 2^40
-          const double r = mod_near64(acc[0][j], acc[1][j], acc[2][j], P.inv_pd[i], EACH || NRES < 3 ? P.pd[i] : (double)P.p[i]);
+          const double r = mod_near64(acc[0][j], acc[1][j], acc[2][j], M.inv_pd[i], EACH || NRES < 3 ? M.pd[i] : (double)M.p[i]);
           if (EACH) {
-            sum[j] += P.crt_c[i] * (uint32_t)(int)r;
-            fs[j] = __builtin_fma(r, P.inv_pd[i], fs[j]);
+            sum[j] += M.crt_c[i] * (uint32_t)(int)r;
+            fs[j] = __builtin_fma(r, M.inv_pd[i], fs[j]);
           } else {
-            w[i][j] = (uint32_t)((int)r + P.p[i]);
+            w[i][j] = (uint32_t)((int)r + M.p[i]);
           }
         } else {
           // |acc| <= t*t * 126 * 128 <= 2^22 (the fast conversion takes it as it is, start included)
-          w[i][j] = FAST ? (uint32_t)acc[0][j] : mod_near_plus_p(acc[0][j], P.inv_p[i], -P.p[i], P.bias_p[i]);
+          w[i][j] = FAST ? (uint32_t)acc[0][j] : mod_near_plus_p(acc[0][j], M.inv_p[i], -M.p[i], M.bias_p[i]);
         }
       }
       if (APART) __builtin_amdgcn_sched_barrier(0);
     }
-    if (rb + P.rb_step < P.RB3) load_ka(rb + P.rb_step);
+    if (rb + P.rb_step() < P.RB3()) load_ka(rb + P.rb_step());
     if constexpr (EACH) {
       int val[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) val[j] = (int)(sum[j] - P.prod_mod32 * (uint32_t)__double2int_rn(fs[j]));
-      k3_store(P, val, rb, g, tp);
+      for (int j = 0; j < 4; ++j) val[j] = (int)(sum[j] - M.prod_mod32 * (uint32_t)__double2int_rn(fs[j]));
+      k3_store(P, M.inv_m, val, rb, g, tp);
     } else {
-      k3_convert_and_store<NRES, FAST>(P, fc, w, rb, g, tp);
+      k3_convert_and_store<NRES, FAST>(P, M, fc, w, rb, g, tp);
     }
   }
 }
@@ -463,15 +476,17 @@ constexpr int K3_STREAM_BLOCKS = 1024;  // four resident blocks per CU (register
 // M8: 8 x 8 output tiles (four row blocks), the usual case: where a lane's outputs go inside the tile is computed once
 // per kernel instead of once per row block, and the table fragments of a row block sit at immediate LDS offsets.
 template <int NRES, int KS3, bool FAST, bool M8>
-__global__ __launch_bounds__(256) void k3_inverse_crt_stream(K3Params P) {
+__global__ __launch_bounds__(256) void k3_inverse_crt_stream(K3Args P) {
+  Constant<K3Params> &M = constant(P.more);
   extern __shared__ __attribute__((aligned(16))) uint8_t ka_lds[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: unit arithmetic stays scalar
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const int ntb = P.Tp >> 4;
   const int nunits = P.units;                      // (k, block of 16 tiles), the GEMM's rows and columns
-  const int nwaves = gridDim.x * 4;
+  const int nwaves = M.nwaves;
+  const FastDiv by_ntb = {M.by_ntb.mul, M.by_ntb.shift};
   {
-    const int bytes = NRES * P.RB3 * KS3 * 1024;
+    const int bytes = NRES * P.RB3() * KS3 * 1024;
     for (int off = threadIdx.x * 16; off < bytes; off += 256 * 16) *(v4i *)(ka_lds + off) = *(const v4i *)(P.KA + off);
   }
   __syncthreads();
@@ -485,12 +500,12 @@ __global__ __launch_bounds__(256) void k3_inverse_crt_stream(K3Params P) {
 #pragma unroll
   for (int s = 0; s < KS3; ++s)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) voff[s][e] = (uint32_t)min(16 * s + 4 * g + e, P.Q - 1) * row_bytes + (uint32_t)(lane & 15) * 4u;
+    for (int e = 0; e < 4; ++e) voff[s][e] = (uint32_t)min(16 * s + 4 * g + e, P.Q() - 1) * row_bytes + (uint32_t)(lane & 15) * 4u;
 
   auto load_o = [&](int k, int tb, v4i (&of)[NRES][KS3]) {
 #pragma unroll
     for (int i = 0; i < NRES; ++i) {
-      const char *row = (const char *)P.O + (size_t)((uint32_t)((k * NRES + i) * P.Q) * row_bytes + (uint32_t)tb * 64u);
+      const char *row = (const char *)P.O + (size_t)((uint32_t)((k * NRES + i) * P.Q()) * row_bytes + (uint32_t)tb * 64u);
 #pragma unroll
       for (int s = 0; s < KS3; ++s)
 #pragma unroll
@@ -498,13 +513,13 @@ __global__ __launch_bounds__(256) void k3_inverse_crt_stream(K3Params P) {
     }
   };
 
-  const FastCrt fc = fast_crt_constants<NRES, FAST>(P);
-  const int a0 = FAST ? P.acc0 : 0;
+  const FastCrt fc = fast_crt_constants<NRES, FAST>(M);
+  const int a0 = FAST ? M.acc0 : 0;
   const v4i acc_start = (v4i){a0, a0, a0, a0};
   // GEMM row kg = k * TL + slot and columns 16 tb .. + 15 of a unit (TL > 1: packed layers, plan.hpp)
   auto position = [&](int kg, int tb) {
-    const int taug = tb * 16 + (lane & 15), k = kg >> P.tl_shift;
-    return tile_position(P, k, taug < P.Tg ? (kg - (k << P.tl_shift)) * P.Tg + taug : P.T);
+    const int taug = tb * 16 + (lane & 15), k = kg >> P.tl_shift();
+    return tile_position(P, k, taug < P.Tg ? (kg - (k << P.tl_shift())) * P.Tg + taug : P.T);
   };
   if constexpr (M8) {
     // 8 x 8 tiles: outputs 16 rb + 4 g .. + 3 are row u = 2 rb + (g >> 1), columns v = 4 (g & 1) .. + 3 of the tile.  One loop per
@@ -516,7 +531,7 @@ __global__ __launch_bounds__(256) void k3_inverse_crt_stream(K3Params P) {
       // elements between row blocks, and of the lane's first output from the tile's origin
       const uint32_t step = EPI == 2 ? (uint32_t)(P.Wo >> 1) : (uint32_t)(2 * P.Wo), off0 = EPI == 2 ? (uint32_t)(v >> 1) : (uint32_t)(u0 * P.Wo + v);
       for (; unit < nunits; unit += nwaves) {
-        const int kg = (int)fast_div((uint32_t)unit, P.by_ntb), tb = unit - kg * ntb;
+        const int kg = (int)fast_div((uint32_t)unit, by_ntb), tb = unit - kg * ntb;
         v4i o[NRES][KS3];
         load_o(kg, tb, o);
         const TilePos tp = position(kg, tb);
@@ -539,12 +554,12 @@ __global__ __launch_bounds__(256) void k3_inverse_crt_stream(K3Params P) {
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              w[i][j] = FAST ? (uint32_t)acc[j] : mod_near_plus_p(acc[j], P.inv_p[i], -P.p[i], P.bias_p[i]);
+              w[i][j] = FAST ? (uint32_t)acc[j] : mod_near_plus_p(acc[j], M.inv_p[i], -M.p[i], M.bias_p[i]);
           }
           int val[4];
-          if constexpr (FAST && BINARY64) crt_convert_fast64<NRES>(P, fc, w, val);
-          else if constexpr (FAST) crt_convert_fast<NRES>(P, fc, w, val);
-          else k3_convert<NRES, FAST>(P, fc, w, val);
+          if constexpr (FAST && BINARY64) crt_convert_fast64<NRES>(M, fc, w, val);
+          else if constexpr (FAST) crt_convert_fast<NRES>(M, fc, w, val);
+          else k3_convert<NRES, FAST>(M, fc, w, val);
           k3_store_m8<EPI>(P, val, columns && 2 * rb < rows, right, at);
           at += step;
         }
@@ -555,32 +570,32 @@ __global__ __launch_bounds__(256) void k3_inverse_crt_stream(K3Params P) {
       else if (P.epi == 1) units(std::integral_constant<int, 1>(), binary64_tag);
       else units(std::integral_constant<int, 2>(), binary64_tag);
     };
-    if (FAST && P.fastcrt == 2) modes(std::true_type());
+    if (FAST && M.fastcrt == 2) modes(std::true_type());
     else modes(std::false_type());
     return;
   }
   for (; unit < nunits; unit += nwaves) {
-    const int kg = (int)fast_div((uint32_t)unit, P.by_ntb), tb = unit - kg * ntb;
+    const int kg = (int)fast_div((uint32_t)unit, by_ntb), tb = unit - kg * ntb;
     v4i o[NRES][KS3];
     load_o(kg, tb, o);
     const TilePos tp = position(kg, tb);
-    for (int rb = 0; rb < P.RB3; ++rb) {
+    for (int rb = 0; rb < P.RB3(); ++rb) {
       uint32_t w[NRES][4];
 #pragma unroll
       for (int i = 0; i < NRES; ++i) {
         v4i acc = acc_start;
 #pragma unroll
         for (int s = 0; s < KS3; ++s) {
-          const v4i a = *(const v4i *)(ka_lds + (((i * P.RB3 + rb) * KS3) + s) * 1024 + lane * 16);
+          const v4i a = *(const v4i *)(ka_lds + (((i * P.RB3() + rb) * KS3) + s) * 1024 + lane * 16);
           acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, o[i][s], acc, 0, 0, 0);
         }
         // |acc| <= t*t * 126 * 128 <= 2^22: the fast conversion takes it as it is, start included, the general one the
         // residue shifted by +p so that it is non-negative
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          w[i][j] = FAST ? (uint32_t)acc[j] : mod_near_plus_p(acc[j], P.inv_p[i], -P.p[i], P.bias_p[i]);
+          w[i][j] = FAST ? (uint32_t)acc[j] : mod_near_plus_p(acc[j], M.inv_p[i], -M.p[i], M.bias_p[i]);
       }
-      k3_convert_and_store<NRES, FAST>(P, fc, w, rb, g, tp);
+      k3_convert_and_store<NRES, FAST>(P, M, fc, w, rb, g, tp);
     }
   }
 }

@@ -21,19 +21,27 @@
 
 namespace rnswino {
 
-// What the GEMM kernels read, built once with the plan (the pointers per call); the fields up to `slabs` are fetched
-// together at entry, see K1Params.
-struct K2Params {
+// The GEMM kernels' arguments, fetched together at entry, see K1Args.
+struct K2Args {
+  const ResidueParams *more;
   const int8_t *U, *V;
   uint32_t *O;
   int xgroup, gy, gz;         // grid order: values of x per group, row blocks, tile blocks
-  FastDiv by_xgroup, by_gy, by_gz, by_Q;
+  uint32_t xgroup_mul, gy_mul, gz_mul, Q_mul;          // FastDiv's, with the shifts below
   int nkb, ntb, ncb;          // row and tile blocks of 16, channel blocks of 64
-  int xs, Q, P2, slabs;       // n * Q, point groups, points, n * P2
-  int Kp, Tp, v_tile, v_slice;  // bytes between tiles and between 16-channel slices inside a fragment of V
-  Residue8 res[8];
-  double inv_pd[8];           // 16-bit moduli
+  int xs, slabs;              // n * Q, n * P2
+  int P2;                     // points
+  uint32_t shifts;            // bytes: of the divisions by xgroup, gy, gz, Q
+  uint32_t sizes;             // bytes: Q (point groups), 1 if fragments of V are in lane order (layout.hpp)
+  RNSW_HD FastDiv by_xgroup() const { return {xgroup_mul, shifts & 31u}; }
+  RNSW_HD FastDiv by_gy() const { return {gy_mul, shifts >> 8 & 31u}; }
+  RNSW_HD FastDiv by_gz() const { return {gz_mul, shifts >> 16 & 31u}; }
+  RNSW_HD FastDiv by_Q() const { return {Q_mul, shifts >> 24 & 31u}; }
+  RNSW_HD int Q() const { return (int)byte_of(sizes, 0); }
+  // byte of tile l % 16 and slice l / 16 in a fragment of V
+  RNSW_HD int v_offset(int lane) const { return sizes >> 8 ? lane * 16 : (lane & 15) * 64 + (lane >> 4) * 16; }
 };
+static_assert(sizeof(K2Args) <= 112, "kernels_common.hpp");
 
 // Work item (x = residue and point group, y = row block, z = tile block) from the linear workgroup id.  Workgroups
 // are handed to the 8 XCDs round-robin by id, so x = 8 * (...) + id % 8 keeps one x on one XCD.  Within an XCD the
@@ -41,23 +49,23 @@ struct K2Params {
 // of U (same x and y, along z) or of V (same x and z, along y) follow each other closely enough to find it in the
 // XCD's L2, while `xgroup` different x at a time spread the accesses over the L2's channels.
 struct K2Item { int x, i, q, y, z; };
-__device__ __forceinline__ K2Item k2_item(const K2Params &P, uint32_t id) {
+__device__ __forceinline__ K2Item k2_item(const K2Args &P, uint32_t id) {
   K2Item w;
-  const uint32_t r0 = id >> 3, r1 = fast_div(r0, P.by_xgroup), r2 = fast_div(r1, P.by_gy), r3 = fast_div(r2, P.by_gz);
+  const uint32_t r0 = id >> 3, r1 = fast_div(r0, P.by_xgroup()), r2 = fast_div(r1, P.by_gy()), r3 = fast_div(r2, P.by_gz());
   w.y = (int)(r1 - r2 * (uint32_t)P.gy);
   w.z = (int)(r2 - r3 * (uint32_t)P.gz);
   w.x = (int)((r3 * (uint32_t)P.xgroup + (r0 - r1 * (uint32_t)P.xgroup)) * 8 + (id & 7));
-  w.i = (int)fast_div((uint32_t)w.x, P.by_Q);
-  w.q = w.x - w.i * P.Q;
+  w.i = (int)fast_div((uint32_t)w.x, P.by_Q());
+  w.q = w.x - w.i * P.Q();
   return w;
 }
 #define RNSW_K2_FETCH_ARGUMENTS(P)                                                                                                       \
-  asm volatile("" ::"s"(P.U), "s"(P.V), "s"(P.O), "s"(P.xgroup), "s"(P.gy), "s"(P.gz), "s"(P.by_xgroup.mul), "s"(P.by_xgroup.shift),     \
-               "s"(P.by_gy.mul), "s"(P.by_gy.shift), "s"(P.by_gz.mul), "s"(P.by_gz.shift), "s"(P.by_Q.mul), "s"(P.by_Q.shift), "s"(P.nkb), \
-               "s"(P.ntb), "s"(P.ncb), "s"(P.xs), "s"(P.Q), "s"(P.P2), "s"(P.slabs), "s"(P.Kp), "s"(P.Tp), "s"(P.v_tile), "s"(P.v_slice))
+  asm volatile("" ::"s"(P.U), "s"(P.V), "s"(P.O), "s"(P.xgroup), "s"(P.gy), "s"(P.gz), "s"(P.xgroup_mul), "s"(P.gy_mul), "s"(P.gz_mul),  \
+               "s"(P.Q_mul), "s"(P.nkb), "s"(P.ntb), "s"(P.ncb), "s"(P.xs), "s"(P.slabs), "s"(P.P2), "s"(P.shifts), "s"(P.sizes))
 
 template <int KS, int NTB, int RM, bool WIDE>
-__global__ __launch_bounds__(256) void k2_residue_gemm(K2Params P) {
+__global__ __launch_bounds__(256) void k2_residue_gemm(K2Args P) {
+  Constant<ResidueParams> &R = constant(P.more);
   constexpr int PL = WIDE ? 2 : 1;
   constexpr int NACC = WIDE ? 3 : 1;
   constexpr int COLS = 16 * NTB;
@@ -89,7 +97,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(K2Params P) {
       Ur[rm] = P.U + ((size_t)slab * nkb + min(kb0 + rm, nkb - 1)) * ncb * (1024 * PL) + lane * 16;
 #pragma unroll
     for (int tb = 0; tb < NTB; ++tb)
-      Vt[tb] = P.V + ((size_t)min(tb0 + tb, ntb - 1) * P.slabs + slab) * ncb * (1024 * PL) + (lane & 15) * P.v_tile + (lane >> 4) * P.v_slice;
+      Vt[tb] = P.V + ((size_t)min(tb0 + tb, ntb - 1) * P.slabs + slab) * ncb * (1024 * PL) + P.v_offset(lane);
 
     // KS contraction steps from s0 on; the very first step starts the accumulators (no zero fill)
     auto steps = [&](int s0, auto first_tag) {
@@ -109,7 +117,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(K2Params P) {
       // every load of the step is issued before its first product (left alone, the scheduler sinks the loads
       // between the products to save registers, and the wave then waits for them one at a time)
       __builtin_amdgcn_sched_barrier(0);
-      const int a0 = FIRST && biased ? P.res[i].acc_bias : 0;
+      const int a0 = FIRST && biased ? R.res[i].acc_bias : 0;
       const v4i acc0 = (v4i){a0, a0, a0, a0};
 #pragma unroll
       for (int s = 0; s < KS; ++s)
@@ -136,7 +144,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(K2Params P) {
 #pragma unroll
           for (int tb = 0; tb < NTB; ++tb)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[0][rm][tb][j] = mod_near(acc[0][rm][tb][j], P.res[i].inv, -P.res[i].neg_p);
+            for (int j = 0; j < 4; ++j) acc[0][rm][tb][j] = mod_near(acc[0][rm][tb][j], R.res[i].inv, -R.res[i].neg_p);
       }
     };
     steps(0, std::true_type{});
@@ -157,7 +165,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(K2Params P) {
   uint32_t lane_byte = (uint32_t)((4 * (lane >> 4)) * PITCH + (lane & 15) * PL) * 4 + wave;
   asm volatile("" : "+v"(lane_byte));
   uint8_t *tile8 = (uint8_t *)tile + lane_byte;
-  const Residue8 rc = P.res[i];
+  const Residue8 rc = residue(R.res[i]);
   const int p = -rc.neg_p;
   const float inv = in_vgpr(rc.inv), qb = in_vgpr(rc.quot_bias);
   auto exchange = [&](auto biased_tag) {
@@ -170,7 +178,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(K2Params P) {
         for (int j = 0; j < 4; ++j) {
           const int at = ((rm * 16 + j) * PITCH + tb * 16 * PL) * 4;   // row rm*16 + 4*(lane>>4) + j, column tb*16 + lane%16
           if constexpr (WIDE) {
-            const int v = storable16((int)mod_near64(acc[0][rm][tb][j], acc[1][rm][tb][j], acc[NACC - 1][rm][tb][j], P.inv_pd[i], (double)p), p);
+            const int v = storable16((int)mod_near64(acc[0][rm][tb][j], acc[1][rm][tb][j], acc[NACC - 1][rm][tb][j], R.inv_pd[i], (double)p), p);
             const int lo = (int)(int8_t)(v & 0xFF), hi = (v - lo) >> 8;
             tile8[at] = (uint8_t)hi;
             tile8[at + (PL - 1) * 4] = (uint8_t)lo;
@@ -187,11 +195,12 @@ __global__ __launch_bounds__(256) void k2_residue_gemm(K2Params P) {
   // beyond Tp are left out.
   constexpr int VPR = ROWW / 4;           // 16-byte vectors per tile row
   constexpr int RP = 256 / VPR;           // rows per pass of the block
-  const uint32_t krow = (uint32_t)(P.xs * P.Tp) * PL;
+  const int Tp = P.ntb * 16;
+  const uint32_t krow = (uint32_t)(P.xs * Tp) * PL;
   const int r0 = threadIdx.x / VPR, c4 = threadIdx.x % VPR;
-  const int valid_rows = min(ROWS, P.Kp - kb0 * 16);
-  const bool vec_ok = tb0 * 16 * PL + 4 * c4 < P.Tp * PL;
-  uint32_t off = (uint32_t)(kb0 * 16 + r0) * krow + (uint32_t)((i * P.Q + q) * P.Tp + tb0 * 16) * PL + 4 * c4;
+  const int valid_rows = min(ROWS, P.nkb * 16 - kb0 * 16);
+  const bool vec_ok = tb0 * 16 * PL + 4 * c4 < Tp * PL;
+  uint32_t off = (uint32_t)(kb0 * 16 + r0) * krow + (uint32_t)((i * P.Q() + q) * Tp + tb0 * 16) * PL + 4 * c4;
 #pragma unroll
   for (int ps = 0; ps < (ROWS + RP - 1) / RP; ++ps) {
     const int row = ps * RP + r0;

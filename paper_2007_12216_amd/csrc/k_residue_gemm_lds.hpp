@@ -40,7 +40,8 @@ __device__ __forceinline__ void load_to_lds16(const void *base, uint32_t lane_of
 }
 
 template <int WM, int WN, int RM, int NT, int S>
-__global__ __launch_bounds__(256) void k2_residue_gemm_lds(K2Params P) {
+__global__ __launch_bounds__(256) void k2_residue_gemm_lds(K2Args P) {
+  Constant<ResidueParams> &R = constant(P.more);
   static_assert(WM * WN == 4, "four waves per workgroup");
   constexpr int BRF = WM * RM, BTF = WN * NT;     // U and V fragments per step
   constexpr int NF = BRF + BTF;
@@ -56,7 +57,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm_lds(K2Params P) {
   if (item.x >= P.xs) return;                     // x is padded to a multiple of 8 (block-uniform: no barrier is skipped by part of a block)
   const int i = item.i, q = item.q;
   const int kb0 = item.y * BRF, tb0 = item.z * BTF;
-  const Residue8 rc = P.res[i];
+  const Residue8 rc = residue(R.res[i]);
   const int p = -rc.neg_p;
   const float inv = rc.inv;
   const int npts = min(4, P.P2 - 4 * q);          // points of this group that exist (t*t need not be a multiple of 4)
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm_lds(K2Params P) {
     } else {
       base[j] = P.V + (size_t)min(tb0 + f - BRF, ntb - 1) * P.slabs * ncb * 1024;
       slab_stride[j] = (uint32_t)ncb * 1024u;
-      lane_off[j] = (uint32_t)((lane & 15) * P.v_tile + (lane >> 4) * P.v_slice);
+      lane_off[j] = (uint32_t)P.v_offset(lane);
     }
   }
   const uint32_t stage_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t *)stage;
@@ -166,7 +167,8 @@ __global__ __launch_bounds__(256) void k2_residue_gemm_lds(K2Params P) {
   }
   // O is [Kp][n][Q][Tp] words and smaller than 4 GiB.  A lane holds rows 16 (kb) + 4 (lane / 16) + j and tile
   // 16 (tb) + lane % 16: sixteen lanes write 64 consecutive bytes of a row.
-  const uint32_t krow = (uint32_t)(P.xs * P.Tp);
+  const int Tp = P.ntb * 16;
+  const uint32_t krow = (uint32_t)(P.xs * Tp);
 #pragma unroll
   for (int rm = 0; rm < RM; ++rm) {
     const int kb = kb0 + wm * RM + rm;
@@ -175,7 +177,7 @@ __global__ __launch_bounds__(256) void k2_residue_gemm_lds(K2Params P) {
     for (int nt = 0; nt < NT; ++nt) {
       const int tb = tb0 + wn * NT + nt;
       if (tb >= ntb) break;
-      const uint32_t off = (uint32_t)(kb * 16 + 4 * (lane >> 4)) * krow + (uint32_t)((i * P.Q + q) * P.Tp + tb * 16 + (lane & 15));
+      const uint32_t off = (uint32_t)(kb * 16 + 4 * (lane >> 4)) * krow + (uint32_t)((i * P.Q() + q) * Tp + tb * 16 + (lane & 15));
 #pragma unroll
       for (int j = 0; j < 4; ++j) P.O[off + j * krow] = packed[rm][nt][j];
     }

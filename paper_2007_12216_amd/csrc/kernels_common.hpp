@@ -16,7 +16,30 @@ struct Residue8 {
   int neg_p, acc_bias;
 };
 
-// Everything a kernel needs to know about the layer, passed by value.
+// A launch carries a kernel's addresses and what it reads in front of its first loads, at most 112 bytes; the rest lies in device memory, written once
+// with the plan, and is fetched while those loads are in flight.  All of it by value (300 to 500 bytes) is copied anew for every launch: in a
+// row of launches that takes the host 3.5 to 3.9 us each from 120 bytes on, 2.8 up to 112: 16 channels
+// at 16 x 16, whose three launches are more for the host than for the GPU, 12.4 -> 10.5 us a layer; the layers that the GPU bounds +-0.5 %.
+// (All of it in device memory puts a fetch in front of the first loads: 256 channels at 56 x 56 19.75 -> 20.45 us a layer, 19.9 with the pointer to it in
+// scalar registers when a wave starts.)
+// Read through this address space the fields come by scalar loads wherever they are used.
+template <typename T>
+using Constant = const T __attribute__((address_space(4)));
+template <typename T>
+__device__ __forceinline__ Constant<T> &constant(const T *p) { return *(Constant<T> *)p; }
+__device__ __forceinline__ Residue8 residue(Constant<Residue8> &r) { return {r.inv, r.quot_bias, r.neg_p, r.acc_bias}; }
+
+// Small fields of a kernel's arguments share words: byte e of one, a scalar instruction each.
+RNSW_HD uint32_t byte_of(uint32_t word, int e) { return (word >> (8 * e)) & 255u; }
+inline uint32_t pack_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d) { return a | b << 8 | c << 16 | d << 24; }
+
+// What the input transform and the GEMM read behind their first loads.
+struct ResidueParams {
+  alignas(16) Residue8 res[8];
+  double inv_pd[8];           // 16-bit moduli
+};
+
+// Everything the filter transform needs to know about the layer, passed by value, and what the other kernels' parameters are made of.
 struct KParams {
   int N, C, K, H, W, r, m, t, pad;
   int Ho, Wo, th, tw, T, n;

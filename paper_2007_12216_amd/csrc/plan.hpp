@@ -48,6 +48,7 @@ int validate_desc(const rnswino_desc_t &d, Dims &dims);            // fills dims
 
 struct rnswino_plan_s;
 namespace rnswino {
+constexpr size_t PARAMS_BYTES = 1024;
 // Fills the CRT constants of the plan and lays out every table the kernels read into one host blob
 // (offsets are stored in the plan).  Host only.
 void build_tables(rnswino_plan_s &plan, std::vector<char> &blob);
@@ -70,5 +71,6 @@ struct rnswino_plan_s {
   size_t d_tables_bytes;
   // offsets (bytes) into d_tables
   size_t off_KG, off_KB, off_KA;            // int8 Kronecker tables of the filter / input / inverse transform
-  void *kparams;                            // the kernels' parameter blocks, built once with the plan
+  size_t off_params;                        // what the kernels read beside them (PARAMS_BYTES)
+  void *kparams;                            // the kernels' arguments, built once with the plan
 };

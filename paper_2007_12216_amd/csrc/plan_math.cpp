@@ -293,7 +293,8 @@ void build_tables(rnswino_plan_s &pl, std::vector<char> &blob) {
   pl.off_KG = 0;
   pl.off_KB = align256(pl.off_KG + szKG);
   pl.off_KA = align256(pl.off_KB + szKB);
-  pl.d_tables_bytes = align256(pl.off_KA + szKA);
+  pl.off_params = align256(pl.off_KA + szKA);
+  pl.d_tables_bytes = pl.off_params + PARAMS_BYTES;
   blob.assign(pl.d_tables_bytes, 0);
 
   for (int i = 0; i < d.n; ++i) {

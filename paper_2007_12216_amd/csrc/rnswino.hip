@@ -144,12 +144,17 @@ KParams make_params(const rnswino_plan_t *pl) {
   return P;
 }
 
-// ---- the kernels' own parameter blocks (pointers are filled in per call) ----
+// ---- the kernels' arguments (what changes from call to call is filled in there) and what they read from device memory ----
+struct DeviceParams {
+  ResidueParams residues;
+  K3Params k3;
+};
+static_assert(sizeof(DeviceParams) <= PARAMS_BYTES, "build_tables() leaves them that much");
 struct LayerParams {
   KParams k;
-  K1Params k1;
-  K2Params k2;
-  K3Params k3[3];             // per output mode
+  K1Args k1;
+  K2Args k2;
+  K3Args k3[3];               // per output mode
 };
 
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -216,25 +221,40 @@ K1Choice choose_k1(const Dims &d, int n_cus) {
   return c;
 }
 
-K1Params make_k1(const Dims &d, const KParams &P, int n_cus) {
-  const K1Choice c = choose_k1(d, n_cus);
-  K1Params q;
+// the device block: residues' constants, and what the inverse transform converts with (the same in every output mode)
+ResidueParams make_residues(const Dims &d, const KParams &P) {
+  ResidueParams q;
   std::memset(&q, 0, sizeof(q));
-  q.KB = P.KB;
-  q.units = (int)c.units;
-  q.per_xcd = (int)(c.gx / 8);
-  q.ncb = d.Cp / 64;
-  q.split = c.gy > 1 ? (int)c.gz : 0;
-  q.by_ncb = make_fast_div((uint32_t)q.ncb); q.by_tw = make_fast_div((uint32_t)d.tw); q.by_th = make_fast_div((uint32_t)d.th);
-  q.C = d.C; q.H = d.H; q.W = d.W; q.HW = d.H * d.W; q.m = d.m; q.pad = d.pad; q.t = d.t; q.tw = d.tw; q.th = d.th;
-  q.n = d.n; q.T = d.T; q.Tg = d.Tg; q.Cq = d.Cq;
-  while ((1 << q.cq_shift) < d.Cq) ++q.cq_shift;
-  q.total = (long long)d.N * d.C * d.H * d.W;
-  q.CB1 = d.CB1; q.P2 = d.P2; q.RP1 = d.RP1;
   for (int i = 0; i < d.n; ++i) {
     q.res[i] = {P.inv_p[i], P.quot_bias[i], -P.p[i], P.acc_bias[i]};
     q.inv_pd[i] = P.inv_pd[i];
   }
+  return q;
+}
+
+// the multiplier of a division into an argument of its own; returns the shift
+inline uint32_t store_div(uint32_t d, uint32_t &mul) {
+  const FastDiv f = make_fast_div(d);
+  mul = f.mul;
+  return f.shift;
+}
+
+K1Args make_k1(const Dims &d, const KParams &P, const DeviceParams *dev, int n_cus) {
+  const K1Choice c = choose_k1(d, n_cus);
+  K1Args q;
+  std::memset(&q, 0, sizeof(q));
+  q.more = dev ? &dev->residues : nullptr;
+  q.KB = P.KB;
+  q.units = (int)c.units;
+  q.per_xcd = (int)(c.gx / 8);
+  q.ncb = d.Cp / 64;
+  uint32_t cq_shift = 0;
+  while ((1 << cq_shift) < d.Cq) ++cq_shift;
+  const uint32_t s_ncb = store_div((uint32_t)q.ncb, q.ncb_mul), s_tw = store_div((uint32_t)d.tw, q.tw_mul), s_th = store_div((uint32_t)d.th, q.th_mul);
+  q.shifts = pack_bytes(s_ncb, s_tw, s_th, cq_shift);
+  q.sizes = pack_bytes((uint32_t)d.m, (uint32_t)d.t, (uint32_t)d.n, c.gy > 1 ? c.gz : 0);
+  q.C = d.C; q.H = d.H; q.W = d.W; q.pad = d.pad; q.tw = d.tw; q.th = d.th; q.T = d.T; q.Tg = d.Tg;
+  q.total = (long long)d.N * d.C * d.H * d.W;
   return q;
 }
 
@@ -306,21 +326,18 @@ K2Choice choose_k2(const Dims &d, uint32_t flags) {
   return c;
 }
 
-K2Params make_k2(const Dims &d, const KParams &P, uint32_t flags) {
+K2Args make_k2(const Dims &d, const DeviceParams *dev, uint32_t flags) {
   const K2Choice c = choose_k2(d, flags);
   const int brf = c.lds ? c.WM * c.RM : c.RM, btf = c.lds ? c.WN * c.NTB : c.NTB;
-  K2Params q;
+  K2Args q;
   std::memset(&q, 0, sizeof(q));
+  q.more = dev ? &dev->residues : nullptr;
   q.nkb = d.Kp / 16; q.ntb = d.Tp / 16; q.ncb = d.Cp / 64;
   q.xgroup = c.xgroup; q.gy = (q.nkb + brf - 1) / brf; q.gz = (q.ntb + btf - 1) / btf;
-  q.by_xgroup = make_fast_div((uint32_t)c.xgroup); q.by_gy = make_fast_div((uint32_t)q.gy); q.by_gz = make_fast_div((uint32_t)q.gz);
-  q.by_Q = make_fast_div((uint32_t)d.Q);
-  q.xs = d.n * d.Q; q.Q = d.Q; q.P2 = d.P2; q.slabs = d.n * d.P2; q.Kp = d.Kp; q.Tp = d.Tp;
-  q.v_tile = d.vlane ? 16 : 64; q.v_slice = d.vlane ? 256 : 16;
-  for (int i = 0; i < d.n; ++i) {
-    q.res[i] = {P.inv_p[i], P.quot_bias[i], -P.p[i], P.acc_bias[i]};
-    q.inv_pd[i] = P.inv_pd[i];
-  }
+  const uint32_t s_x = store_div((uint32_t)c.xgroup, q.xgroup_mul), s_y = store_div((uint32_t)q.gy, q.gy_mul), s_z = store_div((uint32_t)q.gz, q.gz_mul);
+  q.shifts = pack_bytes(s_x, s_y, s_z, store_div((uint32_t)d.Q, q.Q_mul));
+  q.sizes = pack_bytes((uint32_t)d.Q, d.vlane ? 1 : 0, 0, 0);
+  q.xs = d.n * d.Q; q.P2 = d.P2; q.slabs = d.n * d.P2;
   return q;
 }
 
@@ -359,21 +376,31 @@ K3Choice choose_k3(const Dims &d, const KParams &P, int n_cus, int epi) {
   return c;
 }
 
-K3Params make_k3(const Dims &d, const KParams &P, int n_cus, int epi) {
+K3Args make_k3(const Dims &d, const KParams &P, const DeviceParams *dev, int n_cus, int epi) {
   const K3Choice c = choose_k3(d, P, n_cus, epi);
-  K3Params q;
+  K3Args q;
   std::memset(&q, 0, sizeof(q));
+  q.more = dev ? &dev->k3 : nullptr;
   q.KA = P.KA;
   q.npairs = d.Kg * d.Tg;                          // below 2^31 (checked when the plan is made)
   q.units = c.stream ? d.Kg * (d.Tp / 16) : (q.npairs + 15) / 16;
   q.per_xcd = (int)(c.gx / 8);
-  q.by_Tg = make_fast_div((uint32_t)d.Tg); q.by_tw = make_fast_div((uint32_t)d.tw); q.by_th = make_fast_div((uint32_t)d.th);
-  q.by_ntb = make_fast_div((uint32_t)(d.Tp / 16));
-  q.Tg = d.Tg; q.T = d.T; q.Q = d.Q; q.Tp = d.Tp; q.tw = d.tw; q.th = d.th; q.RB3 = d.RB3; q.rb_step = 4 * (int)c.gy;
-  while ((1 << q.tl_shift) < d.TL) ++q.tl_shift;
-  q.n = d.n; q.m = d.m; q.K = d.K; q.Ho = d.Ho; q.Wo = d.Wo; q.epi = epi;
+  uint32_t tl_shift = 0;
+  while ((1 << tl_shift) < d.TL) ++tl_shift;
+  const uint32_t s_Tg = store_div((uint32_t)d.Tg, q.Tg_mul), s_tw = store_div((uint32_t)d.tw, q.tw_mul), s_th = store_div((uint32_t)d.th, q.th_mul);
+  q.shifts = pack_bytes(s_Tg, s_tw, s_th, tl_shift);
+  q.sizes = pack_bytes((uint32_t)d.Q, (uint32_t)d.RB3, 4 * c.gy, (uint32_t)d.m);
+  q.Tg = d.Tg; q.T = d.T; q.Tp = d.Tp; q.tw = d.tw; q.th = d.th; q.K = d.K; q.Ho = d.Ho; q.Wo = d.Wo; q.epi = epi;
+  return q;
+}
+
+K3Params make_conversion(const Dims &d, const KParams &P, int n_cus) {
+  K3Params q;
+  std::memset(&q, 0, sizeof(q));
   q.fastcrt = P.fastcrt; q.crt24 = P.crt24; q.quot32 = P.quot32; q.acc0 = P.acc0; q.crt_sum0 = P.crt_sum0; q.prod_mod32 = P.prod_mod32;
   q.crt_fs0 = P.crt_fs0; q.crt_fs0d = P.crt_fs0d; q.inv_m = 1.0f / (float)d.m;
+  q.by_ntb = make_fast_div((uint32_t)(d.Tp / 16));
+  q.nwaves = 4 * (int)choose_k3(d, P, n_cus, 0).gx;    // (of a streaming grid: the same in every output mode)
   for (int i = 0; i < d.n; ++i) {
     q.crt_c[i] = P.crt_c[i]; q.inv_p[i] = P.inv_p[i]; q.p[i] = P.p[i]; q.bias_p[i] = P.bias_p[i]; q.inv_pd[i] = P.inv_pd[i]; q.pd[i] = (double)P.p[i];
   }
@@ -410,10 +437,10 @@ K3Params make_k3(const Dims &d, const KParams &P, int n_cus, int epi) {
   X(4, 1, false, false) X(4, 2, false, false)
 
 // ---- K1 ----  (dry: only report whether the instantiation exists)
-bool launch_k1(const Dims &d, int n_cus, const K1Params &P1, const int8_t *x, int8_t *V, hipStream_t st, Timing tm, bool dry = false) {
+bool launch_k1(const Dims &d, int n_cus, const K1Args &L, const int8_t *x, int8_t *V, hipStream_t st, Timing tm, bool dry = false) {
   const K1Choice c = choose_k1(d, n_cus);
   const dim3 grid(c.gx, c.gy, c.gz);
-  K1Params P = P1;
+  K1Args P = L;
   P.x = x; P.V = V;
 #define RNSW_X(ks, pk) \
   if (c.tiles && c.KS1 == ks && c.pack == pk) { if (!dry) launch(k1_input_transform_tiles<ks, pk>, grid, 0, st, tm, P); return true; }
@@ -427,10 +454,10 @@ bool launch_k1(const Dims &d, int n_cus, const K1Params &P1, const int8_t *x, in
 }
 
 // ---- K2 ----
-bool launch_k2(const Dims &d, uint32_t flags, const K2Params &P2, const int8_t *U, const int8_t *V, uint32_t *O, hipStream_t st, Timing tm, bool dry = false) {
+bool launch_k2(const Dims &d, uint32_t flags, const K2Args &L, const int8_t *U, const int8_t *V, uint32_t *O, hipStream_t st, Timing tm, bool dry = false) {
   const K2Choice c = choose_k2(d, flags);
   const dim3 grid(c.blocks);
-  K2Params P = P2;
+  K2Args P = L;
   P.U = U; P.V = V; P.O = O;
   if (c.lds) {
 #define RNSW_X(wm_, wn_, rm, ntb, s_) \
@@ -448,12 +475,12 @@ bool launch_k2(const Dims &d, uint32_t flags, const K2Params &P2, const int8_t *
 }
 
 // ---- K3 ----
-bool launch_k3(const Dims &d, const LayerParams &L, int n_cus, int epi, int shift, const uint32_t *O, int32_t *y, int8_t *act, hipStream_t st,
+bool launch_k3(const Dims &d, const LayerParams &L, int n_cus, int epi, int shift, const uint32_t *O, void *out, hipStream_t st,
                Timing tm, bool dry = false) {
   const K3Choice c = choose_k3(d, L.k, n_cus, epi);
   const dim3 grid(c.gx, c.gy);
-  K3Params P = L.k3[epi];
-  P.O = O; P.y = y; P.act = act; P.shift = shift;
+  K3Args P = L.k3[epi];
+  P.O = O; P.out = out; P.shift = shift;
   if (c.stream) {
 #define RNSW_X(nres, ks3, fs, e8) \
     if (c.NRES == nres && c.KS3 == ks3 && c.fast == fs && c.m8 == e8) { \
@@ -517,7 +544,7 @@ int conv2d_impl(const rnswino_plan_t *plan, const int8_t *x_dev, const void *U_d
   }
   // (rnswino_plan() has checked that all three instantiations exist)
   if (!launch_k1(d, plan->n_cus, L.k1, x_dev, Vp, st, t1) || !launch_k2(d, plan->desc.flags, L.k2, (const int8_t *)U_dev, Vp, Op, st, t2) ||
-      !launch_k3(d, L, plan->n_cus, epi, shift, Op, y_dev, act_dev, st, t3))
+      !launch_k3(d, L, plan->n_cus, epi, shift, Op, epi == 0 ? (void *)y_dev : (void *)act_dev, st, t3))
     return RNSWINO_E_UNSUPPORTED;
   return launch_status();
 }
@@ -563,34 +590,41 @@ int rnswino_plan(rnswino_plan_t **out, const rnswino_desc_t *desc) {
 
   std::vector<char> &blob = pl->h_tables;
   build_tables(*pl, blob);
-  if (!(desc->flags & RNSWINO_FLAG_HOST_ONLY)) {
+  // (the new plan owns what follows, and its destruction gives it back)
+  auto fail = [&](int code) { (void)hipGetLastError(); (void)rnswino_plan_destroy(pl); return code; };
+  const bool on_device = !(desc->flags & RNSWINO_FLAG_HOST_ONLY);
+  if (on_device) {
     int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); delete pl; return RNSWINO_E_NO_DEVICE; }
-    if (hipMalloc(&pl->d_tables, pl->d_tables_bytes) != hipSuccess) { (void)hipGetLastError(); delete pl; return RNSWINO_E_HIP; }
-    if (hipMemcpy(pl->d_tables, blob.data(), pl->d_tables_bytes, hipMemcpyHostToDevice) != hipSuccess) {
-      (void)hipGetLastError(); (void)hipFree(pl->d_tables); delete pl; return RNSWINO_E_HIP;
-    }
+    if (hipGetDevice(&dev) != hipSuccess) return fail(RNSWINO_E_NO_DEVICE);
+    if (hipMalloc(&pl->d_tables, pl->d_tables_bytes) != hipSuccess) { pl->d_tables = nullptr; return fail(RNSWINO_E_HIP); }
     pl->device = dev;
     rc = resolve_scratch(dev);
-    if (rc != RNSWINO_OK) { (void)hipFree(pl->d_tables); delete pl; return rc; }
-    {
-      int cus = 0;
-      if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) pl->n_cus = cus;
-      else (void)hipGetLastError();
-    }
+    if (rc != RNSWINO_OK) return fail(rc);
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) pl->n_cus = cus;
+    else (void)hipGetLastError();
   }
   LayerParams *params = new (std::nothrow) LayerParams;
   pl->kparams = params;
-  if (!params) { (void)rnswino_plan_destroy(pl); return RNSWINO_E_INVALID; }
+  if (!params) return fail(RNSWINO_E_INVALID);
   params->k = make_params(pl);
-  params->k1 = make_k1(d, params->k, pl->n_cus);
-  params->k2 = make_k2(d, params->k, pl->desc.flags);
-  for (int epi = 0; epi < 3; ++epi) params->k3[epi] = make_k3(d, params->k, pl->n_cus, epi);
+  const DeviceParams *dev_params = on_device ? (const DeviceParams *)((char *)pl->d_tables + pl->off_params) : nullptr;   // (host-only plans are never executed)
+  params->k1 = make_k1(d, params->k, dev_params, pl->n_cus);
+  params->k2 = make_k2(d, dev_params, pl->desc.flags);
+  for (int epi = 0; epi < 3; ++epi) params->k3[epi] = make_k3(d, params->k, dev_params, pl->n_cus, epi);
+  if (on_device) {
+    // tables and parameters in one copy
+    DeviceParams dp;
+    dp.residues = make_residues(d, params->k);
+    dp.k3 = make_conversion(d, params->k, pl->n_cus);
+    std::memcpy(blob.data() + pl->off_params, &dp, sizeof(dp));
+    if (hipMemcpy(pl->d_tables, blob.data(), blob.size(), hipMemcpyHostToDevice) != hipSuccess) return fail(RNSWINO_E_HIP);
+  }
   {
     // every kernel the layer would launch, in each output mode, must be an instantiation that exists
     bool ok = launch_k1(d, pl->n_cus, params->k1, nullptr, nullptr, nullptr, Timing(), true) && launch_k2(d, pl->desc.flags, params->k2, nullptr, nullptr, nullptr, nullptr, Timing(), true);
-    for (int epi = 0; epi < 3 && ok; ++epi) ok = launch_k3(d, *params, pl->n_cus, epi, 0, nullptr, nullptr, nullptr, nullptr, Timing(), true);
-    if (!ok) { (void)rnswino_plan_destroy(pl); return RNSWINO_E_UNSUPPORTED; }
+    for (int epi = 0; epi < 3 && ok; ++epi) ok = launch_k3(d, *params, pl->n_cus, epi, 0, nullptr, nullptr, nullptr, Timing(), true);
+    if (!ok) return fail(RNSWINO_E_UNSUPPORTED);
   }
   *out = pl;
   return RNSWINO_OK;
