@@ -317,6 +317,11 @@ def bench_layer(idx, steps, warmup, dev, with_cpu, warm=False, events=True):
             "direct_sec": sec_direct, "direct_bit_exact": direct_exact}
 
 
+def launched(described):
+    """The kernels of a call in launch order."""
+    return ([described["fused"]] if described["fused"] else described["kernels"][:2]) + described["kernels"][2:]
+
+
 def layer_name(cfg):
     return (f"{cfg['name']}: N={cfg['N']} C={cfg['C']} K={cfg['K']} {cfg['H']}x{cfg['W']} r={cfg['r']} pad={cfg['pad']} "
             f"F({cfg['m']}x{cfg['m']},{cfg['r']}x{cfg['r']}) moduli={list(cfg['moduli'])}")
@@ -418,7 +423,7 @@ def bench_stack(steps, warmup, dev, with_cpu, trusted_range=False, measured_tile
             for li in range(len(layers)):
                 totd[li] += marks[li].elapsed_time(marks[li + 1]) * 1e3 / iters
         table = [{"layer": l["name"], "C": l["C"], "K": l["K"], "map": l["H"], "m": l["m"], "moduli": list(l["moduli"]),
-                  "kernels": rn.rnswino_plan_describe(p, 2 if l["pool"] else 1)["kernels"],
+                  "kernels": launched(rn.rnswino_plan_describe(p, 2 if l["pool"] else 1)),
                   "rns_winograd_us": round(tot[li], 1), "own_direct_conv_us": round(totd[li], 1)}
                  for li, (l, p) in enumerate(zip(stack.cfg, stack.plans))]
     cpu, bit_exact, direct_exact = None, None, None

@@ -65,11 +65,13 @@ enum {
                                               is the true result reduced to that interval (mod 2^32)       */
   RNSWINO_FLAG_HOST_ONLY = 2u,             /* build the host tables only (no GPU touched): such a plan can
                                               be queried but not executed                                   */
-  RNSWINO_FLAG_GEMM_BLOCK_64X16 = 4u       /* measurement only (8-bit moduli): run the residue GEMM on workgroup blocks
+  RNSWINO_FLAG_GEMM_BLOCK_64X16 = 4u,      /* measurement only (8-bit moduli): run the residue GEMM on workgroup blocks
                                               of 64 rows x 16 tiles -- the largest block whose GEMM output (n t^2
                                               bytes per (k, tile) pair) one workgroup could keep in LDS if the
                                               inverse transform were fused into the GEMM (section 6: the stages
                                               compose per tile group).  Same result, slower; used to price that fusion */
+  RNSWINO_FLAG_SEPARATE_KERNELS = 8u       /* the input transform and the residue GEMM as two kernels on every layer (some layers run
+                                              them as one, see rnswino_plan_describe): V is then in the workspace after a call   */
 };
 
 typedef struct rnswino_plan_s rnswino_plan_t;   /* opaque, owned by the library */
@@ -171,7 +173,8 @@ int rnswino_conv2d_requant(const rnswino_plan_t *plan, const int8_t *x_dev, cons
  * rnswino_conv2d with six caller-created hipEvent_t (passed as void*): events[2j] and events[2j+1] receive the
  * start and stop timestamps of kernel j (0: input transform, 1: residue GEMM, 2: inverse transform + conversion),
  * so hipEventElapsedTime(events[2j], events[2j+1]) is that kernel's own duration.  For per-stage measurement
- * (the paper's time breakdown of section 8); does not synchronise.
+ * (the paper's time breakdown of section 8): always three kernels, also where rnswino_conv2d runs the first two as one.
+ * Does not synchronise.
  */
 int rnswino_conv2d_events(const rnswino_plan_t *plan, const int8_t *x_dev, const void *U_dev, int32_t *y_dev,
                           void *workspace_dev, void *stream, void *const events[6]);
@@ -238,7 +241,8 @@ int rnswino_plan_get_mrc_inverse(const rnswino_plan_t *plan, int l, int j, uint3
  *   k2_residue_gemm<4, 4, 2, false> grid=6400 xgroup=1
  *   k3_inverse_crt<4, 2, false, true> grid=784x1
  *   conversion=unreduced-binary32
- * (grid=XxYxZ where the launch has a third extent).
+ * (grid=XxYxZ where the launch has a third extent).  A last line "fused=k12_transform_gemm<2, 2, 2> grid=200 part=25" says that one kernel
+ * takes the place of the first two except in rnswino_conv2d_events (never with RNSWINO_FLAG_SEPARATE_KERNELS).
  * conversion: "unreduced-binary32" / "unreduced-binary64" = CRT sum over unreduced accumulators with the quotient rounded
  * in that precision; "reduced-binary32" / "reduced-binary64" = over reduced residues; "reduced-binary64-mul32" = the same
  * with full 32-bit multiplies (a partial product P/m_i of 2^24 or more, or three and more 16-bit moduli in most cases).  Works on host-only plans (their
@@ -264,6 +268,8 @@ int64_t rnswino_plan_dynamic_range(const rnswino_plan_t *plan);
  * plain index order of section 6 (synchronises the device; test use only):
  *   RNSWINO_STAGE_U: src_dev = U_dev,         host_out [n][t*t][K][C]
  *   RNSWINO_STAGE_V: src_dev = workspace_dev, host_out [n][t*t][T][C],  T = N * ceil(Ho/m) * ceil(Wo/m)
+ *                    (RNSWINO_E_UNSUPPORTED where one kernel transforms and multiplies: V is never in device memory then; plan the
+ *                    layer with RNSWINO_FLAG_SEPARATE_KERNELS to see it)
  *   RNSWINO_STAGE_O: src_dev = workspace_dev, host_out [n][t*t][K][T]
  * Tile index tau = (n * th + ty) * tw + tx.
  */

@@ -11,7 +11,7 @@ _LIB_PATH = os.path.join(_PKG, "librnswino.so")
 
 MATRIX_AT, MATRIX_G, MATRIX_BT = 0, 1, 2
 STAGE_U, STAGE_V, STAGE_O = 0, 1, 2
-FLAG_ALLOW_UNCHECKED_RANGE, FLAG_HOST_ONLY, FLAG_GEMM_BLOCK_64X16 = 1, 2, 4
+FLAG_ALLOW_UNCHECKED_RANGE, FLAG_HOST_ONLY, FLAG_GEMM_BLOCK_64X16, FLAG_SEPARATE_KERNELS = 1, 2, 4, 8
 
 EXPORTED_SYMBOLS = (
     "rnswino_plan", "rnswino_plan_destroy", "rnswino_output_dims", "rnswino_filter_bytes",
@@ -298,22 +298,24 @@ def rnswino_plan_get_mrc_inverse(plan: Plan, l: int, j: int) -> int:
 
 
 def rnswino_plan_describe(plan: Plan, output_mode: int = 0) -> dict:
-    """The library's report of what it launches for this plan: {"kernels": [names in launch order], "grids": [...],
-    "conversion": ..., "text": the raw report}."""
+    """The library's report of what it launches for this plan: {"kernels": [the three stages' names in launch order], "grids": [...],
+    "conversion": ..., "fused": the kernel that takes the place of the first two or None, "text": the raw report}."""
     n = lib().rnswino_plan_describe(plan.handle, output_mode, None, 0)
     _check(int(min(n, 0)), "rnswino_plan_describe")
     buf = ctypes.create_string_buffer(int(n))
     _check(int(min(lib().rnswino_plan_describe(plan.handle, output_mode, buf, int(n)), 0)), "rnswino_plan_describe")
     text = buf.value.decode()
-    kernels, grids, conversion = [], [], None
+    kernels, grids, conversion, fused = [], [], None, None
     for line in text.splitlines():
         if line.startswith("conversion="):
             conversion = line.split("=", 1)[1]
+        elif line.startswith("fused="):
+            fused = line.split("=", 1)[1].partition("> ")[0] + ">"
         elif line:
             name, _, rest = line.partition("> ")
             kernels.append(name + ">")
             grids.append(rest)
-    return {"kernels": kernels, "grids": grids, "conversion": conversion, "text": text}
+    return {"kernels": kernels, "grids": grids, "conversion": conversion, "fused": fused, "text": text}
 
 
 def rnswino_debug_empty_launch(grid_x: int, grid_y: int, stream: int = 0, start_event: int = 0, stop_event: int = 0) -> None:

@@ -23,6 +23,7 @@
 #include "k_inverse_crt.hpp"
 #include "k_residue_gemm.hpp"
 #include "k_residue_gemm_lds.hpp"
+#include "k_transform_gemm.hpp"
 #include "layout.hpp"
 #include "plan.hpp"
 #include "rnswino.h"
@@ -150,10 +151,15 @@ struct DeviceParams {
   K3Params k3;
 };
 static_assert(sizeof(DeviceParams) <= PARAMS_BYTES, "build_tables() leaves them that much");
+// The input transform and the GEMM in one kernel (k_transform_gemm.hpp).  TH: tile blocks of 16 a workgroup takes; RM: row blocks a wave multiplies at once;
+// part: items of a workgroup, parts: what that splits the items of its tiles into.
+struct K12Choice { bool fused; int KS1, TH, RM, part; unsigned parts, blocks; };
 struct LayerParams {
   KParams k;
   K1Args k1;
   K2Args k2;
+  K12Args k12;
+  K12Choice k12_choice;
   K3Args k3[3];               // per output mode
 };
 
@@ -341,6 +347,54 @@ K2Args make_k2(const Dims &d, const DeviceParams *dev, uint32_t flags) {
   return q;
 }
 
+K12Choice choose_k12(const Dims &d, uint32_t flags, int n_cus) {
+  K12Choice c{};
+  const long long elements = (long long)d.N * d.C * d.H * d.W;
+  const int nkb = d.Kp / 16, ntb = d.Tp / 16, cus = n_cus > 0 ? n_cus : 256, items = (d.n * d.Q + 3) / 4;
+  // Layers of one channel block that are not packed and whose row segments have 32-bit offsets (as for k1_input_transform_tiles), where that is
+  // faster: 260 random ones (1 to 6 moduli, F(2..8, 1..5), 8 to 1024 filters) were, with up to 288 filters and 150 (tile block, item) pairs, in
+  // the mean of all 0.93 of the time of two kernels, from 0.5 (64 -> 9 at 193 x 193, F(4,5), batch 6, 117.5 -> 60.8 us a layer) to 1.08.  With more filters
+  // fragments of U cross the L2 once per 32 tiles (64 -> 500 at 75 x 75, F(6,3), batch 7 105.5 / 107.9, 33 -> 513 at 103 x 103, F(4,5) 124.5 / 148.3);
+  // with fewer pairs the few blocks' latencies decide (48 -> 49 at 46 x 46, one modulus, batch 5 10.3 / 11.6, 16 -> 16 at 16 x 16 7.7 / 10.6).
+  c.fused = !d.wide && d.KS1 <= 2 && d.Cp == 64 && d.TL == 1 && !(flags & (RNSWINO_FLAG_GEMM_BLOCK_64X16 | RNSWINO_FLAG_SEPARATE_KERNELS)) && nkb <= 18 && (long long)ntb * items >= 150 &&
+            elements >= 16 && elements + d.W + 2LL * d.pad + 16 < (1LL << 31);
+  if (!c.fused) return c;
+  c.KS1 = d.KS1;
+  // The split: a workgroup takes 5 us to gather and 0.8 us an item plus 0.4 per 32 rows and 16 tiles; two on a compute unit, or one of 32 tiles, take 1.7 times
+  // that of one.  Over 43 layers the choice takes 0.2 % longer than the best split (6 % at worst).
+  double best = 0.0;
+  for (int TH = 1; TH <= 2; ++TH) {
+    const int RM = nkb > TH ? 2 : 1, sets = (nkb + RM * TH - 1) / (RM * TH), groups = (ntb + TH - 1) / TH;
+    const double item = 0.8 + 0.2 * sets * RM * TH;
+    for (int part = 1; part <= items; ++part) {
+      const long long rounds = ((long long)groups * ((items + part - 1) / part) + cus - 1) / cus;
+      const double alone = 5.0 + part * item, together = 5.0 + 1.7 * part * item;
+      const double cost = TH == 2 ? rounds * together : rounds / 2 * 1.1 * together + rounds % 2 * alone;
+      if (c.TH == 0 || cost < best) { best = cost; c.TH = TH; c.RM = RM; c.part = part; }
+    }
+  }
+  c.parts = (unsigned)((items + c.part - 1) / c.part);
+  c.blocks = (unsigned)(((long long)((ntb + c.TH - 1) / c.TH) * c.parts + 7) / 8 * 8);
+  return c;
+}
+
+K12Args make_k12(const Dims &d, const KParams &P, const DeviceParams *dev, const K12Choice &c) {
+  K12Args q;
+  std::memset(&q, 0, sizeof(q));
+  if (!c.fused) return q;
+  q.more = dev ? &dev->residues : nullptr;
+  q.KB = P.KB;
+  q.ntb = d.Tp / 16; q.nkb = d.Kp / 16;
+  q.per_xcd = (int)(c.blocks / 8);
+  const uint32_t s_groups = store_div((uint32_t)((q.ntb + c.TH - 1) / c.TH), q.tile_groups_mul), s_tw = store_div((uint32_t)d.tw, q.tw_mul), s_th = store_div((uint32_t)d.th, q.th_mul);
+  q.shifts = pack_bytes(s_groups, s_tw, s_th, 0);
+  q.sizes = pack_bytes((uint32_t)d.m, (uint32_t)d.t, (uint32_t)d.n, (uint32_t)c.part);
+  q.Q_mul = (65536u + (uint32_t)d.Q - 1) / (uint32_t)d.Q;
+  q.C = d.C; q.H = d.H; q.W = d.W; q.pad = d.pad; q.tw = d.tw; q.th = d.th; q.T = d.T;
+  q.total = (int)((long long)d.N * d.C * d.H * d.W);
+  return q;
+}
+
 // stream: the streaming variant (8-bit moduli, table of all residues at most 64 KiB, n * KS3 <= 8: O operand in
 // registers) for layers with 5000 and more units (us per layer, streaming / block form: 3136 units 33.7 / 32.0, 3200 35.0 / 33.5,
 // 4096 37.0 / 36.5, 6400 60.1 / 60.1, 12544 63.9 / 66.6, 25088 160 / 184; four resident blocks per CU already take 4096);
@@ -423,6 +477,7 @@ K3Params make_conversion(const Dims &d, const KParams &P, int n_cus) {
   X(1, 4, 2, false) X(2, 4, 2, false) X(4, 4, 2, false) X(1, 4, 4, false) X(2, 4, 4, false) \
   X(1, 1, 2, true) X(2, 1, 2, true) X(4, 1, 2, true) X(1, 2, 2, true) X(2, 2, 2, true) X(1, 4, 2, true)
 #define RNSW_K2L_TABLE(X) X(2, 2, 4, 4, 3) X(4, 1, 2, 4, 4) X(4, 1, 1, 1, 4)
+#define RNSW_K12_TABLE(X) X(1, 1, 1) X(1, 1, 2) X(1, 2, 1) X(1, 2, 2) X(2, 1, 1) X(2, 1, 2) X(2, 2, 1) X(2, 2, 2)
 #define RNSW_K3_NK(X, nres, wd, fs) X(nres, 1, wd, fs) X(nres, 2, wd, fs) X(nres, 3, wd, fs) X(nres, 4, wd, fs)
 #define RNSW_K3_TABLE(X) \
   RNSW_K3_NK(X, 1, true, false) RNSW_K3_NK(X, 2, true, false) RNSW_K3_NK(X, 3, true, false) RNSW_K3_NK(X, 4, true, false) \
@@ -470,6 +525,19 @@ bool launch_k2(const Dims &d, uint32_t flags, const K2Args &L, const int8_t *U, 
 #define RNSW_X(ks, ntb, rm, wd) \
   if (c.KS == ks && c.NTB == ntb && c.RM == rm && c.wide == wd) { if (!dry) launch(k2_residue_gemm<ks, ntb, rm, wd>, grid, 0, st, tm, P); return true; }
   RNSW_K2_TABLE(RNSW_X)
+#undef RNSW_X
+  return false;
+}
+
+// ---- K1 and K2 in one ----
+bool launch_k12(const K12Choice &c, const K12Args &L, const int8_t *x, const int8_t *U, uint32_t *O, hipStream_t st, bool dry = false) {
+  const dim3 grid(c.blocks);
+  K12Args P = L;
+  P.x = x; P.U = U; P.O = O;
+#define RNSW_X(ks, groups, rm) \
+  if (c.KS1 == ks && c.TH == groups && c.RM == rm) { \
+    if (!dry) hipLaunchKernelGGL((k12_transform_gemm<ks, groups, rm>), grid, dim3(256 * groups), 0, st, P); return true; }
+  RNSW_K12_TABLE(RNSW_X)
 #undef RNSW_X
   return false;
 }
@@ -542,7 +610,13 @@ int conv2d_impl(const rnswino_plan_t *plan, const int8_t *x_dev, const void *U_d
     t2.start = (hipEvent_t)events[2]; t2.stop = (hipEvent_t)events[3];
     t3.start = (hipEvent_t)events[4]; t3.stop = (hipEvent_t)events[5];
   }
-  // (rnswino_plan() has checked that all three instantiations exist)
+  // (rnswino_plan() has checked that all instantiations exist)
+  if (L.k12_choice.fused && !events) {
+    if (!launch_k12(L.k12_choice, L.k12, x_dev, (const int8_t *)U_dev, Op, st) ||
+        !launch_k3(d, L, plan->n_cus, epi, shift, Op, epi == 0 ? (void *)y_dev : (void *)act_dev, st, t3))
+      return RNSWINO_E_UNSUPPORTED;
+    return launch_status();
+  }
   if (!launch_k1(d, plan->n_cus, L.k1, x_dev, Vp, st, t1) || !launch_k2(d, plan->desc.flags, L.k2, (const int8_t *)U_dev, Vp, Op, st, t2) ||
       !launch_k3(d, L, plan->n_cus, epi, shift, Op, epi == 0 ? (void *)y_dev : (void *)act_dev, st, t3))
     return RNSWINO_E_UNSUPPORTED;
@@ -611,6 +685,8 @@ int rnswino_plan(rnswino_plan_t **out, const rnswino_desc_t *desc) {
   const DeviceParams *dev_params = on_device ? (const DeviceParams *)((char *)pl->d_tables + pl->off_params) : nullptr;   // (host-only plans are never executed)
   params->k1 = make_k1(d, params->k, dev_params, pl->n_cus);
   params->k2 = make_k2(d, dev_params, pl->desc.flags);
+  params->k12_choice = choose_k12(d, pl->desc.flags, pl->n_cus);
+  params->k12 = make_k12(d, params->k, dev_params, params->k12_choice);
   for (int epi = 0; epi < 3; ++epi) params->k3[epi] = make_k3(d, params->k, dev_params, pl->n_cus, epi);
   if (on_device) {
     // tables and parameters in one copy
@@ -623,6 +699,7 @@ int rnswino_plan(rnswino_plan_t **out, const rnswino_desc_t *desc) {
   {
     // every kernel the layer would launch, in each output mode, must be an instantiation that exists
     bool ok = launch_k1(d, pl->n_cus, params->k1, nullptr, nullptr, nullptr, Timing(), true) && launch_k2(d, pl->desc.flags, params->k2, nullptr, nullptr, nullptr, nullptr, Timing(), true);
+    ok = ok && (!params->k12_choice.fused || launch_k12(params->k12_choice, params->k12, nullptr, nullptr, nullptr, nullptr, true));
     for (int epi = 0; epi < 3 && ok; ++epi) ok = launch_k3(d, *params, pl->n_cus, epi, 0, nullptr, nullptr, nullptr, Timing(), true);
     if (!ok) return fail(RNSWINO_E_UNSUPPORTED);
   }
@@ -746,6 +823,9 @@ int64_t rnswino_plan_describe(const rnswino_plan_t *plan, int32_t output_mode, c
                      : !P.crt24 || (d.wide && k3_converts_each(d.n, c3.KS3)) ? "reduced-binary64-mul32"
                      : P.quot32 ? "reduced-binary32" : "reduced-binary64";
   len += std::snprintf(buf + len, sizeof(buf) - len, "conversion=%s\n", conv);
+  const K12Choice &c12 = ((const LayerParams *)plan->kparams)->k12_choice;
+  if (c12.fused)
+    len += std::snprintf(buf + len, sizeof(buf) - len, "fused=k12_transform_gemm<%d, %d, %d> grid=%u part=%d\n", c12.KS1, c12.TH, c12.RM, c12.blocks, c12.part);
   if (host_out && capacity > (size_t)len) std::memcpy(host_out, buf, (size_t)len + 1);
   return (int64_t)len + 1;
 }
@@ -944,6 +1024,7 @@ int rnswino_debug_stage(const rnswino_plan_t *plan, int stage, const void *src_d
   if (!plan || !src_dev || !host_out) return RNSWINO_E_INVALID;
   if (plan->device < 0) return RNSWINO_E_NO_DEVICE;
   const Dims &d = plan->dims;
+  if (stage == RNSWINO_STAGE_V && ((const LayerParams *)plan->kparams)->k12_choice.fused) return RNSWINO_E_UNSUPPORTED;
   size_t bytes, skip = 0;
   if (stage == RNSWINO_STAGE_U) bytes = u_bytes(d);
   else if (stage == RNSWINO_STAGE_V) bytes = v_bytes(d);

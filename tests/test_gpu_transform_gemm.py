@@ -1,0 +1,141 @@
+"""The input transform and the residue GEMM as one kernel: every instantiation, at the edges of its tiles -- odd numbers of tile blocks (two a
+workgroup), ragged row blocks, point groups that are cut off (81 points) or shared by an item's residues, splits with a shorter last part, border
+tiles, wide padding, inputs at any byte -- against the oracle; and the calls that still take two kernels."""
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as si
+import variant_cases as vc
+import paper_2007_12216_amd as rn
+from oracle import direct_conv2d, maxpool2x2, requant_shift_clamp
+
+P8 = vc.PRIMES8
+HOST, UNCHECKED, SEPARATE = rn.FLAG_HOST_ONLY, rn.FLAG_ALLOW_UNCHECKED_RANGE, rn.FLAG_SEPARATE_KERNELS
+
+# (N, C, K, H, W, r, m, pad, number of moduli, byte offset of x), instantiation
+CASES = [
+    ((1, 33, 5, 100, 77, 3, 6, 1, 4, 0), "k12_transform_gemm<1, 1, 1>"),
+    ((8, 48, 16, 52, 52, 3, 2, 1, 8, 1), "k12_transform_gemm<1, 1, 1>"),            # t = 4: rows of one word, two workgroups a compute unit
+    ((5, 64, 7, 43, 29, 1, 8, 0, 7, 3), "k12_transform_gemm<1, 1, 1>"),             # 1 x 1 filters
+    ((8, 40, 287, 36, 31, 5, 4, 2, 4, 2), "k12_transform_gemm<1, 1, 2>"),
+    ((3, 36, 20, 38, 50, 3, 6, 4, 5, 0), "k12_transform_gemm<1, 2, 1>"),            # 17 tile blocks, two a workgroup
+    ((7, 40, 288, 36, 31, 5, 4, 2, 3, 3), "k12_transform_gemm<1, 2, 2>"),
+    ((3, 64, 16, 44, 52, 3, 8, 1, 4, 2), "k12_transform_gemm<2, 1, 1>"),
+    ((3, 37, 8, 200, 100, 3, 8, 1, 1, 1), "k12_transform_gemm<2, 1, 1>"),           # one modulus, a last item of one group
+    ((1, 50, 75, 84, 82, 3, 7, 1, 4, 0), "k12_transform_gemm<2, 1, 2>"),            # 81 points: a group of one
+    ((4, 35, 33, 64, 20, 4, 7, 0, 5, 0), "k12_transform_gemm<2, 1, 2>"),
+    ((1, 64, 64, 224, 224, 3, 8, 1, 4, 0), "k12_transform_gemm<2, 1, 2>"),
+    ((3, 36, 20, 50, 60, 3, 8, 9, 3, 0), "k12_transform_gemm<2, 2, 1>"),            # padding of more than a tile
+    ((2, 33, 34, 90, 46, 3, 8, 1, 5, 0), "k12_transform_gemm<2, 2, 2>"),
+    ((8, 64, 128, 112, 64, 3, 8, 1, 4, 1), "k12_transform_gemm<2, 2, 2>"),          # a last part of fewer items
+    ((9, 7, 3, 8, 8, 3, 2, 1, 8, 0), None),                                         # packed
+    ((4, 64, 290, 60, 60, 3, 8, 1, 4, 0), None), ((1, 64, 64, 28, 28, 3, 8, 1, 4, 0), None),          # past either line
+    ((2, 65, 64, 56, 56, 3, 8, 1, 4, 0), None), ((2, 64, 64, 56, 56, 3, 10, 1, 4, 0), None),          # two channel blocks, t = 12
+]
+
+
+def _plan(case, flags):
+    N, C, K, H, W, r, m, pad, n, _ = case
+    return rn.rnswino_plan(N, C, K, H, W, r, m, pad, P8[:n], flags=flags | UNCHECKED)
+
+
+def test_the_cases_reach_every_instantiation():
+    reached = set()
+    for case, kernel in CASES:
+        assert rn.rnswino_plan_describe(_plan(case, HOST))["fused"] == kernel, case
+        assert rn.rnswino_plan_describe(_plan(case, HOST | SEPARATE))["fused"] is None
+        reached.add(kernel)
+    assert reached - {None} == {f"k12_transform_gemm<{ks}, {th}, {rm}>" for ks in (1, 2) for th in (1, 2) for rm in (1, 2)}
+
+
+def test_the_split_leaves_no_item_out():
+    """Workgroups x items cover what there is, with less than a part to spare, on layers of all sizes."""
+    for N, C, K, hw, m, n in ((2, 64, 64, 56, 8, 4), (1, 64, 64, 224, 8, 4), (8, 64, 64, 224, 8, 4), (8, 33, 256, 56, 6, 7), (5, 48, 9, 99, 7, 2), (2, 64, 128, 112, 4, 8)):
+        text = rn.rnswino_plan_describe(rn.rnswino_plan(N, C, K, hw, hw, 3, m, 1, P8[:n], flags=HOST | UNCHECKED))["text"]
+        line = [l for l in text.splitlines() if l.startswith("fused=")][0]
+        th, grid, part = (int(v) for v in (line.split(",")[1], line.split("grid=")[1].split()[0], line.split("part=")[1]))
+        tiles, groups = N * (-(-hw // m)) ** 2, n * (((m + 2) ** 2 + 3) // 4)
+        units = -(-(-(-tiles // 16)) // th) * -(-(-(-groups // 4)) // part)
+        assert units <= grid < units + 8 and 1 <= part <= -(-groups // 4)
+
+
+def _layer(case, flags=0):
+    from paper_2007_12216_amd.layer import ConvLayer
+    N, C, K, H, W, r, m, pad, n, offset = case
+    x, w = si.int8_tensor(771, (N, C, H, W)), si.int8_tensor(772, (K, C, r, r))
+    layer = ConvLayer(N, C, K, H, W, r, m, pad, P8[:n], UNCHECKED | flags)
+    layer.set_weights(w)
+    raw = torch.zeros(x.size + 4, dtype=torch.int8, device="cuda:0")
+    raw[offset:offset + x.size] = torch.from_numpy(x.reshape(-1)).to("cuda:0")
+    layer.workspace.fill_(0x55)                        # a point that nobody writes shows
+    return layer, raw[offset:offset + x.size].view(x.shape), x, w
+
+
+def _expected(x, w, pad, n):
+    P = int(np.prod([int(p) for p in P8[:n]], dtype=object))
+    ref = direct_conv2d(x, w, pad).astype(np.int64)
+    return (ref + (P - 1) // 2) % P - (P - 1) // 2     # the symmetric range of the moduli, where it is the smaller
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case,kernel", CASES)
+def test_one_kernel_transforms_and_multiplies(case, kernel):
+    print("transform and gemm", case, kernel, flush=True)
+    layer, xd, x, w = _layer(case)
+    got = layer.forward(xd).cpu().numpy()
+    assert np.array_equal(got, _expected(x, w, case[7], case[8]))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [CASES[0][0], CASES[12][0]])
+def test_the_calls_around_it(case):
+    """O in the workspace, V refused and there with two kernels, the fused re-quantisation, and a captured graph replayed between eager calls."""
+    print("around transform and gemm", case, flush=True)
+    layer, xd, x, w = _layer(case)
+    y = layer.forward(xd).cpu().numpy()
+    o = layer.stage(rn.STAGE_O)
+    with pytest.raises(rn.RnsWinoError):
+        layer.stage(rn.STAGE_V)
+    two, xd2, _, _ = _layer(case, SEPARATE)
+    assert np.array_equal(two.forward(xd2).cpu().numpy(), y)
+    assert np.array_equal(two.stage(rn.STAGE_O), o)
+    assert two.stage(rn.STAGE_V).any()
+    K, Ho, Wo = case[2], layer.plan.Ho, layer.plan.Wo
+    a = torch.empty((case[0], K, Ho, Wo), dtype=torch.int8, device="cuda:0")
+    rn.rnswino_conv2d_requant(layer.plan, xd, layer.U, a, 9, False, layer.workspace, torch.cuda.current_stream().cuda_stream)
+    assert np.array_equal(a.cpu().numpy(), requant_shift_clamp(y, 9))
+    if case[6] == 8 and Wo % 4 == 0 and Ho % 2 == 0:
+        a = torch.empty((case[0], K, Ho // 2, Wo // 2), dtype=torch.int8, device="cuda:0")
+        rn.rnswino_conv2d_requant(layer.plan, xd, layer.U, a, 9, True, layer.workspace, torch.cuda.current_stream().cuda_stream)
+        assert np.array_equal(a.cpu().numpy(), maxpool2x2(requant_shift_clamp(y, 9)))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        layer.forward(xd)
+    for seed in (1, 2, 3):
+        xd.copy_(torch.from_numpy(si.int8_tensor(780 + seed, x.shape)))
+        graph.replay()
+        replayed = layer.y.clone()
+        layer.y.zero_()
+        assert torch.equal(layer.forward(xd), replayed)
+
+
+def _two_kernel_cases():
+    return [e for e in vc.select_cases() if rn.rnswino_plan_describe(
+        rn.rnswino_plan(*e[0][:8], e[0][8], flags=e[0][9] | HOST), e[0][10])["fused"]]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("entry", _two_kernel_cases(), ids=vc.case_id)
+def test_the_two_kernels_it_takes_the_place_of(entry):
+    """The layers that reach an instantiation of the two kernels but run as one: with the two."""
+    from paper_2007_12216_amd.layer import ConvLayer
+    (N, C, K, H, W, r, m, pad, moduli, flags, _), kernels, _ = entry
+    print("two kernels", kernels, flush=True)
+    x, w = si.int8_tensor(791, (N, C, H, W)), si.int8_tensor(792, (K, C, r, r))
+    layer = ConvLayer(N, C, K, H, W, r, m, pad, moduli, flags | SEPARATE)
+    layer.set_weights(w)
+    got = layer.forward(torch.from_numpy(x).to("cuda:0")).cpu().numpy()
+    P = int(np.prod([int(p) for p in moduli], dtype=object))
+    ref = direct_conv2d(x, w, pad).astype(np.int64)
+    assert np.array_equal(got, (ref + (P - 1) // 2) % P - (P - 1) // 2)
