@@ -463,8 +463,8 @@ __global__ __launch_bounds__(256) void k3_inverse_crt(K3Args P) {
 // come from LDS.  A unit's loads are hidden by the other waves of the SIMD (four resident blocks per CU).
 // Positions in 32 bits, pooling by lane swaps and one loop per output mode and conversion took a unit's vector instructions from about 350 to
 // 300 (four residues, two steps, pooled, binary32): 64 -> 128 at 112 x 112, batch 8, pooled, 19.6 -> 18.2 us; the median of the layers of the VGG16
-// stack, batch 8, that come here 21.3 -> 20.4.  32 of the 300 still add addresses: the lane offsets of the loads are the same for every unit, so the
-// compiler widens them to 64 bits in front of the loop and adds the unit's base to them, once a load.
+// stack, batch 8, that come here 21.3 -> 20.4.  Loads that keep their lane's offset in 32 bits (load_o) took another 32 and four to eight registers: the
+// stack's layers 793.8 -> 785.4 us together.
 // What bounds it: a unit's first products wait for all its loads and for the stores of the unit before.  On 64 -> 64 at 224 x 224, batch 8,
 // pooled (168 MB of O, 42.8 us before that): without the loads of O 30, without the stores 40, without the conversion 40.5, without
 // loads and stores 26.8; the same bytes in 16-byte loads, a quarter as many, 42.3.  More loads in flight make it slower: the next
@@ -503,13 +503,21 @@ __global__ __launch_bounds__(256) void k3_inverse_crt_stream(K3Args P) {
     for (int e = 0; e < 4; ++e) voff[s][e] = (uint32_t)min(16 * s + 4 * g + e, P.Q() - 1) * row_bytes + (uint32_t)(lane & 15) * 4u;
 
   auto load_o = [&](int k, int tb, v4i (&of)[NRES][KS3]) {
+    uint32_t at[KS3][4];                               // (known to be the same for every unit, they would be widened in front of the loop, and each load would add
+#pragma unroll                                         // the unit's address to them in 64 bits)
+    for (int s = 0; s < KS3; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        at[s][e] = voff[s][e];
+        asm volatile("" : "+v"(at[s][e]));
+      }
 #pragma unroll
     for (int i = 0; i < NRES; ++i) {
       const char *row = (const char *)P.O + (size_t)((uint32_t)((k * NRES + i) * P.Q()) * row_bytes + (uint32_t)tb * 64u);
 #pragma unroll
       for (int s = 0; s < KS3; ++s)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) of[i][s][e] = *(const int *)(row + voff[s][e]);
+        for (int e = 0; e < 4; ++e) of[i][s][e] = *(const int *)(row + at[s][e]);
     }
   };
 
