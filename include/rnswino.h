@@ -241,7 +241,7 @@ int rnswino_plan_get_mrc_inverse(const rnswino_plan_t *plan, int l, int j, uint3
  *   k2_residue_gemm<4, 4, 2, false> grid=6400 xgroup=1
  *   k3_inverse_crt<4, 2, false, true> grid=784x1
  *   conversion=unreduced-binary32
- * (grid=XxYxZ where the launch has a third extent).  A last line "fused=k12_transform_gemm<2, 2, 2> grid=200 part=25" says that one kernel
+ * (grid=XxYxZ where the launch has a third extent).  A last line "fused=k12_transform_gemm<2, 2, 2, false> grid=200 part=25" says that one kernel
  * takes the place of the first two except in rnswino_conv2d_events (never with RNSWINO_FLAG_SEPARATE_KERNELS).
  * conversion: "unreduced-binary32" / "unreduced-binary64" = CRT sum over unreduced accumulators with the quotient rounded
  * in that precision; "reduced-binary32" / "reduced-binary64" = over reduced residues; "reduced-binary64-mul32" = the same

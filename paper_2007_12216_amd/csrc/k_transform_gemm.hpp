@@ -1,5 +1,5 @@
-// K1 and K2 in one kernel, for layers of one block of 64 channels (33 to 64, or fewer on few tiles; 8-bit moduli, t <= 10): the input transform
-// of 16 or 32 tiles and the residue GEMM over all their channels, V passing through LDS and never through device memory.
+// K1 and K2 in one kernel, for layers of one block of 64 channels (33 to 64, fewer on few tiles, or 16 tiles of up to four; 8-bit moduli, t <= 10): the input
+// transform of 16 or 32 tiles and the residue GEMM over all their channels, V passing through LDS and never through device memory.
 //
 // Block = TH blocks of 16 tiles, 4 TH waves.  A wave gathers the pixels of 16 tiles in 16 channels once (the channels of one slice of V) and
 // keeps them in registers as operand fragments (128 registers at t = 9, 10).  Then the block goes through its items: four groups of four
@@ -15,8 +15,13 @@
 // 224 x 224, batch 1, 32.4 -> 27.0.  On the way there (us of this kernel on the first two): 32 tiles a block 83 and 33, 16 tiles 93 and 36 (U crosses the L2
 // twice as often); all blocks of a part through the items in the same order 100 and 42 (they wait for the same fragments from memory), U from a single resident
 // fragment 64 and 26; multiply-adds right behind their quotients 103 and 40 (16 tiles); points of one residue an item 105 and 47 (16 tiles).
-// 65 to 128 channels (eight waves, 16 tiles) lose: 128 -> 128 at 112 x 112, batch 8, 94 -> 110 us a layer, as do the packed layers (3 -> 64 at 224 x 224 106 -> 143).
-// Grid: one-dimensional, ceil(Tp / (16 TH)) x parts of the items, rounded up to a multiple of 8 (kernels_common.hpp).
+// 65 to 128 channels (eight waves, 16 tiles) lose: 128 -> 128 at 112 x 112, batch 8, 94 -> 110 us a layer.
+//
+// PACK: layers of up to four channels, 16 tiles a block.  A fragment of U then is four bytes in 16 places and zeros: made in registers from one byte quadruple
+// per filter and point, where the GEMM fetched 1 KiB (and exchanged its results through LDS).  What bounds it are the words of O, 123 MB of 3 -> 64 at 224 x 224,
+// batch 8, and the residues: K1 8.9 + K2 45.6 us, so 34 (a layer 107.4 -> 87.6; with fragments from L2 143).  The filters may be split over workgroups, each
+// transforming anew.
+// Grid: one-dimensional, ceil(Tp / (16 TH)) x parts of the filters x parts of the items, rounded up to a multiple of 8 (kernels_common.hpp).
 #pragma once
 #include "k_input_transform.hpp"
 #include "k_residue_gemm.hpp"
@@ -34,11 +39,12 @@ struct K12Args {
   int C, H, W, pad, tw, th, T;
   int total;                  // N * C * H * W
   uint32_t Q_mul;             // ceil(2^16 / Q), Q = ceil(t*t / 4)
-  uint32_t shifts;            // bytes: of the divisions by ngroups, tw, th
+  uint32_t shifts;            // bytes: of the divisions by the tile blocks' groups, tw, th; packed layers: parts the filters are split into
   uint32_t sizes;             // bytes: m, t, n, items of a part
   RNSW_HD FastDiv by_tile_groups() const { return {tile_groups_mul, shifts & 31u}; }
   RNSW_HD FastDiv by_tw() const { return {tw_mul, shifts >> 8 & 31u}; }
   RNSW_HD FastDiv by_th() const { return {th_mul, shifts >> 16 & 31u}; }
+  RNSW_HD int row_parts() const { return (int)(shifts >> 24); }
   RNSW_HD int m() const { return (int)byte_of(sizes, 0); }
   RNSW_HD int t() const { return (int)byte_of(sizes, 1); }
   RNSW_HD int n() const { return (int)byte_of(sizes, 2); }
@@ -57,7 +63,7 @@ __device__ __forceinline__ void biased_lowbytes(uint32_t (&r)[4], int a0, int a1
       : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) : "v"(neg_p), "v"(a0), "v"(a1), "v"(a2), "v"(a3));
 }
 
-template <int KS1, int TH, int RM>
+template <int KS1, int TH, int RM, bool PACK>
 __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
   Constant<ResidueParams> &R = constant(P.more);
   constexpr int ROWS = KS1 == 1 ? 8 : 10;
@@ -72,7 +78,8 @@ __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, h = lane >> 4, col = lane & 15;
   const int slice = wave & 3, th = wave >> 2;                          // of V: what this wave transforms
   const int unit = (int)(blockIdx.x & 7) * P.per_xcd + (int)(blockIdx.x >> 3);
-  const int tile_groups = (P.ntb + TH - 1) / TH, part = (int)fast_div((uint32_t)unit, P.by_tile_groups()), tb0 = (unit - part * tile_groups) * TH;
+  const int tile_groups = (P.ntb + TH - 1) / TH, which = (int)fast_div((uint32_t)unit, P.by_tile_groups()), tb0 = (unit - which * tile_groups) * TH;
+  const int part = PACK ? which / P.row_parts() : which;
   const int ngroups = P.n() * Q;
   const int first = part * P.part();
   if (4 * first >= ngroups) return;                                     // the grid is padded to a multiple of 8
@@ -87,12 +94,14 @@ __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
     return {tile, ty * P.m() - P.pad, tx * P.m() - P.pad, img};
   };
   struct Segment { Origin o; int from; bool live; };
-  const Origin own = origin(min(tau, P.T - 1));
+  const Origin own = PACK ? Origin() : origin(min(tau, P.T - 1));
+  const int Tg = PACK ? (P.T + 15) >> 4 : P.T;
   auto segment = [&](int u) -> Segment {
-    const int ch = 16 * u + 4 * slice + h;                             // channel order of layout.hpp
+    const int c64 = 16 * u + 4 * slice + h;                            // channel order of layout.hpp
+    const int tile = PACK ? (4 * u + slice) * Tg + tau : tau, ch = PACK ? h : c64;
     Segment s;
-    s.live = tau < P.T && ch < P.C;
-    s.o = own;
+    s.live = tau < Tg && tile < P.T && ch < P.C;
+    s.o = PACK ? origin(s.live ? tile : 0) : own;
     s.from = (s.o.img * P.C + (s.live ? ch : 0)) * HW + s.o.x0 + mis;
     return s;
   };
@@ -159,7 +168,7 @@ __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
   // The tile blocks of a part begin at different items and go round: side by side through the same ones, all would wait for the same
   // fragments of U on their way from memory.
   const int count = min(P.part(), ((ngroups + 3) >> 2) - first);
-  int left = count, item = first + (int)((uint32_t)(unit - part * tile_groups) % (uint32_t)count);
+  int left = count, item = first + (int)((uint32_t)(unit - which * tile_groups) % (uint32_t)count);
   auto after = [&](int it) { return it + 1 == first + count ? first : it + 1; };
   struct Group { int i, q; };                                          // residue and points 4 q .. 4 q + 3; past the last group: that one again
   auto group = [&](int number) -> Group {
@@ -201,6 +210,19 @@ __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
       frag += rows.step;
     }
   };
+  // Packed layers (16 tiles of four channels a block): row block kb holds filter kb in 16 slots, its fragment the same four bytes in the 16 places where a row's
+  // slot is the channels'.  So lane l fetches those of filter k0 + l, and every fragment is made from a lane's word: row r has it in word r / 4 of
+  // slice r % 4.
+  const int filters = PACK ? (P.nkb + P.row_parts() - 1) / P.row_parts() : 0, k0 = PACK ? (which - part * P.row_parts()) * filters : 0;
+  uint32_t words[4], diagonal[4];
+  auto load_words = [&](const Group &p) {
+    const int8_t *first = P.U + (size_t)(uint32_t)(p.i * P2 + 4 * p.q) * slab_bytes;
+    const uint32_t lane_at = (uint32_t)min(k0 + lane, P.nkb - 1) * 1024u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) words[e] = *(const uint32_t *)(first + (size_t)((uint32_t)min(e, P2 - 1 - 4 * p.q) * slab_bytes) + lane_at);
+  };
+#pragma unroll
+  for (int d = 0; d < 4; ++d) diagonal[d] = PACK && (col & 3) == h && (col >> 2) == d ? 0xFFFFFFFFu : 0u;
   Group at = mine(item);
   {
     v4i va[ROWS], vb[ROWS];
@@ -219,8 +241,10 @@ __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
     settle(3, vb, cb);
     __builtin_amdgcn_sched_barrier(0);                                 // (requested any earlier, these take more registers than there are: 0.5 us a call)
     load_table(item);
+    if constexpr (PACK) load_words(at);
+    else
 #pragma unroll
-    for (int e = 0; e < 4; ++e) load_u(rows_of(at, 0), e, lane16);
+      for (int e = 0; e < 4; ++e) load_u(rows_of(at, 0), e, lane16);
   }
   __syncthreads();                                                     // the staged pixels make room for V
   // Everything requested so far is awaited here: otherwise the compiler, merging this entry state with the loop's own, makes the loop's waits wait for its
@@ -266,6 +290,46 @@ __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
     const float inv = in_vgpr(r.inv), qb = in_vgpr(r.quot_bias);
     const v4i start = (v4i){r.acc_bias, r.acc_bias, r.acc_bias, r.acc_bias};
     const uint8_t *vfrag = lds + buf + (uint32_t)(4 * wq * TH * 1024) + lane16;
+    if constexpr (PACK) {
+      v4i vf[4][TH];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int x = 0; x < TH; ++x) vf[e][x] = *(const v4i *)(vfrag + (e * TH + x) * 1024);
+      uint32_t mine_now[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mine_now[e] = words[e];
+      load_words(next);
+      const int kend = min(k0 + filters, P.nkb);
+      char *row = (char *)P.O + (size_t)(uint32_t)((uint32_t)(at.i * Q + at.q) * (uint32_t)P.ntb * 64u) + (size_t)((uint32_t)((k0 + half) * 16) * krow);
+      for (int k = k0 + half; k < kend; k += TH) {
+        uint32_t word[TH][4], store_at[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          store_at[j] = lane_store[j];
+          asm volatile("" : "+v"(store_at[j]));
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)mine_now[e], k - k0);
+          const v4i frag = (v4i){(int)(w & diagonal[0]), (int)(w & diagonal[1]), (int)(w & diagonal[2]), (int)(w & diagonal[3])};
+          const uint32_t sel = e == 1 ? 0x0c0c0400u : e == 2 ? 0x0c040100u : 0x04020100u;
+#pragma unroll
+          for (int x = 0; x < TH; ++x) {
+            const v4i acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(frag, vf[e][x], start, 0, 0, 0);
+            uint32_t low[4];
+            biased_lowbytes(low, acc[0], acc[1], acc[2], acc[3], inv, qb, r.neg_p);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) word[x][j] = e == 0 ? low[j] : __builtin_amdgcn_perm(low[j], word[x][j], sel);
+          }
+        }
+#pragma unroll
+        for (int x = 0; x < TH; ++x)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) *(uint32_t *)(row + (uint32_t)min(tb0 + x, P.ntb - 1) * 64u + store_at[j]) = word[x][j];
+        row += (size_t)(16 * TH * krow);
+      }
+    } else {
     int set = 0;
     do {
       const bool same = set + 1 < sets;
@@ -310,6 +374,7 @@ __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
         row += kb + 1 < P.nkb ? (size_t)(16 * krow) : 0;
       }
     } while (++set < sets);
+    }
     at = next;
     item = following;
     buf ^= VBUF;

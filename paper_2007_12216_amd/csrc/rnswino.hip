@@ -152,8 +152,8 @@ struct DeviceParams {
 };
 static_assert(sizeof(DeviceParams) <= PARAMS_BYTES, "build_tables() leaves them that much");
 // The input transform and the GEMM in one kernel (k_transform_gemm.hpp).  TH: tile blocks of 16 a workgroup takes; RM: row blocks a wave multiplies at once;
-// part: items of a workgroup, parts: what that splits the items of its tiles into.
-struct K12Choice { bool fused; int KS1, TH, RM, part; unsigned parts, blocks; };
+// part: items of a workgroup, parts: what that splits the items of its tiles into; row_parts: packed layers, what the filters are split into.
+struct K12Choice { bool fused, pack; int KS1, TH, RM, part; unsigned parts, row_parts, blocks; };
 struct LayerParams {
   KParams k;
   K1Args k1;
@@ -351,30 +351,43 @@ K12Choice choose_k12(const Dims &d, uint32_t flags, int n_cus) {
   K12Choice c{};
   const long long elements = (long long)d.N * d.C * d.H * d.W;
   const int nkb = d.Kp / 16, ntb = d.Tp / 16, cus = n_cus > 0 ? n_cus : 256, items = (d.n * d.Q + 3) / 4;
-  // Layers of one channel block that are not packed and whose row segments have 32-bit offsets (as for k1_input_transform_tiles), where that is
-  // faster: 260 random ones (1 to 6 moduli, F(2..8, 1..5), 8 to 1024 filters) were, with up to 288 filters and 150 (tile block, item) pairs, in
-  // the mean of all 0.93 of the time of two kernels, from 0.5 (64 -> 9 at 193 x 193, F(4,5), batch 6, 117.5 -> 60.8 us a layer) to 1.08.  With more filters
-  // fragments of U cross the L2 once per 32 tiles (64 -> 500 at 75 x 75, F(6,3), batch 7 105.5 / 107.9, 33 -> 513 at 103 x 103, F(4,5) 124.5 / 148.3);
+  // 8-bit moduli, one channel block, row segments with 32-bit offsets (as for k1_input_transform_tiles), and where it is faster.
+  // Layers that are not packed: 260 random ones (1 to 6 moduli, F(2..8, 1..5), 8 to 1024 filters) were, with up to 288 filters and 150 (tile block, item)
+  // pairs, in the mean of all 0.93 of the time of two kernels, from 0.5 (64 -> 9 at 193 x 193, F(4,5), batch 6, 117.5 -> 60.8 us a layer) to 1.08.  With more
+  // filters fragments of U cross the L2 once per 32 tiles (64 -> 500 at 75 x 75, F(6,3), batch 7 105.5 / 107.9, 33 -> 513 at 103 x 103, F(4,5) 124.5 / 148.3);
   // with fewer pairs the few blocks' latencies decide (48 -> 49 at 46 x 46, one modulus, batch 5 10.3 / 11.6, 16 -> 16 at 16 x 16 7.7 / 10.6).
-  c.fused = !d.wide && d.KS1 <= 2 && d.Cp == 64 && d.TL == 1 && !(flags & (RNSWINO_FLAG_GEMM_BLOCK_64X16 | RNSWINO_FLAG_SEPARATE_KERNELS)) && nkb <= 18 && (long long)ntb * items >= 150 &&
-            elements >= 16 && elements + d.W + 2LL * d.pad + 16 < (1LL << 31);
+  // Packed layers of up to four channels: 70 random ones (1 to 4 channels, 8 to 256 filters, 2 to 4 moduli) were from 12 500 (tile block, item, filter)
+  // triples on 0.88 of it (0.81 to 0.95; 3 -> 64 at 224 x 224, batch 8, 107.4 -> 87.6), below mostly above it (the same at batch 2, 8 500, 34.9 / 37.4,
+  // at batch 1 23.5 / 26.8; 3 -> 26 at 220 x 220, F(4,5), batch 3, 11 200, 29.1 / 31.9).
+  if (d.wide || d.KS1 > 2 || d.Cp != 64 || (flags & (RNSWINO_FLAG_GEMM_BLOCK_64X16 | RNSWINO_FLAG_SEPARATE_KERNELS)) || elements < 16 ||
+      elements + d.W + 2LL * d.pad + 16 >= (1LL << 31))
+    return c;
+  c.pack = d.TL == 16;
+  if (c.pack) c.fused = d.K <= 8192 && (long long)ntb * items * d.K >= 12500;
+  else c.fused = d.TL == 1 && nkb <= 18 && (long long)ntb * items >= 150;
   if (!c.fused) return c;
   c.KS1 = d.KS1;
-  // The split: a workgroup takes 5 us to gather and 0.8 us an item plus 0.4 per 32 rows and 16 tiles; two on a compute unit, or one of 32 tiles, take 1.7 times
-  // that of one.  Over 43 layers the choice takes 0.2 % longer than the best split (6 % at worst).
+  // The split.  A workgroup takes 5 us to gather (3 on packed layers) and 0.8 us an item plus 0.4 per 32 rows and 16 tiles (0.08 per filter); two on a compute
+  // unit take 1.7 (1.5) times the work of one, and so does one of 32 tiles.  Over 43 layers the choice takes 0.2 % longer than the best split (6 % at
+  // worst), over 21 packed ones 0.2 % (3 %).  Packed layers take one item a workgroup, and up to three parts of the filters more than the 64 that fit a wave's lanes
+  // ask for (two items: 3 -> 64 at 224 x 224, batch 8, 110.9 us a layer).
+  const double gather = c.pack ? 3.0 : 5.0, factor = c.pack ? 1.5 : 1.7;
+  const int row_parts0 = c.pack ? (d.K + 63) / 64 : 1, row_parts1 = c.pack ? row_parts0 + 3 : 1, most = c.pack ? 1 : items;
   double best = 0.0;
   for (int TH = 1; TH <= 2; ++TH) {
-    const int RM = nkb > TH ? 2 : 1, sets = (nkb + RM * TH - 1) / (RM * TH), groups = (ntb + TH - 1) / TH;
-    const double item = 0.8 + 0.2 * sets * RM * TH;
-    for (int part = 1; part <= items; ++part) {
-      const long long rounds = ((long long)groups * ((items + part - 1) / part) + cus - 1) / cus;
-      const double alone = 5.0 + part * item, together = 5.0 + 1.7 * part * item;
-      const double cost = TH == 2 ? rounds * together : rounds / 2 * 1.1 * together + rounds % 2 * alone;
-      if (c.TH == 0 || cost < best) { best = cost; c.TH = TH; c.RM = RM; c.part = part; }
+    const int RM = !c.pack && nkb > TH ? 2 : 1, sets = (nkb + RM * TH - 1) / (RM * TH), groups = (ntb + TH - 1) / TH;
+    for (int row_parts = row_parts0; row_parts <= row_parts1; ++row_parts) {
+      const double item = 0.8 + (c.pack ? 0.08 * ((d.K + row_parts - 1) / row_parts) : 0.2 * sets * RM * TH);
+      for (int part = 1; part <= most; ++part) {
+        const long long rounds = ((long long)groups * row_parts * ((items + part - 1) / part) + cus - 1) / cus;
+        const double alone = gather + part * item, together = gather + factor * part * item;
+        const double cost = TH == 2 ? rounds * together : rounds / 2 * 1.1 * together + rounds % 2 * alone;
+        if (c.TH == 0 || cost < best) { best = cost; c.TH = TH; c.RM = RM; c.part = part; c.row_parts = (unsigned)row_parts; }
+      }
     }
   }
   c.parts = (unsigned)((items + c.part - 1) / c.part);
-  c.blocks = (unsigned)(((long long)((ntb + c.TH - 1) / c.TH) * c.parts + 7) / 8 * 8);
+  c.blocks = (unsigned)(((long long)((ntb + c.TH - 1) / c.TH) * c.parts * c.row_parts + 7) / 8 * 8);
   return c;
 }
 
@@ -387,7 +400,7 @@ K12Args make_k12(const Dims &d, const KParams &P, const DeviceParams *dev, const
   q.ntb = d.Tp / 16; q.nkb = d.Kp / 16;
   q.per_xcd = (int)(c.blocks / 8);
   const uint32_t s_groups = store_div((uint32_t)((q.ntb + c.TH - 1) / c.TH), q.tile_groups_mul), s_tw = store_div((uint32_t)d.tw, q.tw_mul), s_th = store_div((uint32_t)d.th, q.th_mul);
-  q.shifts = pack_bytes(s_groups, s_tw, s_th, 0);
+  q.shifts = pack_bytes(s_groups, s_tw, s_th, c.row_parts);
   q.sizes = pack_bytes((uint32_t)d.m, (uint32_t)d.t, (uint32_t)d.n, (uint32_t)c.part);
   q.Q_mul = (65536u + (uint32_t)d.Q - 1) / (uint32_t)d.Q;
   q.C = d.C; q.H = d.H; q.W = d.W; q.pad = d.pad; q.tw = d.tw; q.th = d.th; q.T = d.T;
@@ -477,7 +490,9 @@ K3Params make_conversion(const Dims &d, const KParams &P, int n_cus) {
   X(1, 4, 2, false) X(2, 4, 2, false) X(4, 4, 2, false) X(1, 4, 4, false) X(2, 4, 4, false) \
   X(1, 1, 2, true) X(2, 1, 2, true) X(4, 1, 2, true) X(1, 2, 2, true) X(2, 2, 2, true) X(1, 4, 2, true)
 #define RNSW_K2L_TABLE(X) X(2, 2, 4, 4, 3) X(4, 1, 2, 4, 4) X(4, 1, 1, 1, 4)
-#define RNSW_K12_TABLE(X) X(1, 1, 1) X(1, 1, 2) X(1, 2, 1) X(1, 2, 2) X(2, 1, 1) X(2, 1, 2) X(2, 2, 1) X(2, 2, 2)
+#define RNSW_K12_TABLE(X) \
+  X(1, 1, 1, false) X(1, 1, 2, false) X(1, 2, 1, false) X(1, 2, 2, false) X(2, 1, 1, false) X(2, 1, 2, false) X(2, 2, 1, false) X(2, 2, 2, false) \
+  X(1, 1, 1, true) X(1, 2, 1, true) X(2, 1, 1, true) X(2, 2, 1, true)
 #define RNSW_K3_NK(X, nres, wd, fs) X(nres, 1, wd, fs) X(nres, 2, wd, fs) X(nres, 3, wd, fs) X(nres, 4, wd, fs)
 #define RNSW_K3_TABLE(X) \
   RNSW_K3_NK(X, 1, true, false) RNSW_K3_NK(X, 2, true, false) RNSW_K3_NK(X, 3, true, false) RNSW_K3_NK(X, 4, true, false) \
@@ -534,9 +549,9 @@ bool launch_k12(const K12Choice &c, const K12Args &L, const int8_t *x, const int
   const dim3 grid(c.blocks);
   K12Args P = L;
   P.x = x; P.U = U; P.O = O;
-#define RNSW_X(ks, groups, rm) \
-  if (c.KS1 == ks && c.TH == groups && c.RM == rm) { \
-    if (!dry) hipLaunchKernelGGL((k12_transform_gemm<ks, groups, rm>), grid, dim3(256 * groups), 0, st, P); return true; }
+#define RNSW_X(ks, groups, rm, pk) \
+  if (c.KS1 == ks && c.TH == groups && c.RM == rm && c.pack == pk) { \
+    if (!dry) hipLaunchKernelGGL((k12_transform_gemm<ks, groups, rm, pk>), grid, dim3(256 * groups), 0, st, P); return true; }
   RNSW_K12_TABLE(RNSW_X)
 #undef RNSW_X
   return false;
@@ -825,7 +840,7 @@ int64_t rnswino_plan_describe(const rnswino_plan_t *plan, int32_t output_mode, c
   len += std::snprintf(buf + len, sizeof(buf) - len, "conversion=%s\n", conv);
   const K12Choice &c12 = ((const LayerParams *)plan->kparams)->k12_choice;
   if (c12.fused)
-    len += std::snprintf(buf + len, sizeof(buf) - len, "fused=k12_transform_gemm<%d, %d, %d> grid=%u part=%d\n", c12.KS1, c12.TH, c12.RM, c12.blocks, c12.part);
+    len += std::snprintf(buf + len, sizeof(buf) - len, "fused=k12_transform_gemm<%d, %d, %d, %s> grid=%u part=%d\n", c12.KS1, c12.TH, c12.RM, tf(c12.pack), c12.blocks, c12.part);
   if (host_out && capacity > (size_t)len) std::memcpy(host_out, buf, (size_t)len + 1);
   return (int64_t)len + 1;
 }

@@ -15,21 +15,26 @@ HOST, UNCHECKED, SEPARATE = rn.FLAG_HOST_ONLY, rn.FLAG_ALLOW_UNCHECKED_RANGE, rn
 
 # (N, C, K, H, W, r, m, pad, number of moduli, byte offset of x), instantiation
 CASES = [
-    ((1, 33, 5, 100, 77, 3, 6, 1, 4, 0), "k12_transform_gemm<1, 1, 1>"),
-    ((8, 48, 16, 52, 52, 3, 2, 1, 8, 1), "k12_transform_gemm<1, 1, 1>"),            # t = 4: rows of one word, two workgroups a compute unit
-    ((5, 64, 7, 43, 29, 1, 8, 0, 7, 3), "k12_transform_gemm<1, 1, 1>"),             # 1 x 1 filters
-    ((8, 40, 287, 36, 31, 5, 4, 2, 4, 2), "k12_transform_gemm<1, 1, 2>"),
-    ((3, 36, 20, 38, 50, 3, 6, 4, 5, 0), "k12_transform_gemm<1, 2, 1>"),            # 17 tile blocks, two a workgroup
-    ((7, 40, 288, 36, 31, 5, 4, 2, 3, 3), "k12_transform_gemm<1, 2, 2>"),
-    ((3, 64, 16, 44, 52, 3, 8, 1, 4, 2), "k12_transform_gemm<2, 1, 1>"),
-    ((3, 37, 8, 200, 100, 3, 8, 1, 1, 1), "k12_transform_gemm<2, 1, 1>"),           # one modulus, a last item of one group
-    ((1, 50, 75, 84, 82, 3, 7, 1, 4, 0), "k12_transform_gemm<2, 1, 2>"),            # 81 points: a group of one
-    ((4, 35, 33, 64, 20, 4, 7, 0, 5, 0), "k12_transform_gemm<2, 1, 2>"),
-    ((1, 64, 64, 224, 224, 3, 8, 1, 4, 0), "k12_transform_gemm<2, 1, 2>"),
-    ((3, 36, 20, 50, 60, 3, 8, 9, 3, 0), "k12_transform_gemm<2, 2, 1>"),            # padding of more than a tile
-    ((2, 33, 34, 90, 46, 3, 8, 1, 5, 0), "k12_transform_gemm<2, 2, 2>"),
-    ((8, 64, 128, 112, 64, 3, 8, 1, 4, 1), "k12_transform_gemm<2, 2, 2>"),          # a last part of fewer items
-    ((9, 7, 3, 8, 8, 3, 2, 1, 8, 0), None),                                         # packed
+    ((1, 33, 5, 100, 77, 3, 6, 1, 4, 0), "k12_transform_gemm<1, 1, 1, false>"),
+    ((8, 48, 16, 52, 52, 3, 2, 1, 8, 1), "k12_transform_gemm<1, 1, 1, false>"),            # t = 4: rows of one word, two workgroups a compute unit
+    ((5, 64, 7, 43, 29, 1, 8, 0, 7, 3), "k12_transform_gemm<1, 1, 1, false>"),             # 1 x 1 filters
+    ((8, 40, 287, 36, 31, 5, 4, 2, 4, 2), "k12_transform_gemm<1, 1, 2, false>"),
+    ((3, 36, 20, 38, 50, 3, 6, 4, 5, 0), "k12_transform_gemm<1, 2, 1, false>"),            # 17 tile blocks, two a workgroup
+    ((7, 40, 288, 36, 31, 5, 4, 2, 3, 3), "k12_transform_gemm<1, 2, 2, false>"),
+    ((3, 64, 16, 44, 52, 3, 8, 1, 4, 2), "k12_transform_gemm<2, 1, 1, false>"),
+    ((3, 37, 8, 200, 100, 3, 8, 1, 1, 1), "k12_transform_gemm<2, 1, 1, false>"),           # one modulus, a last item of one group
+    ((1, 50, 75, 84, 82, 3, 7, 1, 4, 0), "k12_transform_gemm<2, 1, 2, false>"),            # 81 points: a group of one
+    ((4, 35, 33, 64, 20, 4, 7, 0, 5, 0), "k12_transform_gemm<2, 1, 2, false>"),
+    ((1, 64, 64, 224, 224, 3, 8, 1, 4, 0), "k12_transform_gemm<2, 1, 2, false>"),
+    ((3, 36, 20, 50, 60, 3, 8, 9, 3, 0), "k12_transform_gemm<2, 2, 1, false>"),            # padding of more than a tile
+    ((2, 33, 34, 90, 46, 3, 8, 1, 5, 0), "k12_transform_gemm<2, 2, 2, false>"),
+    ((8, 64, 128, 112, 64, 3, 8, 1, 4, 1), "k12_transform_gemm<2, 2, 2, false>"),          # a last part of fewer items
+    ((4, 2, 129, 68, 159, 3, 4, 1, 4, 1), "k12_transform_gemm<1, 1, 1, true>"),     # packed: 16 tiles of up to four channels; filters in parts
+    ((8, 3, 58, 88, 134, 3, 4, 1, 4, 0), "k12_transform_gemm<1, 2, 1, true>"),
+    ((5, 4, 102, 120, 117, 3, 8, 1, 4, 2), "k12_transform_gemm<2, 1, 1, true>"),
+    ((7, 1, 125, 103, 69, 3, 8, 1, 4, 3), "k12_transform_gemm<2, 2, 1, true>"),
+    ((6, 3, 120, 100, 104, 3, 8, 4, 4, 0), "k12_transform_gemm<2, 1, 1, true>"),
+    ((9, 7, 30, 80, 80, 3, 2, 1, 4, 0), None), ((1, 3, 64, 224, 224, 3, 8, 1, 3, 0), None),           # 8 tiles a block; too few
     ((4, 64, 290, 60, 60, 3, 8, 1, 4, 0), None), ((1, 64, 64, 28, 28, 3, 8, 1, 4, 0), None),          # past either line
     ((2, 65, 64, 56, 56, 3, 8, 1, 4, 0), None), ((2, 64, 64, 56, 56, 3, 10, 1, 4, 0), None),          # two channel blocks, t = 12
 ]
@@ -46,7 +51,8 @@ def test_the_cases_reach_every_instantiation():
         assert rn.rnswino_plan_describe(_plan(case, HOST))["fused"] == kernel, case
         assert rn.rnswino_plan_describe(_plan(case, HOST | SEPARATE))["fused"] is None
         reached.add(kernel)
-    assert reached - {None} == {f"k12_transform_gemm<{ks}, {th}, {rm}>" for ks in (1, 2) for th in (1, 2) for rm in (1, 2)}
+    assert reached - {None} == {f"k12_transform_gemm<{ks}, {th}, {rm}, false>" for ks in (1, 2) for th in (1, 2) for rm in (1, 2)} | \
+        {f"k12_transform_gemm<{ks}, {th}, 1, true>" for ks in (1, 2) for th in (1, 2)}
 
 
 def test_the_split_leaves_no_item_out():
@@ -88,7 +94,7 @@ def test_one_kernel_transforms_and_multiplies(case, kernel):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("case", [CASES[0][0], CASES[12][0]])
+@pytest.mark.parametrize("case", [CASES[0][0], CASES[12][0], CASES[15][0]])
 def test_the_calls_around_it(case):
     """O in the workspace, V refused and there with two kernels, the fused re-quantisation, and a captured graph replayed between eager calls."""
     print("around transform and gemm", case, flush=True)
