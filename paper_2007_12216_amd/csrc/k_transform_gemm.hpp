@@ -1,8 +1,8 @@
-// K1 and K2 in one kernel, for layers of one block of 64 channels (33 to 64, fewer on few tiles, or 16 tiles of up to four; 8-bit moduli, t <= 10): the input
+// K1 and K2 in one kernel, for layers of one block of 64 channels (33 to 64, fewer on few tiles, or, t <= 10, 16 tiles of up to four; 8-bit moduli): the input
 // transform of 16 or 32 tiles and the residue GEMM over all their channels, V passing through LDS and never through device memory.
 //
 // Block = TH blocks of 16 tiles, 4 TH waves.  A wave gathers the pixels of 16 tiles in 16 channels once (the channels of one slice of V) and
-// keeps them in registers as operand fragments (128 registers at t = 9, 10).  Then the block goes through its items: four groups of four
+// keeps them in registers as operand fragments (128 registers at t = 9, 10; with three and four contraction steps, t > 10, two waves share a slice's channels).  Then the block goes through its items: four groups of four
 // transform points, the groups of all residues in a row (25 items of F(8,3) with four moduli; by 16 points of a residue there would be
 // 28, a sixteenth of a sixth of them used).  Per item every wave transforms its slice of the 16 points (products and residues as in k1_input_transform_tiles)
 // and writes 4 x 16 bytes a lane to LDS; behind the barrier wave (group, TH-th of the row blocks) multiplies the group's four points one after the
@@ -63,20 +63,25 @@ __device__ __forceinline__ void biased_lowbytes(uint32_t (&r)[4], int a0, int a1
       : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) : "v"(neg_p), "v"(a0), "v"(a1), "v"(a2), "v"(a3));
 }
 
+// Waves of a workgroup / 4: with three and four steps a wave takes half of a slice's channels, so that its pixels fit the same registers.
+constexpr int k12_quads(int ks1, int th) { return ks1 > 2 ? 2 * th : th; }
+
 template <int KS1, int TH, int RM, bool PACK>
-__global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
+__global__ __launch_bounds__(256 * k12_quads(KS1, TH), 2) void k12_transform_gemm(K12Args P) {
   Constant<ResidueParams> &R = constant(P.more);
-  constexpr int ROWS = KS1 == 1 ? 8 : 10;
-  constexpr int WPR = KS1 == 1 ? 2 : 3;                                // words of a row
+  constexpr int QUADS = k12_quads(KS1, TH), NU = KS1 > 2 ? 2 : 4;      // channel groups of four a wave takes
+  constexpr int ROWS = KS1 == 1 ? 8 : KS1 == 2 ? 10 : KS1 == 3 ? 12 : 16;
+  constexpr int WPR = KS1 == 1 ? 2 : KS1 == 4 ? 4 : 3;                 // words of a row
+  constexpr bool ALIGNED = KS1 < 4;                                    // a 16-byte load from a multiple of four holds a row
   constexpr int VBUF = 16 * TH * 1024;                                 // 16 points of V: [point][tile block][slice][tile][16 B]
   // gather: per wave [4 channels][step][slice h][tile][16 slots]; then two buffers of V
-  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * VBUF];
+  __shared__ __attribute__((aligned(16))) uint8_t lds[16384 * QUADS * KS1 > 2 * VBUF ? 16384 * QUADS * KS1 : 2 * VBUF];
   asm volatile("" ::"s"(P.more), "s"(P.x), "s"(P.KB), "s"(P.U), "s"(P.O), "s"(P.per_xcd), "s"(P.ntb), "s"(P.nkb), "s"(P.tile_groups_mul),
                "s"(P.tw_mul), "s"(P.th_mul), "s"(P.C), "s"(P.H), "s"(P.W), "s"(P.pad), "s"(P.tw), "s"(P.th), "s"(P.T), "s"(P.total), "s"(P.Q_mul), "s"(P.shifts),
                "s"(P.sizes));
   const int t = P.t(), P2 = t * t, CB1 = (P2 + 15) >> 4, Q = (P2 + 3) >> 2, HW = P.H * P.W;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, h = lane >> 4, col = lane & 15;
-  const int slice = wave & 3, th = wave >> 2;                          // of V: what this wave transforms
+  const int slice = wave & 3, th = KS1 > 2 ? 0 : wave >> 2, u0 = KS1 > 2 ? NU * (wave >> 2) : 0;             // of V: what this wave transforms
   const int unit = (int)(blockIdx.x & 7) * P.per_xcd + (int)(blockIdx.x >> 3);
   const int tile_groups = (P.ntb + TH - 1) / TH, which = (int)fast_div((uint32_t)unit, P.by_tile_groups()), tb0 = (unit - which * tile_groups) * TH;
   const int part = PACK ? which / P.row_parts() : which;
@@ -97,7 +102,7 @@ __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
   const Origin own = PACK ? Origin() : origin(min(tau, P.T - 1));
   const int Tg = PACK ? (P.T + 15) >> 4 : P.T;
   auto segment = [&](int u) -> Segment {
-    const int c64 = 16 * u + 4 * slice + h;                            // channel order of layout.hpp
+    const int c64 = 16 * (u0 + u) + 4 * slice + h;                            // channel order of layout.hpp
     const int tile = PACK ? (4 * u + slice) * Tg + tau : tau, ch = PACK ? h : c64;
     Segment s;
     s.live = tau < Tg && tile < P.T && ch < P.C;
@@ -106,22 +111,23 @@ __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
     return s;
   };
   auto wanted = [&](const Segment &s, int a) { return s.from + min(max(s.o.y0 + a, 0), P.H - 1) * P.W; };
-  v4i pix[16][KS1];
+  auto load_at = [&](int want) { return ALIGNED ? aligned_segment_at(want, mis, last) : min(max(want, mis), last); };
+  v4i pix[4 * NU][KS1];
   uint8_t *const staged = lds + wave * (4 * KS1 * 1024);
   auto request = [&](int u, v4i (&val)[ROWS], int &clamped) {
     const Segment s = segment(u);
     clamped = 0;
 #pragma unroll
     for (int a = 0; a < ROWS; ++a) {
-      const int want = wanted(s, a), at = aligned_segment_at(want, mis, last);
-      clamped |= at ^ (want & ~3);
+      const int want = wanted(s, a), at = load_at(want);
+      clamped |= at ^ (ALIGNED ? want & ~3 : want);
       __builtin_memcpy(&val[a], xa + (uint32_t)at, 16);                // one 16-byte load
     }
   };
   auto settle = [&](int u, v4i (&val)[ROWS], int clamped) {
     const Segment s = segment(u);
     const unsigned long long m0 = byte_range(max(-s.o.x0, 0), min(t, P.W - s.o.x0), 0), m1 = byte_range(max(-s.o.x0, 0), min(t, P.W - s.o.x0), 8);
-    const uint32_t mask[3] = {s.live ? (uint32_t)m0 : 0u, s.live ? (uint32_t)(m0 >> 32) : 0u, s.live ? (uint32_t)m1 : 0u};
+    const uint32_t mask[4] = {s.live ? (uint32_t)m0 : 0u, s.live ? (uint32_t)(m0 >> 32) : 0u, s.live ? (uint32_t)m1 : 0u, s.live ? (uint32_t)(m1 >> 32) : 0u};
     const int rows_in = min(t, P.H - s.o.y0);                          // row a is inside the image and the tile: -y0 <= a < rows_in
     uint32_t slots[16 * KS1];
 #pragma unroll
@@ -129,19 +135,20 @@ __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
     if (__builtin_expect(__any(clamped != 0), 0)) {
 #pragma unroll
       for (int a = 0; a < ROWS; ++a) {
-        const int want = wanted(s, a), at = aligned_segment_at(want, mis, last);
+        const int want = wanted(s, a), at = load_at(want);
         unsigned long long w0 = (uint32_t)val[a][0] | (unsigned long long)(uint32_t)val[a][1] << 32;
         unsigned long long w1 = (uint32_t)val[a][2] | (unsigned long long)(uint32_t)val[a][3] << 32;
         move_segment(want - at, w0, w1);
         slots[a * WPR] = (uint32_t)w0; slots[a * WPR + 1] = (uint32_t)(w0 >> 32);
         if (WPR > 2) slots[a * WPR + 2] = (uint32_t)w1;
+        if (WPR > 3) slots[a * WPR + 3] = (uint32_t)(w1 >> 32);
       }
     } else {
 #pragma unroll
       for (int a = 0; a < ROWS; ++a) {
         const uint32_t by = (uint32_t)wanted(s, a);                    // its low two bits count
 #pragma unroll
-        for (int d = 0; d < WPR; ++d) slots[a * WPR + d] = __builtin_amdgcn_alignbyte((uint32_t)val[a][d + 1], (uint32_t)val[a][d], by);
+        for (int d = 0; d < WPR; ++d) slots[a * WPR + d] = ALIGNED ? __builtin_amdgcn_alignbyte((uint32_t)val[a][ALIGNED ? d + 1 : d], (uint32_t)val[a][d], by) : (uint32_t)val[a][d];
       }
     }
 #pragma unroll
@@ -175,7 +182,7 @@ __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
     const int g = min(number, ngroups - 1), i = (int)(((uint32_t)g * P.Q_mul) >> 16);      // exact: 200 groups of 25 at most
     return {i, g - i * Q};
   };
-  const int wq = wave & 3, half = wave >> 2;                           // of O: what this wave multiplies: a group, every TH-th set of row blocks
+  const int wq = wave & 3, half = wave >> 2;                           // of O: what this wave multiplies: a group, every QUADS-th set of row blocks
   auto mine = [&](int it) -> Group {
     Group p = group(4 * it + wq);
     p.i = __builtin_amdgcn_readfirstlane(p.i);
@@ -193,13 +200,13 @@ __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
     for (int s = 0; s < KS1; ++s) tab[s] = *(const v4i *)(P.KB + s * 1024 + at);
     consts = *(const v4i *)((const char *)P.more + (uint32_t)group(4 * it + h).i * (uint32_t)sizeof(Residue8));
   };
-  const int sets = (P.nkb + RM * TH - 1) / (RM * TH);
+  const int sets = (P.nkb + RM * QUADS - 1) / (RM * QUADS);
   // Fragments of set `set` at the points of a group: uniform addresses plus the lane's.  (Were the lane's offset known to be the same for the whole
   // loop, the compiler would widen it in front of it and add 64-bit vectors for every load.)
   const uint32_t slab_bytes = (uint32_t)P.nkb * 1024u;
   struct Rows { const int8_t *first; uint32_t step; int last; };       // of U: first row block at the group's first point, to the next row block, last point's number
   auto rows_of = [&](const Group &p, int set) -> Rows {
-    const int kb = min((set * TH + half) * RM, P.nkb - 1);             // past the last row block: that one again
+    const int kb = min((set * QUADS + half) * RM, P.nkb - 1);             // past the last row block: that one again
     return {P.U + (size_t)(uint32_t)(p.i * P2 + 4 * p.q) * slab_bytes + (size_t)(uint32_t)kb * 1024u, kb + 1 < P.nkb ? 1024u : 0u, min(P2 - 1 - 4 * p.q, 3)};
   };
   auto load_u = [&](const Rows &rows, int e, uint32_t lane_at) {
@@ -231,14 +238,16 @@ __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
     request(1, vb, cb);
     __builtin_amdgcn_sched_barrier(0);
     settle(0, va, ca);
-    request(2, va, ca);
+    if constexpr (NU == 4) request(2, va, ca);
     __builtin_amdgcn_sched_barrier(0);
     settle(1, vb, cb);
-    request(3, vb, cb);
-    __builtin_amdgcn_sched_barrier(0);
-    settle(2, va, ca);
-    __builtin_amdgcn_sched_barrier(0);
-    settle(3, vb, cb);
+    if constexpr (NU == 4) {
+      request(3, vb, cb);
+      __builtin_amdgcn_sched_barrier(0);
+      settle(2, va, ca);
+      __builtin_amdgcn_sched_barrier(0);
+      settle(3, vb, cb);
+    }
     __builtin_amdgcn_sched_barrier(0);                                 // (requested any earlier, these take more registers than there are: 0.5 us a call)
     load_table(item);
     if constexpr (PACK) load_words(at);
@@ -261,9 +270,9 @@ __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
       const float inv = __int_as_float(consts[0]), qb = __int_as_float(consts[1]);
       const int neg_p = consts[2];
       const v4i start = (v4i){consts[3], consts[3], consts[3], consts[3]};
-      v4i out[4];                                                      // out[e]: 16 channels of point 16 cbk + 4 h + e
+      uint32_t out[4][NU];                                             // out[e]: the wave's 16 (or 8) channels of the point that table row 4 h + e is for
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < NU; ++u) {
         v4i acc[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -276,11 +285,15 @@ __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
         {
           uint32_t low[4];
           biased_lowbytes(low, acc[0][e], acc[1][e], acc[2][e], acc[3][e], inv, qb, neg_p);
-          out[e][u] = (int)pack_low_bytes(low[0], low[1], low[2], low[3]);
+          out[e][u] = pack_low_bytes(low[0], low[1], low[2], low[3]);
         }
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) *(v4i *)(lds + buf + ((4 * h + e) * TH + th) * 1024 + slice * 256 + col * 16) = out[e];
+      for (int e = 0; e < 4; ++e) {
+        uint8_t *const to = lds + buf + ((4 * h + e) * TH + th) * 1024 + slice * 256 + col * 16 + u0 * 4;
+        if constexpr (NU == 4) *(v4i *)to = (v4i){(int)out[e][0], (int)out[e][1], (int)out[e][NU - 2], (int)out[e][NU - 1]};
+        else *(v2i *)to = (v2i){(int)out[e][0], (int)out[e][1]};
+      }
     }
     const int following = after(item);
     load_table(following);                                             // (once more than there are items: fetched, not used)
@@ -363,7 +376,7 @@ __global__ __launch_bounds__(256 * TH, 2) void k12_transform_gemm(K12Args P) {
             for (int j = 0; j < 4; ++j) word[rm][x][j] = e == 0 ? low[j] : __builtin_amdgcn_perm(low[j], word[rm][x][j], sel);
           }
       }
-      const int kb = min((set * TH + half) * RM, P.nkb - 1);
+      const int kb = min((set * QUADS + half) * RM, P.nkb - 1);
       char *row = (char *)P.O + (size_t)(uint32_t)((uint32_t)(at.i * Q + at.q) * (uint32_t)P.ntb * 64u) + (size_t)((uint32_t)(kb * 16) * krow);
 #pragma unroll
       for (int rm = 0; rm < RM; ++rm) {

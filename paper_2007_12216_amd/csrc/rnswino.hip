@@ -356,32 +356,37 @@ K12Choice choose_k12(const Dims &d, uint32_t flags, int n_cus) {
   // pairs, in the mean of all 0.93 of the time of two kernels, from 0.5 (64 -> 9 at 193 x 193, F(4,5), batch 6, 117.5 -> 60.8 us a layer) to 1.08.  With more
   // filters fragments of U cross the L2 once per 32 tiles (64 -> 500 at 75 x 75, F(6,3), batch 7 105.5 / 107.9, 33 -> 513 at 103 x 103, F(4,5) 124.5 / 148.3);
   // with fewer pairs the few blocks' latencies decide (48 -> 49 at 46 x 46, one modulus, batch 5 10.3 / 11.6, 16 -> 16 at 16 x 16 7.7 / 10.6).
+  // (Those were t <= 10.)  With three steps, t = 11, 12, 14 of them were from 400 pairs on 0.83 of it (0.65 to 0.99; 64 -> 283 at 36 x 36, F(8,5), batch 8, 468,
+  // 35.9 / 33.8; below, 64 -> 202 at 42 x 42, three moduli, batch 5, 324, 25.3 / 27.0), with four, whose rows take unaligned loads, 8 from 1400 on 0.89 (0.83 to
+  // 0.98; 64 -> 64 at 112 x 112, F(14,3), batch 8, 2048, 69.4 / 63.4; below both ways: 40 -> 80 at 94 x 94, F(12,5), batch 5, 1280, 47.5 / 52.8, 64 -> 113 at
+  // 157 x 157, batch 2, 1200, 58.6 / 53.6; 48 -> 64 at 35 x 35, batch 8, 320, 19.1 / 24.9).
   // Packed layers of up to four channels: 70 random ones (1 to 4 channels, 8 to 256 filters, 2 to 4 moduli) were from 12 500 (tile block, item, filter)
   // triples on 0.88 of it (0.81 to 0.95; 3 -> 64 at 224 x 224, batch 8, 107.4 -> 87.6), below mostly above it (the same at batch 2, 8 500, 34.9 / 37.4,
   // at batch 1 23.5 / 26.8; 3 -> 26 at 220 x 220, F(4,5), batch 3, 11 200, 29.1 / 31.9).
-  if (d.wide || d.KS1 > 2 || d.Cp != 64 || (flags & (RNSWINO_FLAG_GEMM_BLOCK_64X16 | RNSWINO_FLAG_SEPARATE_KERNELS)) || elements < 16 ||
+  if (d.wide || d.Cp != 64 || (flags & (RNSWINO_FLAG_GEMM_BLOCK_64X16 | RNSWINO_FLAG_SEPARATE_KERNELS)) || elements < 16 ||
       elements + d.W + 2LL * d.pad + 16 >= (1LL << 31))
     return c;
-  c.pack = d.TL == 16;
+  c.pack = d.TL == 16 && d.KS1 <= 2;
   if (c.pack) c.fused = d.K <= 8192 && (long long)ntb * items * d.K >= 12500;
-  else c.fused = d.TL == 1 && nkb <= 18 && (long long)ntb * items >= 150;
+  else c.fused = d.TL == 1 && nkb <= 18 && (long long)ntb * items >= (d.KS1 <= 2 ? 150 : d.KS1 == 3 ? 400 : 1400);
   if (!c.fused) return c;
   c.KS1 = d.KS1;
   // The split.  A workgroup takes 5 us to gather (3 on packed layers) and 0.8 us an item plus 0.4 per 32 rows and 16 tiles (0.08 per filter); two on a compute
   // unit take 1.7 (1.5) times the work of one, and so does one of 32 tiles.  Over 43 layers the choice takes 0.2 % longer than the best split (6 % at
   // worst), over 21 packed ones 0.2 % (3 %).  Packed layers take one item a workgroup, and up to three parts of the filters more than the 64 that fit a wave's lanes
   // ask for (two items: 3 -> 64 at 224 x 224, batch 8, 110.9 us a layer).
-  const double gather = c.pack ? 3.0 : 5.0, factor = c.pack ? 1.5 : 1.7;
+  const bool wide_tile = d.KS1 > 2;                    // one workgroup of 16 tiles a compute unit: 6 us to gather, 1 us an item plus 0.2 per 16 rows of a wave
+  const double gather = c.pack ? 3.0 : wide_tile ? 6.0 : 5.0, factor = c.pack ? 1.5 : 1.7;
   const int row_parts0 = c.pack ? (d.K + 63) / 64 : 1, row_parts1 = c.pack ? row_parts0 + 3 : 1, most = c.pack ? 1 : items;
   double best = 0.0;
-  for (int TH = 1; TH <= 2; ++TH) {
-    const int RM = !c.pack && nkb > TH ? 2 : 1, sets = (nkb + RM * TH - 1) / (RM * TH), groups = (ntb + TH - 1) / TH;
+  for (int TH = 1; TH <= (wide_tile ? 1 : 2); ++TH) {
+    const int quads = k12_quads(c.KS1, TH), RM = !c.pack && nkb > quads ? 2 : 1, sets = (nkb + RM * quads - 1) / (RM * quads), groups = (ntb + TH - 1) / TH;
     for (int row_parts = row_parts0; row_parts <= row_parts1; ++row_parts) {
-      const double item = 0.8 + (c.pack ? 0.08 * ((d.K + row_parts - 1) / row_parts) : 0.2 * sets * RM * TH);
+      const double item = wide_tile ? 1.0 + 0.2 * sets * RM : 0.8 + (c.pack ? 0.08 * ((d.K + row_parts - 1) / row_parts) : 0.2 * sets * RM * TH);
       for (int part = 1; part <= most; ++part) {
         const long long rounds = ((long long)groups * row_parts * ((items + part - 1) / part) + cus - 1) / cus;
         const double alone = gather + part * item, together = gather + factor * part * item;
-        const double cost = TH == 2 ? rounds * together : rounds / 2 * 1.1 * together + rounds % 2 * alone;
+        const double cost = wide_tile ? rounds * alone : TH == 2 ? rounds * together : rounds / 2 * 1.1 * together + rounds % 2 * alone;
         if (c.TH == 0 || cost < best) { best = cost; c.TH = TH; c.RM = RM; c.part = part; c.row_parts = (unsigned)row_parts; }
       }
     }
@@ -492,6 +497,7 @@ K3Params make_conversion(const Dims &d, const KParams &P, int n_cus) {
 #define RNSW_K2L_TABLE(X) X(2, 2, 4, 4, 3) X(4, 1, 2, 4, 4) X(4, 1, 1, 1, 4)
 #define RNSW_K12_TABLE(X) \
   X(1, 1, 1, false) X(1, 1, 2, false) X(1, 2, 1, false) X(1, 2, 2, false) X(2, 1, 1, false) X(2, 1, 2, false) X(2, 2, 1, false) X(2, 2, 2, false) \
+  X(3, 1, 1, false) X(3, 1, 2, false) X(4, 1, 1, false) X(4, 1, 2, false) \
   X(1, 1, 1, true) X(1, 2, 1, true) X(2, 1, 1, true) X(2, 2, 1, true)
 #define RNSW_K3_NK(X, nres, wd, fs) X(nres, 1, wd, fs) X(nres, 2, wd, fs) X(nres, 3, wd, fs) X(nres, 4, wd, fs)
 #define RNSW_K3_TABLE(X) \
@@ -551,7 +557,7 @@ bool launch_k12(const K12Choice &c, const K12Args &L, const int8_t *x, const int
   P.x = x; P.U = U; P.O = O;
 #define RNSW_X(ks, groups, rm, pk) \
   if (c.KS1 == ks && c.TH == groups && c.RM == rm && c.pack == pk) { \
-    if (!dry) hipLaunchKernelGGL((k12_transform_gemm<ks, groups, rm, pk>), grid, dim3(256 * groups), 0, st, P); return true; }
+    if (!dry) hipLaunchKernelGGL((k12_transform_gemm<ks, groups, rm, pk>), grid, dim3(256 * k12_quads(ks, groups)), 0, st, P); return true; }
   RNSW_K12_TABLE(RNSW_X)
 #undef RNSW_X
   return false;

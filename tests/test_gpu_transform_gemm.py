@@ -34,6 +34,11 @@ CASES = [
     ((5, 4, 102, 120, 117, 3, 8, 1, 4, 2), "k12_transform_gemm<2, 1, 1, true>"),
     ((7, 1, 125, 103, 69, 3, 8, 1, 4, 3), "k12_transform_gemm<2, 2, 1, true>"),
     ((6, 3, 120, 100, 104, 3, 8, 4, 4, 0), "k12_transform_gemm<2, 1, 1, true>"),
+    ((3, 64, 16, 80, 61, 5, 8, 2, 5, 1), "k12_transform_gemm<3, 1, 1, false>"),     # t = 12
+    ((5, 40, 75, 70, 58, 3, 9, 1, 4, 3), "k12_transform_gemm<3, 1, 2, false>"),     # t = 11: 121 points
+    ((6, 33, 7, 101, 93, 5, 12, 2, 4, 2), "k12_transform_gemm<4, 1, 1, false>"),    # t = 16
+    ((4, 64, 50, 112, 123, 3, 11, 6, 4, 1), "k12_transform_gemm<4, 1, 2, false>"),  # t = 13, padding of half a tile
+    ((8, 48, 64, 35, 35, 5, 12, 2, 4, 0), None),
     ((9, 7, 30, 80, 80, 3, 2, 1, 4, 0), None), ((1, 3, 64, 224, 224, 3, 8, 1, 3, 0), None),           # 8 tiles a block; too few
     ((4, 64, 290, 60, 60, 3, 8, 1, 4, 0), None), ((1, 64, 64, 28, 28, 3, 8, 1, 4, 0), None),          # past either line
     ((2, 65, 64, 56, 56, 3, 8, 1, 4, 0), None), ((2, 64, 64, 56, 56, 3, 10, 1, 4, 0), None),          # two channel blocks, t = 12
@@ -52,7 +57,7 @@ def test_the_cases_reach_every_instantiation():
         assert rn.rnswino_plan_describe(_plan(case, HOST | SEPARATE))["fused"] is None
         reached.add(kernel)
     assert reached - {None} == {f"k12_transform_gemm<{ks}, {th}, {rm}, false>" for ks in (1, 2) for th in (1, 2) for rm in (1, 2)} | \
-        {f"k12_transform_gemm<{ks}, {th}, 1, true>" for ks in (1, 2) for th in (1, 2)}
+        {f"k12_transform_gemm<{ks}, 1, {rm}, false>" for ks in (3, 4) for rm in (1, 2)} | {f"k12_transform_gemm<{ks}, {th}, 1, true>" for ks in (1, 2) for th in (1, 2)}
 
 
 def test_the_split_leaves_no_item_out():
