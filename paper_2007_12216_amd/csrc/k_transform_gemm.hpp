@@ -19,7 +19,7 @@
 //
 // PACK: layers of up to four channels, 16 tiles a block.  A fragment of U then is four bytes in 16 places and zeros: made in registers from one byte quadruple
 // per filter and point, where the GEMM fetched 1 KiB (and exchanged its results through LDS).  What bounds it are the words of O, 123 MB of 3 -> 64 at 224 x 224,
-// batch 8, and the residues: K1 8.9 + K2 45.6 us, so 34 (a layer 107.4 -> 87.6; with fragments from L2 143).  The filters may be split over workgroups, each
+// batch 8, and the residues: K1 8.9 + K2 45.6 us, so 41 (a layer with cold operands 107.4 -> 87.6; with fragments from L2 143).  The filters may be split over workgroups, each
 // transforming anew.
 // Grid: one-dimensional, ceil(Tp / (16 TH)) x parts of the filters x parts of the items, rounded up to a multiple of 8 (kernels_common.hpp).
 #pragma once
