@@ -2,9 +2,10 @@
 // transform of 16 or 32 tiles and the residue GEMM over all their channels, V passing through LDS and never through device memory.
 //
 // Block = TH blocks of 16 tiles, 4 TH waves.  A wave gathers the pixels of 16 tiles in 16 channels once (the channels of one slice of V) and
-// keeps them in registers as operand fragments (128 registers at t = 9, 10; with three and four contraction steps, t > 10, two waves share a slice's channels).  Then the block goes through its items: four groups of four
+// keeps them in registers as operand fragments (128 registers at t = 9, 10; with three and four contraction steps, t > 10, two waves share a slice's
+// channels).  Then the block goes through its items: four groups of four
 // transform points, the groups of all residues in a row (25 items of F(8,3) with four moduli; by 16 points of a residue there would be
-// 28, a sixteenth of a sixth of them used).  Per item every wave transforms its slice of the 16 points (products and residues as in k1_input_transform_tiles)
+// 28, four of them with four points).  Per item every wave transforms its slice of the 16 points (products and residues as in k1_input_transform_tiles)
 // and writes 4 x 16 bytes a lane to LDS; behind the barrier wave (group, TH-th of the row blocks) multiplies the group's four points one after the
 // other with fragments of U from L2, requested a set of row blocks ahead, and stores finished words of O (as k2_residue_gemm_lds does).  V has two buffers: one
 // barrier an item.
