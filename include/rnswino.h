@@ -71,7 +71,7 @@ enum {
                                               inverse transform were fused into the GEMM (section 6: the stages
                                               compose per tile group).  Same result, slower; used to price that fusion */
   RNSWINO_FLAG_SEPARATE_KERNELS = 8u       /* the input transform and the residue GEMM as two kernels on every layer (some layers run
-                                              them as one, see rnswino_plan_describe): V is then in the workspace after a call   */
+                                              them as one, see rnswino_plan_describe): V itself is then in the workspace after a call */
 };
 
 typedef struct rnswino_plan_s rnswino_plan_t;   /* opaque, owned by the library */
@@ -241,8 +241,9 @@ int rnswino_plan_get_mrc_inverse(const rnswino_plan_t *plan, int l, int j, uint3
  *   k2_residue_gemm<4, 4, 2, false> grid=6400 xgroup=1
  *   k3_inverse_crt<4, 2, false, true> grid=784x1
  *   conversion=unreduced-binary32
- * (grid=XxYxZ where the launch has a third extent).  A last line "fused=k12_transform_gemm<2, 2, 2, false> grid=200 part=25" says that one kernel
- * takes the place of the first two except in rnswino_conv2d_events (never with RNSWINO_FLAG_SEPARATE_KERNELS).
+ * (grid=XxYxZ where the launch has a third extent).  A last line "fused=k12_transform_gemm<2, 2, 2, false> grid=200 copies=98 part=25" says that one kernel
+ * takes the place of the first two except in rnswino_conv2d_events (never with RNSWINO_FLAG_SEPARATE_KERNELS);
+ * `copies` more workgroups of it leave a copy of the input in the workspace, in V's place, which rnswino_debug_stage transforms.
  * conversion: "unreduced-binary32" / "unreduced-binary64" = CRT sum over unreduced accumulators with the quotient rounded
  * in that precision; "reduced-binary32" / "reduced-binary64" = over reduced residues; "reduced-binary64-mul32" = the same
  * with full 32-bit multiplies (a partial product P/m_i of 2^24 or more, or three and more 16-bit moduli in most cases).  Works on host-only plans (their
@@ -268,8 +269,8 @@ int64_t rnswino_plan_dynamic_range(const rnswino_plan_t *plan);
  * plain index order of section 6 (synchronises the device; test use only):
  *   RNSWINO_STAGE_U: src_dev = U_dev,         host_out [n][t*t][K][C]
  *   RNSWINO_STAGE_V: src_dev = workspace_dev, host_out [n][t*t][T][C],  T = N * ceil(Ho/m) * ceil(Wo/m)
- *                    (RNSWINO_E_UNSUPPORTED where one kernel transforms and multiplies: V is never in device memory then; plan the
- *                    layer with RNSWINO_FLAG_SEPARATE_KERNELS to see it)
+ *                    (where one kernel transforms and multiplies, the input transform runs here, on the input that the call left in
+ *                    the workspace, in memory allocated for that)
  *   RNSWINO_STAGE_O: src_dev = workspace_dev, host_out [n][t*t][K][T]
  * Tile index tau = (n * th + ty) * tw + tx.
  */

@@ -71,6 +71,18 @@ RNSW_HD unsigned long long byte_range(int lo, int hi, int at) {
   return below_h & ~below_l;
 }
 
+// ---- a copy by several workgroups ----
+// Bytes [first, end) of workgroup `block` of `copies`, whole steps but for the last share (2^31 bytes and 256 steps of 2^16 at most: no sum leaves 32
+// bits); a load of 16 bytes that would end behind the last byte ends with it.
+struct CopyShare {
+  uint32_t first, end;
+};
+RNSW_HD CopyShare copy_share(uint32_t bytes, uint32_t block, uint32_t copies, uint32_t step) {
+  const uint32_t share = (bytes / copies / step + 1) * step, first = block * share;
+  return {first, first + share < bytes ? first + share : bytes};
+}
+RNSW_HD uint32_t piece_at(uint32_t at, uint32_t bytes) { return at < bytes - 16 ? at : bytes - 16; }
+
 // ---- staged patches (direct convolution) ----
 // The longest run of padded pixels that `pixels` consecutive output pixels, beginning at a multiple of `pixels`, need for all r x r
 // taps: every row boundary among them adds r - 1 pixels of border, every image boundary r - 1 rows more.

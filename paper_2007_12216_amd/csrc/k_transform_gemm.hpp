@@ -22,7 +22,8 @@
 // per filter and point, where the GEMM fetched 1 KiB (and exchanged its results through LDS).  What bounds it are the words of O, 123 MB of 3 -> 64 at 224 x 224,
 // batch 8, and the residues: K1 8.9 + K2 45.6 us, so 41 (a layer with cold operands 107.4 -> 87.6; with fragments from L2 143).  The filters may be split over workgroups, each
 // transforming anew.
-// Grid: one-dimensional, ceil(Tp / (16 TH)) x parts of the filters x parts of the items, rounded up to a multiple of 8 (kernels_common.hpp).
+// Grid: one-dimensional, ceil(Tp / (16 TH)) x parts of the filters x parts of the items, rounded up to a multiple of 8 (kernels_common.hpp); in
+// front of them the workgroups of keep_input(), a multiple of 8 too.
 #pragma once
 #include "k_input_transform.hpp"
 #include "k_residue_gemm.hpp"
@@ -42,6 +43,7 @@ struct K12Args {
   uint32_t Q_mul;             // ceil(2^16 / Q), Q = ceil(t*t / 4)
   uint32_t shifts;            // bytes: of the divisions by the tile blocks' groups, tw, th; packed layers: parts the filters are split into
   uint32_t sizes;             // bytes: m, t, n, items of a part
+  uint32_t kept;              // the input's copy: where it lies in front of O, in 256 bytes, and in the upper five bits its workgroups / 8 (0: none is kept)
   RNSW_HD FastDiv by_tile_groups() const { return {tile_groups_mul, shifts & 31u}; }
   RNSW_HD FastDiv by_tw() const { return {tw_mul, shifts >> 8 & 31u}; }
   RNSW_HD FastDiv by_th() const { return {th_mul, shifts >> 16 & 31u}; }
@@ -50,6 +52,8 @@ struct K12Args {
   RNSW_HD int t() const { return (int)byte_of(sizes, 1); }
   RNSW_HD int n() const { return (int)byte_of(sizes, 2); }
   RNSW_HD int part() const { return (int)(sizes >> 24); }
+  RNSW_HD size_t kept_offset() const { return (size_t)(kept & 0x07FFFFFFu) * 256u; }
+  RNSW_HD uint32_t copies() const { return kept >> 27 << 3; }
 };
 static_assert(sizeof(K12Args) <= 112, "kernels_common.hpp");
 
@@ -63,6 +67,26 @@ __device__ __forceinline__ void biased_lowbytes(uint32_t (&r)[4], int a0, int a1
   asm("v_mad_i32_i24 %0, %0, %4, %5\n\tv_mad_i32_i24 %1, %1, %4, %6\n\tv_mad_i32_i24 %2, %2, %4, %7\n\tv_mad_i32_i24 %3, %3, %4, %8"
       : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) : "v"(neg_p), "v"(a0), "v"(a1), "v"(a2), "v"(a3));
 }
+
+// A call leaves in the workspace what V can be had from again: not V itself but, in its place, the input (rnswino_debug_stage transforms it).  Workgroup
+// `block` of `copies` copies its share of it, 16 bytes a load, the last ones moved back to end with the input, which has 16 bytes and more.
+// They come first and run on compute units that the others leave idle: 64 -> 64 at 224 x 224, batch 8, 125.5 us a layer without them, 129.5 with them;
+// 64 -> 128 at 112 x 112, pooled, 51.4 and 51.9 (behind the others, one per 256 KB, 54), the stack at batch 8 766.8 and 770.1.
+template <int THREADS>
+__device__ __forceinline__ void keep_input(const int8_t *x, int8_t *to, uint32_t block, uint32_t copies, uint32_t bytes) {
+  constexpr int AHEAD = 2;                             // (eight take what the others wait for: 0.5 us of 64 -> 64 at 224 x 224, batch 1)
+  constexpr uint32_t STEP = THREADS * 16 * AHEAD;
+  typedef int Bytes __attribute__((ext_vector_type(4), aligned(1), may_alias));
+  const CopyShare own = copy_share(bytes, block, copies, STEP);
+  for (uint32_t at = own.first + threadIdx.x * 16u; at < own.end; at += STEP) {
+    Bytes val[AHEAD];
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) val[j] = *(const Bytes *)(x + piece_at(at + j * (THREADS * 16u), bytes));
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) *(Bytes *)(to + piece_at(at + j * (THREADS * 16u), bytes)) = val[j];
+  }
+}
+__global__ __launch_bounds__(256) void k_keep_input(const int8_t *x, int8_t *to, uint32_t copies, uint32_t bytes) { keep_input<256>(x, to, blockIdx.x, copies, bytes); }
 
 // Waves of a workgroup / 4: with three and four steps a wave takes half of a slice's channels, so that its pixels fit the same registers.
 constexpr int k12_quads(int ks1, int th) { return ks1 > 2 ? 2 * th : th; }
@@ -79,11 +103,13 @@ __global__ __launch_bounds__(256 * k12_quads(KS1, TH), 2) void k12_transform_gem
   __shared__ __attribute__((aligned(16))) uint8_t lds[16384 * QUADS * KS1 > 2 * VBUF ? 16384 * QUADS * KS1 : 2 * VBUF];
   asm volatile("" ::"s"(P.more), "s"(P.x), "s"(P.KB), "s"(P.U), "s"(P.O), "s"(P.per_xcd), "s"(P.ntb), "s"(P.nkb), "s"(P.tile_groups_mul),
                "s"(P.tw_mul), "s"(P.th_mul), "s"(P.C), "s"(P.H), "s"(P.W), "s"(P.pad), "s"(P.tw), "s"(P.th), "s"(P.T), "s"(P.total), "s"(P.Q_mul), "s"(P.shifts),
-               "s"(P.sizes));
+               "s"(P.sizes), "s"(P.kept));
+  if (blockIdx.x < P.copies()) return keep_input<256 * QUADS>(P.x, (int8_t *)P.O - P.kept_offset(), blockIdx.x, P.copies(), P.total);
+  const uint32_t id = blockIdx.x - P.copies();
   const int t = P.t(), P2 = t * t, CB1 = (P2 + 15) >> 4, Q = (P2 + 3) >> 2, HW = P.H * P.W;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, h = lane >> 4, col = lane & 15;
   const int slice = wave & 3, th = KS1 > 2 ? 0 : wave >> 2, u0 = KS1 > 2 ? NU * (wave >> 2) : 0;             // of V: what this wave transforms
-  const int unit = (int)(blockIdx.x & 7) * P.per_xcd + (int)(blockIdx.x >> 3);
+  const int unit = (int)(id & 7) * P.per_xcd + (int)(id >> 3);
   const int tile_groups = (P.ntb + TH - 1) / TH, which = (int)fast_div((uint32_t)unit, P.by_tile_groups()), tb0 = (unit - which * tile_groups) * TH;
   const int part = PACK ? which / P.row_parts() : which;
   const int ngroups = P.n() * Q;

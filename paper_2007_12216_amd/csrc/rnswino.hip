@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -152,8 +153,9 @@ struct DeviceParams {
 };
 static_assert(sizeof(DeviceParams) <= PARAMS_BYTES, "build_tables() leaves them that much");
 // The input transform and the GEMM in one kernel (k_transform_gemm.hpp).  TH: tile blocks of 16 a workgroup takes; RM: row blocks a wave multiplies at once;
-// part: items of a workgroup, parts: what that splits the items of its tiles into; row_parts: packed layers, what the filters are split into.
-struct K12Choice { bool fused, pack; int KS1, TH, RM, part; unsigned parts, row_parts, blocks; };
+// part: items of a workgroup, parts: what that splits the items of its tiles into; row_parts: packed layers, what the filters are split into; copies:
+// workgroups that copy the input into V's place.
+struct K12Choice { bool fused, pack; int KS1, TH, RM, part; unsigned parts, row_parts, blocks, copies; };
 struct LayerParams {
   KParams k;
   K1Args k1;
@@ -393,6 +395,10 @@ K12Choice choose_k12(const Dims &d, uint32_t flags, int n_cus) {
   }
   c.parts = (unsigned)((items + c.part - 1) / c.part);
   c.blocks = (unsigned)(((long long)((ntb + c.TH - 1) / c.TH) * c.parts * c.row_parts + 7) / 8 * 8);
+  // As many copies as the other workgroups leave compute units idle, or as finish with them at 24 KB a us, none of less than 16 KiB.  (V is never smaller than
+  // the input: a tile of t x t pixels for m x m outputs, 64 channels.)
+  const double idle = cus - 1 - (int)((c.blocks - 1) % (unsigned)cus), copies = std::min(std::max(idle, elements / (24e3 * best)), elements / 16384.0);
+  c.copies = 8u * (unsigned)std::min(std::max(copies / 8, 1.0), 31.0);
   return c;
 }
 
@@ -410,6 +416,7 @@ K12Args make_k12(const Dims &d, const KParams &P, const DeviceParams *dev, const
   q.Q_mul = (65536u + (uint32_t)d.Q - 1) / (uint32_t)d.Q;
   q.C = d.C; q.H = d.H; q.W = d.W; q.pad = d.pad; q.tw = d.tw; q.th = d.th; q.T = d.T;
   q.total = (int)((long long)d.N * d.C * d.H * d.W);
+  q.kept = (uint32_t)(align256(v_bytes(d)) / 256) | c.copies / 8 << 27;           // (V has at most four times the bytes of O, below 16 GiB)
   return q;
 }
 
@@ -551,9 +558,10 @@ bool launch_k2(const Dims &d, uint32_t flags, const K2Args &L, const int8_t *U, 
 }
 
 // ---- K1 and K2 in one ----
-bool launch_k12(const K12Choice &c, const K12Args &L, const int8_t *x, const int8_t *U, uint32_t *O, hipStream_t st, bool dry = false) {
-  const dim3 grid(c.blocks);
+bool launch_k12(const K12Choice &c, const K12Args &L, const int8_t *x, const int8_t *U, uint32_t *O, bool keep, hipStream_t st, bool dry = false) {
+  const dim3 grid(c.blocks + (keep ? c.copies : 0));
   K12Args P = L;
+  if (!keep) P.kept = 0;
   P.x = x; P.U = U; P.O = O;
 #define RNSW_X(ks, groups, rm, pk) \
   if (c.KS1 == ks && c.TH == groups && c.RM == rm && c.pack == pk) { \
@@ -610,10 +618,10 @@ std::string all_kernel_variants() {
   return out;
 }
 
-// epi: 0 = int32 y_dev; 1 / 2 = int8 act_dev after shift/clamp (/ and 2x2 max-pool)
+// epi: 0 = int32 y_dev; 1 / 2 = int8 act_dev after shift/clamp (/ and 2x2 max-pool); keep: somebody may ask for the workspace's V afterwards
 int conv2d_impl(const rnswino_plan_t *plan, const int8_t *x_dev, const void *U_dev, int32_t *y_dev,
                 void *workspace_dev, void *stream, void *const *events, int epi = 0, int shift = 0,
-                int8_t *act_dev = nullptr) {
+                int8_t *act_dev = nullptr, bool keep = true) {
   if (!plan || !x_dev || !U_dev || !workspace_dev) return RNSWINO_E_INVALID;
   if (epi == 0 ? !y_dev : !act_dev) return RNSWINO_E_INVALID;
   if (plan->device < 0) return RNSWINO_E_NO_DEVICE;
@@ -633,7 +641,7 @@ int conv2d_impl(const rnswino_plan_t *plan, const int8_t *x_dev, const void *U_d
   }
   // (rnswino_plan() has checked that all instantiations exist)
   if (L.k12_choice.fused && !events) {
-    if (!launch_k12(L.k12_choice, L.k12, x_dev, (const int8_t *)U_dev, Op, st) ||
+    if (!launch_k12(L.k12_choice, L.k12, x_dev, (const int8_t *)U_dev, Op, keep, st) ||
         !launch_k3(d, L, plan->n_cus, epi, shift, Op, epi == 0 ? (void *)y_dev : (void *)act_dev, st, t3))
       return RNSWINO_E_UNSUPPORTED;
     return launch_status();
@@ -641,6 +649,8 @@ int conv2d_impl(const rnswino_plan_t *plan, const int8_t *x_dev, const void *U_d
   if (!launch_k1(d, plan->n_cus, L.k1, x_dev, Vp, st, t1) || !launch_k2(d, plan->desc.flags, L.k2, (const int8_t *)U_dev, Vp, Op, st, t2) ||
       !launch_k3(d, L, plan->n_cus, epi, shift, Op, epi == 0 ? (void *)y_dev : (void *)act_dev, st, t3))
     return RNSWINO_E_UNSUPPORTED;
+  // in the workspace is then what the one kernel leaves there
+  if (L.k12_choice.fused) hipLaunchKernelGGL(k_keep_input, dim3(L.k12_choice.copies), dim3(256), 0, st, x_dev, Vp, L.k12_choice.copies, (uint32_t)L.k12.total);
   return launch_status();
 }
 
@@ -720,7 +730,7 @@ int rnswino_plan(rnswino_plan_t **out, const rnswino_desc_t *desc) {
   {
     // every kernel the layer would launch, in each output mode, must be an instantiation that exists
     bool ok = launch_k1(d, pl->n_cus, params->k1, nullptr, nullptr, nullptr, Timing(), true) && launch_k2(d, pl->desc.flags, params->k2, nullptr, nullptr, nullptr, nullptr, Timing(), true);
-    ok = ok && (!params->k12_choice.fused || launch_k12(params->k12_choice, params->k12, nullptr, nullptr, nullptr, nullptr, true));
+    ok = ok && (!params->k12_choice.fused || launch_k12(params->k12_choice, params->k12, nullptr, nullptr, nullptr, false, nullptr, true));
     for (int epi = 0; epi < 3 && ok; ++epi) ok = launch_k3(d, *params, pl->n_cus, epi, 0, nullptr, nullptr, nullptr, Timing(), true);
     if (!ok) return fail(RNSWINO_E_UNSUPPORTED);
   }
@@ -811,7 +821,7 @@ int rnswino_conv2d_static(const rnswino_plan_t *plan, const int8_t *x_dev, const
   if (rnswino_workspace_bytes(plan) > (size_t)RNSWINO_STATIC_WORKSPACE_BYTES) return RNSWINO_E_WORKSPACE;
   void *ws = plan->device < MAX_DEVICES ? scratch_ptr[plan->device] : nullptr;   // set when the plan was made
   if (!ws) return RNSWINO_E_HIP;
-  return conv2d_impl(plan, x_dev, U_dev, y_dev, ws, stream, nullptr);
+  return conv2d_impl(plan, x_dev, U_dev, y_dev, ws, stream, nullptr, 0, 0, nullptr, false);
 }
 
 int64_t rnswino_plan_describe(const rnswino_plan_t *plan, int32_t output_mode, char *host_out, size_t capacity) {
@@ -846,7 +856,8 @@ int64_t rnswino_plan_describe(const rnswino_plan_t *plan, int32_t output_mode, c
   len += std::snprintf(buf + len, sizeof(buf) - len, "conversion=%s\n", conv);
   const K12Choice &c12 = ((const LayerParams *)plan->kparams)->k12_choice;
   if (c12.fused)
-    len += std::snprintf(buf + len, sizeof(buf) - len, "fused=k12_transform_gemm<%d, %d, %d, %s> grid=%u part=%d\n", c12.KS1, c12.TH, c12.RM, tf(c12.pack), c12.blocks, c12.part);
+    len += std::snprintf(buf + len, sizeof(buf) - len, "fused=k12_transform_gemm<%d, %d, %d, %s> grid=%u copies=%u part=%d\n", c12.KS1, c12.TH, c12.RM, tf(c12.pack), c12.blocks,
+                         c12.copies, c12.part);
   if (host_out && capacity > (size_t)len) std::memcpy(host_out, buf, (size_t)len + 1);
   return (int64_t)len + 1;
 }
@@ -1045,15 +1056,29 @@ int rnswino_debug_stage(const rnswino_plan_t *plan, int stage, const void *src_d
   if (!plan || !src_dev || !host_out) return RNSWINO_E_INVALID;
   if (plan->device < 0) return RNSWINO_E_NO_DEVICE;
   const Dims &d = plan->dims;
-  if (stage == RNSWINO_STAGE_V && ((const LayerParams *)plan->kparams)->k12_choice.fused) return RNSWINO_E_UNSUPPORTED;
+  const LayerParams &L = *(const LayerParams *)plan->kparams;
   size_t bytes, skip = 0;
   if (stage == RNSWINO_STAGE_U) bytes = u_bytes(d);
   else if (stage == RNSWINO_STAGE_V) bytes = v_bytes(d);
   else if (stage == RNSWINO_STAGE_O) { bytes = o_bytes(d); skip = align256(v_bytes(d)); }
   else return RNSWINO_E_INVALID;
   std::vector<int8_t> raw(bytes);
-  if (hipDeviceSynchronize() != hipSuccess ||
-      hipMemcpy(raw.data(), (const char *)src_dev + skip, bytes, hipMemcpyDeviceToHost) != hipSuccess) {
+  const char *from = (const char *)src_dev + skip;
+  void *v = nullptr;
+  bool ok = hipDeviceSynchronize() == hipSuccess;
+  if (ok && stage == RNSWINO_STAGE_V && L.k12_choice.fused) {
+    // the workspace holds the input in V's place: transformed here, on the plan's device
+    int current = plan->device;
+    ok = hipGetDevice(&current) == hipSuccess && hipSetDevice(plan->device) == hipSuccess && hipDeviceSynchronize() == hipSuccess;
+    if (ok && hipMalloc(&v, bytes) != hipSuccess) { v = nullptr; ok = false; }
+    ok = ok && launch_k1(d, plan->n_cus, L.k1, (const int8_t *)src_dev, (int8_t *)v, nullptr, Timing()) && hipGetLastError() == hipSuccess &&
+         hipDeviceSynchronize() == hipSuccess;
+    ok = hipSetDevice(current) == hipSuccess && ok;
+    from = (const char *)v;
+  }
+  ok = ok && hipMemcpy(raw.data(), from, bytes, hipMemcpyDeviceToHost) == hipSuccess;
+  if (v) ok = hipFree(v) == hipSuccess && ok;
+  if (!ok) {
     (void)hipGetLastError();
     return RNSWINO_E_HIP;
   }

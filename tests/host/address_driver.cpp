@@ -121,6 +121,31 @@ static void segments() {
   }
 }
 
+// copy_share() and piece_at(): every byte is in some share's pieces, and no piece leaves the buffer
+static void copies() {
+  for (int e = 0; e < 4000; ++e) {
+    const uint32_t threads = 256u << between(0, 1), step = threads * 32, n = 8 * (uint32_t)between(1, 31);
+    const uint32_t bytes = (uint32_t)between(16, e % 3 ? 3000 : 4000000);
+    uint32_t covered = 0;                                  // [0, covered) is copied: the shares follow each other, and so do a share's steps
+    for (uint32_t block = 0; block < n; ++block) {
+      const CopyShare s = copy_share(bytes, block, n, step);
+      if (s.first >= s.end) continue;
+      for (uint32_t at = s.first; at < s.end; at += step)
+        for (uint32_t piece = at; piece < at + step && piece < bytes; piece += 16) {
+          const uint32_t got = piece_at(piece, bytes);
+          CHECK(got <= covered && got + 16 <= bytes, "%u bytes, share %u of %u: piece at %u, %u covered", bytes, block, n, got, covered);
+          covered = std::max(covered, got + 16);
+        }
+    }
+    CHECK(covered == bytes, "%u bytes in %u shares: %u covered", bytes, n, covered);
+  }
+  for (uint32_t n = 8; n <= 248; n += 8)                   // the largest input: no sum leaves 32 bits
+    for (uint32_t block = 0; block < n; ++block) {
+      const CopyShare s = copy_share(0x7FFFFFFFu, block, n, 16384);
+      CHECK((uint64_t)s.first == (uint64_t)block * (0x7FFFFFFFull / n / 16384 + 1) * 16384 && (s.end > s.first || s.first >= 0x7FFFFFFFu), "share %u of %u", block, n);
+    }
+}
+
 // patch_pixels() against the patches of every block of every shape, taken pixel by pixel
 static void patches() {
   for (int e = 0; e < 6000; ++e) {
@@ -170,6 +195,7 @@ int main(int argc, char **argv) {
   const std::string part = argc > 1 ? argv[1] : "";
   if (part == "divisions") divisions();
   else if (part == "segments") segments();
+  else if (part == "copies") copies();
   else if (part == "patches") patches();
   else if (part == "residues") residues();
   else return 2;

@@ -101,17 +101,14 @@ def test_one_kernel_transforms_and_multiplies(case, kernel):
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", [CASES[0][0], CASES[12][0], CASES[15][0]])
 def test_the_calls_around_it(case):
-    """O in the workspace, V refused and there with two kernels, the fused re-quantisation, and a captured graph replayed between eager calls."""
+    """O in the workspace, the fused re-quantisation, and a captured graph replayed between eager calls."""
     print("around transform and gemm", case, flush=True)
     layer, xd, x, w = _layer(case)
     y = layer.forward(xd).cpu().numpy()
     o = layer.stage(rn.STAGE_O)
-    with pytest.raises(rn.RnsWinoError):
-        layer.stage(rn.STAGE_V)
     two, xd2, _, _ = _layer(case, SEPARATE)
     assert np.array_equal(two.forward(xd2).cpu().numpy(), y)
     assert np.array_equal(two.stage(rn.STAGE_O), o)
-    assert two.stage(rn.STAGE_V).any()
     K, Ho, Wo = case[2], layer.plan.Ho, layer.plan.Wo
     a = torch.empty((case[0], K, Ho, Wo), dtype=torch.int8, device="cuda:0")
     rn.rnswino_conv2d_requant(layer.plan, xd, layer.U, a, 9, False, layer.workspace, torch.cuda.current_stream().cuda_stream)
@@ -129,6 +126,39 @@ def test_the_calls_around_it(case):
         replayed = layer.y.clone()
         layer.y.zero_()
         assert torch.equal(layer.forward(xd), replayed)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [CASES[0][0], CASES[2][0], CASES[12][0], CASES[14][0], CASES[17][0], CASES[20][0]])
+def test_V_of_every_call(case):
+    """V as the two kernels leave it, after each of the calls that take a workspace, and O beside it, as often as one asks."""
+    print("V", case, flush=True)
+    layer, xd, x, w = _layer(case)
+    two, xd2, _, _ = _layer(case, SEPARATE)
+    two.forward(xd2)
+    v, o = two.stage(rn.STAGE_V), two.stage(rn.STAGE_O)
+    stream = torch.cuda.current_stream().cuda_stream
+    a = torch.empty(tuple(layer.y.shape), dtype=torch.int8, device="cuda:0")
+    events = [torch.cuda.Event(enable_timing=True) for _ in range(6)]
+    for e in events:
+        e.record()                                     # (created with their first use)
+    for call in (lambda: layer.forward(xd), lambda: rn.rnswino_conv2d_requant(layer.plan, xd, layer.U, a, 9, False, layer.workspace, stream),
+                 lambda: rn.rnswino_conv2d_events(layer.plan, xd, layer.U, layer.y, layer.workspace, stream, [e.cuda_event for e in events])):
+        layer.workspace.fill_(0x55)
+        call()
+        for _ in range(2):
+            assert np.array_equal(layer.stage(rn.STAGE_V), v)
+        assert np.array_equal(layer.stage(rn.STAGE_O), o)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        layer.forward(xd)
+    xd.zero_()                                         # V is that of the call, whatever becomes of its input
+    for _ in range(3):
+        graph.replay()
+        assert not layer.stage(rn.STAGE_V).any()
+        layer.forward(xd2)
+        xd2_v = layer.stage(rn.STAGE_V)
+        assert np.array_equal(xd2_v, v)
 
 
 def _two_kernel_cases():

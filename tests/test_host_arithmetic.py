@@ -1,5 +1,5 @@
 """The integer arithmetic that the kernels' addresses and residues rest on, on the host (csrc/address_math.hpp is compiled into both):
-divisions by multiplication, the 16-byte row segments at the ends of a tensor, the size of a staged patch, and the residues of sums
+divisions by multiplication, the 16-byte row segments at the ends of a tensor, a copy by several workgroups, the size of a staged patch, and the residues of sums
 read as binary32 numbers, under AddressSanitizer and UndefinedBehaviorSanitizer."""
 import os
 import shutil
@@ -24,7 +24,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("part", ["divisions", "segments", "patches", "residues"])
+@pytest.mark.parametrize("part", ["divisions", "segments", "copies", "patches", "residues"])
 def test_address_and_residue_arithmetic(driver, part):
     run = subprocess.run([driver, part], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
     assert run.returncode == 0 and "bad=0" in run.stdout, run.stdout[-4000:]
