@@ -241,9 +241,9 @@ int rnswino_plan_get_mrc_inverse(const rnswino_plan_t *plan, int l, int j, uint3
  *   k2_residue_gemm<4, 4, 2, false> grid=6400 xgroup=1
  *   k3_inverse_crt<4, 2, false, true> grid=784x1
  *   conversion=unreduced-binary32
- * (grid=XxYxZ where the launch has a third extent).  A last line "fused=k12_transform_gemm<2, 2, 2, false> grid=200 copies=98 part=25" says that one kernel
- * takes the place of the first two except in rnswino_conv2d_events (never with RNSWINO_FLAG_SEPARATE_KERNELS);
- * `copies` more workgroups of it leave a copy of the input in the workspace, in V's place, which rnswino_debug_stage transforms.
+ * (grid=XxYxZ where the launch has a third extent).  A last line "fused=k12_transform_gemm<2, 2, 2, false> grid=200 copies=56 part=25" says that one kernel
+ * takes the place of the first two except in rnswino_conv2d_events (never with RNSWINO_FLAG_SEPARATE_KERNELS).
+ * It leaves a copy of the input in the workspace, in V's place, which rnswino_debug_stage transforms; `copies` more workgroups do only that (0: all share in it).
  * conversion: "unreduced-binary32" / "unreduced-binary64" = CRT sum over unreduced accumulators with the quotient rounded
  * in that precision; "reduced-binary32" / "reduced-binary64" = over reduced residues; "reduced-binary64-mul32" = the same
  * with full 32-bit multiplies (a partial product P/m_i of 2^24 or more, or three and more 16-bit moduli in most cases).  Works on host-only plans (their

@@ -72,16 +72,20 @@ RNSW_HD unsigned long long byte_range(int lo, int hi, int at) {
 }
 
 // ---- a copy by several workgroups ----
-// Bytes [first, end) of workgroup `block` of `copies`, whole steps but for the last share (2^31 bytes and 256 steps of 2^16 at most: no sum leaves 32
-// bits); a load of 16 bytes that would end behind the last byte ends with it.
+// Bytes [first, end) of workgroup `block`, a share of whole steps but for the last one (the product in 64 bits: with many workgroups that have next to nothing
+// to copy it leaves 32).  A load of 16 bytes that would end behind them ends with them; below 16 (a last share) with the first 16 of all.
 struct CopyShare {
   uint32_t first, end;
 };
-RNSW_HD CopyShare copy_share(uint32_t bytes, uint32_t block, uint32_t copies, uint32_t step) {
-  const uint32_t share = (bytes / copies / step + 1) * step, first = block * share;
-  return {first, first + share < bytes ? first + share : bytes};
+inline uint32_t share_of(uint32_t bytes, uint32_t blocks, uint32_t step) { return (bytes / blocks / step + 1) * step; }
+RNSW_HD CopyShare copy_share(uint32_t bytes, uint32_t block, uint32_t share) {
+  const uint64_t first = (uint64_t)block * share;
+  return {(uint32_t)(first < bytes ? first : bytes), (uint32_t)(first + share < bytes ? first + share : bytes)};
 }
-RNSW_HD uint32_t piece_at(uint32_t at, uint32_t bytes) { return at < bytes - 16 ? at : bytes - 16; }
+RNSW_HD uint32_t piece_at(uint32_t at, uint32_t end) {
+  const uint32_t last = end > 16 ? end - 16 : 0;
+  return at < last ? at : last;
+}
 
 // ---- staged patches (direct convolution) ----
 // The longest run of padded pixels that `pixels` consecutive output pixels, beginning at a multiple of `pixels`, need for all r x r

@@ -23,7 +23,7 @@
 // batch 8, and the residues: K1 8.9 + K2 45.6 us, so 41 (a layer with cold operands 107.4 -> 87.6; with fragments from L2 143).  The filters may be split over workgroups, each
 // transforming anew.
 // Grid: one-dimensional, ceil(Tp / (16 TH)) x parts of the filters x parts of the items, rounded up to a multiple of 8 (kernels_common.hpp); in
-// front of them the workgroups of keep_input(), a multiple of 8 too.
+// front of them the workgroups that only copy the input, also a multiple of 8, or none.
 #pragma once
 #include "k_input_transform.hpp"
 #include "k_residue_gemm.hpp"
@@ -43,7 +43,7 @@ struct K12Args {
   uint32_t Q_mul;             // ceil(2^16 / Q), Q = ceil(t*t / 4)
   uint32_t shifts;            // bytes: of the divisions by the tile blocks' groups, tw, th; packed layers: parts the filters are split into
   uint32_t sizes;             // bytes: m, t, n, items of a part
-  uint32_t kept;              // the input's copy: where it lies in front of O, in 256 bytes, and in the upper five bits its workgroups / 8 (0: none is kept)
+  uint32_t kept;              // the input's copy: where it lies in front of O, in 256 bytes; in the upper five bits its own workgroups / 8
   RNSW_HD FastDiv by_tile_groups() const { return {tile_groups_mul, shifts & 31u}; }
   RNSW_HD FastDiv by_tw() const { return {tw_mul, shifts >> 8 & 31u}; }
   RNSW_HD FastDiv by_th() const { return {th_mul, shifts >> 16 & 31u}; }
@@ -68,25 +68,40 @@ __device__ __forceinline__ void biased_lowbytes(uint32_t (&r)[4], int a0, int a1
       : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) : "v"(neg_p), "v"(a0), "v"(a1), "v"(a2), "v"(a3));
 }
 
-// A call leaves in the workspace what V can be had from again: not V itself but, in its place, the input (rnswino_debug_stage transforms it).  Workgroup
-// `block` of `copies` copies its share of it, 16 bytes a load, the last ones moved back to end with the input, which has 16 bytes and more.
-// They come first and run on compute units that the others leave idle: 64 -> 64 at 224 x 224, batch 8, 125.5 us a layer without them, 129.5 with them;
-// 64 -> 128 at 112 x 112, pooled, 51.4 and 51.9 (behind the others, one per 256 KB, 54), the stack at batch 8 766.8 and 770.1.
+// A call leaves in the workspace what V can be had from again: not V itself but, in its place, the input (rnswino_debug_stage transforms it).  Workgroups
+// copy it, each its share, four loads of 16 bytes a thread at a time: either ones of their own, on compute units that the others leave idle, or all of them,
+// requested behind the gather and stored behind the wait in front of the items.  What it costs is the traffic: us a layer without a copy, with own
+// workgroups and by all: 64 -> 64 at 224 x 224, batch 8 (56 of 256 compute units idle) 125.9, 130.7, 131.3; batch 1 (8 idle) 25.8, 25.6, 26.0; 64 -> 128 at
+// 112 x 112, batch 8 (8) 59.7, 60.5, 61.3; where none is idle, 64 -> 51 at 188 x 48, three moduli, 27.1, 38.5, 27.6; 48 -> 9 at 124 x 142, F(14,3), 36.4, 51.4, 37.6.
 template <int THREADS>
-__device__ __forceinline__ void keep_input(const int8_t *x, int8_t *to, uint32_t block, uint32_t copies, uint32_t bytes) {
-  constexpr int AHEAD = 2;                             // (eight take what the others wait for: 0.5 us of 64 -> 64 at 224 x 224, batch 1)
-  constexpr uint32_t STEP = THREADS * 16 * AHEAD;
+struct InputCopy {
   typedef int Bytes __attribute__((ext_vector_type(4), aligned(1), may_alias));
-  const CopyShare own = copy_share(bytes, block, copies, STEP);
-  for (uint32_t at = own.first + threadIdx.x * 16u; at < own.end; at += STEP) {
-    Bytes val[AHEAD];
+  static constexpr int AHEAD = 4;
+  static constexpr uint32_t STEP = THREADS * 16;
+  const int8_t *from;
+  int8_t *to;
+  uint32_t at, end;                                    // uniform: what is left of the share
+  Bytes held[AHEAD];
+  __device__ __forceinline__ InputCopy(const int8_t *x, int8_t *v, CopyShare own) : from(x), to(v), at(own.first), end(own.end) {}
+  __device__ __forceinline__ uint32_t place(int j) const { return piece_at(at + threadIdx.x * 16u + j * STEP, end); }
+  __device__ __forceinline__ void request() {
+    if (at >= end) return;
 #pragma unroll
-    for (int j = 0; j < AHEAD; ++j) val[j] = *(const Bytes *)(x + piece_at(at + j * (THREADS * 16u), bytes));
-#pragma unroll
-    for (int j = 0; j < AHEAD; ++j) *(Bytes *)(to + piece_at(at + j * (THREADS * 16u), bytes)) = val[j];
+    for (int j = 0; j < AHEAD; ++j) held[j] = *(const Bytes *)(from + place(j));
   }
+  __device__ __forceinline__ void store() {
+    if (at >= end) return;
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) *(Bytes *)(to + place(j)) = held[j];
+    at += AHEAD * STEP;
+  }
+  __device__ __forceinline__ void rest() {
+    while (at < end) { request(); store(); }
+  }
+};
+__global__ __launch_bounds__(256) void k_keep_input(const int8_t *x, int8_t *to, uint32_t bytes, uint32_t share) {
+  InputCopy<256>(x, to, copy_share(bytes, blockIdx.x, share)).rest();
 }
-__global__ __launch_bounds__(256) void k_keep_input(const int8_t *x, int8_t *to, uint32_t copies, uint32_t bytes) { keep_input<256>(x, to, blockIdx.x, copies, bytes); }
 
 // Waves of a workgroup / 4: with three and four steps a wave takes half of a slice's channels, so that its pixels fit the same registers.
 constexpr int k12_quads(int ks1, int th) { return ks1 > 2 ? 2 * th : th; }
@@ -104,17 +119,21 @@ __global__ __launch_bounds__(256 * k12_quads(KS1, TH), 2) void k12_transform_gem
   asm volatile("" ::"s"(P.more), "s"(P.x), "s"(P.KB), "s"(P.U), "s"(P.O), "s"(P.per_xcd), "s"(P.ntb), "s"(P.nkb), "s"(P.tile_groups_mul),
                "s"(P.tw_mul), "s"(P.th_mul), "s"(P.C), "s"(P.H), "s"(P.W), "s"(P.pad), "s"(P.tw), "s"(P.th), "s"(P.T), "s"(P.total), "s"(P.Q_mul), "s"(P.shifts),
                "s"(P.sizes), "s"(P.kept));
-  if (blockIdx.x < P.copies()) return keep_input<256 * QUADS>(P.x, (int8_t *)P.O - P.kept_offset(), blockIdx.x, P.copies(), P.total);
-  const uint32_t id = blockIdx.x - P.copies();
   const int t = P.t(), P2 = t * t, CB1 = (P2 + 15) >> 4, Q = (P2 + 3) >> 2, HW = P.H * P.W;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, h = lane >> 4, col = lane & 15;
   const int slice = wave & 3, th = KS1 > 2 ? 0 : wave >> 2, u0 = KS1 > 2 ? NU * (wave >> 2) : 0;             // of V: what this wave transforms
+  const uint32_t copies = P.copies(), id = blockIdx.x - copies;
   const int unit = (int)(id & 7) * P.per_xcd + (int)(id >> 3);
+  auto share = [&](uint32_t block) { return InputCopy<256 * QUADS>(P.x, (int8_t *)P.O - P.kept_offset(), copy_share((uint32_t)P.total, block, R.kept_share)); };
+  if (blockIdx.x < copies) return share(blockIdx.x).rest();
   const int tile_groups = (P.ntb + TH - 1) / TH, which = (int)fast_div((uint32_t)unit, P.by_tile_groups()), tb0 = (unit - which * tile_groups) * TH;
   const int part = PACK ? which / P.row_parts() : which;
   const int ngroups = P.n() * Q;
   const int first = part * P.part();
-  if (4 * first >= ngroups) return;                                     // the grid is padded to a multiple of 8
+  if (4 * first >= ngroups) {                                           // the grid is padded to a multiple of 8
+    if (!copies) share((uint32_t)unit).rest();
+    return;
+  }
   const int tau = min(tb0 + th, P.ntb - 1) * 16 + col;                 // past the last tile block: that one again
   // ---- gather: lane (channel h of four, tile) takes the t row segments of one channel after the other (see k1_input_transform_tiles) ----
   const int mis = (int)((uint32_t)(uintptr_t)P.x & 3u), last = P.total - 16 + mis;
@@ -258,6 +277,7 @@ __global__ __launch_bounds__(256 * k12_quads(KS1, TH), 2) void k12_transform_gem
 #pragma unroll
   for (int d = 0; d < 4; ++d) diagonal[d] = PACK && (col & 3) == h && (col >> 2) == d ? 0xFFFFFFFFu : 0u;
   Group at = mine(item);
+  InputCopy<256 * QUADS> copy(nullptr, nullptr, {0, 0});
   {
     v4i va[ROWS], vb[ROWS];
     int ca, cb;
@@ -275,6 +295,9 @@ __global__ __launch_bounds__(256 * k12_quads(KS1, TH), 2) void k12_transform_gem
       __builtin_amdgcn_sched_barrier(0);
       settle(3, vb, cb);
     }
+    copy = share((uint32_t)unit);
+    if (copies) copy.end = 0;
+    copy.request();
     __builtin_amdgcn_sched_barrier(0);                                 // (requested any earlier, these take more registers than there are: 0.5 us a call)
     load_table(item);
     if constexpr (PACK) load_words(at);
@@ -286,6 +309,8 @@ __global__ __launch_bounds__(256 * k12_quads(KS1, TH), 2) void k12_transform_gem
   // Everything requested so far is awaited here: otherwise the compiler, merging this entry state with the loop's own, makes the loop's waits wait for its
   // stores.
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), other counters untouched
+  copy.store();
+  copy.rest();
 
   const uint32_t krow = (uint32_t)(P.n() * Q) * (uint32_t)(P.ntb * 16) * 4u;             // bytes of a row of O, which is smaller than 4 GiB
   uint32_t lane_store[4];

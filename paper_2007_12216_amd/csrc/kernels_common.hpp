@@ -37,6 +37,7 @@ inline uint32_t pack_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d) { ret
 struct ResidueParams {
   alignas(16) Residue8 res[8];
   double inv_pd[8];           // 16-bit moduli
+  uint32_t kept_share;        // k_transform_gemm.hpp: bytes of the input that a workgroup copies
 };
 
 // Everything the filter transform needs to know about the layer, passed by value, and what the other kernels' parameters are made of.

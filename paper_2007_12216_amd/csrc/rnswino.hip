@@ -154,7 +154,7 @@ struct DeviceParams {
 static_assert(sizeof(DeviceParams) <= PARAMS_BYTES, "build_tables() leaves them that much");
 // The input transform and the GEMM in one kernel (k_transform_gemm.hpp).  TH: tile blocks of 16 a workgroup takes; RM: row blocks a wave multiplies at once;
 // part: items of a workgroup, parts: what that splits the items of its tiles into; row_parts: packed layers, what the filters are split into; copies:
-// workgroups that copy the input into V's place.
+// workgroups that only copy the input into V's place (0: every other one copies a share).
 struct K12Choice { bool fused, pack; int KS1, TH, RM, part; unsigned parts, row_parts, blocks, copies; };
 struct LayerParams {
   KParams k;
@@ -395,10 +395,10 @@ K12Choice choose_k12(const Dims &d, uint32_t flags, int n_cus) {
   }
   c.parts = (unsigned)((items + c.part - 1) / c.part);
   c.blocks = (unsigned)(((long long)((ntb + c.TH - 1) / c.TH) * c.parts * c.row_parts + 7) / 8 * 8);
-  // As many copies as the other workgroups leave compute units idle, or as finish with them at 24 KB a us, none of less than 16 KiB.  (V is never smaller than
-  // the input: a tile of t x t pixels for m x m outputs, 64 channels.)
-  const double idle = cus - 1 - (int)((c.blocks - 1) % (unsigned)cus), copies = std::min(std::max(idle, elements / (24e3 * best)), elements / 16384.0);
-  c.copies = 8u * (unsigned)std::min(std::max(copies / 8, 1.0), 31.0);
+  // The input's copy (V, whose place it takes, is never smaller: a tile of t x t pixels for m x m outputs, 64 channels): by workgroups of its own on the compute
+  // units that the others leave idle, if those have time for it at 32 KB a us each (measured 36), else by all (figures: InputCopy).
+  const unsigned idle = std::min(((unsigned)cus - 1 - (c.blocks - 1) % (unsigned)cus) / 8 * 8, 248u);
+  if ((double)elements <= 32e3 * idle * best) c.copies = idle;
   return c;
 }
 
@@ -416,7 +416,7 @@ K12Args make_k12(const Dims &d, const KParams &P, const DeviceParams *dev, const
   q.Q_mul = (65536u + (uint32_t)d.Q - 1) / (uint32_t)d.Q;
   q.C = d.C; q.H = d.H; q.W = d.W; q.pad = d.pad; q.tw = d.tw; q.th = d.th; q.T = d.T;
   q.total = (int)((long long)d.N * d.C * d.H * d.W);
-  q.kept = (uint32_t)(align256(v_bytes(d)) / 256) | c.copies / 8 << 27;           // (V has at most four times the bytes of O, below 16 GiB)
+  q.kept = (uint32_t)(align256(v_bytes(d)) / 256) | c.copies / 8 << 27;          // (V has at most four times the bytes of O, below 16 GiB)
   return q;
 }
 
@@ -558,10 +558,9 @@ bool launch_k2(const Dims &d, uint32_t flags, const K2Args &L, const int8_t *U, 
 }
 
 // ---- K1 and K2 in one ----
-bool launch_k12(const K12Choice &c, const K12Args &L, const int8_t *x, const int8_t *U, uint32_t *O, bool keep, hipStream_t st, bool dry = false) {
-  const dim3 grid(c.blocks + (keep ? c.copies : 0));
+bool launch_k12(const K12Choice &c, const K12Args &L, const int8_t *x, const int8_t *U, uint32_t *O, hipStream_t st, bool dry = false) {
+  const dim3 grid(c.copies + c.blocks);
   K12Args P = L;
-  if (!keep) P.kept = 0;
   P.x = x; P.U = U; P.O = O;
 #define RNSW_X(ks, groups, rm, pk) \
   if (c.KS1 == ks && c.TH == groups && c.RM == rm && c.pack == pk) { \
@@ -618,10 +617,10 @@ std::string all_kernel_variants() {
   return out;
 }
 
-// epi: 0 = int32 y_dev; 1 / 2 = int8 act_dev after shift/clamp (/ and 2x2 max-pool); keep: somebody may ask for the workspace's V afterwards
+// epi: 0 = int32 y_dev; 1 / 2 = int8 act_dev after shift/clamp (/ and 2x2 max-pool)
 int conv2d_impl(const rnswino_plan_t *plan, const int8_t *x_dev, const void *U_dev, int32_t *y_dev,
                 void *workspace_dev, void *stream, void *const *events, int epi = 0, int shift = 0,
-                int8_t *act_dev = nullptr, bool keep = true) {
+                int8_t *act_dev = nullptr) {
   if (!plan || !x_dev || !U_dev || !workspace_dev) return RNSWINO_E_INVALID;
   if (epi == 0 ? !y_dev : !act_dev) return RNSWINO_E_INVALID;
   if (plan->device < 0) return RNSWINO_E_NO_DEVICE;
@@ -641,7 +640,7 @@ int conv2d_impl(const rnswino_plan_t *plan, const int8_t *x_dev, const void *U_d
   }
   // (rnswino_plan() has checked that all instantiations exist)
   if (L.k12_choice.fused && !events) {
-    if (!launch_k12(L.k12_choice, L.k12, x_dev, (const int8_t *)U_dev, Op, keep, st) ||
+    if (!launch_k12(L.k12_choice, L.k12, x_dev, (const int8_t *)U_dev, Op, st) ||
         !launch_k3(d, L, plan->n_cus, epi, shift, Op, epi == 0 ? (void *)y_dev : (void *)act_dev, st, t3))
       return RNSWINO_E_UNSUPPORTED;
     return launch_status();
@@ -650,7 +649,8 @@ int conv2d_impl(const rnswino_plan_t *plan, const int8_t *x_dev, const void *U_d
       !launch_k3(d, L, plan->n_cus, epi, shift, Op, epi == 0 ? (void *)y_dev : (void *)act_dev, st, t3))
     return RNSWINO_E_UNSUPPORTED;
   // in the workspace is then what the one kernel leaves there
-  if (L.k12_choice.fused) hipLaunchKernelGGL(k_keep_input, dim3(L.k12_choice.copies), dim3(256), 0, st, x_dev, Vp, L.k12_choice.copies, (uint32_t)L.k12.total);
+  if (L.k12_choice.fused) hipLaunchKernelGGL(k_keep_input, dim3(256), dim3(256), 0, st, x_dev, Vp, (uint32_t)L.k12.total,
+                                                share_of((uint32_t)L.k12.total, 256, 4096));
   return launch_status();
 }
 
@@ -723,6 +723,9 @@ int rnswino_plan(rnswino_plan_t **out, const rnswino_desc_t *desc) {
     // tables and parameters in one copy
     DeviceParams dp;
     dp.residues = make_residues(d, params->k);
+    if (params->k12_choice.fused)
+      dp.residues.kept_share = share_of((uint32_t)params->k12.total, params->k12_choice.copies ? params->k12_choice.copies : params->k12_choice.blocks,
+                                        16u * 256u * (uint32_t)k12_quads(params->k12_choice.KS1, params->k12_choice.TH));
     dp.k3 = make_conversion(d, params->k, pl->n_cus);
     std::memcpy(blob.data() + pl->off_params, &dp, sizeof(dp));
     if (hipMemcpy(pl->d_tables, blob.data(), blob.size(), hipMemcpyHostToDevice) != hipSuccess) return fail(RNSWINO_E_HIP);
@@ -730,7 +733,7 @@ int rnswino_plan(rnswino_plan_t **out, const rnswino_desc_t *desc) {
   {
     // every kernel the layer would launch, in each output mode, must be an instantiation that exists
     bool ok = launch_k1(d, pl->n_cus, params->k1, nullptr, nullptr, nullptr, Timing(), true) && launch_k2(d, pl->desc.flags, params->k2, nullptr, nullptr, nullptr, nullptr, Timing(), true);
-    ok = ok && (!params->k12_choice.fused || launch_k12(params->k12_choice, params->k12, nullptr, nullptr, nullptr, false, nullptr, true));
+    ok = ok && (!params->k12_choice.fused || launch_k12(params->k12_choice, params->k12, nullptr, nullptr, nullptr, nullptr, true));
     for (int epi = 0; epi < 3 && ok; ++epi) ok = launch_k3(d, *params, pl->n_cus, epi, 0, nullptr, nullptr, nullptr, Timing(), true);
     if (!ok) return fail(RNSWINO_E_UNSUPPORTED);
   }
@@ -821,7 +824,7 @@ int rnswino_conv2d_static(const rnswino_plan_t *plan, const int8_t *x_dev, const
   if (rnswino_workspace_bytes(plan) > (size_t)RNSWINO_STATIC_WORKSPACE_BYTES) return RNSWINO_E_WORKSPACE;
   void *ws = plan->device < MAX_DEVICES ? scratch_ptr[plan->device] : nullptr;   // set when the plan was made
   if (!ws) return RNSWINO_E_HIP;
-  return conv2d_impl(plan, x_dev, U_dev, y_dev, ws, stream, nullptr, 0, 0, nullptr, false);
+  return conv2d_impl(plan, x_dev, U_dev, y_dev, ws, stream, nullptr);
 }
 
 int64_t rnswino_plan_describe(const rnswino_plan_t *plan, int32_t output_mode, char *host_out, size_t capacity) {

@@ -124,26 +124,31 @@ static void segments() {
 // copy_share() and piece_at(): every byte is in some share's pieces, and no piece leaves the buffer
 static void copies() {
   for (int e = 0; e < 4000; ++e) {
-    const uint32_t threads = 256u << between(0, 1), step = threads * 32, n = 8 * (uint32_t)between(1, 31);
-    const uint32_t bytes = (uint32_t)between(16, e % 3 ? 3000 : 4000000);
-    uint32_t covered = 0;                                  // [0, covered) is copied: the shares follow each other, and so do a share's steps
+    const uint32_t step = 4096u << between(0, 2), n = 8 * (uint32_t)(e % 2 ? between(1, 31) : between(1, 400));
+    const uint32_t bytes = (uint32_t)between(16, e % 3 ? 3000 : 4000000), share = share_of(bytes, n, step);
+    CHECK(share % step == 0 && (uint64_t)share * n > bytes, "%u bytes, %u shares of %u", bytes, n, share);
+    uint32_t covered = 0;                                  // [0, covered) is copied: the shares follow each other, and so do a share's pieces
     for (uint32_t block = 0; block < n; ++block) {
-      const CopyShare s = copy_share(bytes, block, n, step);
+      const CopyShare s = copy_share(bytes, block, share);
+      CHECK(s.first <= s.end && s.end <= bytes && s.end - s.first <= share, "%u bytes, share %u of %u: [%u, %u)", bytes, block, n, s.first, s.end);
       if (s.first >= s.end) continue;
-      for (uint32_t at = s.first; at < s.end; at += step)
-        for (uint32_t piece = at; piece < at + step && piece < bytes; piece += 16) {
-          const uint32_t got = piece_at(piece, bytes);
-          CHECK(got <= covered && got + 16 <= bytes, "%u bytes, share %u of %u: piece at %u, %u covered", bytes, block, n, got, covered);
-          covered = std::max(covered, got + 16);
-        }
+      for (uint32_t at = s.first; at < s.first + 4 * share; at += 16) {        // (threads past the end of a share repeat its last piece)
+        const uint32_t got = piece_at(at, s.end);
+        CHECK(got <= covered && got + 16 <= bytes && got < s.end, "%u bytes, share %u of %u: piece at %u, %u covered", bytes, block, n, got, covered);
+        if (got + 16 <= covered && at >= s.end) break;
+        covered = std::max(covered, got + 16);
+      }
     }
     CHECK(covered == bytes, "%u bytes in %u shares: %u covered", bytes, n, covered);
   }
-  for (uint32_t n = 8; n <= 248; n += 8)                   // the largest input: no sum leaves 32 bits
-    for (uint32_t block = 0; block < n; ++block) {
-      const CopyShare s = copy_share(0x7FFFFFFFu, block, n, 16384);
-      CHECK((uint64_t)s.first == (uint64_t)block * (0x7FFFFFFFull / n / 16384 + 1) * 16384 && (s.end > s.first || s.first >= 0x7FFFFFFFu), "share %u of %u", block, n);
+  for (uint32_t n = 8; n < 1u << 21; n += n < 4096 ? 8 : 4096) {               // the largest input, and more workgroups than it has steps
+    const uint32_t share = share_of(0x7FFFFFFFu, n, 16384);
+    for (uint32_t block : {0u, 1u, n / 2, n - 2, n - 1}) {
+      const CopyShare s = copy_share(0x7FFFFFFFu, block, share);
+      const uint64_t first = std::min((uint64_t)block * share, (uint64_t)0x7FFFFFFF), end = std::min((uint64_t)(block + 1) * share, (uint64_t)0x7FFFFFFF);
+      CHECK(s.first == first && s.end == end, "share %u of %u", block, n);
     }
+  }
 }
 
 // patch_pixels() against the patches of every block of every shape, taken pixel by pixel
