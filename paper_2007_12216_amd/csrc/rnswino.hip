@@ -354,23 +354,22 @@ K12Choice choose_k12(const Dims &d, uint32_t flags, int n_cus) {
   const long long elements = (long long)d.N * d.C * d.H * d.W;
   const int nkb = d.Kp / 16, ntb = d.Tp / 16, cus = n_cus > 0 ? n_cus : 256, items = (d.n * d.Q + 3) / 4;
   // 8-bit moduli, one channel block, row segments with 32-bit offsets (as for k1_input_transform_tiles), and where it is faster.
-  // Layers that are not packed: 260 random ones (1 to 6 moduli, F(2..8, 1..5), 8 to 1024 filters) were, with up to 288 filters and 150 (tile block, item)
-  // pairs, in the mean of all 0.93 of the time of two kernels, from 0.5 (64 -> 9 at 193 x 193, F(4,5), batch 6, 117.5 -> 60.8 us a layer) to 1.08.  With more
-  // filters fragments of U cross the L2 once per 32 tiles (64 -> 500 at 75 x 75, F(6,3), batch 7 105.5 / 107.9, 33 -> 513 at 103 x 103, F(4,5) 124.5 / 148.3);
-  // with fewer pairs the few blocks' latencies decide (48 -> 49 at 46 x 46, one modulus, batch 5 10.3 / 11.6, 16 -> 16 at 16 x 16 7.7 / 10.6).
-  // (Those were t <= 10.)  With three steps, t = 11, 12, 14 of them were from 400 pairs on 0.83 of it (0.65 to 0.99; 64 -> 283 at 36 x 36, F(8,5), batch 8, 468,
-  // 35.9 / 33.8; below, 64 -> 202 at 42 x 42, three moduli, batch 5, 324, 25.3 / 27.0), with four, whose rows take unaligned loads, 8 from 1400 on 0.89 (0.83 to
-  // 0.98; 64 -> 64 at 112 x 112, F(14,3), batch 8, 2048, 69.4 / 63.4; below both ways: 40 -> 80 at 94 x 94, F(12,5), batch 5, 1280, 47.5 / 52.8, 64 -> 113 at
-  // 157 x 157, batch 2, 1200, 58.6 / 53.6; 48 -> 64 at 35 x 35, batch 8, 320, 19.1 / 24.9).
-  // Packed layers of up to four channels: 70 random ones (1 to 4 channels, 8 to 256 filters, 2 to 4 moduli) were from 12 500 (tile block, item, filter)
-  // triples on 0.88 of it (0.81 to 0.95; 3 -> 64 at 224 x 224, batch 8, 107.4 -> 87.6), below mostly above it (the same at batch 2, 8 500, 34.9 / 37.4,
-  // at batch 1 23.5 / 26.8; 3 -> 26 at 220 x 220, F(4,5), batch 3, 11 200, 29.1 / 31.9).
+  // The lines lie where random layers (4340 in profiles/transform_gemm_dispatch.csv: us as one kernel and as two, the input's copy included) stop gaining:
+  // inside them 3695 take 0.875 of the time of two kernels in the mean, 91 of them (2.5 %) over 1.02 (up to 1.14); outside 645 take 1.004, 240 of them over 1.02.
+  // - Filters: fragments of U cross the L2 once per 32 (t > 10: 16) tiles.  Over 160 filters at t <= 10 the mean is 0.97 (t <= 8; 1.03 at t = 9, 10), over
+  //   128 at t > 10 1.00 to 1.03 (42 -> 281 at 79 x 77, F(9,3), six moduli, batch 9, 147.8 -> 172.0).
+  // - (Tile block, item) pairs: with few, the few workgroups' latencies decide.  t <= 8 from 150 on 0.86 (40 -> 10 at 182 x 144, F(4,5), batch 9, 186.8 -> 88.2),
+  //   t = 9, 10 from 300 on 0.90 (150 to 300: 0.96, up to 1.04), t = 11, 12 from 400 on 0.87, t > 12, whose rows take unaligned loads, from 2400 on 0.86 (1400
+  //   to 2400: 0.97, up to 1.16).
+  // - Packed layers of up to four channels: a workgroup gathers for one item, which pays for itself where (item, filter) pairs are 800 and more, or (tile
+  //   block, item, filter) triples 37 500: 0.90.  With fewer 1.03 (1 -> 13 at 221 x 240, F(4,4), batch 6, 41.6 -> 57.5); below 12 500 triples the GPU is not full.
   if (d.wide || d.Cp != 64 || (flags & (RNSWINO_FLAG_GEMM_BLOCK_64X16 | RNSWINO_FLAG_SEPARATE_KERNELS)) || elements < 16 ||
       elements + d.W + 2LL * d.pad + 16 >= (1LL << 31))
     return c;
   c.pack = d.TL == 16 && d.KS1 <= 2;
-  if (c.pack) c.fused = d.K <= 8192 && (long long)ntb * items * d.K >= 12500;
-  else c.fused = d.TL == 1 && nkb <= 18 && (long long)ntb * items >= (d.KS1 <= 2 ? 150 : d.KS1 == 3 ? 400 : 1400);
+  const long long pairs = (long long)ntb * items;
+  if (c.pack) c.fused = d.K <= 8192 && pairs * d.K >= ((long long)items * d.K >= 800 ? 12500 : 37500);
+  else c.fused = d.TL == 1 && nkb <= (d.KS1 <= 2 ? 10 : 8) && pairs >= (d.KS1 == 1 ? 150 : d.KS1 == 2 ? 300 : d.KS1 == 3 ? 400 : 2400);
   if (!c.fused) return c;
   c.KS1 = d.KS1;
   // The split.  A workgroup takes 5 us to gather (3 on packed layers) and 0.8 us an item plus 0.4 per 32 rows and 16 tiles (0.08 per filter); two on a compute
