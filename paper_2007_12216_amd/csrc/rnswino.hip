@@ -607,6 +607,9 @@ std::string all_kernel_variants() {
 #define RNSW_X(wm_, wn_, rm, ntb, s_) out += "k2_residue_gemm_lds<" #wm_ ", " #wn_ ", " #rm ", " #ntb ", " #s_ ">\n";
   RNSW_K2L_TABLE(RNSW_X)
 #undef RNSW_X
+#define RNSW_X(ks, groups, rm, pk) out += "k12_transform_gemm<" #ks ", " #groups ", " #rm ", " #pk ">\n";
+  RNSW_K12_TABLE(RNSW_X)
+#undef RNSW_X
 #define RNSW_X(nres, ks3, wd, fs) out += "k3_inverse_crt<" #nres ", " #ks3 ", " #wd ", " #fs ">\n";
   RNSW_K3_TABLE(RNSW_X)
 #undef RNSW_X

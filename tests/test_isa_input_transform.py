@@ -23,5 +23,5 @@ def test_the_layer_kernels_take_few_arguments(assembly_file):
     """A launch of up to 112 bytes of arguments takes the host three quarters of the time of one of 120 and more."""
     text = open(assembly_file).read()
     sizes = {name: int(size) for size, name in re.findall(r"\.kernarg_segment_size:\s+(\d+)(?:(?!\.kernarg_segment_size).)*?\.name:\s+(_Z\w+)", text, re.S)}
-    layer = {n: s for n, s in sizes.items() if any(k in n for k in ("k1_input", "k2_residue", "k3_inverse"))}
+    layer = {n: s for n, s in sizes.items() if any(k in n for k in ("k1_input", "k2_residue", "k12_transform", "k3_inverse"))}
     assert len(layer) == len(rn.rnswino_kernel_variants()) and max(layer.values()) <= 112, layer

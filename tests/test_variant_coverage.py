@@ -15,7 +15,7 @@ UNCHECKED = rn.FLAG_ALLOW_UNCHECKED_RANGE
 def test_the_variant_cases_reach_every_instantiation():
     kept = vc.select_cases()
     reached = {k for _, kernels, _ in kept for k in kernels}
-    every = set(rn.rnswino_kernel_variants())
+    every = {k for k in rn.rnswino_kernel_variants() if not k.startswith("k12_transform_gemm")}      # (that one: test_gpu_transform_gemm.py)
     assert len(every) > 100
     assert every - reached == set(), sorted(every - reached)
     assert reached - every == set()
