@@ -107,7 +107,7 @@ __device__ __forceinline__ TilePos tile_position(const K3Args &P, int k, int tau
 }
 
 // CRT conversion of the four outputs of one lane (row block rb, lane group g) and their store: int32 y, or, for
-// chained layers, int8 clamp(y >> P.shift) with an optional 2x2 max-pool (the shift is monotone, so it commutes with
+// chained layers, int8 clamp(y >> shift) with an optional 2x2 max-pool (the shift is monotone, so it commutes with
 // the max).  Must be called by all lanes of a wave (the pooled mode exchanges rows between lanes).
 template <int NRES, bool CRT24, bool QUOT32>
 __device__ __forceinline__ void crt_convert(Constant<K3Params> &P, const uint32_t (&w)[NRES][4], int (&val)[4]) {

@@ -1,7 +1,7 @@
-// K1 and K2 in one kernel, for layers of one block of 64 channels (33 to 64, fewer on few tiles, or, t <= 10, 16 tiles of up to four; 8-bit moduli): the input
+// K1 and K2 in one kernel, for layers of one block of 64 channels (33 to 64, or, t <= 10, 16 tiles of up to four; 8-bit moduli): the input
 // transform of 16 or 32 tiles and the residue GEMM over all their channels, V passing through LDS and never through device memory.
 //
-// Block = TH blocks of 16 tiles, 4 TH waves.  A wave gathers the pixels of 16 tiles in 16 channels once (the channels of one slice of V) and
+// Block = TH blocks of 16 tiles, 4 k12_quads() waves.  A wave gathers the pixels of 16 tiles in 16 channels once (the channels of one slice of V) and
 // keeps them in registers as operand fragments (128 registers at t = 9, 10; with three and four contraction steps, t > 10, two waves share a slice's
 // channels).  Then the block goes through its items: four groups of four
 // transform points, the groups of all residues in a row (25 items of F(8,3) with four moduli; by 16 points of a residue there would be
@@ -30,6 +30,18 @@
 
 namespace rnswino {
 
+// The residue of group g of Q: g / Q as a product with this, 16 bits shifted out; with eight moduli and t = 16 there are 512 groups, 64 a residue.
+RNSW_HD constexpr uint32_t group_mul(uint32_t Q) { return (65535u + Q) / Q; }
+constexpr bool group_division_is_exact() {
+  for (uint32_t t = 2; t <= 16; ++t) {
+    const uint32_t Q = (t * t + 3) / 4;
+    for (uint32_t g = 0; g < 8 * Q; ++g)
+      if (g * group_mul(Q) >> 16 != g / Q) return false;
+  }
+  return true;
+}
+static_assert(group_division_is_exact(), "");
+
 struct K12Args {
   const ResidueParams *more;
   const int8_t *x;
@@ -40,7 +52,7 @@ struct K12Args {
   uint32_t tile_groups_mul, tw_mul, th_mul;          // FastDiv's, with the shifts below
   int C, H, W, pad, tw, th, T;
   int total;                  // N * C * H * W
-  uint32_t Q_mul;             // ceil(2^16 / Q), Q = ceil(t*t / 4)
+  uint32_t Q_mul;             // group_mul(Q), Q = ceil(t*t / 4)
   uint32_t shifts;            // bytes: of the divisions by the tile blocks' groups, tw, th; packed layers: parts the filters are split into
   uint32_t sizes;             // bytes: m, t, n, items of a part
   uint32_t kept;              // the input's copy: where it lies in front of O, in 256 bytes; in the upper five bits its own workgroups / 8
@@ -210,7 +222,7 @@ __global__ __launch_bounds__(256 * k12_quads(KS1, TH), 2) void k12_transform_gem
 #pragma unroll
     for (int q = 0; q < 4 * KS1; ++q)
       *(v4i *)(staged + h * (KS1 * 1024) + q * 256 + col * 16) = (v4i){(int)slots[4 * q], (int)slots[4 * q + 1], (int)slots[4 * q + 2], (int)slots[4 * q + 3]};
-    // (a wave reads only what it has written)
+    // (A wave reads only what it has written, and its LDS accesses stay in order; the compiler keeps them so, the addresses being one array's.)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -225,7 +237,7 @@ __global__ __launch_bounds__(256 * k12_quads(KS1, TH), 2) void k12_transform_gem
   auto after = [&](int it) { return it + 1 == first + count ? first : it + 1; };
   struct Group { int i, q; };                                          // residue and points 4 q .. 4 q + 3; past the last group: that one again
   auto group = [&](int number) -> Group {
-    const int g = min(number, ngroups - 1), i = (int)(((uint32_t)g * P.Q_mul) >> 16);      // exact: 200 groups of 25 at most
+    const int g = min(number, ngroups - 1), i = (int)(((uint32_t)g * P.Q_mul) >> 16);
     return {i, g - i * Q};
   };
   const int wq = wave & 3, half = wave >> 2;                           // of O: what this wave multiplies: a group, every QUADS-th set of row blocks

@@ -412,7 +412,7 @@ K12Args make_k12(const Dims &d, const KParams &P, const DeviceParams *dev, const
   const uint32_t s_groups = store_div((uint32_t)((q.ntb + c.TH - 1) / c.TH), q.tile_groups_mul), s_tw = store_div((uint32_t)d.tw, q.tw_mul), s_th = store_div((uint32_t)d.th, q.th_mul);
   q.shifts = pack_bytes(s_groups, s_tw, s_th, c.row_parts);
   q.sizes = pack_bytes((uint32_t)d.m, (uint32_t)d.t, (uint32_t)d.n, (uint32_t)c.part);
-  q.Q_mul = (65536u + (uint32_t)d.Q - 1) / (uint32_t)d.Q;
+  q.Q_mul = group_mul((uint32_t)d.Q);
   q.C = d.C; q.H = d.H; q.W = d.W; q.pad = d.pad; q.tw = d.tw; q.th = d.th; q.T = d.T;
   q.total = (int)((long long)d.N * d.C * d.H * d.W);
   q.kept = (uint32_t)(align256(v_bytes(d)) / 256) | c.copies / 8 << 27;          // (V has at most four times the bytes of O, below 16 GiB)
