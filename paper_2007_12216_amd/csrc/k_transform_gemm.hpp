@@ -10,8 +10,8 @@
 // other with fragments of U from L2, requested a set of row blocks ahead, and stores finished words of O (as k2_residue_gemm_lds does).  V has two buffers: one
 // barrier an item.
 //
-// What bounds it: the vector unit (400 instructions a wave and item, of them 256 residues' multiply-adds and 48 matrix instructions: 60 % of
-// the time on 64 -> 64 at 224 x 224, batch 8, matrix cores 25 %), blocks of 196 on 256 compute units there, and the way of U.  V's way to memory
+// What bounds it: the vector unit (400 instructions a wave and item, of them 256 residues' multiply-adds and 48 matrix instructions: 53 % of
+// the time on 64 -> 64 at 224 x 224, batch 8, matrix cores 22 %), 196 blocks on 256 compute units there, and the way of U.  V's way to memory
 // and back was 320 MB of that layer: K1 43 + K2 61 us, so 83 (a layer 168 -> 131 us); 64 -> 128 at 112 x 112 68 -> 60, at batch 1 20.4 -> 18.9, 64 -> 64 at
 // 224 x 224, batch 1, 32.4 -> 27.0.  On the way there (us of this kernel on the first two): 32 tiles a block 83 and 33, 16 tiles 93 and 36 (U crosses the L2
 // twice as often); all blocks of a part through the items in the same order 100 and 42 (they wait for the same fragments from memory), U from a single resident

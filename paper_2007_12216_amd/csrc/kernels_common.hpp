@@ -19,7 +19,8 @@ struct Residue8 {
 // A launch carries a kernel's addresses and what it reads in front of its first loads, at most 112 bytes; the rest lies in device memory, written once
 // with the plan, and is fetched while those loads are in flight.  All of it by value (300 to 500 bytes) is copied anew for every launch: in a
 // row of launches that takes the host 3.5 to 3.9 us each from 120 bytes on, 2.8 up to 112: 16 channels
-// at 16 x 16, whose three launches are more for the host than for the GPU, 12.4 -> 10.5 us a layer; the layers that the GPU bounds +-0.5 %.
+// at 16 x 16, whose three launches are more for the host than for the GPU, 12.4 -> 9.7 us a layer (medians of three
+// comparisons of four, 11.1 -> 10.7 in the other; runs of one side differ by 14 to 39 %); the layers that the GPU bounds +-0.5 %.
 // (All of it in device memory puts a fetch in front of the first loads: 256 channels at 56 x 56 19.75 -> 20.45 us a layer, 19.9 with the pointer to it in
 // scalar registers when a wave starts.)
 // Read through this address space the fields come by scalar loads wherever they are used.
